@@ -234,10 +234,12 @@ int32_t wfst_decode_batch_slot(wfst_decoder *dec, int32_t slot, const void *logl
                                const wfst_boost_table *const *boosts, const wfst_boost_fst *const *fsts,
                                void *stream, int32_t *words, int32_t *nwords, float *cost, int32_t *flags);
 
-/* How many workgroups the launches of this decoder get from now on.  n = 0 (the default): one per
- * utterance (or channel) of the call.  n > 0: at most n; they take the call's utterances, longest
- * first, one after the other from a counter on the device, so that all of them are busy until the
- * call's work runs out and they end at nearly the same time.  This is for several batches in flight
+/* How many workgroups the launches of this decoder get from now on.  n = 0 (the default): at least one
+ * per utterance (or channel) of the call, and as many as there are compute units if the call has few
+ * enough: 2, 4 or 8 workgroups then decode an utterance together.  n > 0: at most n, alone or together
+ * likewise; they take the call's utterances, longest first, one after the other from a counter on
+ * the device, so that all of them are busy until the call's work runs out and they end at nearly
+ * the same time.  This is for several batches in flight
  * (batch slots): the GPU hands the workgroups of a launch to fixed groups of compute units in launch
  * order, so with one workgroup per utterance a compute unit that a short utterance has left can
  * stay idle while the next workgroup in line waits for another group.  With n chosen so that the
@@ -409,6 +411,9 @@ int32_t wfst_get_counters(wfst_decoder *dec, int64_t counters[8], int32_t reset)
  * cost a launch about 1 %; not available with narrow arc records); [15] is always counted.
  */
 int32_t wfst_debug_set_phase_timing(wfst_decoder *dec, int32_t on);
+/* Workgroups that decode an utterance together, for tests and measurements: 1, 2, 4 or 8 (fewer where the
+ * launch does not get as many), 0 (the default): chosen for every launch.  Results do not depend on it. */
+int32_t wfst_debug_set_cluster_size(wfst_decoder *dec, int32_t n);
 int32_t wfst_debug_phase_ticks(wfst_decoder *dec, int64_t ticks[16], int32_t reset);
 
 /* Device memory the decoder holds, in bytes (graph + channel state). */

@@ -63,6 +63,7 @@
 #include <cstddef>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <numeric>
 #include <string>
@@ -1809,7 +1810,7 @@ __device__ __forceinline__ void select_and_trace(Ctx &x, const LaunchArgs &a, in
           else if (pass == 1) { const int pos = nw - 1 - k; if (pos < a.max_words) words[pos] = ol; }
           ++k;
         }
-        i = bp.x;
+        i = bp.x & 0xffff;                                      // (the upper half: the source's state in the boosting acceptor)
         if (emitting) --f;                                      // an emitting arc consumed a frame
       }
       nw = k;
@@ -2022,6 +2023,8 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel(De
   }
 }
 
+
+#include "wfst_channel.h"
 
 // ------------------------------------------------------------------ lattice links
 // One workgroup per closed token set A_t of one channel, after decoding.  The set's tokens go
@@ -2327,7 +2330,15 @@ struct wfst_decoder {
   std::vector<char> slot_by_length;    // the slot's pool is currently shared out by length
   std::vector<char> chan_ready;        // the channel has been initialised since its arena was last moved
   int phase_timing = 0;                // launches time their phases (wfst_debug_set_phase_timing)
+  int cluster_size = 0;                // workgroups per utterance (wfst_debug_set_cluster_size); 0: chosen per launch
+  int stream_max_active = 10000;       // what the channels were last initialised with
   int launch_workgroups = 0;           // most workgroups a launch gets (wfst_set_launch_workgroups); 0: one per list entry
+  // clusters (several workgroups per channel): memory of their workgroups, one area per batch slot (and
+  // one for the calls that name channels), allocated by the first launch that needs it
+  struct ClusterArea { size_t wgs = 0, cand = 0; ClusterArgs a{}; };
+  std::vector<ClusterArea> areas;
+  unsigned launch_seq = 0;
+  int n_cu = 0;
   std::string err;
 };
 
@@ -2590,6 +2601,67 @@ int alloc_channels(wfst_decoder *d) {
   return WFST_OK;
 }
 
+#ifndef WFST_LEAN
+#define WFST_LEAN 5
+#endif
+// How many workgroups decode each utterance of a launch (1, 2, 4 or 8), and how many such clusters
+// the launch gets.  `frames`: what every utterance consumes, longest first.
+//
+// The estimate: a frame takes a cluster a fixed time (barriers, exchanges, chains of dependent loads) plus its
+// share of the work, which goes with the tokens, at most about max_active of them; measured at 1,000 and
+// 11,000 tokens per frame.  The launch ends with its busiest cluster: no earlier than the longest
+// utterance, than an equal share of all frames, and than the k + 1 shortest of the k * clusters + 1 longest.
+int plan_clusters(wfst_decoder *d, const std::vector<int> &frames, int max_active, int &n_clusters, bool &lean) {
+  const int n = (int)frames.size();
+  const int budget = d->launch_workgroups > 0 ? std::min(d->launch_workgroups, d->n_cu) : d->n_cu;
+  const float k_tok = (float)std::min(max_active, d->g.S) * 1e-3f;
+  // solo: the kernel that keeps records in registers up to about 5,000 tokens, the older one beyond
+  lean = k_tok <= (float)WFST_LEAN;
+  const float t_us[4] = {lean ? 13.0f + 7.5f * k_tok : 20.0f + 6.8f * k_tok, 19.0f + 4.6f * k_tok, 19.0f + 2.8f * k_tok, 21.0f + 1.9f * k_tok};
+  long long total = 0;
+  for (int f : frames) total += f;
+  int best = 0; float best_t = 0.0f;
+  for (int lg = 0; (1 << lg) <= kMaxG && (1 << lg) <= budget; ++lg) {
+    const int C = lg == 0 && d->launch_workgroups <= 0 ? std::min(n, 256) : std::min(n, budget >> lg);
+    float most = std::max((float)frames[0], (float)total / (float)C);
+    for (int k = 1; k * C < n; ++k) most = std::max(most, (float)(k + 1) * (float)frames[k * C]);
+    const float t = most * t_us[lg];
+    if (lg == 0 || t < best_t) { best = lg; best_t = t; }
+  }
+  if (d->g.earc8 || frames[0] == 0) best = 0;        // (narrow records, a mere initialisation or result: one workgroup each)
+  else if (d->cluster_size > 0)
+    for (best = 0; (2 << best) <= std::min(d->cluster_size, budget);) ++best;
+  n_clusters = std::min(n, std::max(1, budget >> best));
+  return 1 << best;
+}
+
+int cluster_area(wfst_decoder *d, int slot_id, int n_wg, int G, ClusterArgs &out) {
+  if (d->areas.empty()) d->areas.resize((size_t)d->n_slots + 1);
+  auto &ar = d->areas[slot_id];
+  const size_t qc = (size_t)d->c.qcap, region = (size_t)d->c.region_cap;
+  const int seg_cap = (int)(region * (size_t)std::max(1, 4 / G));
+  const size_t cand = (size_t)n_wg * 2 * G * (size_t)seg_cap;
+  int rc;
+  if (ar.wgs < (size_t)n_wg) {
+    const size_t w = (size_t)n_wg;
+    if ((rc = dev_alloc(d, &ar.a.tok, w * 2 * qc))) return rc;
+    if ((rc = dev_alloc(d, &ar.a.gi, w * 2 * qc))) return rc;
+    if ((rc = dev_alloc(d, &ar.a.wl, w * 2 * qc))) return rc;
+    if ((rc = dev_alloc(d, &ar.a.box, w * 2 * kBoxWords))) return rc;
+    if ((rc = dev_alloc(d, &ar.a.hello, w * 2))) return rc;
+    HIP_TRY(d, hipMemset(ar.a.hello, 0, w * 2 * sizeof(unsigned long long)));
+    HIP_TRY(d, hipDeviceSynchronize());
+    ar.wgs = w;
+  }
+  if (ar.cand < cand) {
+    if ((rc = dev_alloc(d, &ar.a.cand, cand))) return rc;
+    ar.cand = cand;
+  }
+  out = ar.a;
+  out.G = G; out.seg_cap = seg_cap; out.qcap = (int)qc; out.seq = ++d->launch_seq; out.ticks = 5000;
+  return WFST_OK;
+}
+
 // Stage {channel, frames, io row} triples and launch one workgroup per entry.
 // `slot`: whose pair of timing events brackets the kernel (n_slots = the calls that name channels).
 int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int> &nfr,
@@ -2600,7 +2672,22 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
   const size_t N = (size_t)d->opts.max_channels;
   // workgroups of the launch: one per entry, or at most launch_workgroups, which then take the
   // entries in list order from a counter that travels with the lists
-  const int n_wg = d->launch_workgroups > 0 ? std::min(n, d->launch_workgroups) : n;
+  int n_clusters = 0;
+  bool lean = false;
+  int G = 1;
+  {
+    std::vector<int> by_length(nfr);
+    std::sort(by_length.begin(), by_length.end(), std::greater<int>());
+    G = plan_clusters(d, by_length, a.mode & kModeInit ? a.max_active : d->stream_max_active, n_clusters, lean);
+    if (a.mode & kModeInit && !(a.mode & kModeFinal)) d->stream_max_active = a.max_active;
+  }
+  int n_wg = d->launch_workgroups > 0 ? std::min(n, d->launch_workgroups) : n;
+  ClusterArgs cl{};
+  if (G > 1) {
+    n_wg = n_clusters * G;
+    const int rca = cluster_area(d, slot_id, n_wg, G, cl);
+    if (rca) return rca;
+  }
   // (the lists live on the device until the kernel ends, since its workgroups read them as they go:
   // one area per batch slot, and one for the calls that name channels; calls that share an area do
   // not overlap in time, so the stream orders this copy after the last kernel that read the area)
@@ -2614,7 +2701,7 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
     pack[3 * (size_t)n + i] = (int)d->cur_capn[chan[i]];
     std::memcpy(&pack[4 * (size_t)n + 2 + 2 * (size_t)i], &d->cur_start[chan[i]], sizeof(unsigned long long));
   }
-  pack[4 * (size_t)n] = n_wg; pack[4 * (size_t)n + 1] = 0;
+  pack[4 * (size_t)n] = n_wg / G; pack[4 * (size_t)n + 1] = 0;
   d->ring_pos = (d->ring_pos + 1) % wfst_decoder::kRing;
   HIP_TRY(d, hipMemcpyAsync(slot, pack.data(), pack.size() * sizeof(int), hipMemcpyHostToDevice, st));
   a.lists = slot; a.n_jobs = n;
@@ -2627,6 +2714,19 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
     if (n_wg < n) hipLaunchKernelGGL((wfst_channel_kernel<NARROW, BOOST, PROF, OPT, true>), dim3(n_wg), dim3(kBlock), 0, st, d->g, d->c, a); \
     else hipLaunchKernelGGL((wfst_channel_kernel<NARROW, BOOST, PROF, OPT, false>), dim3(n_wg), dim3(kBlock), 0, st, d->g, d->c, a); \
   } while (0)
+#define WFST_LAUNCH2(CL, NARROW, BOOST, PROF, OPT, QUEUE) \
+  hipLaunchKernelGGL((wfst_channel_kernel2<CL, NARROW, BOOST, PROF, OPT, QUEUE>), dim3(n_wg), dim3(kBlock), 0, st, d->g, d->c, a, cl)
+  if ((G > 1 || lean) && !d->g.earc8) {
+    const bool q = n_wg < n;
+    if (G > 1) {
+      if (d->phase_timing) { if (boost) WFST_LAUNCH2(true, false, true, true, true, true); else if (opt) WFST_LAUNCH2(true, false, false, true, true, true); else WFST_LAUNCH2(true, false, false, true, false, true); }
+      else if (boost) WFST_LAUNCH2(true, false, true, false, true, true);
+      else if (opt) WFST_LAUNCH2(true, false, false, false, true, true); else WFST_LAUNCH2(true, false, false, false, false, true);
+    } else if (d->phase_timing) { if (boost) WFST_LAUNCH2(false, false, true, true, true, true); else if (opt) WFST_LAUNCH2(false, false, false, true, true, true); else WFST_LAUNCH2(false, false, false, true, false, true); }
+    else if (boost) WFST_LAUNCH2(false, false, true, false, true, true);
+    else if (opt) WFST_LAUNCH2(false, false, false, false, true, true);
+    else if (q) WFST_LAUNCH2(false, false, false, false, false, true); else WFST_LAUNCH2(false, false, false, false, false, false);
+  } else
   if (d->g.earc8) {                            // (no lean instances and no phase timing with narrow arc records)
     if (boost) WFST_LAUNCH(true, true, false, true); else WFST_LAUNCH(true, false, false, true);
   } else if (d->phase_timing) {
@@ -2974,6 +3074,10 @@ int32_t wfst_decoder_create(const wfst_graph_csr *graph, const wfst_opts *opts, 
     return fail(nullptr, WFST_ERR_INVALID_ARG, "recycle_lattice and keep_token_records exclude each other (a lattice needs every frame)");
   wfst_decoder *d = new wfst_decoder();
   d->opts = *opts; d->V = graph->num_classes;
+  {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&d->n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || d->n_cu < 1) d->n_cu = 256;
+  }
   d->n_slots = std::max(1, opts->batch_slots); d->slot_channels = opts->max_channels / d->n_slots;
   rc = upload_graph(d, graph);
   if (!rc) rc = alloc_channels(d);
@@ -3413,6 +3517,13 @@ int32_t wfst_set_launch_workgroups(wfst_decoder *d, int32_t n) {
   if (!d) return WFST_ERR_INVALID_ARG;
   if (n < 0) return fail(d, WFST_ERR_INVALID_ARG, "launch workgroups must be >= 0");
   d->launch_workgroups = n;
+  return WFST_OK;
+}
+
+int32_t wfst_debug_set_cluster_size(wfst_decoder *d, int32_t n) {
+  if (!d) return WFST_ERR_INVALID_ARG;
+  if (n != 0 && n != 1 && n != 2 && n != 4 && n != 8) return fail(d, WFST_ERR_INVALID_ARG, "cluster size must be 0, 1, 2, 4 or 8");
+  d->cluster_size = n;
   return WFST_OK;
 }
 

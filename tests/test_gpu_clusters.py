@@ -1,0 +1,63 @@
+"""Several workgroups per utterance: the oracle's results whatever their number, on the graphs where
+their sharing can go wrong (keys that tie, hub states, closure rounds larger than a table, more
+destinations than registers and tables hold, options, boosting), and on one channel that changes hands."""
+import numpy as np
+import pytest
+
+import test_gpu_parity as parity
+from test_gpu_parity import c2_refs, torch_cuda  # noqa: F401  (fixtures)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def cluster(request, monkeypatch):
+    """Every decoder made in the test gives each utterance this many workgroups."""
+    import paper_2311_04996_amd as package
+
+    class ClusterDecoder(package.Decoder):
+        def __init__(self, *a, **kw):
+            super().__init__(*a, **kw)
+            self.debug_set_cluster_size(request.param)
+    monkeypatch.setattr(package, "Decoder", ClusterDecoder)
+    return request.param
+
+
+@pytest.mark.parametrize("cluster", [1, 2, 4, 8], indirect=True)
+def test_small_and_tie_heavy_graphs(torch_cuda, cluster):
+    parity.test_micro_graphs_with_ties_and_negative_epsilon(torch_cuda)
+    parity.test_boost_fst_on_micro_graphs(torch_cuda)
+    parity.test_self_loop_candidates_that_tie_exactly_with_candidates_of_other_arcs(torch_cuda)
+    parity.test_random_small_configurations(torch_cuda)
+    parity.test_dead_and_nonfinal_and_minus_inf(torch_cuda)
+
+
+@pytest.mark.parametrize("cluster", [1, 2, 4, 8], indirect=True)
+def test_hubs_large_closures_and_many_duplicates(torch_cuda, cluster):
+    parity.test_more_high_degree_states_than_the_shared_list_holds(torch_cuda)
+    parity.test_state_with_more_than_a_million_arcs(torch_cuda)
+    parity.test_epsilon_rounds_larger_than_one_chunk_and_one_table(torch_cuda)
+
+
+@pytest.mark.parametrize("cluster", [2, 8], indirect=True)
+def test_options_and_streams(torch_cuda, c1, c2, c2_refs, cluster):
+    parity.test_boost_fst_with_frequent_long_matches(torch_cuda, c2)
+    parity.test_cost_offsets_match_the_oracle_with_the_same_option(torch_cuda, c1, c2)
+    parity.test_advance_and_partial_in_one_launch(torch_cuda, c2)
+    parity.test_lattice_arena_overflow_in_a_batch_does_not_touch_the_neighbours(torch_cuda, c2)
+    parity.test_recycled_lattice_stream_ten_times_the_window(torch_cuda, c2)
+
+
+def test_a_stream_whose_chunks_are_decoded_by_different_numbers_of_workgroups(torch_cuda, c2, c2_refs):
+    from paper_2311_04996_amd import Decoder
+    b = int(np.argmax(c2.lengths))
+    n = min(int(c2.lengths[b]), 200)
+    dec = Decoder(c2.graph, max_channels=1, max_frames=n, max_active_hint=c2.max_active, record_digests=True)
+    ll = torch_cuda.from_numpy(np.ascontiguousarray(c2.loglikes[b:b + 1, :n])).cuda()
+    dec.init_channel(0, c2.beam, c2.max_active)
+    for k, t in enumerate(range(0, n, 8)):
+        dec.debug_set_cluster_size((8, 1, 2, 4, 1, 8)[k % 6])
+        dec.advance_chunk([0], ll[:, t:t + 8].contiguous(), [min(8, n - t)])
+    cnt, dig = dec.debug_frame_digests(0)
+    assert (cnt == c2_refs[b].digest_count[:n + 1]).all() and (dig == c2_refs[b].digest_sum[:n + 1]).all()
+    dec.close()
