@@ -22,11 +22,11 @@
 // 16 waves several times; spread over 8 compute units the steps are down to one round each.
 //
 // Workgroups talk through words {tag, value} of 64 bits, written and polled with relaxed
-// device-scope atomics, the tag being the number of the exchange; the candidates travel the same way (two 8-byte
-// device-scope stores; the writer waits for them before it posts the sizes).  Measured: 1.1 us for an
-// exchange between any two compute units, 0.75 us more with 2 KB of data; an exchange made with
-// device-scope fences takes 9 us on an idle chip and over 100 us on a full one, since a fence writes
-// back and invalidates whole L2 caches.
+// atomics, the tag being the number of the exchange; the candidates travel the same way (two 8-byte
+// stores; the writer waits for them before it posts the sizes).  A cluster's workgroups run on one
+// XCD, so all of this stays in its L2.  Between compute units of different XCDs an exchange takes 1.1 us,
+// 0.75 us more with 2 KB of data; one made with device-scope fences takes 9 us on an idle chip and
+// over 100 us on a full one, since a fence writes back and invalidates whole L2 caches.
 
 constexpr int kMaxG = 8;                      // workgroups of a cluster
 #ifndef WFST_KR
@@ -38,20 +38,24 @@ constexpr unsigned kRefTok = 0x80000000u;     // low word of a table value: a to
 constexpr unsigned kRefStay = 0xFFFFFFFFu;    // ... or: a self-loop candidate won here
 constexpr int kBoxWords = 512;                // mailbox words of one workgroup and exchange parity
 constexpr int kBoxAux = 8, kBoxSel = 12, kBoxHist = 16;
+constexpr int kSpins = 1 << 23;               // most polls of a wait (seconds)
+constexpr int kXcds = 8;                      // XCDs of the chip
+constexpr int kHwXccId = 20 | (4 - 1) << 11;   // hardware register XCC_ID, bits 0-3: the XCD a wave runs on
 constexpr int kAux = 4;                       // best cost, status, tokens made by the closure, smallest cost in a simple state
 
-struct ClusterArgs {                          // device memory of the clusters' workgroups, by slot (order of arrival)
-  int G;                                      // workgroups per cluster (a launch has n_wg / G clusters)
+struct ClusterArgs {                          // device memory of the workgroups, by ticket of the cluster and number in it
+  int G;                                      // workgroups per cluster
+  int n_clusters;                             // clusters that decode (a launch can have some more, which end at once)
   unsigned seq;                               // number of the launch: tags the words of the formation
   int seg_cap;                                // records per segment
   int qcap;
   unsigned ticks;                             // how long the first workgroup of a cluster waits for the others (10 ns)
-  int4 *cand;                                 // [slot][2][G][seg_cap]
-  int2 *tok;                                  // [slot][2][qcap] the workgroup's own tokens {key + flags, cost}
-  int *gi;                                    // [slot][2][qcap] their numbers in the set
-  int4 *wl;                                   // [slot][2][qcap]
-  unsigned long long *box;                    // [slot][2][kBoxWords]
-  unsigned long long *hello;                  // [slot][2] arrived / decided
+  int4 *cand;                                 // [workgroup][2][G][seg_cap]
+  int2 *tok;                                  // [workgroup][2][qcap] the workgroup's own tokens {key + flags, cost}
+  int *gi;                                    // [workgroup][2][qcap] their numbers in the set
+  int4 *wl;                                   // [workgroup][2][qcap]
+  unsigned long long *box;                    // [workgroup][2][kBoxWords] by XCD and order of arrival there
+  unsigned long long *hello;                  // [workgroup][2] arrived / decided, likewise
 };
 
 struct WaveLds2 {             // ExpandArcs: the work items of one wave (one token per lane)
@@ -130,11 +134,20 @@ template <bool kProf> __device__ __forceinline__ void mark(Cx &x, int phase) {
 }
 
 // ------------------------------------------------------------------ memory other workgroups read or wrote
+// The workgroups of a cluster run on one XCD, and the compute units of an XCD share one L2.  A store of
+// workgroup scope goes through to that L2 (the vector cache writes through) and is acknowledged there, a
+// load of device scope passes the compute unit's vector cache by and is served by the L2, and a
+// read-modify-write is done in it: enough for workgroups of one XCD, and nothing waits for the memory
+// behind the L2.  (A load of workgroup scope may hit a stale line of the vector cache.)  With stores of device
+// scope, which are acknowledged behind the L2: one utterance of 11 k tokens per frame 12.0 instead of 11.2 ms, 32 at
+// once 44.7 instead of 40.8 ms, 256 at once 73.0 instead of 67.2 ms; with the workgroups of a cluster on any
+// XCDs 12.6, 45.9 and 73.3 ms.
+constexpr auto kLoadScope = __HIP_MEMORY_SCOPE_AGENT, kStoreScope = __HIP_MEMORY_SCOPE_WORKGROUP;
 __device__ __forceinline__ unsigned long long aload(const unsigned long long *p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, kLoadScope);
 }
 __device__ __forceinline__ void astore(unsigned long long *p, unsigned long long v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, kStoreScope);
 }
 __device__ __forceinline__ unsigned long long u64_of(int lo, int hi) { return ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo; }
 template <bool kCl> __device__ __forceinline__ void put4(int4 *p, int4 v) {
@@ -165,7 +178,7 @@ __device__ __forceinline__ unsigned poll(Smem2 &sm, const unsigned long long *p,
   for (int spins = 0;; ++spins) {
     const unsigned long long v = aload(p);
     if ((unsigned)(v >> 32) == tag) return (unsigned)v;
-    if ((spins & 1023) == 1023 && (spins > (1 << 21) || __hip_atomic_load(&sm.dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))) { sm.dead = 1; return 0; }
+    if ((spins & 1023) == 1023 && (spins > kSpins || __hip_atomic_load(&sm.dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))) { sm.dead = 1; return 0; }
   }
 }
 __device__ __forceinline__ unsigned long long *box_of(const Cx &x, int r) {
@@ -176,8 +189,8 @@ __device__ __forceinline__ void post(const Cx &x, int word, unsigned v) {
 }
 // The cluster's counter of tokens in the set under construction (the closure takes numbers from it).
 __device__ __forceinline__ unsigned *set_size_of(const Cx &x) { return reinterpret_cast<unsigned *>(x.box0 + kBoxWords - 1); }
-__device__ __forceinline__ void set_counter(const Cx &x, int n) { __hip_atomic_store(set_size_of(x), (unsigned)n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-// Every store of this thread has reached the device's point of coherence.
+__device__ __forceinline__ void set_counter(const Cx &x, int n) { __hip_atomic_store(set_size_of(x), (unsigned)n, __ATOMIC_RELAXED, kStoreScope); }
+// Every store of this thread has reached the L2.
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Owner of a key among 2^lg parts: the top bits of its hash.
@@ -852,7 +865,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
         const unsigned long long *p = box_of(x, tid >> 7) + kBoxHist + (tid & 127);
         unsigned long long v;
         for (int spins = 0; (unsigned)((v = aload(p)) >> 48) != (x.xc & 0xffffu); ++spins)
-          if ((spins & 1023) == 1023 && (spins > (1 << 21) || __hip_atomic_load(&sm.dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))) { sm.dead = 1; break; }
+          if ((spins & 1023) == 1023 && (spins > kSpins || __hip_atomic_load(&sm.dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))) { sm.dead = 1; break; }
         *reinterpret_cast<uint2 *>(&sm.v.s.gh[tid >> 7][2 * (tid & 127)]) = make_uint2((unsigned)v & 0xffffffu, (unsigned)(v >> 24) & 0xffffffu);
       }
       if (tid < 64) {
@@ -897,11 +910,13 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
       for (int r = 0; r < S2; ++r) {
         const uint4 q = *reinterpret_cast<const uint4 *>(kCl ? &sm.v.s.gh[r][4 * tid] : &sm.hist[4 * tid]);
         const int lim = min(kk, ks) - 4 * tid;
-        const unsigned nb = wave_sum((lim > 0 ? q.x : 0u) + (lim > 1 ? q.y : 0u) + (lim > 2 ? q.z : 0u) + (lim > 3 ? q.w : 0u));
+        const unsigned nb = (lim > 0 ? q.x : 0u) + (lim > 1 ? q.y : 0u) + (lim > 2 ? q.z : 0u) + (lim > 3 ? q.w : 0u);
         if (kCl && r < x.me) before += nb;
         if (!kCl || r == x.me) mine = nb;
         all += nb;
       }
+      mine = wave_sum(mine);
+      if (kCl) { before = wave_sum(before); all = wave_sum(all); } else all = mine;
       if (tid == 0) {
         sm.k_keep = kk; sm.redo = redo; sm.n_emit = (int)mine; sm.gbase = (int)before; sm.n_emit_all = (int)min(all, 0x7fffffffu);
         // next frame's selection: enough candidates for max_active distinct destinations
@@ -992,7 +1007,7 @@ __device__ __forceinline__ void apply2(Cx &x, int win, const int4 &rec, int slot
   int at = 0;
   if (lane == 0 && mn) at = atomicAdd(&sm.n_loc, __popcll(mn));
   if (lane == 1 && mw) at = atomicAdd(&sm.made[2], __popcll(mw));
-  if (kCl && lane == 2 && mn) at = (int)__hip_atomic_fetch_add(set_size_of(x), (unsigned)__popcll(mn), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (kCl && lane == 2 && mn) at = (int)__hip_atomic_fetch_add(set_size_of(x), (unsigned)__popcll(mn), __ATOMIC_RELAXED, kStoreScope);
   const int rank = __popcll(mn & lt);
   if (fresh) { li = __builtin_amdgcn_readlane(at, 0) + rank; gx = kCl ? __builtin_amdgcn_readlane(at, 2) + rank : li; }
   else if (win) gx = kCl ? NGI[li] : li;
@@ -1395,6 +1410,20 @@ __device__ __forceinline__ void trace2(Cx &x, const LaunchArgs &a, int io, const
   __syncthreads();
 }
 
+// The next entry of the launch's list (for all workgroups of a cluster); ends with a barrier.
+template <bool kCl>
+__device__ __forceinline__ int next_job2(Cx &x, const LaunchArgs &a) {
+  Smem2 &sm = x.sm;
+  if (kCl) ++x.xc;
+  if (threadIdx.x == 0) {
+    if (!kCl || x.me == 0) { sm.job = atomicAdd(a.lists + 4 * a.n_jobs, 1); if (kCl) post(x, 0, (unsigned)sm.job); }
+    else sm.job = (int)poll(sm, box_of(x, 0), x.xc);
+  }
+  __syncthreads();
+  const int job = uni(sm.job);
+  return kCl && uni(sm.dead) ? a.n_jobs : job;
+}
+
 // ------------------------------------------------------------------ the channel kernel
 // kCl: clusters of up to w.G workgroups per channel; without it a workgroup is on its own and all of
 // its data are the channel's.  kNarrow: the graph has the 8-byte emitting-arc records and the arc loops
@@ -1415,14 +1444,18 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
   int job = blockIdx.x;
   x.G = 1; x.lg = 0; x.me = 0; x.xc = 0;
   if (kCl) {
-    // Clusters are formed in the order in which workgroups start (so all but the last few of a launch find
-    // their partners running already), and nobody waits for a workgroup that has not started: the
-    // first of a cluster waits a fixed time for the others and goes on with those that are there
-    // (a power of two); who comes later, or is not needed, ends.
-    if (tid == 0) { sm.job = atomicAdd(a.lists + 4 * a.n_jobs + 1, 1); sm.dead = 0; }
+    // Clusters are formed on every XCD from the workgroups that start there, in the order in which they
+    // start, and nobody waits for one that has not started: the first of a cluster waits a
+    // fixed time for the others and goes on with those that are there (a power of two); who comes
+    // later, or is not needed, ends.  The launch has as many workgroups on every XCD as the fullest
+    // XCD needs; clusters without a ticket end.
+    const int xcd = (int)__builtin_amdgcn_s_getreg(kHwXccId) & (kXcds - 1);
+    const int cap = (int)gridDim.x / kXcds;      // workgroups per XCD: a multiple of w.G
+    if (tid == 0) { sm.job = atomicAdd(a.lists + 6 * a.n_jobs + 2 + xcd, 1); sm.dead = 0; }
     __syncthreads();
-    const int slot = uni(sm.job);
-    const int s0 = slot / w.G * w.G;
+    const int arrival = uni(sm.job);
+    if (arrival >= cap) return;
+    const int slot = xcd * cap + arrival, s0 = xcd * cap + arrival / w.G * w.G;
     x.me = slot - s0;
     unsigned long long *box = w.box + (size_t)slot * 2 * kBoxWords;
     for (int i = tid; i < 2 * kBoxWords; i += kBlock) astore(box + i, 0ull);
@@ -1430,33 +1463,38 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
     __syncthreads();
     if (tid == 0) {
       if (x.me == 0) {
-        const long long t0 = (long long)wall_clock64();
-        int n = 1;
-        while (n < w.G) {
-          if ((unsigned)(aload(w.hello + 2 * (size_t)(s0 + n)) >> 32) == w.seq) ++n;
-          else if ((long long)wall_clock64() - t0 > (long long)w.ticks) break;
+        const int ticket = atomicAdd(a.lists + 4 * a.n_jobs + 1, 1);
+        int eff = 0;
+        if (ticket < w.n_clusters) {
+          const long long t0 = (long long)wall_clock64();
+          int n = 1;
+          while (n < w.G) {
+            if ((unsigned)(aload(w.hello + 2 * (size_t)(s0 + n)) >> 32) == w.seq) ++n;
+            else if ((long long)wall_clock64() - t0 > (long long)w.ticks) break;
+          }
+          for (eff = 1; 2 * eff <= n;) eff *= 2;
         }
-        int eff = 1;
-        while (2 * eff <= n) eff *= 2;
-        astore(w.hello + 2 * (size_t)s0 + 1, u64_of(eff, (int)w.seq));
-        sm.job = eff;
+        sm.job = eff | ticket << 4;
+        astore(w.hello + 2 * (size_t)s0 + 1, u64_of(sm.job, (int)w.seq));
       } else {
         astore(w.hello + 2 * (size_t)slot, u64_of(1, (int)w.seq));
         sm.job = (int)poll(sm, w.hello + 2 * (size_t)s0 + 1, w.seq);
       }
     }
     __syncthreads();
-    x.G = uni(sm.job);
+    x.G = uni(sm.job) & 15;
     if (x.me >= x.G) return;
+    const size_t first = (size_t)(uni(sm.job) >> 4) * w.G;      // the cluster's place in the work memory
     x.lg = 31 - __clz(x.G);
     x.seg_stride = (size_t)w.G * w.seg_cap;
     x.seg_cap = w.seg_cap * (w.G / x.G);
     x.box0 = w.box + (size_t)s0 * 2 * kBoxWords;
-    x.cand = w.cand + (size_t)s0 * 2 * x.seg_stride;
-    x.tq = w.tok + (size_t)slot * 2 * c.qcap;
-    x.gi = w.gi + (size_t)slot * 2 * c.qcap;
-    x.wl0 = w.wl + (size_t)slot * 2 * c.qcap;
-    job = s0 / w.G;
+    x.cand = w.cand + first * 2 * x.seg_stride;
+    x.tq = w.tok + (first + x.me) * 2 * c.qcap;
+    x.gi = w.gi + (first + x.me) * 2 * c.qcap;
+    x.wl0 = w.wl + (first + x.me) * 2 * c.qcap;
+    job = next_job2<kCl>(x, a);
+    if (job >= a.n_jobs) return;
   }
   for (;;) {
   const int ch = uni(a.lists[job]);
@@ -1649,15 +1687,7 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
   }
   if (!kCl && !kQueue) break;
   if (kCl && uni(sm.dead)) break;
-  if (kCl) {
-    ++x.xc;
-    if (tid == 0) {
-      if (leader) { sm.job = atomicAdd(a.lists + 4 * a.n_jobs, 1); post(x, 0, (unsigned)sm.job); }
-      else sm.job = (int)poll(sm, box_of(x, 0), x.xc);
-    }
-  } else if (tid == 0) sm.job = atomicAdd(a.lists + 4 * a.n_jobs, 1);
-  __syncthreads();             // (also: nobody is still reading this channel's tables when the next one's are set up)
-  job = uni(sm.job);
-  if (job >= a.n_jobs || (kCl && uni(sm.dead))) break;
+  job = next_job2<kCl>(x, a);  // (also: nobody is still reading this channel's tables when the next one's are set up)
+  if (job >= a.n_jobs) break;
   }
 }

@@ -219,8 +219,9 @@ struct DevChannels {
 struct LaunchArgs {
   // device: the launch's lists, n_jobs entries each (the launch may have fewer workgroups): ints
   // [channel id][frames to consume][row in loglikes/outputs][entries of the channel's lattice arena],
-  // then the first entry no workgroup has taken yet (starts at the number of workgroups) and a pad,
-  // then 64-bit [start of the channel's arena in the lattice pool]
+  // then the first entry no workgroup has taken yet (starts at the number of workgroups; clusters: at 0) and
+  // the clusters that have started, then 64-bit [start of the channel's arena in the lattice pool],
+  // then the workgroups that have started, per XCD
   int *lists; int n_jobs;
   const void *ll; long long ll_stride; int V;   // rows of V elements; fp32, or fp16 / bf16 widened when staged
   int ll_dtype;
@@ -2335,7 +2336,7 @@ struct wfst_decoder {
   int launch_workgroups = 0;           // most workgroups a launch gets (wfst_set_launch_workgroups); 0: one per list entry
   // clusters (several workgroups per channel): memory of their workgroups, one area per batch slot (and
   // one for the calls that name channels), allocated by the first launch that needs it
-  struct ClusterArea { size_t wgs = 0, cand = 0; ClusterArgs a{}; };
+  struct ClusterArea { size_t wgs = 0, cand = 0, boxes = 0; ClusterArgs a{}; };
   std::vector<ClusterArea> areas;
   unsigned launch_seq = 0;
   int n_cu = 0;
@@ -2582,7 +2583,7 @@ int alloc_channels(wfst_decoder *d) {
   HIP_TRY(d, hipMemset(c.boost_from_to, 0, N * kBoostSlots * sizeof(unsigned)));
   HIP_TRY(d, hipHostMalloc(reinterpret_cast<void **>(&d->h_boost), N * kBoostStage * sizeof(int)));
   d->boost_on_dev.assign(N, 0);
-  if ((rc = dev_alloc(d, &d->d_params, ((size_t)d->n_slots + 1) * (6 * N + 2)))) return rc;
+  if ((rc = dev_alloc(d, &d->d_params, ((size_t)d->n_slots + 1) * (6 * N + 2 + kXcds)))) return rc;
   if ((rc = dev_alloc(d, &d->d_lat_ctr, (size_t)2))) return rc;
   if (o.keep_token_records) {                   // one entry per token set of every channel (a call may take them all)
     if ((rc = dev_alloc(d, &d->d_set_links, N * ((size_t)c.max_frames + 1) + 2))) return rc;
@@ -2628,37 +2629,40 @@ int plan_clusters(wfst_decoder *d, const std::vector<int> &frames, int max_activ
     const float t = most * t_us[lg];
     if (lg == 0 || t < best_t) { best = lg; best_t = t; }
   }
-  if (d->g.earc8 || frames[0] == 0) best = 0;        // (narrow records, a mere initialisation or result: one workgroup each)
+  // (narrow records, a mere initialisation or result, a part of the chip: one workgroup each)
+  if (d->g.earc8 || frames[0] == 0 || d->n_cu != 32 * kXcds) best = 0;
   else if (d->cluster_size > 0)
     for (best = 0; (2 << best) <= std::min(d->cluster_size, budget);) ++best;
   n_clusters = std::min(n, std::max(1, budget >> best));
   return 1 << best;
 }
 
-int cluster_area(wfst_decoder *d, int slot_id, int n_wg, int G, ClusterArgs &out) {
+int cluster_area(wfst_decoder *d, int slot_id, int n_clusters, int n_wg, int G, ClusterArgs &out) {
   if (d->areas.empty()) d->areas.resize((size_t)d->n_slots + 1);
   auto &ar = d->areas[slot_id];
   const size_t qc = (size_t)d->c.qcap, region = (size_t)d->c.region_cap;
   const int seg_cap = (int)(region * (size_t)std::max(1, 4 / G));
-  const size_t cand = (size_t)n_wg * 2 * G * (size_t)seg_cap;
+  const size_t w = (size_t)n_clusters * G, cand = w * 2 * G * (size_t)seg_cap, boxes = (size_t)n_wg;
   int rc;
-  if (ar.wgs < (size_t)n_wg) {
-    const size_t w = (size_t)n_wg;
+  if (ar.wgs < w) {
     if ((rc = dev_alloc(d, &ar.a.tok, w * 2 * qc))) return rc;
     if ((rc = dev_alloc(d, &ar.a.gi, w * 2 * qc))) return rc;
     if ((rc = dev_alloc(d, &ar.a.wl, w * 2 * qc))) return rc;
-    if ((rc = dev_alloc(d, &ar.a.box, w * 2 * kBoxWords))) return rc;
-    if ((rc = dev_alloc(d, &ar.a.hello, w * 2))) return rc;
-    HIP_TRY(d, hipMemset(ar.a.hello, 0, w * 2 * sizeof(unsigned long long)));
-    HIP_TRY(d, hipDeviceSynchronize());
     ar.wgs = w;
+  }
+  if (ar.boxes < boxes) {
+    if ((rc = dev_alloc(d, &ar.a.box, boxes * 2 * kBoxWords))) return rc;
+    if ((rc = dev_alloc(d, &ar.a.hello, boxes * 2))) return rc;
+    HIP_TRY(d, hipMemset(ar.a.hello, 0, boxes * 2 * sizeof(unsigned long long)));
+    HIP_TRY(d, hipDeviceSynchronize());
+    ar.boxes = boxes;
   }
   if (ar.cand < cand) {
     if ((rc = dev_alloc(d, &ar.a.cand, cand))) return rc;
     ar.cand = cand;
   }
   out = ar.a;
-  out.G = G; out.seg_cap = seg_cap; out.qcap = (int)qc; out.seq = ++d->launch_seq; out.ticks = 5000;
+  out.G = G; out.n_clusters = n_clusters; out.seg_cap = seg_cap; out.qcap = (int)qc; out.seq = ++d->launch_seq; out.ticks = 5000;
   return WFST_OK;
 }
 
@@ -2684,16 +2688,16 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
   int n_wg = d->launch_workgroups > 0 ? std::min(n, d->launch_workgroups) : n;
   ClusterArgs cl{};
   if (G > 1) {
-    n_wg = n_clusters * G;
-    const int rca = cluster_area(d, slot_id, n_wg, G, cl);
+    n_wg = (n_clusters + kXcds - 1) / kXcds * kXcds * G;     // as many on every XCD
+    const int rca = cluster_area(d, slot_id, n_clusters, n_wg, G, cl);
     if (rca) return rca;
   }
   // (the lists live on the device until the kernel ends, since its workgroups read them as they go:
   // one area per batch slot, and one for the calls that name channels; calls that share an area do
   // not overlap in time, so the stream orders this copy after the last kernel that read the area)
-  int *slot = d->d_params + (size_t)slot_id * (6 * N + 2);
+  int *slot = d->d_params + (size_t)slot_id * (6 * N + 2 + kXcds);
   std::vector<int> &pack = d->h_params[d->ring_pos];
-  pack.resize(6 * (size_t)n + 2);
+  pack.assign(6 * (size_t)n + 2 + kXcds, 0);
   std::copy(chan.begin(), chan.end(), pack.begin());
   std::copy(nfr.begin(), nfr.end(), pack.begin() + n);
   std::copy(io.begin(), io.end(), pack.begin() + 2 * n);
@@ -2701,7 +2705,7 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
     pack[3 * (size_t)n + i] = (int)d->cur_capn[chan[i]];
     std::memcpy(&pack[4 * (size_t)n + 2 + 2 * (size_t)i], &d->cur_start[chan[i]], sizeof(unsigned long long));
   }
-  pack[4 * (size_t)n] = n_wg / G; pack[4 * (size_t)n + 1] = 0;
+  pack[4 * (size_t)n] = G > 1 ? 0 : n_wg;
   d->ring_pos = (d->ring_pos + 1) % wfst_decoder::kRing;
   HIP_TRY(d, hipMemcpyAsync(slot, pack.data(), pack.size() * sizeof(int), hipMemcpyHostToDevice, st));
   a.lists = slot; a.n_jobs = n;
