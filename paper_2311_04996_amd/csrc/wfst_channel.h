@@ -117,7 +117,7 @@ struct Cx {                   // block-uniform view of one channel
   // cluster
   int G, lg, me, seg_cap;     // (a cluster that came out smaller than planned has larger segments)
   size_t seg_stride;          // records of one workgroup's segments, all owners
-  unsigned xc;                // exchanges so far
+  unsigned xc, hc;            // exchanges, and histogram exchanges, so far
   unsigned long long *box0;   // slot 0's mailbox
   // own tokens
   int n, n_front, n_emit;     // [0, n_front): not in simple states; [n_front, n_emit): simple; the rest: made by the closure
@@ -183,6 +183,9 @@ __device__ __forceinline__ unsigned poll(Smem2 &sm, const unsigned long long *p,
 }
 __device__ __forceinline__ unsigned long long *box_of(const Cx &x, int r) {
   return x.box0 + ((size_t)r * 2 + (x.xc & 1u)) * kBoxWords;
+}
+__device__ __forceinline__ unsigned long long *hist_of(const Cx &x, int r) {
+  return x.box0 + ((size_t)r * 2 + (x.hc & 1u)) * kBoxWords + kBoxHist;
 }
 __device__ __forceinline__ void post(const Cx &x, int word, unsigned v) {
   astore(box_of(x, x.me) + word, ((unsigned long long)x.xc << 32) | v);
@@ -855,16 +858,18 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
     // ---- cutoff from the histogram of recombined tokens of the whole cluster
     if (kCl) {
       ++x.xc;
-      // two bins per word, 24 bits each, and 16 bits of the tag (a word is posted in every such exchange)
-      if (tid < 128) astore(box_of(x, x.me) + kBoxHist + tid, ((unsigned long long)(x.xc & 0xffffu) << 48) | ((unsigned long long)sm.hist[2 * tid + 1] << 24) | sm.hist[2 * tid]);
+      // two bins per word, 24 bits each, and a tag of 16 bits: histogram exchanges have a number and a parity of
+      // their own, so that a word always replaces the one of two such exchanges ago and a short tag is enough
+      ++x.hc;
+      if (tid < 128) astore(hist_of(x, x.me) + tid, ((unsigned long long)(x.hc & 0xffffu) << 48) | ((unsigned long long)sm.hist[2 * tid + 1] << 24) | sm.hist[2 * tid]);
       if (tid >= 128 && tid < 130) post(x, kBoxSel + tid - 128, tid == 128 ? (unsigned)(k_sel | (sm.overfull << 16)) : (unsigned)n_sel);
     }
     clear_table(sm);
     if (kCl) {
       if (tid < x.G * 128) {
-        const unsigned long long *p = box_of(x, tid >> 7) + kBoxHist + (tid & 127);
+        const unsigned long long *p = hist_of(x, tid >> 7) + (tid & 127);
         unsigned long long v;
-        for (int spins = 0; (unsigned)((v = aload(p)) >> 48) != (x.xc & 0xffffu); ++spins)
+        for (int spins = 0; (unsigned)((v = aload(p)) >> 48) != (x.hc & 0xffffu); ++spins)
           if ((spins & 1023) == 1023 && (spins > kSpins || __hip_atomic_load(&sm.dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))) { sm.dead = 1; break; }
         *reinterpret_cast<uint2 *>(&sm.v.s.gh[tid >> 7][2 * (tid & 127)]) = make_uint2((unsigned)v & 0xffffffu, (unsigned)(v >> 24) & 0xffffffu);
       }
@@ -1410,14 +1415,23 @@ __device__ __forceinline__ void trace2(Cx &x, const LaunchArgs &a, int io, const
   __syncthreads();
 }
 
-// The next entry of the launch's list (for all workgroups of a cluster); ends with a barrier.
+// The next entry of the launch's list (for all workgroups of a cluster); ends with a barrier.  The first
+// workgroup takes it when the others have come here too: an entry without a frame or a result has no other
+// exchange, and a mailbox keeps the words of two exchanges only, so the first workgroup could be two
+// entries ahead and overwrite a word that another has yet to read.  (1 us per utterance.)
 template <bool kCl>
 __device__ __forceinline__ int next_job2(Cx &x, const LaunchArgs &a) {
   Smem2 &sm = x.sm;
-  if (kCl) ++x.xc;
+  if (kCl) {
+    ++x.xc;
+    if (x.me == 0) {
+      if (threadIdx.x > 0 && (int)threadIdx.x < x.G) poll(sm, box_of(x, threadIdx.x), x.xc);
+      __syncthreads();
+    }
+  }
   if (threadIdx.x == 0) {
     if (!kCl || x.me == 0) { sm.job = atomicAdd(a.lists + 4 * a.n_jobs, 1); if (kCl) post(x, 0, (unsigned)sm.job); }
-    else sm.job = (int)poll(sm, box_of(x, 0), x.xc);
+    else { post(x, 0, 0u); sm.job = (int)poll(sm, box_of(x, 0), x.xc); }
   }
   __syncthreads();
   const int job = uni(sm.job);
@@ -1442,7 +1456,7 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
   }
   Cx x{g, c, w, sm};
   int job = blockIdx.x;
-  x.G = 1; x.lg = 0; x.me = 0; x.xc = 0;
+  x.G = 1; x.lg = 0; x.me = 0; x.xc = 0; x.hc = 0;
   if (kCl) {
     // Clusters are formed on every XCD from the workgroups that start there, in the order in which they
     // start, and nobody waits for one that has not started: the first of a cluster waits a

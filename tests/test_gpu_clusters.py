@@ -61,3 +61,24 @@ def test_a_stream_whose_chunks_are_decoded_by_different_numbers_of_workgroups(to
     cnt, dig = dec.debug_frame_digests(0)
     assert (cnt == c2_refs[b].digest_count[:n + 1]).all() and (dig == c2_refs[b].digest_sum[:n + 1]).all()
     dec.close()
+
+
+def test_calls_with_many_entries_that_have_nothing_to_do(torch_cuda, c2, c2_refs):
+    """Entries without a frame have no exchange but the one that hands them out: the workgroups of
+    a cluster go through a row of them, and then decode on as if they had not been there."""
+    from paper_2311_04996_amd import Decoder
+    n_ch, n = 96, 48
+    b = int(np.argmax(c2.lengths))
+    dec = Decoder(c2.graph, max_channels=n_ch, max_frames=n, max_active_hint=c2.max_active, record_digests=True)
+    dec.debug_set_cluster_size(8)
+    dec.set_launch_workgroups(8)                  # one cluster takes them all
+    dec.init_channels(list(range(n_ch)), c2.beam, c2.max_active)
+    ll = torch_cuda.from_numpy(np.ascontiguousarray(c2.loglikes[b:b + 1, :n])).cuda()
+    busy = (0, 41, 95)
+    for t in range(0, n, 8):
+        rows = ll[:, t:t + 8].expand(n_ch, -1, -1).contiguous()
+        dec.advance_chunk(list(range(n_ch)), rows, [8 if ch in busy else 0 for ch in range(n_ch)])
+    for ch in busy:
+        cnt, dig = dec.debug_frame_digests(ch)
+        assert (cnt[:n + 1] == c2_refs[b].digest_count[:n + 1]).all() and (dig[:n + 1] == c2_refs[b].digest_sum[:n + 1]).all()
+    dec.close()
