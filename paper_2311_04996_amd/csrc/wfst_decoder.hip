@@ -4,7 +4,8 @@
 // the whole per-frame iteration of the paper's Section "Algorithm description" on the
 // device: ExpandArcs over emitting arcs -> recombination -> Prune (beam + max-active) ->
 // epsilon closure -> backpointer store, frame after frame, synchronising only with
-// workgroup barriers.  There is no per-frame kernel launch (the overhead the paper removes
+// workgroup barriers.  (Where a call leaves compute units idle, several workgroups decode a
+// channel together: wfst_channel.h.)  There is no per-frame kernel launch (the overhead the paper removes
 // with CUDA graphs) and no per-frame device-to-host copy (the lattice stays in HBM and the
 // traceback runs on the device).
 //
@@ -2336,7 +2337,7 @@ struct wfst_decoder {
   int launch_workgroups = 0;           // most workgroups a launch gets (wfst_set_launch_workgroups); 0: one per list entry
   // clusters (several workgroups per channel): memory of their workgroups, one area per batch slot (and
   // one for the calls that name channels), allocated by the first launch that needs it
-  struct ClusterArea { size_t wgs = 0, cand = 0, boxes = 0; ClusterArgs a{}; };
+  struct ClusterArea { size_t wgs = 0, cand = 0, boxes = 0; bool failed = false; std::vector<std::pair<void *, size_t>> mem; ClusterArgs a{}; };
   std::vector<ClusterArea> areas;
   unsigned launch_seq = 0;
   int n_cu = 0;
@@ -2637,29 +2638,50 @@ int plan_clusters(wfst_decoder *d, const std::vector<int> &frames, int max_activ
   return 1 << best;
 }
 
+void dev_free(wfst_decoder *d, void *p, size_t bytes) {
+  const auto it = std::find(d->allocs.begin(), d->allocs.end(), p);
+  if (!p || it == d->allocs.end()) return;
+  d->allocs.erase(it);
+  d->dev_bytes -= (int64_t)std::max<size_t>(bytes, 1);
+  (void)hipFree(p);
+}
+void free_cluster_area(wfst_decoder *d, wfst_decoder::ClusterArea &ar) {
+  for (auto &m : ar.mem) dev_free(d, m.first, m.second);
+  ar.mem.clear();
+  ar.wgs = ar.cand = ar.boxes = 0; ar.a = ClusterArgs{};
+}
+
+// Memory of a launch's clusters.  Returns an error if there is none: the launch then does without clusters.
 int cluster_area(wfst_decoder *d, int slot_id, int n_clusters, int n_wg, int G, ClusterArgs &out) {
   if (d->areas.empty()) d->areas.resize((size_t)d->n_slots + 1);
   auto &ar = d->areas[slot_id];
   const size_t qc = (size_t)d->c.qcap, region = (size_t)d->c.region_cap;
   const int seg_cap = (int)(region * (size_t)std::max(1, 4 / G));
   const size_t w = (size_t)n_clusters * G, cand = w * 2 * G * (size_t)seg_cap, boxes = (size_t)n_wg;
-  int rc;
-  if (ar.wgs < w) {
-    if ((rc = dev_alloc(d, &ar.a.tok, w * 2 * qc))) return rc;
-    if ((rc = dev_alloc(d, &ar.a.gi, w * 2 * qc))) return rc;
-    if ((rc = dev_alloc(d, &ar.a.wl, w * 2 * qc))) return rc;
-    ar.wgs = w;
-  }
-  if (ar.boxes < boxes) {
-    if ((rc = dev_alloc(d, &ar.a.box, boxes * 2 * kBoxWords))) return rc;
-    if ((rc = dev_alloc(d, &ar.a.hello, boxes * 2))) return rc;
-    HIP_TRY(d, hipMemset(ar.a.hello, 0, boxes * 2 * sizeof(unsigned long long)));
+  if (ar.failed) return WFST_ERR_OOM;
+  if (ar.wgs < w || ar.boxes < boxes || ar.cand < cand) {
+    // at least twice as much as before, so that calls of growing size come here a few times only; no
+    // launch that uses the old memory is under way when it is given back
     HIP_TRY(d, hipDeviceSynchronize());
-    ar.boxes = boxes;
-  }
-  if (ar.cand < cand) {
-    if ((rc = dev_alloc(d, &ar.a.cand, cand))) return rc;
-    ar.cand = cand;
+    const size_t cu = (size_t)d->n_cu;
+    const size_t nw = std::max({w, ar.wgs, std::min(2 * ar.wgs, cu)}), nb = std::max({boxes, ar.boxes, std::min(2 * ar.boxes, cu)});
+    const size_t nc = std::max({cand, ar.cand, std::min(2 * ar.cand, cu * 2 * kMaxG * region)});
+    free_cluster_area(d, ar);
+    auto get = [&](auto *&p, size_t n) {
+      const int e = dev_alloc(d, &p, n);
+      if (!e) ar.mem.emplace_back(p, n * sizeof(*p));
+      return e;
+    };
+    int rc = get(ar.a.tok, nw * 2 * qc);
+    if (!rc) rc = get(ar.a.gi, nw * 2 * qc);
+    if (!rc) rc = get(ar.a.wl, nw * 2 * qc);
+    if (!rc) rc = get(ar.a.box, nb * 2 * kBoxWords);
+    if (!rc) rc = get(ar.a.hello, nb * 2);
+    if (!rc) rc = get(ar.a.cand, nc);
+    if (rc) { free_cluster_area(d, ar); ar.failed = true; d->err.clear(); return rc; }
+    HIP_TRY(d, hipMemset(ar.a.hello, 0, nb * 2 * sizeof(unsigned long long)));
+    HIP_TRY(d, hipDeviceSynchronize());
+    ar.wgs = nw; ar.boxes = nb; ar.cand = nc;
   }
   out = ar.a;
   out.G = G; out.n_clusters = n_clusters; out.seg_cap = seg_cap; out.qcap = (int)qc; out.seq = ++d->launch_seq; out.ticks = 5000;
@@ -2688,9 +2710,11 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
   int n_wg = d->launch_workgroups > 0 ? std::min(n, d->launch_workgroups) : n;
   ClusterArgs cl{};
   if (G > 1) {
-    n_wg = (n_clusters + kXcds - 1) / kXcds * kXcds * G;     // as many on every XCD
-    const int rca = cluster_area(d, slot_id, n_clusters, n_wg, G, cl);
-    if (rca) return rca;
+    const int n_all = (n_clusters + kXcds - 1) / kXcds * kXcds * G;     // as many on every XCD
+    const int rca = cluster_area(d, slot_id, n_clusters, n_all, G, cl);
+    if (rca == WFST_ERR_OOM) G = 1;                          // no memory for clusters: a workgroup per utterance, as ever
+    else if (rca) return rca;
+    else n_wg = n_all;
   }
   // (the lists live on the device until the kernel ends, since its workgroups read them as they go:
   // one area per batch slot, and one for the calls that name channels; calls that share an area do

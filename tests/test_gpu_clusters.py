@@ -82,3 +82,23 @@ def test_calls_with_many_entries_that_have_nothing_to_do(torch_cuda, c2, c2_refs
         cnt, dig = dec.debug_frame_digests(ch)
         assert (cnt[:n + 1] == c2_refs[b].digest_count[:n + 1]).all() and (dig[:n + 1] == c2_refs[b].digest_sum[:n + 1]).all()
     dec.close()
+
+
+def test_memory_of_the_clusters_is_given_back_as_calls_grow(torch_cuda, c2, c2_refs):
+    """Calls of growing size: the decoder's memory stays within twice what the largest call alone takes."""
+    from paper_2311_04996_amd import Decoder
+    b = int(np.argmax(c2.lengths))
+    ll = torch_cuda.from_numpy(np.ascontiguousarray(c2.loglikes[b:b + 1, :16])).cuda()
+    held = []
+    for sizes in ((24,), (1, 2, 3, 5, 8, 12, 16, 20, 24)):
+        dec = Decoder(c2.graph, max_channels=24, max_frames=16, max_active_hint=c2.max_active, record_digests=True)
+        dec.debug_set_cluster_size(8)
+        start = dec.device_bytes()
+        for n in sizes:
+            dec.init_channels(list(range(n)), c2.beam, c2.max_active)
+            dec.advance_chunk(list(range(n)), ll.expand(n, -1, -1).contiguous(), [16] * n)
+            cnt, dig = dec.debug_frame_digests(n - 1)
+            assert (cnt[:17] == c2_refs[b].digest_count[:17]).all() and (dig[:17] == c2_refs[b].digest_sum[:17]).all()
+        held.append(dec.device_bytes() - start)
+        dec.close()
+    assert 0 < held[0] and held[1] <= 2 * held[0]
