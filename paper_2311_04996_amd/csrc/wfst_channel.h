@@ -1045,7 +1045,8 @@ __device__ __forceinline__ void apply2(Cx &x, int win, const int4 &rec, int slot
 // improved in the previous round that have epsilon arcs.  The set's tokens that an epsilon arc can
 // enter sit in the LDS table (put there when they were made), so a round's candidates meet them
 // directly.  If they do not fit, every round's candidates go into an empty table and all tokens look
-// themselves up.  On entry wl0 holds sm.made[2] entries; ends behind an exchange in which nobody had a candidate.
+// themselves up.  On entry wl0 holds sm.made[2] entries; ends behind an exchange in which nobody had a candidate, or
+// somebody an overflow.
 template <bool kCl, bool kBoost, bool kProf>
 __device__ __forceinline__ void closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat_base, const Cutoff &cut) {
   Smem2 &sm = x.sm;
@@ -1126,6 +1127,9 @@ __device__ __forceinline__ void closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
     post_sizes<kCl>(x);
     take_sizes<kCl>(x);
     if (!uni(sm.x_any) || (kCl && uni(sm.dead))) break;
+    // An overflow ends the closure, and with the frame the channel: a token that found no room has left the
+    // number of its candidate in the table, which would now be looked for among this round's candidates.
+    if (uni(sm.x_status)) break;
     const int n_own = uni(sm.seg_pre[S]);
     mark<kProf>(x, kPhEpsRecombine);
     if (n_own > 0) {

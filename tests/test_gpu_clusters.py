@@ -102,3 +102,51 @@ def test_memory_of_the_clusters_is_given_back_as_calls_grow(torch_cuda, c2, c2_r
         held.append(dec.device_bytes() - start)
         dec.close()
     assert 0 < held[0] and held[1] <= 2 * held[0]
+
+
+def _closure_overflow_graph(middle_first):
+    """Start -> 6,000 dead ends and a hub, all over label 1, or one state over label 2.  The hub reaches 4,000
+    states over epsilon arcs in one closure round, and 2,000 of them a second time, at the same cost, in the
+    next one over eight states in the middle, whose arc ids are lower than the hub's or higher."""
+    from workloads.graphs import _csr
+    n_dead, n_z, n_mid = 6000, 4000, 8
+    mid0 = 1 if middle_first else 2
+    hub = 1 + n_mid if middle_first else 1
+    one, z0 = 2 + n_mid, 3 + n_mid
+    dead0 = z0 + n_z
+    S = dead0 + n_dead
+    src, dst, il = [], [], []
+
+    def arcs(s, d, label):
+        src.extend([s] * len(d)), dst.extend(d), il.extend([label] * len(d))
+    arcs(0, list(range(dead0, S)) + [hub], 1)
+    arcs(0, [one], 2)
+    arcs(hub, list(range(z0, z0 + n_z)) + list(range(mid0, mid0 + n_mid)), 0)
+    for k in range(n_mid):
+        arcs(mid0 + k, list(range(z0 + 250 * k, z0 + 250 * (k + 1))), 0)
+    n = len(src)
+    return _csr(S, 0, 2, np.array(src), np.array(dst), np.array(il), np.zeros(n, np.int64), np.zeros(n))
+
+
+@pytest.mark.parametrize("cluster", [1, 2, 4, 8], indirect=True)
+def test_a_closure_that_runs_out_of_room_ends_there(torch_cuda, cluster):
+    """10,009 tokens, 8,192 places: the channel is flagged and stops.  What the next closure round would
+    compare its exact ties with, the candidates of tokens that found no room, is gone by then."""
+    from paper_2311_04996_amd import Decoder, FLAG_CAPACITY, FLAG_DEAD
+    for middle_first in (False, True):
+        g = _closure_overflow_graph(middle_first)
+        dec = Decoder(g, max_channels=2, max_frames=2, max_active_hint=1000, lattice_bytes_per_channel=1 << 18,
+                      record_digests=True)
+        both = np.zeros((2, 2, 2), np.float32)
+        both[1, :, 0] = -1000.0                      # the second utterance keeps to the one state
+        lengths = np.array([1, 1], np.int32)
+        _, nwords, cost, flags = dec.decode_batch(torch_cuda.from_numpy(both).cuda(), lengths, 5.0, 5000)
+        torch_cuda.cuda.synchronize()
+        assert flags.tolist()[0] & (FLAG_CAPACITY | FLAG_DEAD) == FLAG_CAPACITY | FLAG_DEAD and int(nwords[0]) == 0
+        (ref,) = parity.oracle_batch(g, both[1:], lengths[1:], 5.0, 5000)
+        cnt, dig = dec.debug_frame_digests(1)
+        assert int(flags[1]) == ref.flags and float(cost[1]) == ref.cost
+        assert (cnt == ref.digest_count).all() and (dig == ref.digest_sum).all()
+        dec.close()
+        # with room for all of them the ties are decided as the oracle decides them
+        parity.check_batch(torch_cuda, g, both, lengths, 5.0, 5000, max_active_hint=10000)
