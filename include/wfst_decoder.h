@@ -414,6 +414,11 @@ int32_t wfst_debug_set_phase_timing(wfst_decoder *dec, int32_t on);
 /* Workgroups that decode an utterance together, for tests and measurements: 1, 2, 4 or 8 (fewer where the
  * launch does not get as many), 0 (the default): chosen for every launch.  Results do not depend on it. */
 int32_t wfst_debug_set_cluster_size(wfst_decoder *dec, int32_t n);
+/* The waits of such workgroups, for tests: how long the first one waits for the others to start (10 ns units,
+ * at most the default, 50 us; with 0 most utterances are decoded by fewer than planned, with the same result), and how
+ * often one looks for another's word before it gives up (at most the default, seconds).  Negative: the
+ * default.  An utterance whose workgroups have given up is reported with WFST_FLAG_CAPACITY | WFST_FLAG_DEAD. */
+int32_t wfst_debug_set_cluster_waits(wfst_decoder *dec, int32_t start_ticks, int32_t polls);
 int32_t wfst_debug_phase_ticks(wfst_decoder *dec, int64_t ticks[16], int32_t reset);
 
 /* Device memory the decoder holds, in bytes (graph + channel state). */

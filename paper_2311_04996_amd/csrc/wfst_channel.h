@@ -38,9 +38,11 @@ constexpr unsigned kRefTok = 0x80000000u;     // low word of a table value: a to
 constexpr unsigned kRefStay = 0xFFFFFFFFu;    // ... or: a self-loop candidate won here
 constexpr int kBoxWords = 512;                // mailbox words of one workgroup and exchange parity
 constexpr int kBoxAux = 8, kBoxSel = 12, kBoxHist = 16;
-constexpr int kSpins = 1 << 23;               // most polls of a wait (seconds)
+constexpr int kPolls = 1 << 23;               // most polls of a wait (seconds)
+constexpr int kStartTicks = 5000;             // how long the first workgroup of a cluster waits for the others (50 us)
 constexpr int kXcds = 8;                      // XCDs of the chip
 constexpr int kHwXccId = 20 | (4 - 1) << 11;   // hardware register XCC_ID, bits 0-3: the XCD a wave runs on
+constexpr int kListInts = 2 + kXcds + 2;       // counters in a launch's lists (an even number: 64-bit entries before them)
 constexpr int kAux = 4;                       // best cost, status, tokens made by the closure, smallest cost in a simple state
 
 struct ClusterArgs {                          // device memory of the workgroups, by ticket of the cluster and number in it
@@ -50,6 +52,7 @@ struct ClusterArgs {                          // device memory of the workgroups
   int seg_cap;                                // records per segment
   int qcap;
   unsigned ticks;                             // how long the first workgroup of a cluster waits for the others (10 ns)
+  int polls;                                  // how often a workgroup looks for another's word before it gives up
   int4 *cand;                                 // [workgroup][2][G][seg_cap]
   int2 *tok;                                  // [workgroup][2][qcap] the workgroup's own tokens {key + flags, cost}
   int *gi;                                    // [workgroup][2][qcap] their numbers in the set
@@ -85,13 +88,14 @@ struct Smem2 {
   int xn[kMaxG * kMaxG];                      // segment sizes of the cluster: [writer][owner]
   int seg_pre[kMaxG + 1];                     // own candidates: prefix sums over the segments
   unsigned x_best, x_minsimple;
-  int x_any, x_made, x_status;
+  int x_any, x_status, x_made;                // (the first two are read together)
   unsigned best_ord, min_simple;
   float stay_ac;
   int n_hub, next_run, done_waves;
   int made[4];                                // tokens made so far: outside simple states, in simple states; worklist entries; table entries
   int n_loc, n_win, n_in;
-  int map_bad, status, overfull, dead;
+  int map_bad, status, overfull;
+  int polls, dead;                            // most polls of a wait; one has ended without its word
   int k_sel, n_sel, n_sel_c, k_keep, redo, n_emit, n_emit_all, gbase;
   unsigned ratio;
   int path_frames, trace_from, trace_words, sel_idx, job;
@@ -172,14 +176,19 @@ template <bool kCl> __device__ __forceinline__ int2 get_lat(const int2 *p) {
   return make_int2((int)(unsigned)a, (int)(a >> 32));
 }
 
-// Wait until the word carries the tag; returns its value.  The wait is bounded (seconds): a partner
-// that never posts ends the channel with an error instead of hanging the launch.
-__device__ __forceinline__ unsigned poll(Smem2 &sm, const unsigned long long *p, unsigned tag) {
-  for (int spins = 0;; ++spins) {
+// Wait until the word carries the tag (its bits from kShift on); returns the word.  The wait is bounded
+// (seconds): a partner that never posts ends the channel with an error instead of hanging the
+// launch.  The word is then 0 (no tag is) and sm.dead is set.
+template <int kShift>
+__device__ __forceinline__ unsigned long long poll_word(Smem2 &sm, const unsigned long long *p, unsigned tag, int polls) {
+  for (int n = 0;; ++n) {
     const unsigned long long v = aload(p);
-    if ((unsigned)(v >> 32) == tag) return (unsigned)v;
-    if ((spins & 1023) == 1023 && (spins > kSpins || __hip_atomic_load(&sm.dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))) { sm.dead = 1; return 0; }
+    if ((unsigned)(v >> kShift) == tag) return v;
+    if (n >= polls || ((n & 1023) == 1023 && __hip_atomic_load(&sm.dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))) { sm.dead = 1; return 0; }
   }
+}
+__device__ __forceinline__ unsigned poll(Smem2 &sm, const unsigned long long *p, unsigned tag) {
+  return (unsigned)poll_word<32>(sm, p, tag, sm.polls);
 }
 __device__ __forceinline__ unsigned long long *box_of(const Cx &x, int r) {
   return x.box0 + ((size_t)r * 2 + (x.xc & 1u)) * kBoxWords;
@@ -222,8 +231,13 @@ __device__ __forceinline__ void take_sizes(Cx &x) {
       const int G = x.G, lg = x.lg;
       unsigned v = 0;
       const int r = lane >> lg, p = lane & (G - 1);
-      if (lane < G * G) { v = poll(sm, box_of(x, r) + p, x.xc); sm.xn[r * kMaxG + p] = (int)min(v, (unsigned)x.seg_cap); }
-      const unsigned long long any = __ballot(v != 0);
+      bool lost = false;
+      if (lane < G * G) {
+        const unsigned long long w = poll_word<32>(sm, box_of(x, r) + p, x.xc, sm.polls);
+        v = (unsigned)w; lost = w == 0ull;
+        sm.xn[r * kMaxG + p] = (int)min(v, (unsigned)x.seg_cap);
+      }
+      const unsigned long long any = __ballot(lost) ? 0ull : __ballot(v != 0);
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
       int run = 0;
@@ -238,14 +252,15 @@ __device__ __forceinline__ void take_sizes(Cx &x) {
       if (lane == kRegions - 1) sm.x_any = inc > 0;
     }
   } else if (kCl && tid < 128) {
-    unsigned v = 0;
+    unsigned long long w = 0;
     const int which = lane & 3;
     const bool mine = lane < kAux * x.G;
-    if (mine) v = poll(sm, box_of(x, lane >> 2) + kBoxAux + which, x.xc);
+    if (mine) w = poll_word<32>(sm, box_of(x, lane >> 2) + kBoxAux + which, x.xc, sm.polls);
+    const unsigned v = (unsigned)w;
     const unsigned best = wave_min(mine && which == 0 ? v : kOrdNone), ms = wave_min(mine && which == 3 ? v : kOrdNone);
     const unsigned made = wave_sum(mine && which == 2 ? v : 0u);
     const unsigned st_l = __ballot(mine && which == 1 && (v & kStLattice)) != 0ull ? kStLattice : 0;
-    const unsigned st_c = __ballot(mine && which == 1 && (v & kStCapacity)) != 0ull ? kStCapacity : 0;
+    const unsigned st_c = __ballot(mine && (w == 0ull || (which == 1 && (v & kStCapacity)))) != 0ull ? kStCapacity : 0;
     if (lane == 0) { sm.x_best = best; sm.x_minsimple = ms; sm.x_made = (int)made; sm.x_status = (int)(st_l | st_c); }
   }
   __syncthreads();
@@ -698,6 +713,8 @@ __device__ __forceinline__ void make2(Cx &x, int ok, int next, int costbits, int
 // as many table passes as they need, and the records are read again; a selection that turns out too
 // small to decide the cutoff, or a pass that meets too many destinations, is done again (all workgroups
 // of a cluster decide that from the same numbers).
+// A cluster that has broken up gets no tokens: what it knows of the others' candidates and
+// histograms is not complete, and places in the set come from them.
 template <bool kCl, bool kProf, bool kOpt>
 __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2 *NQ, int *NGI, unsigned lat_base, Cutoff &cut, bool init) {
   Smem2 &sm = x.sm;
@@ -868,9 +885,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
     if (kCl) {
       if (tid < x.G * 128) {
         const unsigned long long *p = hist_of(x, tid >> 7) + (tid & 127);
-        unsigned long long v;
-        for (int spins = 0; (unsigned)((v = aload(p)) >> 48) != (x.hc & 0xffffu); ++spins)
-          if ((spins & 1023) == 1023 && (spins > kSpins || __hip_atomic_load(&sm.dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))) { sm.dead = 1; break; }
+        const unsigned long long v = poll_word<48>(sm, p, x.hc & 0xffffu, sm.polls);
         *reinterpret_cast<uint2 *>(&sm.v.s.gh[tid >> 7][2 * (tid & 127)]) = make_uint2((unsigned)v & 0xffffffu, (unsigned)(v >> 24) & 0xffffffu);
       }
       if (tid < 64) {
@@ -922,6 +937,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
       }
       mine = wave_sum(mine);
       if (kCl) { before = wave_sum(before); all = wave_sum(all); } else all = mine;
+      if (kCl && sm.dead) { kk = 0; redo = 0; mine = before = all = 0; }
       if (tid == 0) {
         sm.k_keep = kk; sm.redo = redo; sm.n_emit = (int)mine; sm.gbase = (int)before; sm.n_emit_all = (int)min(all, 0x7fffffffu);
         // next frame's selection: enough candidates for max_active distinct destinations
@@ -940,7 +956,6 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
     if (redo == 2) mult *= 2;
     else { k_sel = 256; n_sel = n_own + n_tok; n_sel_c = n_own; }
     __syncthreads();
-    if (kCl && uni(sm.dead)) break;
   }
   cut.k_keep = uni(sm.k_keep);
   mark<kProf>(x, kPhOther);
@@ -1126,10 +1141,10 @@ __device__ __forceinline__ void closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
     mark<kProf>(x, kPhEpsExpand);
     post_sizes<kCl>(x);
     take_sizes<kCl>(x);
-    if (!uni(sm.x_any) || (kCl && uni(sm.dead))) break;
-    // An overflow ends the closure, and with the frame the channel: a token that found no room has left the
-    // number of its candidate in the table, which would now be looked for among this round's candidates.
-    if (uni(sm.x_status)) break;
+    // An overflow (or a cluster that has broken up) ends the closure, and with the frame the channel: a token that
+    // found no room has left the number of its candidate in the table, which would now be looked for among this
+    // round's candidates.
+    if (uni((int)(sm.x_any == 0) | sm.x_status)) break;
     const int n_own = uni(sm.seg_pre[S]);
     mark<kProf>(x, kPhEpsRecombine);
     if (n_own > 0) {
@@ -1326,6 +1341,7 @@ __device__ __forceinline__ void trace2(Cx &x, const LaunchArgs &a, int io, const
       if (lane == 0) { sm.red64 = bf; sm.red64b = br; sm.sel_idx = jf; sm.trace_from = jr; }
     }
     __syncthreads();
+    if (uni(sm.dead)) return;                    // (the entry will be reported as lost)
   }
   const bool any_final = sm.red64 != ~0ull;
   const unsigned long long best = any_final ? sm.red64 : sm.red64b;
@@ -1422,15 +1438,19 @@ __device__ __forceinline__ void trace2(Cx &x, const LaunchArgs &a, int io, const
 // The next entry of the launch's list (for all workgroups of a cluster); ends with a barrier.  The first
 // workgroup takes it when the others have come here too: an entry without a frame or a result has no other
 // exchange, and a mailbox keeps the words of two exchanges only, so the first workgroup could be two
-// entries ahead and overwrite a word that another has yet to read.  (1 us per utterance.)
+// entries ahead and overwrite a word that another has yet to read.  (1 us per utterance.)  A cluster
+// that has broken up takes none, and the first workgroup knows behind this whether the others have
+// done their part of the last entry.
 template <bool kCl>
 __device__ __forceinline__ int next_job2(Cx &x, const LaunchArgs &a) {
   Smem2 &sm = x.sm;
   if (kCl) {
+    if (uni(sm.dead)) return a.n_jobs;
     ++x.xc;
     if (x.me == 0) {
       if (threadIdx.x > 0 && (int)threadIdx.x < x.G) poll(sm, box_of(x, threadIdx.x), x.xc);
       __syncthreads();
+      if (uni(sm.dead)) return a.n_jobs;
     }
   }
   if (threadIdx.x == 0) {
@@ -1440,6 +1460,25 @@ __device__ __forceinline__ int next_job2(Cx &x, const LaunchArgs &a) {
   __syncthreads();
   const int job = uni(sm.job);
   return kCl && uni(sm.dead) ? a.n_jobs : job;
+}
+
+// An entry that no cluster has finished: its channel stops, and its result says so.
+__device__ __forceinline__ void report_lost(const DevChannels &c, const LaunchArgs &a, int ch, int io) {
+  ChanState &s = c.st[ch];
+  const int status = (a.mode & kModeInit ? 0 : s.status) | kStCapacity;
+  s.status = status; s.n_tok = 0; s.path_frames = 0;
+  if (a.mode & kModeInit) { s.frame = -1; s.lat_used = 0; }
+  if (a.mode & kModeFinal) { a.nwords[io] = 0; a.cost[io] = INFINITY; a.flags[io] = status | WFST_FLAG_DEAD; }
+}
+// What the first workgroup of a cluster that has broken up leaves behind: a report for its entry (ch; -1:
+// it has none), and, if the other clusters that have started have gone the same way, for the entries left.
+__device__ __forceinline__ void give_up2(const DevChannels &c, const LaunchArgs &a, const ClusterArgs &w, int ch, int io) {
+  if (threadIdx.x != 0) return;
+  if (ch >= 0) report_lost(c, a, ch, io);
+  int *const n_started = a.lists + 4 * a.n_jobs + 1, *const n_gone = a.lists + 6 * a.n_jobs + 2 + kXcds;
+  const int gone = atomicAdd(n_gone, 1) + 1;
+  if (gone < min(__hip_atomic_load(n_started, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), w.n_clusters)) return;
+  for (int j; (j = atomicAdd(a.lists + 4 * a.n_jobs, 1)) < a.n_jobs;) report_lost(c, a, a.lists[j], a.lists[2 * a.n_jobs + j]);
 }
 
 // ------------------------------------------------------------------ the channel kernel
@@ -1469,7 +1508,7 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
     // XCD needs; clusters without a ticket end.
     const int xcd = (int)__builtin_amdgcn_s_getreg(kHwXccId) & (kXcds - 1);
     const int cap = (int)gridDim.x / kXcds;      // workgroups per XCD: a multiple of w.G
-    if (tid == 0) { sm.job = atomicAdd(a.lists + 6 * a.n_jobs + 2 + xcd, 1); sm.dead = 0; }
+    if (tid == 0) { sm.job = atomicAdd(a.lists + 6 * a.n_jobs + 2 + xcd, 1); sm.polls = w.polls; sm.dead = 0; }
     __syncthreads();
     const int arrival = uni(sm.job);
     if (arrival >= cap) return;
@@ -1496,7 +1535,7 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
         astore(w.hello + 2 * (size_t)s0 + 1, u64_of(sm.job, (int)w.seq));
       } else {
         astore(w.hello + 2 * (size_t)slot, u64_of(1, (int)w.seq));
-        sm.job = (int)poll(sm, w.hello + 2 * (size_t)s0 + 1, w.seq);
+        sm.job = (int)poll_word<32>(sm, w.hello + 2 * (size_t)s0 + 1, w.seq, kPolls);
       }
     }
     __syncthreads();
@@ -1512,6 +1551,7 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
     x.gi = w.gi + (first + x.me) * 2 * c.qcap;
     x.wl0 = w.wl + (first + x.me) * 2 * c.qcap;
     job = next_job2<kCl>(x, a);
+    if (x.me == 0 && uni(sm.dead)) give_up2(c, a, w, -1, 0);
     if (job >= a.n_jobs) return;
   }
   for (;;) {
@@ -1704,8 +1744,8 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
     for (int i = 0; i < 8; ++i) if (sm.ctr[i]) atomicAdd((unsigned long long *)&c.counters[i], (unsigned long long)sm.ctr[i]);
   }
   if (!kCl && !kQueue) break;
-  if (kCl && uni(sm.dead)) break;
   job = next_job2<kCl>(x, a);  // (also: nobody is still reading this channel's tables when the next one's are set up)
+  if (kCl && x.me == 0 && uni(sm.dead)) give_up2(c, a, w, ch, io);
   if (job >= a.n_jobs) break;
   }
 }

@@ -222,7 +222,7 @@ struct LaunchArgs {
   // [channel id][frames to consume][row in loglikes/outputs][entries of the channel's lattice arena],
   // then the first entry no workgroup has taken yet (starts at the number of workgroups; clusters: at 0) and
   // the clusters that have started, then 64-bit [start of the channel's arena in the lattice pool],
-  // then the workgroups that have started, per XCD
+  // then the workgroups that have started, per XCD, the clusters that have broken up, and a pad
   int *lists; int n_jobs;
   const void *ll; long long ll_stride; int V;   // rows of V elements; fp32, or fp16 / bf16 widened when staged
   int ll_dtype;
@@ -2334,6 +2334,7 @@ struct wfst_decoder {
   int phase_timing = 0;                // launches time their phases (wfst_debug_set_phase_timing)
   int cluster_size = 0;                // workgroups per utterance (wfst_debug_set_cluster_size); 0: chosen per launch
   int stream_max_active = 10000;       // what the channels were last initialised with
+  int start_ticks = kStartTicks, polls = kPolls;   // waits of clusters (wfst_debug_set_cluster_waits)
   int launch_workgroups = 0;           // most workgroups a launch gets (wfst_set_launch_workgroups); 0: one per list entry
   // clusters (several workgroups per channel): memory of their workgroups, one area per batch slot (and
   // one for the calls that name channels), allocated by the first launch that needs it
@@ -2584,7 +2585,7 @@ int alloc_channels(wfst_decoder *d) {
   HIP_TRY(d, hipMemset(c.boost_from_to, 0, N * kBoostSlots * sizeof(unsigned)));
   HIP_TRY(d, hipHostMalloc(reinterpret_cast<void **>(&d->h_boost), N * kBoostStage * sizeof(int)));
   d->boost_on_dev.assign(N, 0);
-  if ((rc = dev_alloc(d, &d->d_params, ((size_t)d->n_slots + 1) * (6 * N + 2 + kXcds)))) return rc;
+  if ((rc = dev_alloc(d, &d->d_params, ((size_t)d->n_slots + 1) * (6 * N + kListInts)))) return rc;
   if ((rc = dev_alloc(d, &d->d_lat_ctr, (size_t)2))) return rc;
   if (o.keep_token_records) {                   // one entry per token set of every channel (a call may take them all)
     if ((rc = dev_alloc(d, &d->d_set_links, N * ((size_t)c.max_frames + 1) + 2))) return rc;
@@ -2684,7 +2685,8 @@ int cluster_area(wfst_decoder *d, int slot_id, int n_clusters, int n_wg, int G, 
     ar.wgs = nw; ar.boxes = nb; ar.cand = nc;
   }
   out = ar.a;
-  out.G = G; out.n_clusters = n_clusters; out.seg_cap = seg_cap; out.qcap = (int)qc; out.seq = ++d->launch_seq; out.ticks = 5000;
+  out.G = G; out.n_clusters = n_clusters; out.seg_cap = seg_cap; out.qcap = (int)qc; out.seq = ++d->launch_seq;
+  out.ticks = (unsigned)d->start_ticks; out.polls = d->polls;
   return WFST_OK;
 }
 
@@ -2719,9 +2721,9 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
   // (the lists live on the device until the kernel ends, since its workgroups read them as they go:
   // one area per batch slot, and one for the calls that name channels; calls that share an area do
   // not overlap in time, so the stream orders this copy after the last kernel that read the area)
-  int *slot = d->d_params + (size_t)slot_id * (6 * N + 2 + kXcds);
+  int *slot = d->d_params + (size_t)slot_id * (6 * N + kListInts);
   std::vector<int> &pack = d->h_params[d->ring_pos];
-  pack.assign(6 * (size_t)n + 2 + kXcds, 0);
+  pack.assign(6 * (size_t)n + kListInts, 0);
   std::copy(chan.begin(), chan.end(), pack.begin());
   std::copy(nfr.begin(), nfr.end(), pack.begin() + n);
   std::copy(io.begin(), io.end(), pack.begin() + 2 * n);
@@ -3552,6 +3554,13 @@ int32_t wfst_debug_set_cluster_size(wfst_decoder *d, int32_t n) {
   if (!d) return WFST_ERR_INVALID_ARG;
   if (n != 0 && n != 1 && n != 2 && n != 4 && n != 8) return fail(d, WFST_ERR_INVALID_ARG, "cluster size must be 0, 1, 2, 4 or 8");
   d->cluster_size = n;
+  return WFST_OK;
+}
+
+int32_t wfst_debug_set_cluster_waits(wfst_decoder *d, int32_t start_ticks, int32_t polls) {
+  if (!d) return WFST_ERR_INVALID_ARG;
+  d->start_ticks = start_ticks < 0 ? kStartTicks : std::min(start_ticks, kStartTicks);
+  d->polls = polls < 0 ? kPolls : std::min(polls, kPolls);
   return WFST_OK;
 }
 

@@ -150,3 +150,71 @@ def test_a_closure_that_runs_out_of_room_ends_there(torch_cuda, cluster):
         dec.close()
         # with room for all of them the ties are decided as the oracle decides them
         parity.check_batch(torch_cuda, g, both, lengths, 5.0, 5000, max_active_hint=10000)
+
+
+def test_clusters_smaller_than_planned(torch_cuda, c1, c2, c2_refs, monkeypatch):
+    """The first workgroup of a cluster goes on with those that have started; if it waits for none, clusters of
+    every size below the planned one come up."""
+    import paper_2311_04996_amd as package
+
+    class Impatient(package.Decoder):
+        def __init__(self, *a, **kw):
+            super().__init__(*a, **kw)
+            self.debug_set_cluster_size(8)
+            self.debug_set_cluster_waits(start_ticks=self.ticks)
+    monkeypatch.setattr(package, "Decoder", Impatient)
+    for Impatient.ticks in (0, 20, 60):                 # 10 ns each
+        parity.check_batch(torch_cuda, c2.graph, c2.loglikes, c2.lengths, c2.beam, c2.max_active, refs=c2_refs)
+        parity.test_random_small_configurations(torch_cuda)
+        parity.test_boost_fst_with_frequent_long_matches(torch_cuda, c2)
+    parity.test_candidate_overflow_is_reported_not_fatal(torch_cuda, c2)
+
+
+@pytest.mark.parametrize("polls", [0, 5, 13, 21, 34, 60, 100, 300])
+def test_no_utterance_is_lost_when_clusters_break_up(torch_cuda, c2, polls):
+    """Waits that end after a few looks: clusters break up in any of their exchanges.  Every entry of the list
+    still has the oracle's result, or is reported as stopped; so is a stream; and the next call is as if
+    nothing had been."""
+    from paper_2311_04996_amd import Decoder, FLAG_CAPACITY, FLAG_DEAD
+    lost = FLAG_CAPACITY | FLAG_DEAD
+    B, T = 72, 24                                      # more than the 32 clusters there are of 8
+    ll = np.ascontiguousarray(np.concatenate([c2.loglikes[:24, 4 * k:4 * k + T] for k in range(3)]))
+    lengths = (T - np.arange(B) % 7).astype(np.int32)
+    refs = parity.oracle_batch(c2.graph, ll, lengths, c2.beam, c2.max_active)
+    dev = torch_cuda.from_numpy(ll).cuda()
+    dec = Decoder(c2.graph, max_channels=B, max_frames=T, max_active_hint=c2.max_active)
+
+    def decode():
+        out = dec.decode_batch(dev, lengths, c2.beam, c2.max_active)
+        torch_cuda.cuda.synchronize()
+        words, nwords, cost, flags = (t.cpu().numpy() for t in out)
+        stopped = 0
+        for b, r in enumerate(refs):
+            if flags[b] & lost:
+                assert flags[b] == lost and nwords[b] == 0 and np.isinf(cost[b])
+                stopped += 1
+            else:
+                assert flags[b] == r.flags and cost[b] == np.float32(r.cost) and words[b, :nwords[b]].tolist() == r.words.tolist()
+        return stopped
+
+    dec.debug_set_cluster_size(8)
+    for size in (8, 2):
+        dec.debug_set_cluster_size(size)
+        dec.debug_set_cluster_waits(polls=polls)
+        stopped = decode()
+        print(f"polls {polls}, {size} workgroups: {stopped} of {B} stopped", flush=True)
+        assert stopped > 0 or polls > 0                # (a word takes longer than one look)
+        dec.debug_set_cluster_waits()
+        assert decode() == 0
+    dec.init_channels(list(range(B)), c2.beam, c2.max_active)
+    dec.debug_set_cluster_waits(polls=polls)
+    dec.advance_chunk(list(range(B)), dev, lengths)
+    dec.debug_set_cluster_waits()
+    for b, r in enumerate(refs):
+        words, cost, flags = dec.get_partial(b, finalize=True)
+        if flags & lost:
+            assert flags == lost and len(words) == 0 and np.isinf(cost)
+        else:
+            assert flags == r.flags and cost == np.float32(r.cost) and words.tolist() == r.words.tolist()
+    assert decode() == 0
+    dec.close()
