@@ -37,7 +37,8 @@ constexpr int kMapMax = kTabSlots * 3 / 4;    // most destinations in a table
 constexpr unsigned kRefTok = 0x80000000u;     // low word of a table value: a token of the set, by local number
 constexpr unsigned kRefStay = 0xFFFFFFFFu;    // ... or: a self-loop candidate won here
 constexpr int kBoxWords = 512;                // mailbox words of one workgroup and exchange parity
-constexpr int kBoxAux = 8, kBoxSel = 12, kBoxHist = 16;
+constexpr int kBoxAux = 8, kBoxSel = 12, kBoxHist = 16;   // (three words of selection)
+static_assert(kRegions == 4 && kMaxG == 2 * kRegions, "a region of keys is at most two workgroups'");
 constexpr int kPolls = 1 << 23;               // most polls of a wait (seconds)
 constexpr int kStartTicks = 5000;             // how long the first workgroup of a cluster waits for the others (50 us)
 constexpr int kXcds = 8;                      // XCDs of the chip
@@ -93,7 +94,9 @@ struct Smem2 {
   float stay_ac;
   int n_hub, next_run, done_waves;
   int made[4];                                // tokens made so far: outside simple states, in simple states; worklist entries; table entries
-  int n_loc, n_win, n_in;
+  int n_loc, n_win;
+  int n_in;                                   // candidates of the workgroup that shares a region of keys with this one (0: none does);
+                                              // where a region may hold too many, those inside the beam in the fullest one
   int map_bad, status, overfull;
   int polls, dead;                            // most polls of a wait; one has ended without its word
   int k_sel, n_sel, n_sel_c, k_keep, redo, n_emit, n_emit_all, gbase;
@@ -241,8 +244,10 @@ __device__ __forceinline__ void take_sizes(Cx &x) {
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
       int run = 0;
-      for (int q = 0; q < G; ++q) { if (q < lane) run += sm.xn[q * kMaxG + x.me]; }
+      const int own = lane == 63 ? x.me ^ 1 : x.me;
+      for (int q = 0; q < G; ++q) { if (q < lane) run += sm.xn[q * kMaxG + own]; }
       if (lane <= G) sm.seg_pre[lane] = run;
+      if (lane == 63) sm.n_in = G == kMaxG ? run : 0;
       if (lane == 0) sm.x_any = any != 0ull;
     } else {
       const int n = lane < kRegions ? min(sm.n_seg[lane], region_cap) : 0;
@@ -731,6 +736,29 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
   const int n_tok = x.n;
   const bool small = n_own <= kKR * kBlock;
   int k_sel = 256, n_sel = n_own + n_tok, n_sel_c = n_own;
+  if (kCl && !init && n_own + uni(sm.n_in) > x.c.region_cap) {
+    // One workgroup's buffer has four regions, by the top bits of the key's hash, and a channel whose
+    // candidates inside the beam do not fit theirs stops.  The segments of a cluster hold more, so they
+    // are counted here, all of them, but only where a region can have that many.
+    unsigned *const n_reg = sm.wave_tot;
+    __syncthreads();
+    if (tid < kRegions) n_reg[tid] = 0;
+    __syncthreads();
+    for (int i0 = 0; i0 < n_own; i0 += kBlock) {
+      int r = -1;
+      if (i0 + tid < n_own) {
+        const int4 cd = get4<kCl>(cand_at<kCl>(x, i0 + tid, 0));
+        if (cut.in_beam(__int_as_float(cd.y))) r = part_of(key_of(cd.x), kRegionBits);
+      }
+#pragma unroll
+      for (int q = 0; q < kRegions; ++q) {
+        const unsigned long long m = __ballot(r == q);
+        if (lane == 0 && m) atomicAdd(&n_reg[q], (unsigned)__popcll(m));
+      }
+    }
+    __syncthreads();
+    if (tid == 0) sm.n_in = (int)max(max(n_reg[0], n_reg[1]), max(n_reg[2], n_reg[3]));
+  }
   unsigned long long won = 0;
   // the lane's records, one per kBlock candidates: picked by a rolled loop (its body is large)
   static_assert(kKR == 3, "three named records");
@@ -746,12 +774,6 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
     if (tid < n_own) rec0 = get4<kCl>(cand_at<kCl>(x, tid, 0));
     if (kBlock + tid < n_own) rec1 = get4<kCl>(cand_at<kCl>(x, kBlock + tid, 0));
     if (2 * kBlock + tid < n_own) rec2 = get4<kCl>(cand_at<kCl>(x, 2 * kBlock + tid, 0));
-    // as many in-beam candidates as would overflow one workgroup's buffer (a cluster's is larger)
-    if (kCl && n_own > x.c.region_cap * max(1, 4 / x.G)) {
-      const unsigned in = (tid < n_own && cut.in_beam(__int_as_float(rec0.y)) ? 1u : 0u) + (kBlock + tid < n_own && cut.in_beam(__int_as_float(rec1.y)) ? 1u : 0u) +
-                          (2 * kBlock + tid < n_own && cut.in_beam(__int_as_float(rec2.y)) ? 1u : 0u);
-      if (in) atomicAdd(&sm.n_in, (int)in);
-    }
   } else if (n_own > kGroupTarget) {
     // ---- select: bins of the implied candidates, and of a sample of the others (one run of 64 in 2^sel_shift)
     if (tid < 256) { sm.hist2[tid] = 0; sm.hist3[tid] = 0; }
@@ -766,13 +788,10 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
     int n_sampled = 0;
     for (int i0 = (tid >> 6) << 6; (i0 << sh) < n_own; i0 += kBlock) {
       const int i = (i0 << sh) + lane;
-      int in = 0;
       if (i < n_own) {
         const float c = __int_as_float(get4<kCl>(cand_at<kCl>(x, i, 0)).y);
-        in = (int)cut.in_beam(c);
-        if (in) atomicAdd(&sm.hist2[cut.bin(c)], 1u);
+        if (cut.in_beam(c)) atomicAdd(&sm.hist2[cut.bin(c)], 1u);
       }
-      if (kCl) { const unsigned long long m = __ballot(in); if (lane == 0 && m) atomicAdd(&sm.n_in, __popcll(m) << sh); }
     }
     n_sampled = ((n_own >> (6 + sh)) << 6) + min(n_own & ((64 << sh) - 1), 64);
     __syncthreads();
@@ -879,7 +898,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
       // their own, so that a word always replaces the one of two such exchanges ago and a short tag is enough
       ++x.hc;
       if (tid < 128) astore(hist_of(x, x.me) + tid, ((unsigned long long)(x.hc & 0xffffu) << 48) | ((unsigned long long)sm.hist[2 * tid + 1] << 24) | sm.hist[2 * tid]);
-      if (tid >= 128 && tid < 130) post(x, kBoxSel + tid - 128, tid == 128 ? (unsigned)(k_sel | (sm.overfull << 16)) : (unsigned)n_sel);
+      if (tid >= 128 && tid < 131) post(x, kBoxSel + tid - 128, tid == 128 ? (unsigned)(k_sel | (sm.overfull << 16)) : (unsigned)(tid == 129 ? n_sel : sm.n_in));
     }
     clear_table(sm);
     if (kCl) {
@@ -889,12 +908,16 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
         *reinterpret_cast<uint2 *>(&sm.v.s.gh[tid >> 7][2 * (tid & 127)]) = make_uint2((unsigned)v & 0xffffffu, (unsigned)(v >> 24) & 0xffffffu);
       }
       if (tid < 64) {
-        const bool mine = lane < 2 * x.G;
+        const int which = lane & 3;
+        const bool mine = lane < 4 * x.G && which < 3;
         unsigned v = 0;
-        if (mine) v = poll(sm, box_of(x, lane >> 1) + kBoxSel + (lane & 1), x.xc);
-        const unsigned ks = wave_min(mine && !(lane & 1) ? v & 0xffffu : 256u);
-        const unsigned over = __ballot(mine && !(lane & 1) && (v >> 16) != 0) != 0ull;
-        const unsigned ns = wave_sum(mine && (lane & 1) ? v : 0u);
+        if (mine) v = poll(sm, box_of(x, lane >> 2) + kBoxSel + which, x.xc);
+        const unsigned ks = wave_min(mine && which == 0 ? v & 0xffffu : 256u);
+        const unsigned over = __ballot(mine && which == 0 && (v >> 16) != 0) != 0ull;
+        const unsigned ns = wave_sum(mine && which == 1 ? v : 0u);
+        if (x.G == kMaxG) v += (unsigned)__shfl_xor((int)v, 4, 64);    // two workgroups to a region
+        const unsigned long long crowded = __ballot(mine && which == 2 && v > (unsigned)x.c.region_cap);
+        if (lane == 0 && crowded) atomicOr(&sm.status, kStCapacity);
         if (lane == 0) { sm.k_sel = (int)ks; sm.overfull = (int)over; sm.n_sel = (int)ns; }
       }
       __syncthreads();
@@ -1000,7 +1023,6 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
   __syncthreads();
   x.n_front = uni(sm.made[0]); x.n_emit = n_emit;
   if (tid == 0) {
-    if (kCl && uni(sm.n_in) > x.c.region_cap * max(1, 4 / x.G)) atomicOr(&sm.status, kStCapacity);
     sm.n_loc = n_emit; if (!init) sm.ctr[kCtKept] += min(n_emit, x.c.qcap);
     if (kCl && x.me == 0) set_counter(x, sm.n_emit_all);
   }
@@ -1676,7 +1698,6 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
     if (tid == 0) {
       sm.next_run = kWaves; sm.done_waves = 0; sm.n_hub = 0; sm.min_simple = kOrdNone;
       sm.made[0] = 0; sm.made[1] = 0; sm.made[2] = 0; sm.made[3] = 0; sm.map_bad = 0; sm.n_win = 0; sm.overfull = 0;
-      sm.n_in = 0;
       sm.ctr[kCtTok] += x.n;
       if (leader && t >= 0) sm.ctr[kCtFrames]++;
     }

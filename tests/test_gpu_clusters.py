@@ -218,3 +218,45 @@ def test_no_utterance_is_lost_when_clusters_break_up(torch_cuda, c2, polls):
             assert flags == r.flags and cost == np.float32(r.cost) and words.tolist() == r.words.tolist()
     assert decode() == 0
     dec.close()
+
+
+@pytest.mark.parametrize("cluster", [2, 4, 8], indirect=True)
+@pytest.mark.parametrize("sample", [0, 4096])
+def test_a_sample_of_the_candidates_never_stops_a_channel(torch_cuda, cluster, sample):
+    """Some 76,000 candidates per frame: their bins are estimated from a sample, where one run of 64 can stand for
+    all of a workgroup's; whether they fit the buffer is counted."""
+    from workloads import ctc_loglikes, tlg_shaped_graph
+    g = tlg_shaped_graph(31, 200_000, 1_400_000, num_classes=129, alpha=1.8, k_max=5000, p_eps=0.2,
+                         num_words=50_000, extra_lo=3, extra_hi=5)
+    lengths = np.array([40, 33, 21], np.int32)
+    ll = ctc_loglikes(31, lengths, 40, 129, sigma=2.0, p_blank=0.3, blank_boost=6.0, token_boost=4.0)
+    refs = parity.check_batch(torch_cuda, g, ll, lengths, 25.0, 10000, max_active_hint=10000, selection_sample=sample,
+                              lattice_bytes_per_channel=1 << 23)
+    assert sum(int(r.counters[7]) for r in refs) > 6144 * cluster * int(lengths.sum())   # the sample is taken
+
+
+@pytest.mark.parametrize("cluster", [1, 2, 4, 8], indirect=True)
+def test_the_candidate_capacity_is_the_same_for_every_number_of_workgroups(torch_cuda, cluster):
+    """Candidates all inside the beam, in four regions by the top bits of the key's hash: 1,024 in the fullest fit a
+    capacity of 4,096, one more does not."""
+    from paper_2311_04996_amd import Decoder, FLAG_CAPACITY, FLAG_DEAD
+    from workloads.graphs import _csr
+
+    def fullest(n):                                    # states 1..n without arcs follow the start state's n arcs
+        first = (1 + n + 1) // 2
+        key = (first + np.arange(n)).astype(np.uint64)
+        return int(np.bincount((key * 0x9E3779B1 & 0xFFFFFFFF).astype(np.int64) >> 30, minlength=4).max())
+    fits = max(n for n in range(3800, 4097) if fullest(n) == 1024)
+    for n, fit in ((fits, True), (min(k for k in range(fits, 4200) if fullest(k) == 1025), False)):
+        g = _csr(n + 1, 0, 2, np.zeros(n), np.arange(1, n + 1), np.ones(n), np.zeros(n), np.zeros(n))
+        ll = np.zeros((1, 1, 2), np.float32)
+        dec = Decoder(g, max_channels=1, max_frames=1, max_active_hint=1000, candidate_capacity=4096,
+                      lattice_bytes_per_channel=1 << 18, record_digests=True)
+        _, nwords, cost, flags = dec.decode_batch(torch_cuda.from_numpy(ll).cuda(), np.array([1], np.int32), 5.0, 5000)
+        (ref,) = parity.oracle_batch(g, ll, [1], 5.0, 5000)
+        if fit:
+            cnt, dig = dec.debug_frame_digests(0)
+            assert int(flags[0]) == ref.flags and (cnt == ref.digest_count).all() and (dig == ref.digest_sum).all()
+        else:
+            assert int(flags[0]) == FLAG_CAPACITY | FLAG_DEAD and int(nwords[0]) == 0
+        dec.close()
