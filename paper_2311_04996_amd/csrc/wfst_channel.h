@@ -70,7 +70,7 @@ struct WaveLds2 {             // ExpandArcs: the work items of one wave (one tok
   int2 pend[2 * kWaveTok];    // ring: records of tokens whose state has to be read from the graph
   int pend_tok[2 * kWaveTok]; //       local number | number in the set << 16
 };
-struct Smem2 {
+struct alignas(16) Smem2 {
   union {
     struct { float ac[kMaxV]; WaveLds2 w[kWaves]; HubLds hub; } e;
     TableLds t;
@@ -109,6 +109,7 @@ struct Smem2 {
   long long prof_t0;
 };
 static_assert(sizeof(Smem2) <= 160 * 1024, "LDS of a compute unit");
+static_assert(offsetof(Smem2, u) % 16 == 0 && sizeof(TableLds) % 16 == 0 && offsetof(Smem2, v.s.gh) % 16 == 0, "16 bytes at a time");
 static_assert(kKR * kBlock <= kMapMax, "one register-held round fits the table");
 
 struct Cx {                   // block-uniform view of one channel
@@ -925,9 +926,14 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
     if (tid < 64) {
       const int S2 = kCl ? x.G : 1;
       const int ks = kCl ? sm.k_sel : k_sel, ns = kCl ? sm.n_sel : n_sel;
+      // (16 bytes at a time from the cluster's histograms; the workgroup's own is not aligned to that)
+      auto bins4 = [&](int r) {
+        if (kCl) return *reinterpret_cast<const uint4 *>(&sm.v.s.gh[r][4 * tid]);
+        return make_uint4(sm.hist[4 * tid], sm.hist[4 * tid + 1], sm.hist[4 * tid + 2], sm.hist[4 * tid + 3]);
+      };
       unsigned h[4] = {0, 0, 0, 0};
       for (int r = 0; r < S2; ++r) {
-        const uint4 q = *reinterpret_cast<const uint4 *>(kCl ? &sm.v.s.gh[r][4 * tid] : &sm.hist[4 * tid]);
+        const uint4 q = bins4(r);
         h[0] += q.x; h[1] += q.y; h[2] += q.z; h[3] += q.w;
       }
 #pragma unroll
@@ -951,7 +957,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
       // the survivors of every workgroup: where its tokens start in the set, and how many
       unsigned before = 0, mine = 0, all = 0;
       for (int r = 0; r < S2; ++r) {
-        const uint4 q = *reinterpret_cast<const uint4 *>(kCl ? &sm.v.s.gh[r][4 * tid] : &sm.hist[4 * tid]);
+        const uint4 q = bins4(r);
         const int lim = min(kk, ks) - 4 * tid;
         const unsigned nb = (lim > 0 ? q.x : 0u) + (lim > 1 ? q.y : 0u) + (lim > 2 ? q.z : 0u) + (lim > 3 ? q.w : 0u);
         if (kCl && r < x.me) before += nb;
