@@ -82,7 +82,7 @@ struct alignas(16) Smem2 {
       unsigned gh[kMaxG][256];                // the cluster's histograms
     } s;
   } v;
-  unsigned short tokof[kTabSlots];            // closure table: local token of a slot, 0xFFFF: none yet
+  unsigned short tokof[kTabSlots];            // closure table: local token of a slot, 0xFFFF: none yet, or the last of a full set
   unsigned hist[256], hist2[256], hist3[256];
   unsigned wave_tot[kWaves];
   int n_seg[kMaxG];                           // candidates pushed per segment
@@ -1039,16 +1039,17 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
 // ------------------------------------------------------------------ epsilon closure
 // One candidate that is its destination's best (win[u]): a token the set has takes its cost and
 // backpointer, a destination without one gets a token; either way it is expanded in the next round.
+// `full`: the workgroup had as many tokens as a set holds when the round began.
 // All lanes of the wave call it.
 template <bool kCl>
-__device__ __forceinline__ void apply2(Cx &x, int win, const int4 &rec, int slot, int2 *NQ, int *NGI, unsigned lat_base, int4 *WLN) {
+__device__ __forceinline__ void apply2(Cx &x, int win, const int4 &rec, int slot, int2 *NQ, int *NGI, unsigned lat_base, int4 *WLN, bool full) {
   Smem2 &sm = x.sm;
   TableLds &t = sm.u.t;
   const int lane = lane_id() & 63;
   const unsigned long long lt = (1ull << lane) - 1ull;
   if (__ballot(win) == 0ull) return;
   int li = win ? (int)sm.tokof[slot] : 0, gx = 0;
-  const int fresh = win & (int)(li == 0xFFFF);
+  int fresh = win & (int)(li == 0xFFFF);
   const unsigned long long mn = __ballot(fresh), mw = __ballot(win & (int)((unsigned)rec.x >> 31));
   // places: lane 0 takes the new tokens' local numbers, lane 1 the worklist's, lane 2 the numbers in the set (from
   // the cluster's counter)
@@ -1061,7 +1062,12 @@ __device__ __forceinline__ void apply2(Cx &x, int win, const int4 &rec, int slot
   else if (win) gx = kCl ? NGI[li] : li;
   unsigned ms = kOrdNone;
   if (win) {
-    const bool room = gx < x.c.qcap && li < x.c.qcap;
+    bool room = gx < x.c.qcap && li < x.c.qcap;
+    // (the last token of a full set has the number that stands for none: there is no room for a new one, but it may be meant)
+    if (full && fresh && key_of(NQ[kQueueMax - 1].x) == key_of(rec.x)) {
+      li = kQueueMax - 1; gx = kCl ? NGI[li] : li;
+      fresh = 0; room = gx < x.c.qcap;
+    }
     if (!room) atomicOr(&sm.status, kStCapacity);
     else {
       if (fresh) { NQ[li] = make_int2(rec.x, rec.y); if (kCl) NGI[li] = gx; }
@@ -1246,7 +1252,7 @@ __device__ __forceinline__ void closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
             }
           }
           if (sl >= 0) win = (int)((unsigned)t.vals[sl] == (unsigned)i);
-          apply2<kCl>(x, win, cd, sl, NQ, NGI, lat_base, WLN);
+          apply2<kCl>(x, win, cd, sl, NQ, NGI, lat_base, WLN, n_loc0 >= kQueueMax && x.c.qcap == kQueueMax);
         }
         __syncthreads();
         mark<kProf>(x, kPhEpsTabScan);

@@ -260,3 +260,24 @@ def test_the_candidate_capacity_is_the_same_for_every_number_of_workgroups(torch
         else:
             assert int(flags[0]) == FLAG_CAPACITY | FLAG_DEAD and int(nwords[0]) == 0
         dec.close()
+
+
+@pytest.mark.parametrize("cluster", [1, 2], indirect=True)
+@pytest.mark.parametrize("n_z", [2000, 4000])          # the closure's rounds meet in the kept table, or in one of their own
+def test_the_last_token_of_a_full_set_can_still_improve(torch_cuda, cluster, n_z):
+    """65,536 tokens, as many as a set holds: the closure makes the last of them in one round and improves all that
+    it made in the next."""
+    from workloads.graphs import _csr
+    hub, mid, z0 = 1, 2, 3
+    dead0 = z0 + n_z
+    S = 1 + 65536
+    n_dead = S - dead0
+    src = np.repeat([0, hub, mid], [n_dead + 1, n_z + 1, n_z])
+    dst = np.concatenate([[hub], np.arange(dead0, S), [mid], np.arange(z0, dead0), np.arange(z0, dead0)])
+    il = np.repeat([1, 0, 0], [n_dead + 1, n_z + 1, n_z])
+    w = np.concatenate([np.zeros(n_dead + 1), [0.0], np.full(n_z, 0.01), np.full(n_z, 0.005)])
+    g = _csr(S, 0, 2, src, dst, il, np.zeros(len(src)), w)
+    ll = np.zeros((1, 1, 2), np.float32)
+    (ref,) = parity.check_batch(torch_cuda, g, ll, np.array([1], np.int32), 5.0, 5000, max_active_hint=10000,
+                               lattice_bytes_per_channel=1 << 20)
+    assert ref.digest_count.tolist() == [1, 65536]
