@@ -181,7 +181,8 @@ typedef struct {
 /*
  * Build a decoder: validates the graph, splits emitting and epsilon arcs (global arc ids:
  * emitting arcs 0..Ae-1 in (state, given order), epsilon arcs Ae.. likewise), uploads it and
- * allocates the per-channel state.  Errors: INVALID_ARG, BAD_GRAPH, OOM, HIP.
+ * allocates the per-channel state (what several workgroups per utterance need is allocated by the first
+ * calls that use them: wfst_set_launch_workgroups).  Errors: INVALID_ARG, BAD_GRAPH, OOM, HIP.
  */
 int32_t wfst_decoder_create(const wfst_graph_csr *graph, const wfst_opts *opts, wfst_decoder **out);
 int32_t wfst_decoder_destroy(wfst_decoder *dec);
@@ -245,7 +246,16 @@ int32_t wfst_decode_batch_slot(wfst_decoder *dec, int32_t slot, const void *logl
  * stay idle while the next workgroup in line waits for another group.  With n chosen so that the
  * launches in flight together hold exactly the GPU's compute units (256 on MI355X: n = 128 for
  * two or three slots), and a multiple of 32 (8 dies x 4 groups), every workgroup finds a free
- * compute unit at once.  Results do not depend on n.  Errors: INVALID_ARG (n < 0). */
+ * compute unit at once.  Results do not depend on n.  Errors: INVALID_ARG (n < 0).
+ *
+ * Workgroups that decode an utterance together need memory beside the channels' own.  With G of them
+ * per utterance and C utterances at a time it is C * G * (56 B * the token queue's size (4 * max_active_hint, rounded
+ * up to a power of two, 8,192 to 65,536) + 8 B * candidate_capacity * max(G, 4)): at max_active_hint = 10000
+ * 3.1 GB with 2 or 4 workgroups and 5.2 GB with 8, for each batch slot whose calls use all compute units.  A call
+ * that needs more of it than those before allocates it, at least twice as much as there was; a call
+ * that replaces smaller memory first waits for the launch that used it, and giving that back can wait
+ * for other work on the GPU.  If there is none left, the call decodes with one workgroup per utterance.
+ * wfst_device_bytes includes it. */
 int32_t wfst_set_launch_workgroups(wfst_decoder *dec, int32_t n);
 
 /*
@@ -419,6 +429,11 @@ int32_t wfst_debug_set_cluster_size(wfst_decoder *dec, int32_t n);
  * often one looks for another's word before it gives up (at most the default, seconds).  Negative: the
  * default.  An utterance whose workgroups have given up is reported with WFST_FLAG_CAPACITY | WFST_FLAG_DEAD. */
 int32_t wfst_debug_set_cluster_waits(wfst_decoder *dec, int32_t start_ticks, int32_t polls);
+/* Most device memory, in bytes, that such workgroups may take beside the channels' own, in all (negative, the default: no
+ * limit).  It does not take back what they hold.  A launch that finds no more decodes with one workgroup per utterance. */
+int32_t wfst_debug_set_cluster_memory(wfst_decoder *dec, int64_t bytes);
+/* Of the decoder's last launch: how many workgroups, and how many of them decode an utterance together. */
+int32_t wfst_debug_last_launch(wfst_decoder *dec, int32_t *workgroups, int32_t *per_utterance);
 int32_t wfst_debug_phase_ticks(wfst_decoder *dec, int64_t ticks[16], int32_t reset);
 
 /* Device memory the decoder holds, in bytes (graph + channel state). */

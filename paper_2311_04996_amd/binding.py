@@ -24,7 +24,8 @@ EXPORTS = ["wfst_decoder_create", "wfst_decoder_destroy", "wfst_decode_batch", "
            "wfst_advance_chunk", "wfst_advance_chunk_partial", "wfst_get_partial", "wfst_get_partial_batch", "wfst_get_lattice",
            "wfst_get_lattice_noalloc", "wfst_get_lattice_batch",
            "wfst_debug_frame_digests",
-           "wfst_debug_get_tokens", "wfst_debug_get_token_pairs", "wfst_get_counters", "wfst_debug_phase_ticks", "wfst_debug_set_phase_timing", "wfst_debug_set_cluster_size", "wfst_debug_set_cluster_waits", "wfst_set_launch_workgroups", "wfst_device_bytes",
+           "wfst_debug_get_tokens", "wfst_debug_get_token_pairs", "wfst_get_counters", "wfst_debug_phase_ticks", "wfst_debug_set_phase_timing", "wfst_debug_set_cluster_size", "wfst_debug_set_cluster_waits", "wfst_debug_set_cluster_memory",
+           "wfst_debug_last_launch", "wfst_set_launch_workgroups", "wfst_device_bytes",
            "wfst_last_kernel_ms", "wfst_last_error"]
 
 
@@ -124,6 +125,8 @@ def load_library():
     lib.wfst_debug_set_phase_timing.argtypes = [p, i32]
     lib.wfst_debug_set_cluster_size.argtypes = [p, i32]
     lib.wfst_debug_set_cluster_waits.argtypes = [p, i32, i32]
+    lib.wfst_debug_set_cluster_memory.argtypes = [p, i64]
+    lib.wfst_debug_last_launch.argtypes = [p, C.POINTER(i32), C.POINTER(i32)]
     lib.wfst_set_launch_workgroups.argtypes = [p, i32]
     lib.wfst_device_bytes.argtypes = [p]
     lib.wfst_device_bytes.restype = i64
@@ -510,6 +513,15 @@ class Decoder:
 
     def debug_set_cluster_waits(self, start_ticks=-1, polls=-1):
         self._check(self.lib.wfst_debug_set_cluster_waits(self.h, int(start_ticks), int(polls)))
+
+    def debug_set_cluster_memory(self, n_bytes=-1):
+        self._check(self.lib.wfst_debug_set_cluster_memory(self.h, int(n_bytes)))
+
+    def debug_last_launch(self):
+        """(workgroups, workgroups per utterance) of the last launch."""
+        n, g = C.c_int32(), C.c_int32()
+        self._check(self.lib.wfst_debug_last_launch(self.h, C.byref(n), C.byref(g)))
+        return n.value, g.value
 
     def debug_set_phase_timing(self, on=True):
         self._check(self.lib.wfst_debug_set_phase_timing(self.h, int(bool(on))))

@@ -2338,8 +2338,11 @@ struct wfst_decoder {
   int launch_workgroups = 0;           // most workgroups a launch gets (wfst_set_launch_workgroups); 0: one per list entry
   // clusters (several workgroups per channel): memory of their workgroups, one area per batch slot (and
   // one for the calls that name channels), allocated by the first launch that needs it
-  struct ClusterArea { size_t wgs = 0, cand = 0, boxes = 0; bool failed = false; std::vector<std::pair<void *, size_t>> mem; ClusterArgs a{}; };
+  struct ClusterSizes { size_t wgs = 0, cand = 0, boxes = 0; };
+  struct ClusterArea { ClusterSizes n; size_t bytes = 0, refused = 0; std::vector<std::pair<void *, size_t>> mem; ClusterArgs a{}; };
   std::vector<ClusterArea> areas;
+  int64_t cluster_bytes_max = -1;      // most memory all areas together may take (wfst_debug_set_cluster_memory); -1: no limit
+  int last_wgs = 0, last_per_utt = 0;  // of the last launch (wfst_debug_last_launch)
   unsigned launch_seq = 0;
   int n_cu = 0;
   std::string err;
@@ -2649,43 +2652,73 @@ void dev_free(wfst_decoder *d, void *p, size_t bytes) {
 void free_cluster_area(wfst_decoder *d, wfst_decoder::ClusterArea &ar) {
   for (auto &m : ar.mem) dev_free(d, m.first, m.second);
   ar.mem.clear();
-  ar.wgs = ar.cand = ar.boxes = 0; ar.a = ClusterArgs{};
+  ar.n = {}; ar.bytes = 0; ar.a = ClusterArgs{};
+}
+size_t cluster_bytes(const wfst_decoder *d, const wfst_decoder::ClusterSizes &n) {
+  return n.wgs * 2 * (size_t)d->c.qcap * (sizeof(int2) + sizeof(int) + sizeof(int4)) + n.boxes * 2 * (kBoxWords + 1) * sizeof(unsigned long long) +
+         n.cand * sizeof(int4);
+}
+int alloc_cluster_area(wfst_decoder *d, wfst_decoder::ClusterArea &ar, const wfst_decoder::ClusterSizes &n, hipStream_t st) {
+  const size_t qc = (size_t)d->c.qcap, bytes = cluster_bytes(d, n);
+  size_t held = 0;
+  for (const auto &o : d->areas) held += o.bytes;
+  if (d->cluster_bytes_max >= 0 && held + bytes > (size_t)d->cluster_bytes_max) return WFST_ERR_OOM;
+  auto get = [&](auto *&p, size_t k) {
+    const int e = dev_alloc(d, &p, k);
+    if (!e) ar.mem.emplace_back(p, k * sizeof(*p));
+    return e;
+  };
+  int rc = get(ar.a.tok, n.wgs * 2 * qc);
+  if (!rc) rc = get(ar.a.gi, n.wgs * 2 * qc);
+  if (!rc) rc = get(ar.a.wl, n.wgs * 2 * qc);
+  if (!rc) rc = get(ar.a.box, n.boxes * 2 * kBoxWords);
+  if (!rc) rc = get(ar.a.hello, n.boxes * 2);
+  if (!rc) rc = get(ar.a.cand, n.cand);
+  // (ordered before the launch that needs it, and nothing waits)
+  if (!rc && hipMemsetAsync(ar.a.hello, 0, n.boxes * 2 * sizeof(unsigned long long), st) != hipSuccess) rc = WFST_ERR_HIP;
+  if (rc) { free_cluster_area(d, ar); d->err.clear(); return rc; }
+  ar.n = n; ar.bytes = bytes;
+  return WFST_OK;
 }
 
 // Memory of a launch's clusters.  Returns an error if there is none: the launch then does without clusters.
-int cluster_area(wfst_decoder *d, int slot_id, int n_clusters, int n_wg, int G, ClusterArgs &out) {
+int cluster_area(wfst_decoder *d, int slot_id, int n_clusters, int n_wg, int G, hipStream_t st, ClusterArgs &out) {
+  using Sizes = wfst_decoder::ClusterSizes;
   if (d->areas.empty()) d->areas.resize((size_t)d->n_slots + 1);
   auto &ar = d->areas[slot_id];
-  const size_t qc = (size_t)d->c.qcap, region = (size_t)d->c.region_cap;
+  const size_t region = (size_t)d->c.region_cap;
   const int seg_cap = (int)(region * (size_t)std::max(1, 4 / G));
   const size_t w = (size_t)n_clusters * G, cand = w * 2 * G * (size_t)seg_cap, boxes = (size_t)n_wg;
-  if (ar.failed) return WFST_ERR_OOM;
-  if (ar.wgs < w || ar.boxes < boxes || ar.cand < cand) {
-    // at least twice as much as before, so that calls of growing size come here a few times only; no
-    // launch that uses the old memory is under way when it is given back
-    HIP_TRY(d, hipDeviceSynchronize());
+  const Sizes old = ar.n;
+  if (old.wgs < w || old.boxes < boxes || old.cand < cand) {
     const size_t cu = (size_t)d->n_cu;
-    const size_t nw = std::max({w, ar.wgs, std::min(2 * ar.wgs, cu)}), nb = std::max({boxes, ar.boxes, std::min(2 * ar.boxes, cu)});
-    const size_t nc = std::max({cand, ar.cand, std::min(2 * ar.cand, cu * 2 * kMaxG * region)});
-    free_cluster_area(d, ar);
-    auto get = [&](auto *&p, size_t n) {
-      const int e = dev_alloc(d, &p, n);
-      if (!e) ar.mem.emplace_back(p, n * sizeof(*p));
-      return e;
-    };
-    int rc = get(ar.a.tok, nw * 2 * qc);
-    if (!rc) rc = get(ar.a.gi, nw * 2 * qc);
-    if (!rc) rc = get(ar.a.wl, nw * 2 * qc);
-    if (!rc) rc = get(ar.a.box, nb * 2 * kBoxWords);
-    if (!rc) rc = get(ar.a.hello, nb * 2);
-    if (!rc) rc = get(ar.a.cand, nc);
-    if (rc) { free_cluster_area(d, ar); ar.failed = true; d->err.clear(); return rc; }
-    HIP_TRY(d, hipMemset(ar.a.hello, 0, nb * 2 * sizeof(unsigned long long)));
-    HIP_TRY(d, hipDeviceSynchronize());
-    ar.wgs = nw; ar.boxes = nb; ar.cand = nc;
+    const Sizes exact = {std::max(w, old.wgs), std::max(cand, old.cand), std::max(boxes, old.boxes)};
+    // at least twice as much as before, so that calls of growing size come here a few times only
+    const Sizes larger = {std::max(exact.wgs, std::min(2 * old.wgs, cu)), std::max(exact.cand, std::min(2 * old.cand, cu * 2 * kMaxG * region)),
+                          std::max(exact.boxes, std::min(2 * old.boxes, cu))};
+    const size_t need = cluster_bytes(d, exact);
+    if (ar.refused && need >= ar.refused) return WFST_ERR_OOM;       // (what is there still serves smaller calls)
+    // the last launch that uses the old memory has ended before that is given back
+    if (ar.bytes && d->timed[slot_id]) HIP_TRY(d, hipEventSynchronize(d->ev1[slot_id]));
+    int rc = WFST_ERR_OOM;
+    for (const Sizes &n : {larger, exact}) {
+      wfst_decoder::ClusterArea fresh;
+      rc = alloc_cluster_area(d, fresh, n, st);
+      if (rc) continue;
+      free_cluster_area(d, ar);
+      fresh.refused = ar.refused;
+      ar = std::move(fresh);
+      break;
+    }
+    if (rc && ar.bytes) {                        // not beside the old memory: in its place, or else the old again
+      free_cluster_area(d, ar);
+      rc = alloc_cluster_area(d, ar, exact, st);
+      if (rc) (void)alloc_cluster_area(d, ar, old, st);
+    }
+    if (rc) { ar.refused = need; return WFST_ERR_OOM; }
   }
   out = ar.a;
-  out.G = G; out.n_clusters = n_clusters; out.seg_cap = seg_cap; out.qcap = (int)qc; out.seq = ++d->launch_seq;
+  out.G = G; out.n_clusters = n_clusters; out.seg_cap = seg_cap; out.qcap = d->c.qcap; out.seq = ++d->launch_seq;
   out.ticks = (unsigned)d->start_ticks; out.polls = d->polls;
   return WFST_OK;
 }
@@ -2713,11 +2746,12 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
   ClusterArgs cl{};
   if (G > 1) {
     const int n_all = (n_clusters + kXcds - 1) / kXcds * kXcds * G;     // as many on every XCD
-    const int rca = cluster_area(d, slot_id, n_clusters, n_all, G, cl);
+    const int rca = cluster_area(d, slot_id, n_clusters, n_all, G, st, cl);
     if (rca == WFST_ERR_OOM) G = 1;                          // no memory for clusters: a workgroup per utterance, as ever
     else if (rca) return rca;
     else n_wg = n_all;
   }
+  d->last_wgs = n_wg; d->last_per_utt = G;
   // (the lists live on the device until the kernel ends, since its workgroups read them as they go:
   // one area per batch slot, and one for the calls that name channels; calls that share an area do
   // not overlap in time, so the stream orders this copy after the last kernel that read the area)
@@ -3561,6 +3595,19 @@ int32_t wfst_debug_set_cluster_waits(wfst_decoder *d, int32_t start_ticks, int32
   if (!d) return WFST_ERR_INVALID_ARG;
   d->start_ticks = start_ticks < 0 ? kStartTicks : std::min(start_ticks, kStartTicks);
   d->polls = polls < 0 ? kPolls : std::min(polls, kPolls);
+  return WFST_OK;
+}
+
+int32_t wfst_debug_set_cluster_memory(wfst_decoder *d, int64_t bytes) {
+  if (!d) return WFST_ERR_INVALID_ARG;
+  d->cluster_bytes_max = bytes < 0 ? -1 : bytes;
+  for (auto &ar : d->areas) ar.refused = 0;
+  return WFST_OK;
+}
+
+int32_t wfst_debug_last_launch(wfst_decoder *d, int32_t *workgroups, int32_t *per_utterance) {
+  if (!d || !workgroups || !per_utterance) return WFST_ERR_INVALID_ARG;
+  *workgroups = d->last_wgs; *per_utterance = d->last_per_utt;
   return WFST_OK;
 }
 

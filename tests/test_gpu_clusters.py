@@ -281,3 +281,54 @@ def test_the_last_token_of_a_full_set_can_still_improve(torch_cuda, cluster, n_z
     (ref,) = parity.check_batch(torch_cuda, g, ll, np.array([1], np.int32), 5.0, 5000, max_active_hint=10000,
                                lattice_bytes_per_channel=1 << 20)
     assert ref.digest_count.tolist() == [1, 65536]
+
+
+def test_without_memory_for_clusters(torch_cuda, c2, c2_refs):
+    """A bound on the clusters' memory: calls that do not get enough decode with one workgroup per utterance, calls that
+    can do with what is there keep it, and all of them have the oracle's results."""
+    from paper_2311_04996_amd import Decoder
+    B, T = 24, int(c2.lengths[:24].max())
+    ll = torch_cuda.from_numpy(np.ascontiguousarray(c2.loglikes[:B, :T])).cuda()
+    dec = Decoder(c2.graph, max_channels=B, max_frames=T, max_active_hint=c2.max_active)
+    own = dec.device_bytes()
+
+    def decode(n, dec=dec):
+        words, nwords, cost, flags = (t.cpu().numpy() for t in dec.decode_batch(ll[:n].contiguous(), c2.lengths[:n], c2.beam, c2.max_active))
+        for b in range(n):
+            r = c2_refs[b]
+            assert words[b, :nwords[b]].tolist() == r.words.tolist() and cost[b] == np.float32(r.cost) and flags[b] == r.flags
+        return dec.debug_last_launch()[1], dec.device_bytes() - own
+    dec.debug_set_cluster_memory(0)
+    assert decode(B) == (1, 0)
+    dec.debug_set_cluster_memory()
+    g, small = decode(2)
+    assert g == 8 and small > 0
+    dec.debug_set_cluster_memory(small)
+    assert decode(B) == (1, small) and decode(2) == (8, small) and decode(B) == (1, small)
+    other = Decoder(c2.graph, max_channels=B, max_frames=T, max_active_hint=c2.max_active)
+    g, large = decode(B, other)
+    other.close()
+    dec.debug_set_cluster_memory(large)             # enough for exactly these, not beside the old memory
+    assert g == 8 and large > 10 * small and decode(B) == (8, large) and decode(2) == (8, large)
+    dec.debug_set_cluster_memory()
+    assert decode(B) == (8, large)
+    dec.close()
+
+
+def test_the_first_call_with_clusters_waits_for_no_other_stream(torch_cuda, c2):
+    from paper_2311_04996_amd import Decoder
+    torch = torch_cuda
+    ll = torch.from_numpy(np.ascontiguousarray(c2.loglikes[:4, :40])).cuda()
+    dec = Decoder(c2.graph, max_channels=4, max_frames=40, max_active_hint=c2.max_active)
+    a, other, done = torch.randn(8192, 8192, device="cuda"), torch.cuda.Stream(), torch.cuda.Event()
+    out = tuple(torch.zeros(s, dtype=t, device="cuda") for s, t in (((4, 256), torch.int32), (4, torch.int32), (4, torch.float32), (4, torch.int32)))
+    torch.cuda.synchronize()
+    with torch.cuda.stream(other):
+        for _ in range(60):                          # some 10 ms each
+            b = a @ a
+        done.record()
+    dec.decode_batch(ll, np.full(4, 40, np.int32), c2.beam, c2.max_active, out=out)
+    assert not done.query() and dec.debug_last_launch()[1] > 1
+    torch.cuda.synchronize()
+    del b
+    dec.close()
