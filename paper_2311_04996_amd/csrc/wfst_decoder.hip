@@ -2626,9 +2626,11 @@ int plan_clusters(wfst_decoder *d, const std::vector<int> &frames, int max_activ
   const float t_us[4] = {lean ? 13.0f + 7.5f * k_tok : 20.0f + 6.8f * k_tok, 19.0f + 4.6f * k_tok, 19.0f + 2.8f * k_tok, 21.0f + 1.9f * k_tok};
   long long total = 0;
   for (int f : frames) total += f;
+  // clusters start on all XCDs alike (a launch has G workgroups on each for every eight of them)
+  auto room = [&](int lg) { return lg == 0 ? budget : (budget >> lg) / kXcds * kXcds; };
   int best = 0; float best_t = 0.0f;
-  for (int lg = 0; (1 << lg) <= kMaxG && (1 << lg) <= budget; ++lg) {
-    const int C = lg == 0 && d->launch_workgroups <= 0 ? std::min(n, 256) : std::min(n, budget >> lg);
+  for (int lg = 0; (1 << lg) <= kMaxG && room(lg) > 0; ++lg) {
+    const int C = std::min(n, room(lg));
     float most = std::max((float)frames[0], (float)total / (float)C);
     for (int k = 1; k * C < n; ++k) most = std::max(most, (float)(k + 1) * (float)frames[k * C]);
     const float t = most * t_us[lg];
@@ -2637,8 +2639,8 @@ int plan_clusters(wfst_decoder *d, const std::vector<int> &frames, int max_activ
   // (narrow records, a mere initialisation or result, a part of the chip: one workgroup each)
   if (d->g.earc8 || frames[0] == 0 || d->n_cu != 32 * kXcds) best = 0;
   else if (d->cluster_size > 0)
-    for (best = 0; (2 << best) <= std::min(d->cluster_size, budget);) ++best;
-  n_clusters = std::min(n, std::max(1, budget >> best));
+    for (best = 0; (2 << best) <= d->cluster_size && room(best + 1) > 0;) ++best;
+  n_clusters = std::min(n, room(best));
   return 1 << best;
 }
 

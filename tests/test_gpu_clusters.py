@@ -71,7 +71,7 @@ def test_calls_with_many_entries_that_have_nothing_to_do(torch_cuda, c2, c2_refs
     b = int(np.argmax(c2.lengths))
     dec = Decoder(c2.graph, max_channels=n_ch, max_frames=n, max_active_hint=c2.max_active, record_digests=True)
     dec.debug_set_cluster_size(8)
-    dec.set_launch_workgroups(8)                  # one cluster takes them all
+    dec.set_launch_workgroups(64)                 # eight clusters take them all, a run of empty ones each
     dec.init_channels(list(range(n_ch)), c2.beam, c2.max_active)
     ll = torch_cuda.from_numpy(np.ascontiguousarray(c2.loglikes[b:b + 1, :n])).cuda()
     busy = (0, 41, 95)
@@ -331,4 +331,28 @@ def test_the_first_call_with_clusters_waits_for_no_other_stream(torch_cuda, c2):
     assert not done.query() and dec.debug_last_launch()[1] > 1
     torch.cuda.synchronize()
     del b
+    dec.close()
+
+
+@pytest.mark.parametrize("size", [0, 2, 4, 8])
+def test_a_launch_gets_at_most_the_workgroups_it_was_given(torch_cuda, c2, c2_refs, size):
+    """Clusters start on all eight XCDs alike, so a launch with few workgroups gets smaller ones, or none."""
+    from paper_2311_04996_amd import Decoder
+    B, T = 20, 16
+    lengths = np.full(B, T, np.int32)
+    ll = torch_cuda.from_numpy(np.ascontiguousarray(c2.loglikes[:B, :T])).cuda()
+    dec = Decoder(c2.graph, max_channels=B, max_frames=T, max_active_hint=c2.max_active, record_digests=True)
+    dec.debug_set_cluster_size(size)
+    sizes = {}
+    for n in (1, 2, 7, 8, 15, 16, 31, 32, 63, 64, 100, 127, 128, 255, 256, 0):
+        dec.set_launch_workgroups(n)
+        dec.decode_batch(ll, lengths, c2.beam, c2.max_active)
+        wgs, sizes[n] = dec.debug_last_launch()
+        assert 0 < wgs <= (n or 256) and (size == 0 or sizes[n] <= size)
+        for b in range(B):
+            cnt, dig = dec.debug_frame_digests(b)
+            assert (cnt == c2_refs[b].digest_count[:T + 1]).all() and (dig == c2_refs[b].digest_sum[:T + 1]).all()
+    assert sizes[7] == sizes[8] == sizes[15] == 1 and sizes[0] == sizes[256] == (size or 8)
+    if size:
+        assert sizes[16] == sizes[31] == 2 and sizes[32] == sizes[63] == min(size, 4) and sizes[64] == size
     dec.close()
