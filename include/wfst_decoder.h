@@ -236,11 +236,13 @@ int32_t wfst_decode_batch_slot(wfst_decoder *dec, int32_t slot, const void *logl
                                void *stream, int32_t *words, int32_t *nwords, float *cost, int32_t *flags);
 
 /* How many workgroups the launches of this decoder get from now on.  n = 0 (the default): at least one
- * per utterance (or channel) of the call, and as many as there are compute units if the call has few
- * enough: 2, 4 or 8 workgroups then decode an utterance together.  n > 0: at most n, alone or together
+ * per utterance (or channel) of the call, and if the call has few enough, as many as there are compute
+ * units (as its share of them, while calls on the decoder's other batch slots are in flight): 2, 4 or 8
+ * workgroups then decode an utterance together.  A decoder does not know what else runs on the GPU: with
+ * several decoders at work, give each its n.  n > 0: at most n, alone or together
  * likewise; they take the call's utterances, longest first, one after the other from a counter on
  * the device, so that all of them are busy until the call's work runs out and they end at nearly
- * the same time.  This is for several batches in flight
+ * the same time.  This is for several large batches in flight
  * (batch slots): the GPU hands the workgroups of a launch to fixed groups of compute units in launch
  * order, so with one workgroup per utterance a compute unit that a short utterance has left can
  * stay idle while the next workgroup in line waits for another group.  With n chosen so that the

@@ -504,7 +504,8 @@ class Decoder:
         return c
 
     def set_launch_workgroups(self, n):
-        """At most n workgroups per launch from now on (0: one per utterance); see the header."""
+        """At most n workgroups per launch from now on (0: at least one per utterance, as many as there are
+        compute units if that is more); see the header."""
         self._check(self.lib.wfst_set_launch_workgroups(self.h, int(n)))
 
     def debug_set_cluster_size(self, n):

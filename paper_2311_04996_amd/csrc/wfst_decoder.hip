@@ -2321,7 +2321,8 @@ struct wfst_decoder {
   // batch slots: wfst_decode_batch_slot calls on different slots may be in flight together
   int n_slots = 1, slot_channels = 0;
   std::vector<hipEvent_t> ev0, ev1;    // per slot (+ one pair for the calls that name channels): around the last kernel
-  std::vector<char> timed;
+  std::vector<char> timed, running;    // ... and whether it has been seen to end
+  int in_flight = 0, in_flight_age = 0;   // most launches of other slots that a recent one met, launches since
   // lattice memory: every slot's channels share one pool, shared out equally (streaming) or by
   // utterance length (a batch decode)
   unsigned long long *d_lat_start = nullptr; unsigned *d_lat_capn = nullptr;
@@ -2610,6 +2611,21 @@ int alloc_channels(wfst_decoder *d) {
 #ifndef WFST_LEAN
 #define WFST_LEAN 5
 #endif
+constexpr int kHwQueues = 4;                     // kernels of a process that run at the same time
+// Launches of the decoder's other slots that a new one shares the GPU with: those that have not ended, or as
+// many as there were at one of its last launches (one for every slot), if those were more: the first batch of
+// the next round of batches would otherwise take all compute units from the ones that follow it.
+int launches_in_flight(wfst_decoder *d, int slot_id) {
+  int n = 0;
+  for (int s = 0; s <= d->n_slots; ++s) {
+    if (s == slot_id || !d->running[s]) continue;
+    if (hipEventQuery(d->ev1[s]) == hipErrorNotReady) ++n; else d->running[s] = 0;
+  }
+  (void)hipGetLastError();                       // (what a query that was not ready leaves behind)
+  if (n >= d->in_flight || ++d->in_flight_age >= d->n_slots) { d->in_flight = n; d->in_flight_age = 0; }
+  return d->in_flight;
+}
+
 // How many workgroups decode each utterance of a launch (1, 2, 4 or 8), and how many such clusters
 // the launch gets.  `frames`: what every utterance consumes, longest first.
 //
@@ -2617,9 +2633,16 @@ int alloc_channels(wfst_decoder *d) {
 // share of the work, which goes with the tokens, at most about max_active of them; measured at 1,000 and
 // 11,000 tokens per frame.  The launch ends with its busiest cluster: no earlier than the longest
 // utterance, than an equal share of all frames, and than the k + 1 shortest of the k * clusters + 1 longest.
-int plan_clusters(wfst_decoder *d, const std::vector<int> &frames, int max_active, int &n_clusters, bool &lean) {
+//
+// Several workgroups take more of the chip's time per frame than one (at 7,000 tokens 2, 4 and 8 of them
+// 1.5, 2.3 and 4 times as much), so launches that run at the same time share the compute units instead of planning
+// with all of them each.  Batches at 7,000 tokens and 437 frames at most, ms per batch with all 256 for each
+// launch, with one workgroup per utterance, with a share: 32 on four slots 14 to 19, 13.1, 7.2; 64 on
+// three slots 24 to 30, 17.3, 11.9.  (A process has four hardware queues: of more launches than four the
+// others are in line, not in flight.)
+int plan_clusters(wfst_decoder *d, const std::vector<int> &frames, int max_active, int in_flight, int &n_clusters, bool &lean) {
   const int n = (int)frames.size();
-  const int budget = d->launch_workgroups > 0 ? std::min(d->launch_workgroups, d->n_cu) : d->n_cu;
+  const int budget = d->launch_workgroups > 0 ? std::min(d->launch_workgroups, d->n_cu) : d->n_cu / (1 + std::min(in_flight, kHwQueues - 1));
   const float k_tok = (float)std::min(max_active, d->g.S) * 1e-3f;
   // solo: the kernel that keeps records in registers up to about 5,000 tokens, the older one beyond
   lean = k_tok <= (float)WFST_LEAN;
@@ -2741,7 +2764,8 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
   {
     std::vector<int> by_length(nfr);
     std::sort(by_length.begin(), by_length.end(), std::greater<int>());
-    G = plan_clusters(d, by_length, a.mode & kModeInit ? a.max_active : d->stream_max_active, n_clusters, lean);
+    G = plan_clusters(d, by_length, a.mode & kModeInit ? a.max_active : d->stream_max_active,
+                      d->launch_workgroups > 0 ? 0 : launches_in_flight(d, slot_id), n_clusters, lean);
     if (a.mode & kModeInit && !(a.mode & kModeFinal)) d->stream_max_active = a.max_active;
   }
   int n_wg = d->launch_workgroups > 0 ? std::min(n, d->launch_workgroups) : n;
@@ -2805,7 +2829,7 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
 #undef WFST_LAUNCH
   HIP_TRY(d, hipGetLastError());
   HIP_TRY(d, hipEventRecord(d->ev1[slot_id], st));
-  d->timed[slot_id] = 1;
+  d->timed[slot_id] = 1; d->running[slot_id] = 1;
   d->last_timed = slot_id;
   return WFST_OK;
 }
@@ -3148,7 +3172,7 @@ int32_t wfst_decoder_create(const wfst_graph_csr *graph, const wfst_opts *opts, 
   rc = upload_graph(d, graph);
   if (!rc) rc = alloc_channels(d);
   d->ev0.assign((size_t)d->n_slots + 1, nullptr); d->ev1.assign((size_t)d->n_slots + 1, nullptr);
-  d->timed.assign((size_t)d->n_slots + 1, 0);
+  d->timed.assign((size_t)d->n_slots + 1, 0); d->running.assign((size_t)d->n_slots + 1, 0);
   for (int i = 0; !rc && i <= d->n_slots; ++i)
     if (hipEventCreate(&d->ev0[i]) != hipSuccess || hipEventCreate(&d->ev1[i]) != hipSuccess) {
       d->err = "hipEventCreate failed"; rc = WFST_ERR_HIP;

@@ -356,3 +356,41 @@ def test_a_launch_gets_at_most_the_workgroups_it_was_given(torch_cuda, c2, c2_re
     if size:
         assert sizes[16] == sizes[31] == 2 and sizes[32] == sizes[63] == min(size, 4) and sizes[64] == size
     dec.close()
+
+
+def test_launches_in_flight_share_the_compute_units(torch_cuda, c2, c2_refs):
+    """Batches on three slots and streams, nothing set: the second and the third launch get a half and a third of the
+    compute units while the first runs, the next three a third each, and a batch on its own gets all of them
+    again after as many launches as there are slots."""
+    from paper_2311_04996_amd import Decoder
+    torch = torch_cuda
+    B, T = 24, int(c2.lengths[:24].max())
+    dec = Decoder(c2.graph, max_channels=3 * B, max_frames=T, max_active_hint=c2.max_active, batch_slots=3)
+    ll = torch.from_numpy(np.ascontiguousarray(c2.loglikes[:B, :T])).cuda()
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    for rep in range(2):
+        torch.cuda.synchronize()
+        outs, shapes = [], []
+        for k in range(3):
+            outs.append(dec.decode_batch(ll, c2.lengths[:B], c2.beam, c2.max_active, slot=k, stream=streams[k]))
+            shapes.append(dec.debug_last_launch())
+        torch.cuda.synchronize()
+        for most, (wgs, _) in zip((85, 85, 85) if rep else (256, 128, 85), shapes):
+            assert 24 <= wgs <= most, shapes
+        assert rep or shapes[0] == (192, 8)
+        for out in outs:
+            words, nwords, cost, flags = (x.cpu().numpy() for x in out)
+            for b, r in enumerate(c2_refs[:B]):
+                assert words[b, :nwords[b]].tolist() == r.words.tolist() and cost[b] == np.float32(r.cost) and flags[b] == r.flags
+    for k in range(3):
+        dec.decode_batch(ll, c2.lengths[:B], c2.beam, c2.max_active, slot=0)
+        torch.cuda.synchronize()
+    assert dec.debug_last_launch() == (192, 8)
+    dec.set_launch_workgroups(128)                   # with a number of its own a launch does not share
+    shapes = []
+    for k in range(3):
+        dec.decode_batch(ll, c2.lengths[:B], c2.beam, c2.max_active, slot=k, stream=streams[k])
+        shapes.append(dec.debug_last_launch())
+    assert shapes == [(128, 8)] * 3
+    torch.cuda.synchronize()
+    dec.close()
