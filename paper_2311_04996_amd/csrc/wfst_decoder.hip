@@ -2640,7 +2640,7 @@ int launches_in_flight(wfst_decoder *d, int slot_id) {
 // launch, with one workgroup per utterance, with a share: 32 on four slots 14 to 19, 13.1, 7.2; 64 on
 // three slots 24 to 30, 17.3, 11.9.  (A process has four hardware queues: of more launches than four the
 // others are in line, not in flight.)
-int plan_clusters(wfst_decoder *d, const std::vector<int> &frames, int max_active, int in_flight, int &n_clusters, bool &lean) {
+int plan_clusters(wfst_decoder *d, const std::vector<int> &frames, int max_active, int in_flight, bool solo, int &n_clusters, bool &lean) {
   const int n = (int)frames.size();
   const int budget = d->launch_workgroups > 0 ? std::min(d->launch_workgroups, d->n_cu) : d->n_cu / (1 + std::min(in_flight, kHwQueues - 1));
   const float k_tok = (float)std::min(max_active, d->g.S) * 1e-3f;
@@ -2660,7 +2660,7 @@ int plan_clusters(wfst_decoder *d, const std::vector<int> &frames, int max_activ
     if (lg == 0 || t < best_t) { best = lg; best_t = t; }
   }
   // (narrow records, a mere initialisation or result, a part of the chip: one workgroup each)
-  if (d->g.earc8 || frames[0] == 0 || d->n_cu != 32 * kXcds) best = 0;
+  if (solo || d->g.earc8 || frames[0] == 0 || d->n_cu != 32 * kXcds) best = 0;
   else if (d->cluster_size > 0)
     for (best = 0; (2 << best) <= d->cluster_size && room(best + 1) > 0;) ++best;
   n_clusters = std::min(n, room(best));
@@ -2723,8 +2723,12 @@ int cluster_area(wfst_decoder *d, int slot_id, int n_clusters, int n_wg, int G, 
                           std::max(exact.boxes, std::min(2 * old.boxes, cu))};
     const size_t need = cluster_bytes(d, exact);
     if (ar.refused && need >= ar.refused) return WFST_ERR_OOM;       // (what is there still serves smaller calls)
-    // the last launch that uses the old memory has ended before that is given back
-    if (ar.bytes && d->timed[slot_id]) HIP_TRY(d, hipEventSynchronize(d->ev1[slot_id]));
+    // the last launch that uses the old memory has ended before that is given back (its event may have been
+    // recorded into a graph since)
+    if (ar.bytes && d->timed[slot_id] && hipEventSynchronize(d->ev1[slot_id]) != hipSuccess) {
+      (void)hipGetLastError();
+      HIP_TRY(d, hipDeviceSynchronize());
+    }
     int rc = WFST_ERR_OOM;
     for (const Sizes &n : {larger, exact}) {
       wfst_decoder::ClusterArea fresh;
@@ -2761,11 +2765,16 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
   int n_clusters = 0;
   bool lean = false;
   int G = 1;
+  // A launch that is recorded into a graph runs with the same arguments at every replay, and the number of the launch,
+  // by which the workgroups of a cluster know each other, is one of them; nor can it allocate.
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();
+  const bool recorded = capture != hipStreamCaptureStatusNone;
   {
     std::vector<int> by_length(nfr);
     std::sort(by_length.begin(), by_length.end(), std::greater<int>());
     G = plan_clusters(d, by_length, a.mode & kModeInit ? a.max_active : d->stream_max_active,
-                      d->launch_workgroups > 0 ? 0 : launches_in_flight(d, slot_id), n_clusters, lean);
+                      d->launch_workgroups > 0 || recorded ? 0 : launches_in_flight(d, slot_id), recorded, n_clusters, lean);
     if (a.mode & kModeInit && !(a.mode & kModeFinal)) d->stream_max_active = a.max_active;
   }
   int n_wg = d->launch_workgroups > 0 ? std::min(n, d->launch_workgroups) : n;
@@ -2829,7 +2838,7 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
 #undef WFST_LAUNCH
   HIP_TRY(d, hipGetLastError());
   HIP_TRY(d, hipEventRecord(d->ev1[slot_id], st));
-  d->timed[slot_id] = 1; d->running[slot_id] = 1;
+  d->timed[slot_id] = 1; d->running[slot_id] = !recorded;
   d->last_timed = slot_id;
   return WFST_OK;
 }

@@ -394,3 +394,37 @@ def test_launches_in_flight_share_the_compute_units(torch_cuda, c2, c2_refs):
     assert shapes == [(128, 8)] * 3
     torch.cuda.synchronize()
     dec.close()
+
+
+def test_a_captured_call_is_replayed(torch_cuda, c2, c2_refs):
+    """A call recorded into a graph (the decoder's very first, which must not allocate) has one workgroup per utterance:
+    every replay runs with the arguments of the recording.  Between the replays the inputs change, another
+    decoder decodes, and the decoder itself too."""
+    from paper_2311_04996_amd import Decoder
+    torch = torch_cuda
+    B, T = 6, 60
+    lengths = np.array([60, 41, 60, 7, 33, 60], np.int32)
+    rows = [np.ascontiguousarray(c2.loglikes[k * B:(k + 1) * B, :T]) for k in range(4)]
+    refs = [parity.oracle_batch(c2.graph, r, lengths, c2.beam, c2.max_active) for r in rows]
+    dec, other = (Decoder(c2.graph, max_channels=B, max_frames=T, max_active_hint=c2.max_active) for _ in range(2))
+    ll = torch.from_numpy(rows[0]).cuda()
+    out = tuple(torch.zeros(s, dtype=t, device="cuda") for s, t in (((B, 256), torch.int32), (B, torch.int32), (B, torch.float32), (B, torch.int32)))
+
+    def check(out, want):
+        torch.cuda.synchronize()
+        words, nwords, cost, flags = (t.cpu().numpy() for t in out)
+        for b, r in enumerate(want):
+            assert words[b, :nwords[b]].tolist() == r.words.tolist() and cost[b] == np.float32(r.cost) and flags[b] == r.flags
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        dec.decode_batch(ll, lengths, c2.beam, c2.max_active, out=out)
+    for k in (1, 2, 3, 0):
+        ll.copy_(torch.from_numpy(rows[k]))
+        for t in out:
+            t.zero_()
+        graph.replay()
+        check(out, refs[k])
+        check((dec if k == 3 else other).decode_batch(torch.from_numpy(rows[k]).cuda(), lengths, c2.beam, c2.max_active), refs[k])
+    assert dec.debug_last_launch()[1] > 1
+    dec.close(), other.close()
