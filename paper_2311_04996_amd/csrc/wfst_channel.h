@@ -29,10 +29,7 @@
 // over 100 us on a full one, since a fence writes back and invalidates whole L2 caches.
 
 constexpr int kMaxG = 8;                      // workgroups of a cluster
-#ifndef WFST_KR
-#define WFST_KR 3
-#endif
-constexpr int kKR = WFST_KR;                  // candidate records a lane keeps in registers from fill to token
+constexpr int kKR = 3;                        // candidate records a lane keeps in registers from fill to token
 constexpr int kMapMax = kTabSlots * 3 / 4;    // most destinations in a table
 constexpr unsigned kRefTok = 0x80000000u;     // low word of a table value: a token of the set, by local number
 constexpr unsigned kRefStay = 0xFFFFFFFFu;    // ... or: a self-loop candidate won here
@@ -354,10 +351,7 @@ __device__ __forceinline__ void emit_arcs2(Cx &x, int (&ok)[N], const int4 (&a)[
   }
   push_cands2<kCl, N>(x, ok, next, nc, src, arc, 0);
 }
-#ifndef WFST_HUBDEG
-#define WFST_HUBDEG 128
-#endif
-constexpr int kHubDeg2 = WFST_HUBDEG;         // arcs beyond which a state's arcs are shared by all waves
+constexpr int kHubDeg2 = 128;                 // arcs beyond which a state's arcs are shared by all waves
 __device__ __forceinline__ int next_run2(Smem2 &sm) {
   int r = 0;
   if ((threadIdx.x & 63) == 0) r = atomicAdd(&sm.next_run, 1);
@@ -367,7 +361,7 @@ __device__ __forceinline__ int next_run2(Smem2 &sm) {
 // token's block (header + first arc); the other arcs of the batch are flattened over the 64 lanes
 // (prefix sums in the wave's slice of LDS, one short search per arc), and states with more than
 // kHubDeg2 arcs are listed for all waves.  Returns the emitting arcs expanded (wave-uniform).
-template <bool kCl, bool kNarrow>
+template <bool kCl>
 __device__ __forceinline__ unsigned dense_run2(Cx &x, WaveLds2 &wl, int head, int n, float beam, bool boosted) {
   Smem2 &sm = x.sm;
   HubLds &hb = sm.u.e.hub;
@@ -438,7 +432,7 @@ __device__ __forceinline__ unsigned dense_run2(Cx &x, WaveLds2 &wl, int head, in
       src[u] = wl.src[j]; tc[u] = wl.tcost[j];
       arc[u] = M ? wl.abase[j] + (int)fs : 2 * blk + 1;
       a[u] = make_int4(0, 0, 1, 0);
-      if (ok[u]) a[u] = load_emitting_arc<kNarrow>(x.g, arc[u], boosted);
+      if (ok[u]) a[u] = load_emitting_arc<false>(x.g, arc[u], boosted);
     }
     emit_arcs2<kCl, 2>(x, ok, a, tc, src, arc, beam, boosted);
     f0 += 128;
@@ -449,7 +443,7 @@ __device__ __forceinline__ unsigned dense_run2(Cx &x, WaveLds2 &wl, int head, in
 }
 // On entry sm.next_run == kWaves, sm.done_waves == 0, sm.n_hub == 0 and the hub list's ready
 // and seg_next words are zero (the caller sets them before its barrier).
-template <bool kCl, bool kNarrow, bool kBoost>
+template <bool kCl, bool kBoost>
 __device__ __forceinline__ void expand2(Cx &x, const int2 *Q, const int *GI) {
   Smem2 &sm = x.sm;
   HubLds &hb = sm.u.e.hub;
@@ -494,7 +488,7 @@ __device__ __forceinline__ void expand2(Cx &x, const int2 *Q, const int *GI) {
       const int take = min(pend_n, kWaveTok);
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
-      n_arcs += dense_run2<kCl, kNarrow>(x, wl, pend_head, take, beam, boosted);
+      n_arcs += dense_run2<kCl>(x, wl, pend_head, take, beam, boosted);
       pend_head = (pend_head + take) & (2 * kWaveTok - 1); pend_n -= take;
     }
   }
@@ -531,7 +525,7 @@ __device__ __forceinline__ void expand2(Cx &x, const int2 *Q, const int *GI) {
           ok[u] = f < deg;
           arc[u] = first + (ok[u] ? f : deg - 1);      // lanes past the end repeat the last arc (no branch)
           src[u] = tok; tc[u] = cost;
-          a[u] = load_emitting_arc<kNarrow>(x.g, arc[u], boosted);
+          a[u] = load_emitting_arc<false>(x.g, arc[u], boosted);
         }
         emit_arcs2<kCl, kUE>(x, ok, a, tc, src, arc, beam, boosted);
       }
@@ -1517,13 +1511,12 @@ __device__ __forceinline__ void give_up2(const DevChannels &c, const LaunchArgs 
 
 // ------------------------------------------------------------------ the channel kernel
 // kCl: clusters of up to w.G workgroups per channel; without it a workgroup is on its own and all of
-// its data are the channel's.  kNarrow: the graph has the 8-byte emitting-arc records and the arc loops
-// read them.  kBoost: some channel of the launch has a boosting table or acceptor.  kProf: the phases
+// its data are the channel's.  kBoost: some channel of the launch has a boosting table or acceptor.  kProf: the phases
 // are timed (a debug hook).  kOpt: the decoder has one of its options on (cost offsets, token records
 // for lattices, a recycled arena, frame digests).  kQueue: workgroups (clusters always) take more than one entry
 // of the launch's list.  Every one of these costs the frame loop a percent or two when it is a
 // run-time test.
-template <bool kCl, bool kNarrow, bool kBoost, bool kProf, bool kOpt, bool kQueue>
+template <bool kCl, bool kBoost, bool kProf, bool kOpt, bool kQueue>
 __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(DevGraph g, DevChannels c_arg, LaunchArgs a, ClusterArgs w) {
   __shared__ Smem2 sm;
   const int tid = lane_id();
@@ -1720,7 +1713,7 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
     mark<kProf>(x, kPhOther);
     Cutoff cut;
     if (t >= 0) {
-      expand2<kCl, kNarrow, kBoost>(x, Q, GI);
+      expand2<kCl, kBoost>(x, Q, GI);
       if (kCl) stores_done();
       __syncthreads();
       mark<kProf>(x, kPhExpSetup);

@@ -2608,9 +2608,6 @@ int alloc_channels(wfst_decoder *d) {
   return WFST_OK;
 }
 
-#ifndef WFST_LEAN
-#define WFST_LEAN 5
-#endif
 constexpr int kHwQueues = 4;                     // kernels of a process that run at the same time
 // Launches of the decoder's other slots that a new one shares the GPU with: those that have not ended, or as
 // many as there were at one of its last launches (one for every slot), if those were more: the first batch of
@@ -2645,7 +2642,7 @@ int plan_clusters(wfst_decoder *d, const std::vector<int> &frames, int max_activ
   const int budget = d->launch_workgroups > 0 ? std::min(d->launch_workgroups, d->n_cu) : d->n_cu / (1 + std::min(in_flight, kHwQueues - 1));
   const float k_tok = (float)std::min(max_active, d->g.S) * 1e-3f;
   // solo: the kernel that keeps records in registers up to about 5,000 tokens, the older one beyond
-  lean = k_tok <= (float)WFST_LEAN;
+  lean = k_tok <= 5.0f;
   const float t_us[4] = {lean ? 13.0f + 7.5f * k_tok : 20.0f + 6.8f * k_tok, 19.0f + 4.6f * k_tok, 19.0f + 2.8f * k_tok, 21.0f + 1.9f * k_tok};
   long long total = 0;
   for (int f : frames) total += f;
@@ -2813,18 +2810,18 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
     if (n_wg < n) hipLaunchKernelGGL((wfst_channel_kernel<NARROW, BOOST, PROF, OPT, true>), dim3(n_wg), dim3(kBlock), 0, st, d->g, d->c, a); \
     else hipLaunchKernelGGL((wfst_channel_kernel<NARROW, BOOST, PROF, OPT, false>), dim3(n_wg), dim3(kBlock), 0, st, d->g, d->c, a); \
   } while (0)
-#define WFST_LAUNCH2(CL, NARROW, BOOST, PROF, OPT, QUEUE) \
-  hipLaunchKernelGGL((wfst_channel_kernel2<CL, NARROW, BOOST, PROF, OPT, QUEUE>), dim3(n_wg), dim3(kBlock), 0, st, d->g, d->c, a, cl)
+#define WFST_LAUNCH2(CL, BOOST, PROF, OPT, QUEUE) \
+  hipLaunchKernelGGL((wfst_channel_kernel2<CL, BOOST, PROF, OPT, QUEUE>), dim3(n_wg), dim3(kBlock), 0, st, d->g, d->c, a, cl)
   if ((G > 1 || lean) && !d->g.earc8) {
     const bool q = n_wg < n;
     if (G > 1) {
-      if (d->phase_timing) { if (boost) WFST_LAUNCH2(true, false, true, true, true, true); else if (opt) WFST_LAUNCH2(true, false, false, true, true, true); else WFST_LAUNCH2(true, false, false, true, false, true); }
-      else if (boost) WFST_LAUNCH2(true, false, true, false, true, true);
-      else if (opt) WFST_LAUNCH2(true, false, false, false, true, true); else WFST_LAUNCH2(true, false, false, false, false, true);
-    } else if (d->phase_timing) { if (boost) WFST_LAUNCH2(false, false, true, true, true, true); else if (opt) WFST_LAUNCH2(false, false, false, true, true, true); else WFST_LAUNCH2(false, false, false, true, false, true); }
-    else if (boost) WFST_LAUNCH2(false, false, true, false, true, true);
-    else if (opt) WFST_LAUNCH2(false, false, false, false, true, true);
-    else if (q) WFST_LAUNCH2(false, false, false, false, false, true); else WFST_LAUNCH2(false, false, false, false, false, false);
+      if (d->phase_timing) { if (boost) WFST_LAUNCH2(true, true, true, true, true); else if (opt) WFST_LAUNCH2(true, false, true, true, true); else WFST_LAUNCH2(true, false, true, false, true); }
+      else if (boost) WFST_LAUNCH2(true, true, false, true, true);
+      else if (opt) WFST_LAUNCH2(true, false, false, true, true); else WFST_LAUNCH2(true, false, false, false, true);
+    } else if (d->phase_timing) { if (boost) WFST_LAUNCH2(false, true, true, true, true); else if (opt) WFST_LAUNCH2(false, false, true, true, true); else WFST_LAUNCH2(false, false, true, false, true); }
+    else if (boost) WFST_LAUNCH2(false, true, false, true, true);
+    else if (opt) WFST_LAUNCH2(false, false, false, true, true);
+    else if (q) WFST_LAUNCH2(false, false, false, false, true); else WFST_LAUNCH2(false, false, false, false, false);
   } else
   if (d->g.earc8) {                            // (no lean instances and no phase timing with narrow arc records)
     if (boost) WFST_LAUNCH(true, true, false, true); else WFST_LAUNCH(true, false, false, true);
@@ -2836,6 +2833,7 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
     else { if (opt) WFST_LAUNCH(false, false, false, true); else WFST_LAUNCH(false, false, false, false); }
   }
 #undef WFST_LAUNCH
+#undef WFST_LAUNCH2
   HIP_TRY(d, hipGetLastError());
   HIP_TRY(d, hipEventRecord(d->ev1[slot_id], st));
   d->timed[slot_id] = 1; d->running[slot_id] = !recorded;

@@ -368,31 +368,34 @@ def test_launches_in_flight_share_the_compute_units(torch_cuda, c2, c2_refs):
     dec = Decoder(c2.graph, max_channels=3 * B, max_frames=T, max_active_hint=c2.max_active, batch_slots=3)
     ll = torch.from_numpy(np.ascontiguousarray(c2.loglikes[:B, :T])).cuda()
     streams = [torch.cuda.Stream() for _ in range(3)]
+
+    def check(outs):
+        torch.cuda.synchronize()
+        for out in outs:
+            words, nwords, cost, flags = (x.cpu().numpy() for x in out)
+            for b, r in enumerate(c2_refs[:B]):
+                assert words[b, :nwords[b]].tolist() == r.words.tolist() and cost[b] == np.float32(r.cost) and flags[b] == r.flags
     for rep in range(2):
         torch.cuda.synchronize()
         outs, shapes = [], []
         for k in range(3):
             outs.append(dec.decode_batch(ll, c2.lengths[:B], c2.beam, c2.max_active, slot=k, stream=streams[k]))
             shapes.append(dec.debug_last_launch())
-        torch.cuda.synchronize()
         for most, (wgs, _) in zip((85, 85, 85) if rep else (256, 128, 85), shapes):
             assert 24 <= wgs <= most, shapes
         assert rep or shapes[0] == (192, 8)
-        for out in outs:
-            words, nwords, cost, flags = (x.cpu().numpy() for x in out)
-            for b, r in enumerate(c2_refs[:B]):
-                assert words[b, :nwords[b]].tolist() == r.words.tolist() and cost[b] == np.float32(r.cost) and flags[b] == r.flags
+        check(outs)
     for k in range(3):
         dec.decode_batch(ll, c2.lengths[:B], c2.beam, c2.max_active, slot=0)
         torch.cuda.synchronize()
     assert dec.debug_last_launch() == (192, 8)
     dec.set_launch_workgroups(128)                   # with a number of its own a launch does not share
-    shapes = []
+    outs, shapes = [], []
     for k in range(3):
-        dec.decode_batch(ll, c2.lengths[:B], c2.beam, c2.max_active, slot=k, stream=streams[k])
+        outs.append(dec.decode_batch(ll, c2.lengths[:B], c2.beam, c2.max_active, slot=k, stream=streams[k]))
         shapes.append(dec.debug_last_launch())
-    assert shapes == [(128, 8)] * 3
-    torch.cuda.synchronize()
+    assert shapes == [(128, 8)] * 3                  # three times half of the compute units: some wait for others to end
+    check(outs)
     dec.close()
 
 
