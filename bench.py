@@ -19,7 +19,15 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
-KERNEL = "wfst_channel_kernel"
+
+
+def kernel_of(dec, w, narrow_arcs=False):
+    """The kernel of the decoder's last launch, and how many of its workgroups decode an utterance together."""
+    per_utt = dec.debug_last_launch()[1]
+    if per_utt > 1:
+        return f"wfst_channel_kernel2 ({per_utt} workgroups per utterance)"
+    few = min(w.max_active, w.graph.num_states) <= 5000 and not narrow_arcs
+    return "wfst_channel_kernel2" if few else "wfst_channel_kernel"
 
 
 def algorithmic_bytes(counters, V):
@@ -424,8 +432,9 @@ def main():
         """nsteps decode_batch calls taken in turn by the first n_use batch slots (each on its own
         stream); returns the wall time between two device synchronisations."""
         ms = []
-        # one batch in flight: a workgroup per utterance, the whole chip for the one launch; several: each
-        # launch gets a share of the compute units and its workgroups take the utterances from a queue
+        # one batch in flight: the whole chip for the one launch, which several workgroups may then share an
+        # utterance on; several: each launch gets a share of the compute units and its workgroups take the
+        # utterances from a queue
         dec.set_launch_workgroups(args.launch_workgroups if n_use > 1 else 0)
         torch.cuda.synchronize()
         t0 = time.perf_counter()
@@ -447,10 +456,11 @@ def main():
         for _ in range(max(1, args.warmup) if args.warmup else 0):
             outs[k] = dec.decode_batch(ll, w.lengths, w.beam, w.max_active, stream=streams[k], out=outs[k],
                                        boosts=w.boosts, boost_fsts=w.boost_fsts, slot=k)
-    torch.cuda.synchronize()
+        torch.cuda.synchronize()                     # (launches in flight share the compute units)
     dec.get_counters(reset=True)
     # one batch in flight: the kernel's own duration (for the roofline) and the unpipelined rate
     wall_one, kernel_ms = run_steps(1, args.steps, True)
+    kernel_one, wgs_one = kernel_of(dec, w, args.narrow_arcs), dec.debug_last_launch()[0]
     counters = dec.get_counters() // max(1, args.steps)
     # the timed region proper: `pipeline` batches in flight
     wall = run_steps(n_slots, args.steps, False)[0] if n_slots > 1 else wall_one
@@ -469,7 +479,7 @@ def main():
              "tab_clear", "tab_fill", "tab_winners", "eps_table", "eps_new_tokens", "expand_arcs", "eps_meet", "-"]
     print("[bench] phase share of workgroup time (one batch in flight): " +
           ", ".join(f"{n} {100.0 * t / max(1, ticks.sum()):.1f}%" for n, t in zip(names, ticks) if t) +
-          f"; mean busy time per workgroup {ticks.sum() / 1e5 / B:.1f} ms",
+          f"; mean busy time per utterance {ticks.sum() / 1e5 / B:.1f} ms",
           file=sys.stderr, flush=True)
     for o in outs:
         if o is not None:
@@ -521,7 +531,7 @@ def main():
         "config": {"workload": args.workload, "batch": B, "frames": int(w.lengths.sum()),
                    "states": w.graph.num_states, "arcs": w.graph.num_arcs, "classes": V,
                    "beam": w.beam, "max_active": w.max_active, "batches_in_flight": n_slots,
-                   "workgroups_per_launch": (min(B, args.launch_workgroups) if args.launch_workgroups > 0 and n_slots > 1 else B),
+                   "workgroups_per_launch": (min(B, args.launch_workgroups) if args.launch_workgroups > 0 and n_slots > 1 else wgs_one),
                    "loglike_dtype": args.loglike_dtype, "decoders": 1, "narrow_arcs": bool(args.narrow_arcs),
                    "device_gib": round(dec.device_bytes() / 2**30, 1)},
         "one_batch_in_flight": {"value": w.audio_seconds / (wall_one / args.steps),
@@ -532,7 +542,7 @@ def main():
         "hbm_frac_of_peak": achieved / HBM_PEAK_GBS,
         "timed_region": "K decode_batch calls (init, all frames, final choice, traceback) plus the copy of their "
                         "results to pinned host memory, between two device synchronisations; log-likelihoods resident",
-        "roofline": {"bound": "hbm", "kernel": KERNEL, "achieved": achieved, "peak": HBM_PEAK_GBS,
+        "roofline": {"bound": "hbm", "kernel": kernel_one, "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                      "traffic_source": traffic_source, "traffic_detail": traffic_detail,
                      "algorithmic_bytes_per_launch": abytes, "kernel_ms": kms,
