@@ -2636,10 +2636,14 @@ int launches_in_flight(wfst_decoder *d, int slot_id) {
 // with all of them each.  Batches at 7,000 tokens and 437 frames at most, ms per batch with all 256 for each
 // launch, with one workgroup per utterance, with a share: 32 on four slots 14 to 19, 13.1, 7.2; 64 on
 // three slots 24 to 30, 17.3, 11.9.  (A process has four hardware queues: of more launches than four the
-// others are in line, not in flight.)
+// others are in line, not in flight.)  Launches that were given a number of workgroups keep it, whatever else
+// runs, but what counts is then the time per batch: a part of the launch's, and no less than its
+// compute-unit time over the chip's.  Large graph, 128 workgroups per launch, three slots, ms per batch by the launch's own
+// time and by this: batches of 128 38.4 and 33.7, of 64 28.9 and 23.8, of 32 (medium graph) 21.6 to 26.5 and 19.0.
 int plan_clusters(wfst_decoder *d, const std::vector<int> &frames, int max_active, int in_flight, bool solo, int &n_clusters, bool &lean) {
   const int n = (int)frames.size();
-  const int budget = d->launch_workgroups > 0 ? std::min(d->launch_workgroups, d->n_cu) : d->n_cu / (1 + std::min(in_flight, kHwQueues - 1));
+  const int n_launches = 1 + std::min(in_flight, kHwQueues - 1);
+  const int budget = d->launch_workgroups > 0 ? std::min(d->launch_workgroups, d->n_cu) : d->n_cu / n_launches;
   const float k_tok = (float)std::min(max_active, d->g.S) * 1e-3f;
   // solo: the kernel that keeps records in registers up to about 5,000 tokens, the older one beyond
   lean = k_tok <= 5.0f;
@@ -2653,7 +2657,9 @@ int plan_clusters(wfst_decoder *d, const std::vector<int> &frames, int max_activ
     const int C = std::min(n, room(lg));
     float most = std::max((float)frames[0], (float)total / (float)C);
     for (int k = 1; k * C < n; ++k) most = std::max(most, (float)(k + 1) * (float)frames[k * C]);
-    const float t = most * t_us[lg];
+    // compute-unit time: of workgroups that take utterances from the list until it is empty, or one utterance each
+    const float held = (float)(1 << lg) * t_us[lg] * (C < n ? most * (float)C : (float)total);
+    const float t = std::max(most * t_us[lg] / (float)n_launches, held / (float)d->n_cu);
     if (lg == 0 || t < best_t) { best = lg; best_t = t; }
   }
   // (narrow records, a mere initialisation or result, a part of the chip: one workgroup each)
@@ -2771,7 +2777,7 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
     std::vector<int> by_length(nfr);
     std::sort(by_length.begin(), by_length.end(), std::greater<int>());
     G = plan_clusters(d, by_length, a.mode & kModeInit ? a.max_active : d->stream_max_active,
-                      d->launch_workgroups > 0 || recorded ? 0 : launches_in_flight(d, slot_id), recorded, n_clusters, lean);
+                      recorded ? 0 : launches_in_flight(d, slot_id), recorded, n_clusters, lean);
     if (a.mode & kModeInit && !(a.mode & kModeFinal)) d->stream_max_active = a.max_active;
   }
   int n_wg = d->launch_workgroups > 0 ? std::min(n, d->launch_workgroups) : n;

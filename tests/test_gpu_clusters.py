@@ -389,12 +389,14 @@ def test_launches_in_flight_share_the_compute_units(torch_cuda, c2, c2_refs):
         dec.decode_batch(ll, c2.lengths[:B], c2.beam, c2.max_active, slot=0)
         torch.cuda.synchronize()
     assert dec.debug_last_launch() == (192, 8)
-    dec.set_launch_workgroups(128)                   # with a number of its own a launch does not share
+    # with a number of its own a launch keeps it, but when others are in flight it does not spend twice the
+    # compute-unit time on an earlier end of its own
+    dec.set_launch_workgroups(128)
     outs, shapes = [], []
     for k in range(3):
         outs.append(dec.decode_batch(ll, c2.lengths[:B], c2.beam, c2.max_active, slot=k, stream=streams[k]))
         shapes.append(dec.debug_last_launch())
-    assert shapes == [(128, 8)] * 3                  # three times half of the compute units: some wait for others to end
+    assert shapes[0] == (128, 8) and 64 < shapes[2][0] <= 128 and shapes[2][1] < 8, shapes
     check(outs)
     dec.close()
 
