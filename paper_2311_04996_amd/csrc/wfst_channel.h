@@ -59,13 +59,17 @@ struct ClusterArgs {                          // device memory of the workgroups
   unsigned long long *hello;                  // [workgroup][2] arrived / decided, likewise
 };
 
-struct WaveLds2 {             // ExpandArcs: the work items of one wave (one token per lane)
-  unsigned pre[kWaveTok + 1];
-  int abase[kWaveTok];
-  float tcost[kWaveTok];
-  int src[kWaveTok];          // number of the token in its set | its state in the boosting acceptor << 16
-  int2 pend[2 * kWaveTok];    // ring: records of tokens whose state has to be read from the graph
-  int pend_tok[2 * kWaveTok]; //       local number | number in the set << 16
+constexpr int kHubDeg2 = 128;                 // arcs beyond which a state's arcs are shared by all waves
+// The arcs of up to 64 work items of a wave, flattened over its lanes.  Arc f is the arc of the item whose
+// number is the count of items that end before f: a bit per arc says where an item ends, and a lane counts the bits
+// below its own.  (One LDS read and a count.  A binary search over prefix sums takes six dependent LDS reads, 1.5k
+// cycles per 128 arcs: with it, and with runs of 64 tokens however small the set, one utterance of 10.8 k tokens per
+// frame took 11.2 instead of 10.6 ms, one of 900 tokens 2.06 instead of 2.02 ms.)
+struct alignas(16) WaveItem { int abase; float tcost; int src; int pad; };   // unit address of the first arc minus the arcs of the items before;
+                                              // src: number of the token in its set | its state in the boosting acceptor << 16
+struct alignas(16) WaveLds2 {
+  unsigned long long last[kWaveTok * kHubDeg2 / 64];   // bit f: arc f is the last of its item
+  WaveItem item[kWaveTok + 1];                // items with arcs, in order (lanes behind the last arc may read one more)
 };
 struct alignas(16) Smem2 {
   union {
@@ -351,26 +355,48 @@ __device__ __forceinline__ void emit_arcs2(Cx &x, int (&ok)[N], const int4 (&a)[
   }
   push_cands2<kCl, N>(x, ok, next, nc, src, arc, 0);
 }
-constexpr int kHubDeg2 = 128;                 // arcs beyond which a state's arcs are shared by all waves
 __device__ __forceinline__ int next_run2(Smem2 &sm) {
   int r = 0;
   if ((threadIdx.x & 63) == 0) r = atomicAdd(&sm.next_run, 1);
   return uni(r);
 }
-// n <= 64 tokens of one wave's ring, starting at `head`: a lane reads the 32 bytes at the start of its
-// token's block (header + first arc); the other arcs of the batch are flattened over the 64 lanes
-// (prefix sums in the wave's slice of LDS, one short search per arc), and states with more than
-// kHubDeg2 arcs are listed for all waves.  Returns the emitting arcs expanded (wave-uniform).
+// Lists the items of a wave, one per lane (deg arcs from unit address `first`, at most kHubDeg2 of them; 0: no item);
+// returns the number of arcs.
+__device__ __forceinline__ int list_items(WaveLds2 &wl, unsigned deg, int first, float cost, int src) {
+  const int lane = lane_id() & 63;
+  const unsigned inc = wave_scan_add(deg);
+  const unsigned long long has = __ballot(deg != 0);
+  wl.last[2 * lane] = 0ull; wl.last[2 * lane + 1] = 0ull;
+  static_assert(sizeof(wl.last) == 64 * 16, "cleared by one store per lane");
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  if (deg) {
+    const unsigned e = inc - 1;
+    atomicOr(&wl.last[e >> 6], 1ull << (e & 63));
+    wl.item[__builtin_amdgcn_mbcnt_hi((unsigned)(has >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)has, 0u))] = WaveItem{first - (int)(inc - deg), cost, src, 0};
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  return __builtin_amdgcn_readlane((int)inc, 63);
+}
+// The item of the lane's arc in the w-th run of 64 arcs; `before`: items that end in earlier runs (kept by the caller).
+__device__ __forceinline__ WaveItem item_of(const WaveLds2 &wl, int w, int &before) {
+  const unsigned long long m = wl.last[w & (kWaveTok * kHubDeg2 / 64 - 1)];    // (a run behind the last arc: anything)
+  const unsigned lo = uni((unsigned)m), hi = uni((unsigned)(m >> 32));
+  const int j = before + (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+  before += __popc(lo) + __popc(hi);
+  return wl.item[min(j, kWaveTok)];
+}
+// The tokens of a wave, one per lane (`valid`; gl: local number | number in the set << 16): a lane reads the
+// 16 bytes at the end of its token's header (degrees and the first arc); the other arcs are flattened over the 64
+// lanes, and states with more than kHubDeg2 arcs are listed for all waves.  Returns the emitting arcs expanded
+// (wave-uniform).
 template <bool kCl>
-__device__ __forceinline__ unsigned dense_run2(Cx &x, WaveLds2 &wl, int head, int n, float beam, bool boosted) {
+__device__ __forceinline__ unsigned run2(Cx &x, WaveLds2 &wl, int2 tk, int id, bool valid, float beam, bool boosted) {
   Smem2 &sm = x.sm;
   HubLds &hb = sm.u.e.hub;
   const int lane = lane_id() & 63;
   const unsigned bm = x.g.blk_mask; const int bbits = x.g.blk_bits;
-  const bool valid = lane < n;
-  const int at = (head + lane) & (2 * kWaveTok - 1);
-  const int2 tk = valid ? wl.pend[at] : make_int2(0, 0);
-  const int id = valid ? wl.pend_tok[at] : 0;
   const int blk = (int)((unsigned)tk.x & bm);
   int4 hd = make_int4(0, 0, 0, 1);                       // no arcs; ilabel 1 keeps the acoustic lookup in range
   if (valid) hd = load_block_head(x.g.unit, blk);
@@ -380,7 +406,7 @@ __device__ __forceinline__ unsigned dense_run2(Cx &x, WaveLds2 &wl, int head, in
   if (ne == (int)kPackE) ne = x.g.unit[2 * (size_t)(unsigned)blk].z;        // a very large state: exact degree
   int has = (int)(ne > 0) & (int)(nx == 0);           // the unit after the header is an emitting arc
   unsigned deg = (unsigned)(ne - has);
-  const int first = 2 * blk + 1 + nx + has;           // unit address of the first arc left
+  int first = 2 * blk + 1 + nx + has;                 // unit address of the first arc left
   const float cost = __int_as_float(tk.y);
   int4 a0 = make_int4(hd.y, hd.z, has ? (hd.w & kLabelMask) : 1, 0);
   unsigned n_arcs = (unsigned)__popcll(__ballot(has));
@@ -408,18 +434,13 @@ __device__ __forceinline__ unsigned dense_run2(Cx &x, WaveLds2 &wl, int head, in
       deg = 0;
     }
   }
-  const unsigned inc = wave_scan_add(deg);
-  const unsigned M = (unsigned)__builtin_amdgcn_readlane((int)inc, 63);
-  wl.pre[lane] = inc - deg;
-  wl.abase[lane] = first - (int)(inc - deg);
-  wl.tcost[lane] = cost;
-  wl.src[lane] = srct;
-  if (lane == 0) wl.pre[kWaveTok] = M;
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
+  // two arcs per lane and step; the first step takes the batch's first arcs and 64 of the others.  (A state that found
+  // the shared list full comes back with its next kHubDeg2 arcs: an item has no more.)
+  for (int f0 = -64;; f0 = 0) {
+  const unsigned take = min(deg, (unsigned)kHubDeg2);
+  const unsigned M = (unsigned)list_items(wl, take, first, cost, srct);
   n_arcs += M;
-  // two arcs per lane and step; the first step takes the batch's first arcs and 64 of the others
-  int f0 = -64;
+  int w = 0, before = 0;
   do {
     int ok[2], src[2], arc[2]; int4 a[2]; float tc[2];
 #pragma unroll
@@ -427,10 +448,9 @@ __device__ __forceinline__ unsigned dense_run2(Cx &x, WaveLds2 &wl, int head, in
       const int f = f0 + u * 64 + lane;
       if (u == 0 && f0 < 0) { ok[0] = has; src[0] = srct; arc[0] = 2 * blk + 1; tc[0] = cost; a[0] = a0; continue; }
       ok[u] = f < (int)M;
-      const unsigned fs = ok[u] ? (unsigned)f : max(M, 1u) - 1;       // lanes past the end repeat the last arc (no branch)
-      const int j = wave_owner_of(wl.pre, fs);
-      src[u] = wl.src[j]; tc[u] = wl.tcost[j];
-      arc[u] = M ? wl.abase[j] + (int)fs : 2 * blk + 1;
+      const WaveItem it = item_of(wl, w++, before);
+      src[u] = it.src; tc[u] = it.tcost;
+      arc[u] = it.abase + f;
       a[u] = make_int4(0, 0, 1, 0);
       if (ok[u]) a[u] = load_emitting_arc<false>(x.g, arc[u], boosted);
     }
@@ -439,58 +459,47 @@ __device__ __forceinline__ unsigned dense_run2(Cx &x, WaveLds2 &wl, int head, in
   } while (f0 < (int)M);
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
+  deg -= take; first += (int)take;
+  if (__ballot(deg != 0) == 0ull) break;
+  }
   return n_arcs;
 }
+// A wave's tokens to expand.  The tokens outside simple states come first, then (among simple ones, which are skipped)
+// those the closure made; a run is `size` of them, so that all waves have one where the set is small.
+struct Run { int2 tk; int gl; bool valid; };
+__device__ __forceinline__ int run_size(const Cx &x) {
+  return min(kWaveTok, max(16, (x.n_front + x.n - x.n_emit + kWaves - 1) / kWaves));
+}
+template <bool kCl>
+__device__ __forceinline__ Run load_run(const Cx &x, const int2 *Q, const int *GI, int r, int size) {
+  const int lane = lane_id() & 63, j = r * size + lane;
+  Run run{make_int2((int)kFlagSimple, 0), 0, false};
+  if (lane < size && j < x.n_front + x.n - x.n_emit) {
+    const int i = j < x.n_front ? j : j - x.n_front + x.n_emit;
+    run.tk = Q[i]; run.gl = i | ((kCl ? GI[i] : i) << 16); run.valid = true;
+  }
+  return run;
+}
 // On entry sm.next_run == kWaves, sm.done_waves == 0, sm.n_hub == 0 and the hub list's ready
-// and seg_next words are zero (the caller sets them before its barrier).
+// and seg_next words are zero (the caller sets them before its barrier); `run`: the wave's first run.
 template <bool kCl, bool kBoost>
-__device__ __forceinline__ void expand2(Cx &x, const int2 *Q, const int *GI) {
+__device__ __forceinline__ void expand2(Cx &x, const int2 *Q, const int *GI, Run run) {
   Smem2 &sm = x.sm;
   HubLds &hb = sm.u.e.hub;
   const int tid = lane_id(), lane = tid & 63, wave = tid >> 6;
   const float beam = x.s.beam;
   const bool boosted = kBoost && x.s.boost_n > 0;
-  // Runs of 64 tokens: first the front tokens (none of them simple), then those the closure made
-  // (simple ones are skipped).  A wave collects tokens in its ring and expands 64 of them as a batch.
-  WaveLds2 &wl = sm.u.e.w[wave];
-  const int nf = x.n_front, ne = x.n_emit, nt = x.n;
-  const int R1 = (nf + kWaveTok - 1) / kWaveTok, R = R1 + (nt - ne + kWaveTok - 1) / kWaveTok;
-  const unsigned long long lt = (1ull << lane) - 1ull;
-  auto load = [&](int r, int2 &t, int &gl) {
-    const int i = r < R1 ? r * kWaveTok + lane : ne + (r - R1) * kWaveTok + lane;
-    const bool ok = r < R && i < (r < R1 ? nf : nt);
-    t = make_int2((int)kFlagSimple, 0); gl = 0;
-    if (ok) { t = Q[i]; gl = i | ((kCl ? GI[i] : i) << 16); }
-    return ok;
-  };
-  int r = wave, rn = next_run2(sm);
-  int2 tk, tkn; int gl, gln;
-  bool valid = load(r, tk, gl), validn = load(rn, tkn, gln);
-  int pend_head = 0, pend_n = 0;                       // wave-uniform: the list is ring entries [head, head + n)
+  WaveLds2 &wl = sm.u.e.w[uni(wave)];
+  const int size = run_size(x), total = x.n_front + x.n - x.n_emit;
   // the simple tokens of the emitting step have one arc each
-  unsigned long long n_arcs = tid < 64 ? (unsigned long long)(ne - nf) : 0ull;
-  while (r < R || pend_n > 0) {
-    if (r < R) {
-      const bool other = ((unsigned)tk.x & kFlagSimple) == 0;
-      n_arcs += (unsigned)__popcll(__ballot(valid && !other));
-      const unsigned long long m = __ballot(other);
-      if (other) {
-        const int at = (pend_head + pend_n + __popcll(m & lt)) & (2 * kWaveTok - 1);
-        wl.pend[at] = tk; wl.pend_tok[at] = gl;
-      }
-      pend_n += __popcll(m);
-      const int rnn = next_run2(sm);
-      tk = tkn; gl = gln; valid = validn;
-      validn = load(rnn, tkn, gln);
-      r = rn; rn = rnn;
-    }
-    if (pend_n >= kWaveTok || (r >= R && pend_n > 0)) {
-      const int take = min(pend_n, kWaveTok);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      n_arcs += dense_run2<kCl>(x, wl, pend_head, take, beam, boosted);
-      pend_head = (pend_head + take) & (2 * kWaveTok - 1); pend_n -= take;
-    }
+  unsigned long long n_arcs = tid < 64 ? (unsigned long long)(x.n_emit - x.n_front) : 0ull;
+  for (int r = uni(wave); r * size < total;) {
+    const int rn = size * kWaves >= total ? kWaves : next_run2(sm);
+    const Run nxt = load_run<kCl>(x, Q, GI, rn, size);
+    const bool other = ((unsigned)run.tk.x & kFlagSimple) == 0;      // (valid)
+    n_arcs += (unsigned)__popcll(__ballot(run.valid && !other));
+    n_arcs += run2<kCl>(x, wl, run.tk, run.gl, other, beam, boosted);
+    run = nxt; r = rn;
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   if (lane == 0) atomicAdd(&sm.done_waves, 1);
@@ -1706,14 +1715,15 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
       sm.ctr[kCtTok] += x.n;
       if (leader && t >= 0) sm.ctr[kCtFrames]++;
     }
-    __syncthreads();
     const int2 *Q = x.tq + (size_t)cur * c.qcap; int2 *NQ = x.tq + (size_t)(cur ^ 1) * c.qcap;
     const int *GI = x.gi + (size_t)cur * c.qcap; int *NGI = x.gi + (size_t)(cur ^ 1) * c.qcap;
     const unsigned lat_base = x.s.lat_used;
+    const Run run = load_run<kCl>(x, Q, GI, uni(tid >> 6), run_size(x));     // (ahead of the barrier)
+    __syncthreads();
     mark<kProf>(x, kPhOther);
     Cutoff cut;
     if (t >= 0) {
-      expand2<kCl, kBoost>(x, Q, GI);
+      expand2<kCl, kBoost>(x, Q, GI, run);
       if (kCl) stores_done();
       __syncthreads();
       mark<kProf>(x, kPhExpSetup);
