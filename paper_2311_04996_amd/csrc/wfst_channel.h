@@ -71,13 +71,20 @@ struct alignas(16) WaveLds2 {
   unsigned long long last[kWaveTok * kHubDeg2 / 64];   // bit f: arc f is the last of its item
   WaveItem item[kWaveTok + 1];                // items with arcs, in order (lanes behind the last arc may read one more)
 };
+// The closure does the same over epsilon arcs, with smaller lists (the table lies in the memory of the others).  A
+// state with more than kEpsDeg of them is listed in segments that all waves share.
+constexpr int kEpsTok = 32, kEpsDeg = 64, kEpsSeg = 64 * kU, kEpsSegs = 224;
+struct alignas(16) WaveEps {
+  unsigned long long last[kEpsTok * kEpsDeg / 64];
+  WaveItem item[kEpsTok + 1];
+};
 struct alignas(16) Smem2 {
   union {
     struct { float ac[kMaxV]; WaveLds2 w[kWaves]; HubLds hub; } e;
     TableLds t;
   } u;
   union {
-    EpsLds ek;                                // closure: a chunk of the worklist
+    struct { WaveEps w[kWaves]; WaveItem seg[kEpsSegs]; } ek;   // closure (of a segment `pad` is the number of arcs)
     struct {
       unsigned hasstay[kQueueMax / 32];       // bit i: local token i's first arc is the usual self-loop (other arcs follow)
       unsigned gh[kMaxG][256];                // the cluster's histograms
@@ -91,6 +98,8 @@ struct alignas(16) Smem2 {
   int seg_pre[kMaxG + 1];                     // own candidates: prefix sums over the segments
   unsigned x_best, x_minsimple;
   int x_any, x_status, x_made;                // (the first two are read together)
+  int x_more, x_before;                       // some candidate's state has epsilon arcs; overflows of the frame before
+  int more, status_before, n_eseg;
   unsigned best_ord, min_simple;
   float stay_ac;
   int n_hub, next_run, done_waves;
@@ -222,8 +231,10 @@ __device__ __forceinline__ void post_sizes(Cx &x) {
   if (!kCl) return;
   ++x.xc;
   if (tid < x.G) { post(x, tid, (unsigned)sm.n_seg[tid]); sm.n_seg[tid] = 0; }
+  static_assert(((kStLattice | kStCapacity) & ~0xff) == 0, "the word of the status has 8 bits for it");
   if (tid >= 64 && tid < 64 + kAux)
-    post(x, kBoxAux + tid - 64, tid == 64 ? sm.best_ord : tid == 65 ? (unsigned)sm.status : tid == 66 ? (unsigned)(x.sm.n_loc - x.n_emit) : sm.min_simple);
+    post(x, kBoxAux + tid - 64, tid == 64 ? sm.best_ord : tid == 65 ? (unsigned)(sm.status | sm.status_before << 8 | sm.more << 16) : tid == 66 ? (unsigned)(x.sm.n_loc - x.n_emit) : sm.min_simple);
+  if (tid == 65) sm.more = 0;
 }
 // Take the cluster's sizes: own candidates are [0, seg_pre[segments]) afterwards.  Ends with a barrier.
 template <bool kCl>
@@ -255,7 +266,7 @@ __device__ __forceinline__ void take_sizes(Cx &x) {
       const int n = lane < kRegions ? min(sm.n_seg[lane], region_cap) : 0;
       const int inc = (int)wave_scan_add((unsigned)n);
       if (lane < kRegions) { sm.seg_pre[lane + 1] = inc; sm.n_seg[lane] = 0; }
-      if (lane == 0) { sm.seg_pre[0] = 0; sm.x_best = sm.best_ord; sm.x_status = sm.status; sm.x_made = sm.n_loc - x.n_emit; sm.x_minsimple = sm.min_simple; }
+      if (lane == 0) { sm.seg_pre[0] = 0; sm.x_best = sm.best_ord; sm.x_status = sm.status; sm.x_more = sm.more; sm.more = 0; }
       if (lane == kRegions - 1) sm.x_any = inc > 0;
     }
   } else if (kCl && tid < 128) {
@@ -268,7 +279,10 @@ __device__ __forceinline__ void take_sizes(Cx &x) {
     const unsigned made = wave_sum(mine && which == 2 ? v : 0u);
     const unsigned st_l = __ballot(mine && which == 1 && (v & kStLattice)) != 0ull ? kStLattice : 0;
     const unsigned st_c = __ballot(mine && (w == 0ull || (which == 1 && (v & kStCapacity)))) != 0ull ? kStCapacity : 0;
-    if (lane == 0) { sm.x_best = best; sm.x_minsimple = ms; sm.x_made = (int)made; sm.x_status = (int)(st_l | st_c); }
+    const unsigned b_l = __ballot(mine && which == 1 && (v & kStLattice << 8)) != 0ull ? kStLattice : 0;
+    const unsigned b_c = __ballot(mine && which == 1 && (v & kStCapacity << 8)) != 0ull ? kStCapacity : 0;
+    const int more = __ballot(mine && which == 1 && (v >> 16)) != 0ull;
+    if (lane == 0) { sm.x_best = best; sm.x_minsimple = ms; sm.x_made = (int)made; sm.x_status = (int)(st_l | st_c); sm.x_before = (int)(b_l | b_c); sm.x_more = more; }
   }
   __syncthreads();
 }
@@ -360,14 +374,17 @@ __device__ __forceinline__ int next_run2(Smem2 &sm) {
   if ((threadIdx.x & 63) == 0) r = atomicAdd(&sm.next_run, 1);
   return uni(r);
 }
-// Lists the items of a wave, one per lane (deg arcs from unit address `first`, at most kHubDeg2 of them; 0: no item);
-// returns the number of arcs.
-__device__ __forceinline__ int list_items(WaveLds2 &wl, unsigned deg, int first, float cost, int src) {
+// Lists the items of a wave, one per lane (deg arcs from unit address `first`, at most kHubDeg2 (kEpsDeg) of them; 0: no
+// item); returns the number of arcs.
+template <class L>
+__device__ __forceinline__ int list_items(L &wl, unsigned deg, int first, float cost, int src) {
   const int lane = lane_id() & 63;
+  constexpr int kWords = sizeof(wl.last) / 8;
+  static_assert(kWords == 128 || kWords <= 64, "cleared by one store per lane");
   const unsigned inc = wave_scan_add(deg);
   const unsigned long long has = __ballot(deg != 0);
-  wl.last[2 * lane] = 0ull; wl.last[2 * lane + 1] = 0ull;
-  static_assert(sizeof(wl.last) == 64 * 16, "cleared by one store per lane");
+  if (kWords == 128) { wl.last[2 * lane & (kWords - 1)] = 0ull; wl.last[(2 * lane + 1) & (kWords - 1)] = 0ull; }
+  else if (lane < kWords) wl.last[lane] = 0ull;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   if (deg) {
@@ -380,12 +397,13 @@ __device__ __forceinline__ int list_items(WaveLds2 &wl, unsigned deg, int first,
   return __builtin_amdgcn_readlane((int)inc, 63);
 }
 // The item of the lane's arc in the w-th run of 64 arcs; `before`: items that end in earlier runs (kept by the caller).
-__device__ __forceinline__ WaveItem item_of(const WaveLds2 &wl, int w, int &before) {
-  const unsigned long long m = wl.last[w & (kWaveTok * kHubDeg2 / 64 - 1)];    // (a run behind the last arc: anything)
+template <class L>
+__device__ __forceinline__ WaveItem item_of(const L &wl, int w, int &before) {
+  const unsigned long long m = wl.last[w & (int)(sizeof(wl.last) / 8 - 1)];    // (a run behind the last arc: anything)
   const unsigned lo = uni((unsigned)m), hi = uni((unsigned)(m >> 32));
   const int j = before + (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
   before += __popc(lo) + __popc(hi);
-  return wl.item[min(j, kWaveTok)];
+  return wl.item[min(j, (int)(sizeof(wl.item) / sizeof(WaveItem)) - 1)];
 }
 // The tokens of a wave, one per lane (`valid`; gl: local number | number in the set << 16): a lane reads the
 // 16 bytes at the end of its token's header (degrees and the first arc); the other arcs are flattened over the 64
@@ -1093,88 +1111,116 @@ __device__ __forceinline__ void apply2(Cx &x, int win, const int4 &rec, int slot
   }
 }
 
+// Candidates of kU arcs per lane over epsilon arcs.
+template <bool kCl>
+__device__ __forceinline__ void emit_eps2(Cx &x, int (&ok)[kU], const float (&tc)[kU], const int (&src)[kU], int (&arc)[kU],
+                                          const Cutoff &cut, bool boosted, int buf) {
+  int next[kU]; float nc[kU]; int4 a[kU]; int more = 0;
+#pragma unroll
+  for (int u = 0; u < kU; ++u) { a[u] = make_int4(0, 0, 0, 0); if (ok[u]) a[u] = x.g.unit[arc[u]]; }
+#pragma unroll
+  for (int u = 0; u < kU; ++u) {
+    nc[u] = canon(tc[u] + __int_as_float(a[u].y));
+    next[u] = a[u].x; arc[u] |= (int)kArcEps;
+    if (boosted) {                           // epsilon arcs can carry output labels too
+      const int b = (int)((unsigned)src[u] >> 16);
+      int nb = b;
+      if (ok[u] && a[u].w != 0) nc[u] = canon(nc[u] + boost_step2(x.sm, b, a[u].w, nb));
+      next[u] |= nb << x.g.blk_bits;
+    }
+    ok[u] &= (int)(nc[u] < INFINITY) & (int)cut.keep(nc[u]);
+    more |= ok[u] & (int)((unsigned)next[u] >> 31);
+  }
+  if (__ballot(more) != 0ull) x.sm.more = 1;
+  push_cands2<kCl, kU>(x, ok, next, nc, src, arc, buf);
+}
+
 // Least fixpoint under the frozen predicate `cut`.  The worklist holds the tokens created or
 // improved in the previous round that have epsilon arcs.  The set's tokens that an epsilon arc can
 // enter sit in the LDS table (put there when they were made), so a round's candidates meet them
 // directly.  If they do not fit, every round's candidates go into an empty table and all tokens look
-// themselves up.  On entry wl0 holds sm.made[2] entries; ends behind an exchange in which nobody had a candidate, or
-// somebody an overflow.
+// themselves up.  On entry wl0 holds sm.made[2] entries.
+//
+// A round is bound by its chain (worklist, state, arcs, exchange, table, tokens), and every barrier adds to that the
+// wait for the slowest of 16 waves.  So each wave flattens the arcs of its own items (a flattening
+// over the block took three barriers more), and where no candidate's state has epsilon arcs the
+// round is the last, without one to find that out.  What only that exchange would tell, the size of the
+// set, comes with the next frame's first one: returns true if it is still to come (never with `last`, a launch's last frame).
+// (One utterance of 10.8 k tokens per frame 10.57 -> 9.93 ms, of 900 tokens 2.03 -> 1.90 ms, 64 on a graph that branches
+// everywhere 30.1 -> 28.4 ms.)
 template <bool kCl, bool kBoost, bool kProf>
-__device__ __forceinline__ void closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat_base, const Cutoff &cut) {
+__device__ __forceinline__ bool closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat_base, const Cutoff &cut, bool last) {
   Smem2 &sm = x.sm;
-  EpsLds &ek = sm.v.ek;
   TableLds &t = sm.u.t;
-  const int tid = lane_id();
+  const int tid = lane_id(), lane = tid & 63, wave = uni(tid >> 6);
   const bool boosted = kBoost && x.s.boost_n > 0;
   const int S = kCl ? x.G : kRegions, lg = kCl ? x.lg : 0;
   for (int round = 1;; ++round) {
     const int sel = (round - 1) & 1, buf = kCl ? (round & 1) : 0;
     const int4 *WL = x.wl0 + sel * x.c.qcap; int4 *WLN = x.wl0 + (sel ^ 1) * x.c.qcap;
     const int n_wl = uni(min(sm.made[2], x.c.qcap));
-    __syncthreads();
-    if (tid == 0) sm.made[2] = 0;
-    if (!kCl && n_wl == 0) { __syncthreads(); take_sizes<kCl>(x); break; }
-    for (int cb = 0; cb < n_wl; cb += kBlock) {
-      const int n_items = min(kBlock, n_wl - cb);
-      unsigned deg[1], ex[1];
+    if (!kCl && n_wl == 0) { __syncthreads(); break; }        // (the size of the set is known)
+    // ---- every wave expands items of its own; at least four, so that short lists don't keep all waves busy
+    const int size = min(kEpsTok, max(4, (n_wl + kWaves - 1) / kWaves));
+    WaveEps &we = sm.v.ek.w[wave];
+    unsigned xsum = 0;
+    for (int r = wave; r * size < n_wl; r += kWaves) {
+      const int i = r * size + lane;
       int4 w = make_int4(0, 0, 0, 0);
-      if (tid < n_items) w = WL[cb + tid];
-      const unsigned wblk = (unsigned)w.y & x.g.blk_mask;     // w.y is the token's key: (state in B, block)
-      deg[0] = tid < n_items ? (unsigned)x.g.unit[2 * (size_t)wblk].w >> kPackXShift : 0u;   // the state's header
-      {
-        // epsilon arcs out of the set (a counter): every token is listed as new exactly once
-        const unsigned xsum = wave_sum(w.w ? deg[0] : 0u);
-        if ((tid & 63) == 0 && xsum) atomicAdd((unsigned long long *)&sm.ctr[kCtXarc], (unsigned long long)xsum);
+      unsigned deg = 0;
+      if (lane < size && i < n_wl) {
+        w = WL[i];                                            // w.y is the token's key: (state in B, block)
+        deg = (unsigned)x.g.unit[2 * (size_t)((unsigned)w.y & x.g.blk_mask)].w >> kPackXShift;   // the state's header
       }
-      // block-wide exclusive scan of the arc counts
-      unsigned M = 0;
-      {
-        const int lane = tid & 63, wave = tid >> 6;
-        const unsigned inc = wave_scan_add(deg[0]);
-        if (lane == 63) sm.wave_tot[wave] = inc;
-        __syncthreads();
-        unsigned base = 0;
-#pragma unroll
-        for (int q = 0; q < kWaves; ++q) { const unsigned tt = sm.wave_tot[q]; if (q < wave) base += tt; M += tt; }
-        ex[0] = base + inc - deg[0];
-        M = uni(M);
-      }
-      ek.pre[tid] = ex[0];
-      ek.abase[tid] = 2 * (int)wblk + 1 - (int)ex[0];
-      ek.tcost[tid] = __int_as_float(w.z);         // the token's cost when it was listed
-      ek.ttok[tid] = w.x | (int)(((unsigned)w.y >> x.g.blk_bits) << 16);
-      if (tid == kBlock - 1) ek.pre[kBlock] = M;
-      __syncthreads();
-      for (unsigned f0 = 0; f0 < M; f0 += kBlock * kU) {
-        int ok[kU]; int src[kU]; int4 a[kU]; int arc[kU]; float tc[kU]; int j[kU];
-        owners_of<kU>(ek.pre, n_items, f0, M, ok, j);
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-          arc[u] = ek.abase[j[u]] + (int)(f0 + u * kBlock + tid);
-          src[u] = ek.ttok[j[u]];
-          tc[u] = ek.tcost[j[u]];
-          a[u] = make_int4(0, 0, 0, 0);
-          if (ok[u]) a[u] = x.g.unit[arc[u]];
+      int first = 2 * (int)((unsigned)w.y & x.g.blk_mask) + 1;
+      const float cost = __int_as_float(w.z);                 // the token's cost when it was listed
+      const int src = w.x | (int)(((unsigned)w.y >> x.g.blk_bits) << 16);
+      xsum += w.w ? deg : 0u;
+      if (deg > (unsigned)kEpsDeg) {                          // to the shared list, as far as it has room
+        const int n = ((int)deg + kEpsSeg - 1) / kEpsSeg;
+        const int h = atomicAdd(&sm.n_eseg, n), fit = max(0, min(n, kEpsSegs - h));
+        for (int q = 0; q < fit; ++q, first += kEpsSeg) {
+          sm.v.ek.seg[h + q] = WaveItem{first, cost, src, min(kEpsSeg, (int)deg)};
+          deg -= min((unsigned)kEpsSeg, deg);
         }
-        int next[kU]; float nc[kU];
+      }
+      do {
+        const unsigned take = min(deg, (unsigned)kEpsDeg);
+        const int M = list_items(we, take, first, cost, src);
+        for (int f0 = 0, q = 0, before = 0; f0 < M; f0 += 64 * kU) {
+          int ok[kU], isrc[kU], arc[kU]; float tc[kU];
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-          nc[u] = canon(tc[u] + __int_as_float(a[u].y));
-          next[u] = a[u].x; arc[u] |= (int)kArcEps;
-          if (boosted) {                           // epsilon arcs can carry output labels too
-            const int b = (int)((unsigned)src[u] >> 16);
-            int nb = b;
-            if (ok[u] && a[u].w != 0) nc[u] = canon(nc[u] + boost_step2(sm, b, a[u].w, nb));
-            next[u] |= nb << x.g.blk_bits;
+          for (int u = 0; u < kU; ++u) {
+            const int f = f0 + u * 64 + lane;
+            const WaveItem it = item_of(we, q++, before);
+            ok[u] = f < M; isrc[u] = it.src; tc[u] = it.tcost; arc[u] = it.abase + f;
           }
-          ok[u] &= (int)(nc[u] < INFINITY) & (int)cut.keep(nc[u]);
+          emit_eps2<kCl>(x, ok, tc, isrc, arc, cut, boosted, buf);
         }
-        push_cands2<kCl, kU>(x, ok, next, nc, src, arc, buf);
-      }
-      __syncthreads();                             // ek's readers are done before the next chunk rewrites it
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        deg -= take; first += (int)take;
+      } while (__ballot(deg != 0) != 0ull);
     }
+    // epsilon arcs out of the set (a counter): every token is listed as new exactly once
+    xsum = wave_sum(xsum);
+    if (lane == 0 && xsum) atomicAdd((unsigned long long *)&sm.ctr[kCtXarc], (unsigned long long)xsum);
     if (kCl) stores_done();
     __syncthreads();
+    const int n_seg = uni(min(sm.n_eseg, kEpsSegs));
+    if (n_seg > 0) {                                          // ---- segments of states with many arcs
+      for (int q = wave; q < n_seg; q += kWaves) {
+        const WaveItem it = sm.v.ek.seg[q];
+        int ok[kU], isrc[kU], arc[kU]; float tc[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) { ok[u] = u * 64 + lane < it.pad; isrc[u] = it.src; tc[u] = it.tcost; arc[u] = it.abase + u * 64 + lane; }
+        emit_eps2<kCl>(x, ok, tc, isrc, arc, cut, boosted, buf);
+      }
+      if (kCl) stores_done();
+      __syncthreads();
+      if (tid == 0) sm.n_eseg = 0;
+    }
+    if (tid == 0) sm.made[2] = 0;
     mark<kProf>(x, kPhEpsExpand);
     post_sizes<kCl>(x);
     take_sizes<kCl>(x);
@@ -1182,6 +1228,7 @@ __device__ __forceinline__ void closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
     // found no room has left the number of its candidate in the table, which would now be looked for among this
     // round's candidates.
     if (uni((int)(sm.x_any == 0) | sm.x_status)) break;
+    const bool more = uni(sm.x_more) != 0;
     const int n_own = uni(sm.seg_pre[S]);
     mark<kProf>(x, kPhEpsRecombine);
     if (n_own > 0) {
@@ -1262,21 +1309,19 @@ __device__ __forceinline__ void closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
       }
       if (tid == 0 && map) sm.made[3] = n_map + uni(sm.n_loc) - n_loc0;
     }
-    __syncthreads();
+    if (!more && !(kCl && last)) { mark<kProf>(x, kPhEpsRecombine); return kCl; }
   }
   mark<kProf>(x, kPhEpsRecombine);
+  return false;
 }
 
-// Publish the closed token set as A_f (f = x.s.frame).  Returns true (uniformly in the cluster) if an
-// overflow was flagged and the channel has to stop.
+// The closed token set becomes A_f (f = x.s.frame): the workgroup's own part of that.
 template <bool kCl, bool kOpt>
-__device__ __forceinline__ bool finish2(Cx &x, const int2 *NQ, const int *NGI, unsigned lat_base) {
+__device__ __forceinline__ void finish2(Cx &x, const int2 *NQ, const int *NGI, unsigned lat_base, bool stop) {
   Smem2 &sm = x.sm;
   const int tid = lane_id();
-  const int n = uni(min(sm.n_loc, x.c.qcap)), total = uni(min(sm.n_emit_all + sm.x_made, x.c.qcap));
+  const int n = uni(min(sm.n_loc, x.c.qcap));
   const int f = x.s.frame;
-  const bool leader = !kCl || x.me == 0;
-  const bool stop = uni(sm.x_status) != 0 || (kCl && uni(sm.dead) != 0);
   if (kOpt && !stop) {
     if (x.dig_sum && f <= x.c.max_frames) {
       unsigned long long s = 0;
@@ -1287,27 +1332,32 @@ __device__ __forceinline__ bool finish2(Cx &x, const int2 *NQ, const int *NGI, u
         s += mix64((((unsigned long long)(unsigned)state << 32) | (unsigned)sc.y) ^ ((unsigned long long)b * 0x9E3779B97F4A7C15ull));
       }
       if (s) atomicAdd(&x.dig_sum[f], s);        // (zeroed when the launch began)
-      if (tid == 0 && leader) x.dig_cnt[f] = total;
     }
     if (x.c.tokrec) {                              // lattice output wants the closed set's final records
       int2 *rec = x.c.tokrec + (x.lat - x.c.lattice) + lat_base;
       for (int i = tid; i < n; i += kBlock) { const int2 q = NQ[i]; rec[kCl ? NGI[i] : i] = make_int2((int)((unsigned)q.x & (kKeyMask | kFlagSimple)), q.y); }
     }
   }
-  if (tid == 0) {
-    if (leader) {
-      const int F = x.c.max_frames + 2;            // the per-frame tables are rings (a recycled channel outlives them)
-      x.frame_off[f % F] = lat_base;
-      x.frame_off[(f + 1) % F] = lat_base + (unsigned)total;
-      x.c.frame_ep[(x.frame_off - x.c.frame_off) + f % F] = x.s.lat_epoch;
-    }
-    sm.ctr[kCtStored] += n;
+  if (tid == 0) sm.ctr[kCtStored] += n;
+  x.s.cur ^= 1;
+  x.n = n;
+}
+// Its size and its place in the lattice: the newest set's, which starts at x.s.lat_used.
+template <bool kCl, bool kOpt>
+__device__ __forceinline__ void publish2(Cx &x, bool stop) {
+  const Smem2 &sm = x.sm;
+  const unsigned lat_base = x.s.lat_used;
+  const int total = uni(min(sm.n_emit_all + (kCl ? sm.x_made : sm.n_loc - x.n_emit), x.c.qcap));
+  const int f = x.s.frame;
+  if (threadIdx.x == 0 && (!kCl || x.me == 0)) {
+    const int F = x.c.max_frames + 2;            // the per-frame tables are rings (a recycled channel outlives them)
+    x.frame_off[f % F] = lat_base;
+    x.frame_off[(f + 1) % F] = lat_base + (unsigned)total;
+    x.c.frame_ep[(x.frame_off - x.c.frame_off) + f % F] = x.s.lat_epoch;
+    if (kOpt && !stop && x.dig_sum && f <= x.c.max_frames) x.dig_cnt[f] = total;
   }
   x.s.lat_used = lat_base + (unsigned)total;
   x.s.n_tok = total;
-  x.s.cur ^= 1;
-  x.n = n;
-  return stop;
 }
 
 // ------------------------------------------------------------------ final choice + traceback
@@ -1625,6 +1675,7 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
   if (tid == 0) {
     sm.best_ord = kOrdNone; sm.min_simple = kOrdNone; sm.x_minsimple = kOrdNone;
     sm.n_hub = 0; sm.made[0] = 0; sm.made[1] = 0; sm.n_loc = 0; sm.made[2] = 0; sm.made[3] = 0; sm.n_win = 0;
+    sm.more = 0; sm.status_before = 0; sm.n_eseg = 0; sm.x_before = 0;
     sm.map_bad = 0; sm.status = 0; sm.x_status = 0; sm.overfull = 0; sm.redo = 0; sm.n_emit = 0; sm.n_emit_all = 0; sm.x_made = 0;
     if (!kCl) sm.dead = 0;
     for (int r = 0; r < kMaxG; ++r) sm.n_seg[r] = 0;
@@ -1637,7 +1688,7 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
 
   // the buffers of the current set and of the one under construction
   int cur = kCl ? 0 : x.s.cur;
-  bool stop = false;
+  bool stop = false, open = false;               // open: the newest set's size is still to come
   x.n = 0; x.n_front = 0; x.n_emit = 0;
   if (kOpt && x.dig_sum && leader)               // the workgroups of a cluster add their parts of a digest
     for (int f = (a.mode & kModeInit ? 0 : x.s.frame + 1) + tid; f <= min(c.max_frames, (a.mode & kModeInit ? 0 : x.s.frame) + nfr); f += kBlock)
@@ -1687,9 +1738,6 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
   for (int t = a.mode & kModeInit ? -1 : 0; t < nfr; ++t) {
     if (stop || x.s.status) break;
     if (t >= 0 && x.s.frame >= c.max_frames && !c.recycle) { if (tid == 0) atomicOr(&sm.x_status, kStCapacity); break; }
-    // a recycled arena is a ring over whole frames: a frame's tokens (at most qcap) never straddle
-    // its end, the write position goes back to the start instead and the epoch counts that
-    if (c.recycle && x.s.lat_used + (unsigned)c.qcap > x.lat_cap) { x.s.lat_used = 0; x.s.lat_epoch++; }
     if (t >= 0) {
       const int vs = g.simple_il - 1;          // the class of the simple states' self-loop
       if (tid < a.V) sm.u.e.ac[tid] = row0;
@@ -1697,8 +1745,10 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
       if (tid == (vs & (kBlock - 1))) {
         const float ac = vs < kBlock ? row0 : row1;
         sm.stay_ac = ac;
-        // the best of all simple states' candidates: costs are added monotonically
-        const unsigned ms = sm.x_minsimple;
+        // the best of the simple states' candidates: costs are added monotonically (the cluster's, as far as the last
+        // exchange told, and the workgroup's own)
+        const unsigned ms = min(sm.x_minsimple, sm.min_simple);
+        sm.x_minsimple = kOrdNone; sm.min_simple = kOrdNone;
         const float nc = ms == kOrdNone ? INFINITY : canon((ord2f(ms) + g.simple_w) + ac);
         sm.best_ord = nc < INFINITY ? f2ord(nc) : kOrdNone;
       }
@@ -1710,14 +1760,13 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
     for (int h = tid; h < kHubCap; h += kBlock) { sm.u.e.hub.ready[h] = 0; sm.u.e.hub.seg_next[h] = 0; }
     for (int h = tid; h <= (x.n >> 5); h += kBlock) sm.v.s.hasstay[h & (kQueueMax / 32 - 1)] = 0u;
     if (tid == 0) {
-      sm.next_run = kWaves; sm.done_waves = 0; sm.n_hub = 0; sm.min_simple = kOrdNone;
+      sm.next_run = kWaves; sm.done_waves = 0; sm.n_hub = 0; sm.status_before = sm.status;
       sm.made[0] = 0; sm.made[1] = 0; sm.made[2] = 0; sm.made[3] = 0; sm.map_bad = 0; sm.n_win = 0; sm.overfull = 0;
       sm.ctr[kCtTok] += x.n;
       if (leader && t >= 0) sm.ctr[kCtFrames]++;
     }
     const int2 *Q = x.tq + (size_t)cur * c.qcap; int2 *NQ = x.tq + (size_t)(cur ^ 1) * c.qcap;
     const int *GI = x.gi + (size_t)cur * c.qcap; int *NGI = x.gi + (size_t)(cur ^ 1) * c.qcap;
-    const unsigned lat_base = x.s.lat_used;
     const Run run = load_run<kCl>(x, Q, GI, uni(tid >> 6), run_size(x));     // (ahead of the barrier)
     __syncthreads();
     mark<kProf>(x, kPhOther);
@@ -1731,16 +1780,31 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
       clear_table(sm);
       take_sizes<kCl>(x);
       mark<kProf>(x, kPhExpand);
+      if (open) {                                // the last frame's set, and an overflow of its last round
+        const int before = uni(sm.x_before);
+        publish2<kCl, kOpt>(x, before != 0);
+        open = false;
+        if (before) { __syncthreads(); if (tid == 0) sm.x_status = before; break; }
+      }
     } else {
       clear_table(sm);
       if (tid == 0) { sm.x_best = kOrdNone; for (int r = 0; r <= kMaxG; ++r) sm.seg_pre[r] = 0; }
       __syncthreads();
     }
+    // a recycled arena is a ring over whole frames: a frame's tokens (at most qcap) never straddle
+    // its end, the write position goes back to the start instead and the epoch counts that
+    if (c.recycle && x.s.lat_used + (unsigned)c.qcap > x.lat_cap) { x.s.lat_used = 0; x.s.lat_epoch++; }
+    const unsigned lat_base = x.s.lat_used;
     prune2<kCl, kProf, kOpt>(x, Q, GI, NQ, NGI, lat_base, cut, t < 0);
-    closure2<kCl, kBoost, kProf>(x, NQ, NGI, lat_base, cut);
+    const bool last = t + 1 >= nfr || (x.s.frame + 1 >= c.max_frames && !c.recycle);
+    open = closure2<kCl, kBoost, kProf>(x, NQ, NGI, lat_base, cut, last);
     x.s.frame++;
     cur ^= 1;
-    stop = finish2<kCl, kOpt>(x, NQ, NGI, lat_base);
+    if (!kCl && tid == 0) sm.x_status = sm.status;
+    stop = kCl ? !open && uni(sm.x_status) != 0 : uni(sm.status) != 0;
+    stop |= kCl && uni(sm.dead) != 0;
+    finish2<kCl, kOpt>(x, NQ, NGI, lat_base, stop);
+    if (!open) publish2<kCl, kOpt>(x, stop);
     mark<kProf>(x, kPhFinish);
     if (kCl && uni(sm.dead)) break;
   }

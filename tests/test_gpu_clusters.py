@@ -433,3 +433,62 @@ def test_a_captured_call_is_replayed(torch_cuda, c2, c2_refs):
         check((dec if k == 3 else other).decode_batch(torch.from_numpy(rows[k]).cuda(), lengths, c2.beam, c2.max_active), refs[k])
     assert dec.debug_last_launch()[1] > 1
     dec.close(), other.close()
+
+
+def _epsilon_fan_graph(n_items, deg, seed):
+    """Start -> n_items states over labels 1 and 2 -> `deg` leaves each over epsilon arcs, out of a few more leaves than
+    that; leaves have a self-loop, every eighth an epsilon arc to one more state, and go back to the start."""
+    from workloads.graphs import _csr
+    rng = np.random.default_rng([seed, n_items, deg])
+    n_leaf = deg + 37
+    leaf0, deep = 1 + n_items, 1 + n_items + n_leaf
+    S = deep + 1
+    items, leaves = np.arange(1, 1 + n_items), np.arange(leaf0, deep)
+    ends = np.concatenate([leaf0 + rng.permutation(n_leaf)[:deg] for _ in items])
+    chain = leaves[::8]
+    src = np.concatenate([np.zeros(n_items, np.int64), np.repeat(items, deg), leaves, leaves, chain, [deep]])
+    dst = np.concatenate([items, ends, leaves, np.zeros(n_leaf, np.int64), np.full(len(chain), deep), [deep]])
+    il = np.concatenate([1 + items % 2, np.zeros(n_items * deg, np.int64), np.full(n_leaf, 1), 1 + leaves % 2,
+                         np.zeros(len(chain), np.int64), [1]])
+    ol = np.where(rng.random(len(src)) < 0.2, rng.integers(1, 20, len(src)), 0)
+    return _csr(S, 0, 2, src, dst, il, ol, rng.choice([0.0, 0.25, 0.5, 1.0], len(src)))
+
+
+@pytest.mark.parametrize("cluster", [1, 2, 8], indirect=True)
+def test_epsilon_arcs_around_the_sizes_of_a_waves_list(torch_cuda, cluster):
+    """States with as many epsilon arcs as a wave lists, one more, as many as a segment of the shared list, one more, and
+    more segments than that list holds; worklists of one item to more than all waves take at once."""
+    rng = np.random.default_rng(5)
+    for n_items, deg in ((1, 1), (5, 63), (64, 64), (65, 65), (17, 128), (16, 129), (513, 3), (40, 1000)):
+        ll = rng.choice([-0.5, -1.0, -1.5], (2, 5, 2)).astype(np.float32)
+        parity.check_batch(torch_cuda, _epsilon_fan_graph(n_items, deg, 3), ll, np.array([5, 3], np.int32), 20.0, 4000,
+                           max_active_hint=8000)
+
+
+@pytest.mark.parametrize("cluster", [1, 2, 4, 8], indirect=True)
+def test_an_overflow_in_a_frames_last_closure_round_stops_the_channel(torch_cuda, cluster):
+    """10,002 tokens, 8,192 places, and no round and several frames after the one that finds no room: the channel is flagged
+    all the same, whether another workgroup learns of it in this frame or in the next."""
+    from paper_2311_04996_amd import Decoder, FLAG_CAPACITY, FLAG_DEAD
+    from workloads.graphs import _csr
+    n_dead, n_z = 6000, 4000
+    hub, one, z0, dead0 = 1, 2, 3, 3 + n_z
+    S = dead0 + n_dead
+    dead, z = np.arange(dead0, S), np.arange(z0, dead0)
+    src = np.concatenate([np.zeros(n_dead + 2, np.int64), np.full(n_z, hub), z, [one]])
+    dst = np.concatenate([dead, [hub, one], z, z, [one]])
+    il = np.concatenate([np.ones(n_dead + 1, np.int64), [2], np.zeros(n_z, np.int64), np.ones(n_z, np.int64), [2]])
+    g = _csr(S, 0, 2, src, dst, il, np.zeros(len(src), np.int64), np.zeros(len(src)))
+    ll = np.zeros((2, 4, 2), np.float32)
+    ll[1, :, 0] = -1000.0                            # the second utterance keeps to the one state
+    lengths = np.array([4, 4], np.int32)
+    dec = Decoder(g, max_channels=2, max_frames=4, max_active_hint=1000, lattice_bytes_per_channel=1 << 18, record_digests=True)
+    _, nwords, cost, flags = dec.decode_batch(torch_cuda.from_numpy(ll).cuda(), lengths, 5.0, 5000)
+    torch_cuda.cuda.synchronize()
+    assert flags.tolist()[0] & (FLAG_CAPACITY | FLAG_DEAD) == FLAG_CAPACITY | FLAG_DEAD and int(nwords[0]) == 0
+    (ref,) = parity.oracle_batch(g, ll[1:], lengths[1:], 5.0, 5000)
+    cnt, dig = dec.debug_frame_digests(1)
+    assert int(flags[1]) == ref.flags and float(cost[1]) == ref.cost
+    assert (cnt == ref.digest_count).all() and (dig == ref.digest_sum).all()
+    dec.close()
+    parity.check_batch(torch_cuda, g, ll, lengths, 5.0, 5000, max_active_hint=10000)
