@@ -94,7 +94,6 @@ struct alignas(16) Smem2 {
   unsigned hist[256], hist2[256], hist3[256];
   unsigned wave_tot[kWaves];
   int n_seg[kMaxG];                           // candidates pushed per segment
-  int xn[kMaxG * kMaxG];                      // segment sizes of the cluster: [writer][owner]
   int seg_pre[kMaxG + 1];                     // own candidates: prefix sums over the segments
   unsigned x_best, x_minsimple;
   int x_any, x_status, x_made;                // (the first two are read together)
@@ -143,6 +142,8 @@ struct Cx {                   // block-uniform view of one channel
 // The lane's number, opaque to the compiler: what is computed from it is computed again in every phase
 // instead of being kept (and spilled) through the frame loop.
 __device__ __forceinline__ int lane_id() { int t = threadIdx.x; asm volatile("" : "+v"(t)); return t; }
+// (one LDS instruction that nobody waits for)
+__device__ __forceinline__ void count2(Smem2 &sm, int which, int n) { atomicAdd((unsigned long long *)&sm.ctr[which], (unsigned long long)n); }
 template <bool kProf> __device__ __forceinline__ void mark(Cx &x, int phase) {
   if (kProf && threadIdx.x == 0) {
     const long long now = (long long)wall_clock64();
@@ -216,6 +217,8 @@ __device__ __forceinline__ void post(const Cx &x, int word, unsigned v) {
 // The cluster's counter of tokens in the set under construction (the closure takes numbers from it).
 __device__ __forceinline__ unsigned *set_size_of(const Cx &x) { return reinterpret_cast<unsigned *>(x.box0 + kBoxWords - 1); }
 __device__ __forceinline__ void set_counter(const Cx &x, int n) { __hip_atomic_store(set_size_of(x), (unsigned)n, __ATOMIC_RELAXED, kStoreScope); }
+// Entry f of a per-frame table of n entries (a ring if the stream outlives it).
+__device__ __forceinline__ int ring_at(int f, int n) { return f < n ? f : f % n; }
 // Every store of this thread has reached the L2.
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
@@ -236,7 +239,10 @@ __device__ __forceinline__ void post_sizes(Cx &x) {
     post(x, kBoxAux + tid - 64, tid == 64 ? sm.best_ord : tid == 65 ? (unsigned)(sm.status | sm.status_before << 8 | sm.more << 16) : tid == 66 ? (unsigned)(x.sm.n_loc - x.n_emit) : sm.min_simple);
   if (tid == 65) sm.more = 0;
 }
-// Take the cluster's sizes: own candidates are [0, seg_pre[segments]) afterwards.  Ends with a barrier.
+// Take the cluster's sizes: own candidates are [0, seg_pre[segments]) afterwards.  Ends with a barrier.  Three waves share the
+// work, and sums go by lane reads: the sizes through LDS, one wave for all of the rest and butterflies for minima made an exchange
+// 0.3 us longer (four or five exchanges a frame: one utterance of 10.8 k tokens 9.93 instead of 9.70 ms, with the other trips
+// through LDS that are now not waited for).
 template <bool kCl>
 __device__ __forceinline__ void take_sizes(Cx &x) {
   Smem2 &sm = x.sm;
@@ -251,17 +257,18 @@ __device__ __forceinline__ void take_sizes(Cx &x) {
       if (lane < G * G) {
         const unsigned long long w = poll_word<32>(sm, box_of(x, r) + p, x.xc, sm.polls);
         v = (unsigned)w; lost = w == 0ull;
-        sm.xn[r * kMaxG + p] = (int)min(v, (unsigned)x.seg_cap);
       }
       const unsigned long long any = __ballot(lost) ? 0ull : __ballot(v != 0);
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      int run = 0;
-      const int own = lane == 63 ? x.me ^ 1 : x.me;
-      for (int q = 0; q < G; ++q) { if (q < lane) run += sm.xn[q * kMaxG + own]; }
-      if (lane <= G) sm.seg_pre[lane] = run;
-      if (lane == 63) sm.n_in = G == kMaxG ? run : 0;
-      if (lane == 0) sm.x_any = any != 0ull;
+      // lane r * G + p holds writer r's segment for owner p: the owner's, lane by lane, without a trip through LDS
+      v = min(v, (unsigned)x.seg_cap);
+      int run = 0, pre = 0, in = 0;
+      for (int q = 0; q < G; ++q) {
+        pre = lane == q ? run : pre;
+        run += __builtin_amdgcn_readlane((int)v, (q << lg) + x.me);
+        in += __builtin_amdgcn_readlane((int)v, (q << lg) + (x.me ^ 1));
+      }
+      if (lane <= G) sm.seg_pre[lane] = lane == G ? run : pre;
+      if (lane == 0) { sm.x_any = any != 0ull; sm.n_in = G == kMaxG ? in : 0; }
     } else {
       const int n = lane < kRegions ? min(sm.n_seg[lane], region_cap) : 0;
       const int inc = (int)wave_scan_add((unsigned)n);
@@ -269,20 +276,24 @@ __device__ __forceinline__ void take_sizes(Cx &x) {
       if (lane == 0) { sm.seg_pre[0] = 0; sm.x_best = sm.best_ord; sm.x_status = sm.status; sm.x_more = sm.more; sm.more = 0; }
       if (lane == kRegions - 1) sm.x_any = inc > 0;
     }
-  } else if (kCl && tid < 128) {
+  } else if (kCl && tid < 192) {                 // best costs and status, and (the next wave) tokens made and costs in simple states
     unsigned long long w = 0;
-    const int which = lane & 3;
-    const bool mine = lane < kAux * x.G;
-    if (mine) w = poll_word<32>(sm, box_of(x, lane >> 2) + kBoxAux + which, x.xc, sm.polls);
+    const bool second = tid >= 128;
+    const int which = lane & 1;
+    const bool mine = lane < kAux / 2 * x.G;
+    if (mine) w = poll_word<32>(sm, box_of(x, lane >> 1) + kBoxAux + which + (second ? 2 : 0), x.xc, sm.polls);
     const unsigned v = (unsigned)w;
-    const unsigned best = wave_min(mine && which == 0 ? v : kOrdNone), ms = wave_min(mine && which == 3 ? v : kOrdNone);
-    const unsigned made = wave_sum(mine && which == 2 ? v : 0u);
-    const unsigned st_l = __ballot(mine && which == 1 && (v & kStLattice)) != 0ull ? kStLattice : 0;
-    const unsigned st_c = __ballot(mine && (w == 0ull || (which == 1 && (v & kStCapacity)))) != 0ull ? kStCapacity : 0;
-    const unsigned b_l = __ballot(mine && which == 1 && (v & kStLattice << 8)) != 0ull ? kStLattice : 0;
-    const unsigned b_c = __ballot(mine && which == 1 && (v & kStCapacity << 8)) != 0ull ? kStCapacity : 0;
-    const int more = __ballot(mine && which == 1 && (v >> 16)) != 0ull;
-    if (lane == 0) { sm.x_best = best; sm.x_minsimple = ms; sm.x_made = (int)made; sm.x_status = (int)(st_l | st_c); sm.x_before = (int)(b_l | b_c); sm.x_more = more; }
+    if (second) {
+      const unsigned made = wave_sum(mine && which == 0 ? v : 0u), ms = wave_min(mine && which == 1 ? v : kOrdNone);
+      if (lane == 0) { sm.x_made = (int)made; sm.x_minsimple = ms; }
+    } else {
+      const unsigned best = wave_min(mine && which == 0 ? v : kOrdNone), st = mine && which == 1 ? v : 0u;
+      auto any = [&](unsigned bits) { return __ballot((st & bits) != 0) != 0ull; };
+      const int now = (any(kStLattice) ? kStLattice : 0) | (any(kStCapacity) || __ballot(mine && w == 0ull) != 0ull ? kStCapacity : 0);
+      const int before = (any(kStLattice << 8) ? kStLattice : 0) | (any(kStCapacity << 8) ? kStCapacity : 0);
+      const int more = any(1u << 16);
+      if (lane == 0) { sm.x_best = best; sm.x_status = now; sm.x_before = before; sm.x_more = more; }
+    }
   }
   __syncthreads();
 }
@@ -311,12 +322,16 @@ __device__ __forceinline__ void push_cands2(Cx &x, const int (&ok)[N], const int
   const int lg = kCl ? x.lg : kRegionBits;
   const int cap = kCl ? x.seg_cap : x.c.region_cap;
   int4 *out = kCl ? x.cand + (size_t)(x.me * 2 + buf) * x.seg_stride : x.cand;
+  int p[N], slot[N];                             // (all places are asked for before the first is waited for)
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    p[u] = part_of(key_of(next[u]), lg); slot[u] = 0;
+    if (ok[u]) slot[u] = atomicAdd(&x.sm.n_seg[p[u]], 1);
+  }
 #pragma unroll
   for (int u = 0; u < N; ++u)
     if (ok[u]) {
-      const int p = part_of(key_of(next[u]), lg);
-      const int slot = atomicAdd(&x.sm.n_seg[p], 1);
-      if (slot < cap) put4<kCl>(out + (size_t)p * cap + slot, make_int4(next[u], __float_as_int(nc[u]), src[u], arc[u]));
+      if (slot[u] < cap) put4<kCl>(out + (size_t)p[u] * cap + slot[u], make_int4(next[u], __float_as_int(nc[u]), src[u], arc[u]));
       else atomicOr(&x.sm.status, kStCapacity);
     }
 }
@@ -635,16 +650,14 @@ __device__ __forceinline__ int find2(const Smem2 &sm, int key) {
 
 // The implied self-loop candidates of the tokens (of sub-group g of G): a candidate inside the beam and the
 // selected bins looks its key up; it is its state's recombined token unless the table holds a
-// better one (cost, then arc id).  Returns the lane's winners as bits (bit k: token k * kBlock + tid).
+// better one (cost, then arc id).  `nxt`: the lane's first token.  Returns the lane's winners as bits (bit k: token k * kBlock + tid).
 template <bool kCl>
-__device__ __forceinline__ unsigned long long stays2(Cx &x, const int2 *Q, const Cutoff &cut, int k_sel, int g, int P) {
+__device__ __forceinline__ unsigned long long stays2(Cx &x, const int2 *Q, int2 nxt, const Cutoff &cut, int k_sel, int g, int P) {
   Smem2 &sm = x.sm;
   TableLds &t = sm.u.t;
   const int tid = lane_id(), n = x.n;
   const int lg = kCl ? x.lg : 0;
   unsigned long long won = 0;
-  int2 nxt = make_int2(0, 0);
-  if (tid < n) nxt = Q[tid];
   for (int k = 0; k * kBlock < n; ++k) {
     const int i = k * kBlock + tid;
     const int2 q = nxt;
@@ -837,9 +850,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
           run += (float)hs[j] + hb[j]; run_c += hb[j];
           if (run >= (float)target && first == 256) { first = 4 * tid + j; at = run; at_c = run_c; }
         }
-        int fm = first;
-#pragma unroll
-        for (int sft = 32; sft > 0; sft >>= 1) fm = min(fm, __shfl_xor(fm, sft, 64));
+        const int fm = (int)wave_min((unsigned)first);
         const int owner = __ffsll((long long)__ballot(first == fm && fm != 256)) - 1;
         if (owner >= 0) {
           const float lane_c = hb[0] + hb[1] + hb[2] + hb[3];
@@ -869,6 +880,8 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
       const int r1 = !kCl && P > 1 ? uni(sm.seg_pre[g / (P / kRegions) + 1]) : n_own;
       int4 nxt = make_int4(0, 0, 0, 0);
       if (!small && r0 + tid < r1) nxt = get4<kCl>(cand_at<kCl>(x, r0 + tid, 0));
+      int2 tok0 = make_int2(0, 0);                 // (on its way while the table is filled)
+      if (tid < n_tok) tok0 = Q[tid];
 #pragma unroll 1
       for (int k = 0, i0 = r0; i0 < r1; ++k, i0 += kBlock) {
         const int i = i0 + tid;
@@ -883,7 +896,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
       }
       __syncthreads();
       mark<kProf>(x, kPhTabFill);
-      won |= stays2<kCl>(x, Q, cut, k_sel, g, P);
+      won |= stays2<kCl>(x, Q, tok0, cut, k_sel, g, P);
       __syncthreads();
       mark<kProf>(x, kPhSelect);
       // every candidate that was inserted looks at its slot again: the one still there has won
@@ -924,16 +937,24 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
     }
     clear_table(sm);
     if (kCl) {
+      // (the first wave waits for the words of selection at the same time)
+      const int which = lane & 3;
+      const bool mine = tid < 4 * x.G && which < 3;
+      unsigned v = 0;
       if (tid < x.G * 128) {
         const unsigned long long *p = hist_of(x, tid >> 7) + (tid & 127);
-        const unsigned long long v = poll_word<48>(sm, p, x.hc & 0xffffu, sm.polls);
-        *reinterpret_cast<uint2 *>(&sm.v.s.gh[tid >> 7][2 * (tid & 127)]) = make_uint2((unsigned)v & 0xffffffu, (unsigned)(v >> 24) & 0xffffffu);
+        const unsigned long long *ps = box_of(x, mine ? lane >> 2 : 0) + kBoxSel + which;
+        unsigned long long h = 0;
+        for (int n = 0;; ++n) {
+          h = aload(p);
+          bool there = (unsigned)(h >> 48) == (x.hc & 0xffffu);
+          if (mine) { const unsigned long long w = aload(ps); v = (unsigned)w; there &= (unsigned)(w >> 32) == x.xc; }
+          if (there) break;
+          if (n >= sm.polls || ((n & 1023) == 1023 && __hip_atomic_load(&sm.dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))) { sm.dead = 1; h = 0; v = 0; break; }
+        }
+        *reinterpret_cast<uint2 *>(&sm.v.s.gh[tid >> 7][2 * (tid & 127)]) = make_uint2((unsigned)h & 0xffffffu, (unsigned)(h >> 24) & 0xffffffu);
       }
       if (tid < 64) {
-        const int which = lane & 3;
-        const bool mine = lane < 4 * x.G && which < 3;
-        unsigned v = 0;
-        if (mine) v = poll(sm, box_of(x, lane >> 2) + kBoxSel + which, x.xc);
         const unsigned ks = wave_min(mine && which == 0 ? v & 0xffffu : 256u);
         const unsigned over = __ballot(mine && which == 0 && (v >> 16) != 0) != 0ull;
         const unsigned ns = wave_sum(mine && which == 1 ? v : 0u);
@@ -969,9 +990,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
         int first = 256;
 #pragma unroll
         for (int j = 0; j < 4; ++j) { run += h[j]; if (run > ma && first == 256) first = 4 * tid + j; }
-#pragma unroll
-        for (int sft = 32; sft > 0; sft >>= 1) first = min(first, __shfl_xor(first, sft, 64));
-        kk = first;
+        kk = (int)wave_min((unsigned)first);
         if (tid == 0 && (!kCl || x.me == 0)) { sm.ctr[kCtMaxAct]++; if (kk < 1) sm.ctr[kCtBin0]++; }
         if (kk < 1) kk = 1;
       } else if (ks < 256) redo = 1;                 // too many duplicates among the selected
@@ -1050,7 +1069,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
   __syncthreads();
   x.n_front = uni(sm.made[0]); x.n_emit = n_emit;
   if (tid == 0) {
-    sm.n_loc = n_emit; if (!init) sm.ctr[kCtKept] += min(n_emit, x.c.qcap);
+    sm.n_loc = n_emit; if (!init) count2(sm, kCtKept, min(n_emit, x.c.qcap));
     if (kCl && x.me == 0) set_counter(x, sm.n_emit_all);
   }
   if (tid < 256) sm.hist[tid] = 0;
@@ -1338,7 +1357,7 @@ __device__ __forceinline__ void finish2(Cx &x, const int2 *NQ, const int *NGI, u
       for (int i = tid; i < n; i += kBlock) { const int2 q = NQ[i]; rec[kCl ? NGI[i] : i] = make_int2((int)((unsigned)q.x & (kKeyMask | kFlagSimple)), q.y); }
     }
   }
-  if (tid == 0) sm.ctr[kCtStored] += n;
+  if (tid == 0) count2(sm, kCtStored, n);
   x.s.cur ^= 1;
   x.n = n;
 }
@@ -1351,9 +1370,9 @@ __device__ __forceinline__ void publish2(Cx &x, bool stop) {
   const int f = x.s.frame;
   if (threadIdx.x == 0 && (!kCl || x.me == 0)) {
     const int F = x.c.max_frames + 2;            // the per-frame tables are rings (a recycled channel outlives them)
-    x.frame_off[f % F] = lat_base;
-    x.frame_off[(f + 1) % F] = lat_base + (unsigned)total;
-    x.c.frame_ep[(x.frame_off - x.c.frame_off) + f % F] = x.s.lat_epoch;
+    x.frame_off[ring_at(f, F)] = lat_base;
+    x.frame_off[ring_at(f + 1, F)] = lat_base + (unsigned)total;
+    x.c.frame_ep[(x.frame_off - x.c.frame_off) + ring_at(f, F)] = x.s.lat_epoch;
     if (kOpt && !stop && x.dig_sum && f <= x.c.max_frames) x.dig_cnt[f] = total;
   }
   x.s.lat_used = lat_base + (unsigned)total;
@@ -1762,8 +1781,8 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
     if (tid == 0) {
       sm.next_run = kWaves; sm.done_waves = 0; sm.n_hub = 0; sm.status_before = sm.status;
       sm.made[0] = 0; sm.made[1] = 0; sm.made[2] = 0; sm.made[3] = 0; sm.map_bad = 0; sm.n_win = 0; sm.overfull = 0;
-      sm.ctr[kCtTok] += x.n;
-      if (leader && t >= 0) sm.ctr[kCtFrames]++;
+      count2(sm, kCtTok, x.n);
+      if (leader && t >= 0) count2(sm, kCtFrames, 1);
     }
     const int2 *Q = x.tq + (size_t)cur * c.qcap; int2 *NQ = x.tq + (size_t)(cur ^ 1) * c.qcap;
     const int *GI = x.gi + (size_t)cur * c.qcap; int *NGI = x.gi + (size_t)(cur ^ 1) * c.qcap;
