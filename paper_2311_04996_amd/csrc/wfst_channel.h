@@ -1163,7 +1163,7 @@ __device__ __forceinline__ void emit_eps2(Cx &x, int (&ok)[kU], const float (&tc
 // A round is bound by its chain (worklist, state, arcs, exchange, table, tokens), and every barrier adds to that the
 // wait for the slowest of 16 waves.  So each wave flattens the arcs of its own items (a flattening
 // over the block took three barriers more), and where no candidate's state has epsilon arcs the
-// round is the last, without one to find that out.  What only that exchange would tell, the size of the
+// round is the last, without one to find that out (if it is an odd one).  What only that exchange would tell, the size of the
 // set, comes with the next frame's first one: returns true if it is still to come (never with `last`, a launch's last frame).
 // (One utterance of 10.8 k tokens per frame 10.57 -> 9.93 ms, of 900 tokens 2.03 -> 1.90 ms, 64 on a graph that branches
 // everywhere 30.1 -> 28.4 ms.)
@@ -1328,7 +1328,9 @@ __device__ __forceinline__ bool closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
       }
       if (tid == 0 && map) sm.made[3] = n_map + uni(sm.n_loc) - n_loc0;
     }
-    if (!more && !(kCl && last)) { mark<kProf>(x, kPhEpsRecombine); return kCl; }
+    // (the next frame's arcs go to the segments of even rounds at once, and another workgroup may still be reading those
+    // of this one: an even round needs the exchange behind it)
+    if (!more && !(kCl && (last || buf == 0))) { mark<kProf>(x, kPhEpsRecombine); return kCl; }
   }
   mark<kProf>(x, kPhEpsRecombine);
   return false;
