@@ -89,6 +89,7 @@ struct alignas(16) Smem2 {
       unsigned hasstay[kQueueMax / 32];       // bit i: local token i's first arc is the usual self-loop (other arcs follow)
       unsigned gh[kMaxG][256];                // the cluster's histograms
     } s;
+    int4 mk[kWaves][64];                      // survivors on their way to become tokens
   } v;
   unsigned short tokof[kTabSlots];            // closure table: local token of a slot, 0xFFFF: none yet, or the last of a full set
   unsigned hist[256], hist2[256], hist3[256];
@@ -499,17 +500,17 @@ __device__ __forceinline__ unsigned run2(Cx &x, WaveLds2 &wl, int2 tk, int id, b
 }
 // A wave's tokens to expand.  The tokens outside simple states come first, then (among simple ones, which are skipped)
 // those the closure made; a run is `size` of them, so that all waves have one where the set is small.
-struct Run { int2 tk; int gl; bool valid; };
+struct Run { int2 tk; int i, gi; bool valid; };   // (nothing is made of its numbers before they are needed: that would wait for them)
 __device__ __forceinline__ int run_size(const Cx &x) {
   return min(kWaveTok, max(16, (x.n_front + x.n - x.n_emit + kWaves - 1) / kWaves));
 }
 template <bool kCl>
 __device__ __forceinline__ Run load_run(const Cx &x, const int2 *Q, const int *GI, int r, int size) {
   const int lane = lane_id() & 63, j = r * size + lane;
-  Run run{make_int2((int)kFlagSimple, 0), 0, false};
+  Run run{make_int2((int)kFlagSimple, 0), 0, 0, false};
   if (lane < size && j < x.n_front + x.n - x.n_emit) {
     const int i = j < x.n_front ? j : j - x.n_front + x.n_emit;
-    run.tk = Q[i]; run.gl = i | ((kCl ? GI[i] : i) << 16); run.valid = true;
+    run.tk = Q[i]; run.i = i; if (kCl) run.gi = GI[i]; run.valid = true;
   }
   return run;
 }
@@ -531,7 +532,7 @@ __device__ __forceinline__ void expand2(Cx &x, const int2 *Q, const int *GI, Run
     const Run nxt = load_run<kCl>(x, Q, GI, rn, size);
     const bool other = ((unsigned)run.tk.x & kFlagSimple) == 0;      // (valid)
     n_arcs += (unsigned)__popcll(__ballot(run.valid && !other));
-    n_arcs += run2<kCl>(x, wl, run.tk, run.gl, other, beam, boosted);
+    n_arcs += run2<kCl>(x, wl, run.tk, run.i | ((kCl ? run.gi : run.i) << 16), other, beam, boosted);
     run = nxt; r = rn;
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -1032,8 +1033,11 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
   // ---- survivors become tokens
   const int n_emit = uni(sm.n_emit), gbase = uni(sm.gbase);
   int4 *WL = x.wl0;
-  // first the candidates that won, then the tokens that stay where they are, made from the records of
-  // the current set; one rolled loop over both (its body is large)
+  // First the candidates that won, then the tokens that stay where they are, made from the records of
+  // the current set.  A third of the lanes have one at a time, and making a token is long (LDS counters, the closure's
+  // table), so every wave collects 64 of them before it makes any: 32 utterances of 8.1 k tokens per frame 36.7 -> 36.0 ms,
+  // 64 of 11.7 k on a graph that branches everywhere 27.9 -> 27.2 ms; where a wave has fewer than 64 in all (900 tokens per
+  // frame and workgroup) it makes no difference.
   const int n_c = small ? n_own : uni(min(sm.n_win, x.win_cap));
   const int k_c = (n_c + kBlock - 1) / kBlock, k_all = k_c + (n_tok + kBlock - 1) / kBlock;
   int4 nxt = make_int4(0, 0, 0, 0);
@@ -1042,20 +1046,36 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
     else if ((k - k_c) * kBlock + tid < n_tok) { const int i = (k - k_c) * kBlock + tid; const int2 q = Q[i]; nxt.x = q.x; nxt.y = q.y; nxt.z = kCl ? GI[i] : i; }
   };
   fetch(0);
+  int4 *mk = sm.v.mk[uni(tid >> 6)];
+  int n_mk = 0;
 #pragma unroll 1
-  for (int k = 0; k < k_all; ++k) {
+  for (int k = 0; k <= k_all; ++k) {
     int4 cr = k < k_c && small ? rec_at(k) : nxt;
-    fetch(k + 1);
-    int ok;
-    if (k < k_c) ok = small ? (int)(slot_at(k) >= 0) : (int)(k * kBlock + tid < n_c);
-    else {
-      ok = (int)((won >> (k - k_c)) & 1ull);
-      cr.y = __float_as_int(stay_cost2(x, __int_as_float(cr.y)));
-      cr.z |= (int)((((unsigned)cr.x & kKeyMask) >> x.g.blk_bits) << 16);
-      cr.w = 2 * (int)((unsigned)cr.x & x.g.blk_mask) + 1;     // the self-loop: the unit after the header
+    int ok = 0;
+    if (k < k_all) {
+      fetch(k + 1);
+      if (k < k_c) ok = small ? (int)(slot_at(k) >= 0) : (int)(k * kBlock + tid < n_c);
+      else {
+        ok = (int)((won >> (k - k_c)) & 1ull);
+        cr.y = __float_as_int(stay_cost2(x, __int_as_float(cr.y)));
+        cr.z |= (int)((((unsigned)cr.x & kKeyMask) >> x.g.blk_bits) << 16);
+        cr.w = 2 * (int)((unsigned)cr.x & x.g.blk_mask) + 1;     // the self-loop: the unit after the header
+      }
+      ok &= (int)(cut.bin(__int_as_float(cr.y)) < cut.k_keep);
     }
-    ok &= (int)(cut.bin(__int_as_float(cr.y)) < cut.k_keep);
-    make2<kCl, kOpt>(x, ok, cr.x, cr.y, cr.z, cr.w, cut, NQ, NGI, lat_base, WL, n_emit, gbase);
+    const unsigned long long m = __ballot(ok);
+    const int at = n_mk + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+    if (ok && at < 64) mk[at] = cr;
+    n_mk += __popcll(m);
+    if (n_mk < (k < k_all ? 64 : 1)) continue;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int4 r = mk[lane];
+    make2<kCl, kOpt>(x, (int)(lane < n_mk), r.x, r.y, r.z, r.w, cut, NQ, NGI, lat_base, WL, n_emit, gbase);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (ok && at >= 64) mk[at - 64] = cr;
+    n_mk -= 64;
   }
   if (kOpt && x.c.frame_best && tid == 0 && (!kCl || x.me == 0) && x.s.frame + 1 <= x.c.max_frames) {
     // the lattice kernel needs it for links across this frame's boundary
@@ -1741,19 +1761,25 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
     x.n = kCl ? uni(sm.n_loc) : x.s.n_tok;
   }
 
+  // A frame's row, two classes per lane, is loaded while the frame before waits for the sizes of its segments, and kept as it
+  // is in memory until it is needed: what is converted (or negated) at once is waited for at once.
   const long long ll0 = (long long)io * a.ll_stride;
-  // a frame's acoustic costs, two classes per lane, are loaded a frame ahead; 16-bit rows are widened exactly
-  auto row_cost = [&](int t, int v) -> float {
-    const long long at = ll0 + (long long)t * a.V + v;
-    if (a.ll_dtype == WFST_LOGLIKE_F32) return -static_cast<const float *>(a.ll)[at];
-    if (a.ll_dtype == WFST_LOGLIKE_F16) return -(float)static_cast<const _Float16 *>(a.ll)[at];
-    return -__uint_as_float((unsigned)static_cast<const unsigned short *>(a.ll)[at] << 16);
+  auto load_row = [&](int t, int v, unsigned &raw) {
+    const long long at = ll0 + (long long)t * a.V;
+    if (a.ll_dtype == WFST_LOGLIKE_F32) raw = (static_cast<const unsigned *>(a.ll) + at)[v];
+    else raw = (static_cast<const unsigned short *>(a.ll) + at)[v];
+  };
+  auto row_cost = [&](unsigned raw) -> float {       // 16-bit rows are widened exactly
+    if (a.ll_dtype == WFST_LOGLIKE_F32) return -__uint_as_float(raw);
+    if (a.ll_dtype == WFST_LOGLIKE_F16) return -(float)__builtin_bit_cast(_Float16, (unsigned short)raw);
+    return -__uint_as_float(raw << 16);
   };
   static_assert(kMaxV <= 2 * kBlock, "two classes per lane");
-  float row0 = 0.0f, row1 = 0.0f;
+  unsigned row0 = 0, row1 = 0;
   if (nfr > 0) {
-    if (tid < a.V) row0 = row_cost(0, tid);
-    if (tid + kBlock < a.V) row1 = row_cost(0, tid + kBlock);
+    const int v = lane_id();
+    if (v < a.V) load_row(0, v, row0);
+    if (v + kBlock < a.V) load_row(0, v + kBlock, row1);
   }
   // (step -1 of an initialisation makes the start token's set)
   for (int t = a.mode & kModeInit ? -1 : 0; t < nfr; ++t) {
@@ -1761,10 +1787,10 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
     if (t >= 0 && x.s.frame >= c.max_frames && !c.recycle) { if (tid == 0) atomicOr(&sm.x_status, kStCapacity); break; }
     if (t >= 0) {
       const int vs = g.simple_il - 1;          // the class of the simple states' self-loop
-      if (tid < a.V) sm.u.e.ac[tid] = row0;
-      if (tid + kBlock < a.V) sm.u.e.ac[tid + kBlock] = row1;
+      if (tid < a.V) sm.u.e.ac[tid] = row_cost(row0);
+      if (tid + kBlock < a.V) sm.u.e.ac[tid + kBlock] = row_cost(row1);
       if (tid == (vs & (kBlock - 1))) {
-        const float ac = vs < kBlock ? row0 : row1;
+        const float ac = row_cost(vs < kBlock ? row0 : row1);
         sm.stay_ac = ac;
         // the best of the simple states' candidates: costs are added monotonically (the cluster's, as far as the last
         // exchange told, and the workgroup's own)
@@ -1772,10 +1798,6 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
         sm.x_minsimple = kOrdNone; sm.min_simple = kOrdNone;
         const float nc = ms == kOrdNone ? INFINITY : canon((ord2f(ms) + g.simple_w) + ac);
         sm.best_ord = nc < INFINITY ? f2ord(nc) : kOrdNone;
-      }
-      if (t + 1 < nfr) {
-        if (tid < a.V) row0 = row_cost(t + 1, tid);
-        if (tid + kBlock < a.V) row1 = row_cost(t + 1, tid + kBlock);
       }
     }
     for (int h = tid; h < kHubCap; h += kBlock) { sm.u.e.hub.ready[h] = 0; sm.u.e.hub.seg_next[h] = 0; }
@@ -1799,6 +1821,11 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
       mark<kProf>(x, kPhExpSetup);
       post_sizes<kCl>(x);
       clear_table(sm);
+      if (t + 1 < nfr) {
+        const int v = lane_id();
+        if (v < a.V) load_row(t + 1, v, row0);
+        if (v + kBlock < a.V) load_row(t + 1, v + kBlock, row1);
+      }
       take_sizes<kCl>(x);
       mark<kProf>(x, kPhExpand);
       if (open) {                                // the last frame's set, and an overflow of its last round

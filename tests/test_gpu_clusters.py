@@ -492,3 +492,21 @@ def test_an_overflow_in_a_frames_last_closure_round_stops_the_channel(torch_cuda
     assert (cnt == ref.digest_count).all() and (dig == ref.digest_sum).all()
     dec.close()
     parity.check_batch(torch_cuda, g, ll, lengths, 5.0, 5000, max_active_hint=10000)
+
+
+@pytest.mark.parametrize("cluster", [1, 2, 8], indirect=True)
+def test_survivors_around_the_number_a_wave_collects(torch_cuda, cluster):
+    """Sets of as many tokens as a wave, or all waves of a workgroup, make at a time, one fewer and one more: from candidates
+    in the first frame, and from candidates and tokens that stay where they are in the next ones."""
+    from workloads.graphs import _csr
+    rng = np.random.default_rng(11)
+    for n in (1, 63, 64, 65, 1023, 1025, 2049, 4000):
+        leaves = np.arange(1, n + 1)
+        back = leaves[::3]                           # the others have the self-loop alone
+        src = np.concatenate([np.zeros(n, np.int64), leaves, back])
+        dst = np.concatenate([leaves, leaves, np.zeros(len(back), np.int64)])
+        il = np.concatenate([2 + leaves % 2, np.ones(n, np.int64), np.full(len(back), 2)])
+        w = np.concatenate([rng.choice([0.0, 0.5, 1.0], n), np.zeros(n), np.full(len(back), 0.25)])
+        g = _csr(n + 1, 0, 3, src, dst, il, np.where(rng.random(len(src)) < 0.1, 7, 0), w)
+        ll = rng.choice([-0.5, -1.0, -2.0], (2, 4, 3)).astype(np.float32)
+        parity.check_batch(torch_cuda, g, ll, np.array([4, 2], np.int32), 20.0, 5000, max_active_hint=5000)
