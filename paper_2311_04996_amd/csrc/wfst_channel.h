@@ -1356,14 +1356,15 @@ __device__ __forceinline__ bool closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
   return false;
 }
 
-// The closed token set becomes A_f (f = x.s.frame): the workgroup's own part of that.
+// The closed token set becomes A_f (f = x.s.frame): the workgroup's own part of that.  `bad`: some tokens found no room, and
+// were not written or have a number beyond the arena.
 template <bool kCl, bool kOpt>
-__device__ __forceinline__ void finish2(Cx &x, const int2 *NQ, const int *NGI, unsigned lat_base, bool stop) {
+__device__ __forceinline__ void finish2(Cx &x, const int2 *NQ, const int *NGI, unsigned lat_base, bool bad) {
   Smem2 &sm = x.sm;
   const int tid = lane_id();
   const int n = uni(min(sm.n_loc, x.c.qcap));
   const int f = x.s.frame;
-  if (kOpt && !stop) {
+  if (kOpt && !bad) {
     if (x.dig_sum && f <= x.c.max_frames) {
       unsigned long long s = 0;
       for (int i = tid; i < n; i += kBlock) {
@@ -1376,7 +1377,10 @@ __device__ __forceinline__ void finish2(Cx &x, const int2 *NQ, const int *NGI, u
     }
     if (x.c.tokrec) {                              // lattice output wants the closed set's final records
       int2 *rec = x.c.tokrec + (x.lat - x.c.lattice) + lat_base;
-      for (int i = tid; i < n; i += kBlock) { const int2 q = NQ[i]; rec[kCl ? NGI[i] : i] = make_int2((int)((unsigned)q.x & (kKeyMask | kFlagSimple)), q.y); }
+      for (int i = tid; i < n; i += kBlock) {
+        const int2 q = NQ[i]; const unsigned at = (unsigned)(kCl ? NGI[i] : i);
+        if (lat_base + at < x.lat_cap) rec[at] = make_int2((int)((unsigned)q.x & (kKeyMask | kFlagSimple)), q.y);
+      }
     }
   }
   if (tid == 0) count2(sm, kCtStored, n);
@@ -1849,9 +1853,14 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
     x.s.frame++;
     cur ^= 1;
     if (!kCl && tid == 0) sm.x_status = sm.status;
-    stop = kCl ? !open && uni(sm.x_status) != 0 : uni(sm.status) != 0;
+    // (the workgroup's own status is final behind the closure's last barrier)
+    const bool bad = uni(sm.status) != 0;
+    stop = kCl ? !open && uni(sm.x_status) != 0 : bad;
     stop |= kCl && uni(sm.dead) != 0;
-    finish2<kCl, kOpt>(x, NQ, NGI, lat_base, stop);
+    finish2<kCl, kOpt>(x, NQ, NGI, lat_base, stop || bad);
+    // If the set's size is still to come, the cluster learns of an overflow with it, behind ExpandArcs of the next
+    // frame: until then the workgroup has the tokens of the emitting step, all of them written, and none to expand.
+    if (kCl && bad) { x.n_front = 0; x.n = x.n_emit; }
     if (!open) publish2<kCl, kOpt>(x, stop);
     mark<kProf>(x, kPhFinish);
     if (kCl && uni(sm.dead)) break;

@@ -510,3 +510,59 @@ def test_survivors_around_the_number_a_wave_collects(torch_cuda, cluster):
         g = _csr(n + 1, 0, 3, src, dst, il, np.where(rng.random(len(src)) < 0.1, 7, 0), w)
         ll = rng.choice([-0.5, -1.0, -2.0], (2, 4, 3)).astype(np.float32)
         parity.check_batch(torch_cuda, g, ll, np.array([4, 2], np.int32), 20.0, 5000, max_active_hint=5000)
+
+
+def _late_fan_graph(n_dead, n_z, n_few=20):
+    """Start -> a state with a loop over label 2, from where label 1 leads to `n_dead` dead ends and, over a hub's epsilon arcs,
+    to `n_z` states with a self-loop, and label 3 to a few states and back over label 2."""
+    from workloads.graphs import _csr
+    one, hub, few0 = 1, 2, 3
+    z0 = few0 + n_few
+    dead0 = z0 + n_z
+    S = dead0 + n_dead
+    few, z, dead = np.arange(few0, z0), np.arange(z0, dead0), np.arange(dead0, S)
+    src = np.concatenate([[0], np.full(2 + n_few + n_dead, one), np.full(n_z, hub), few, few, z])
+    dst = np.concatenate([[one], [one, hub], few, dead, z, np.full(n_few, one), np.roll(few, 1), z])
+    il = np.concatenate([[2], [2, 1], np.full(n_few, 3), np.full(n_dead, 1), np.zeros(n_z), np.full(n_few, 2), np.full(n_few, 3),
+                         np.ones(n_z)]).astype(np.int64)
+    w = np.concatenate([np.zeros(3), 0.125 * np.arange(n_few), np.zeros(n_dead + n_z), np.full(2 * n_few, 0.5), np.zeros(n_z)])
+    return _csr(S, 0, 3, src, dst, il, np.where(il == 3, 7, 0), w)
+
+
+@pytest.mark.parametrize("cluster", [1, 2, 4, 8], indirect=True)
+def test_an_arena_that_ends_in_a_frames_only_closure_round_keeps_the_neighbours_records(torch_cuda, cluster):
+    """The 13th frame's 3,001 emitted tokens fit the arena of 4,096, the 3,000 its closure adds do not, and more frames
+    follow: the channel is flagged and its lattice refused, and the lattices of the channels whose arenas lie between
+    and behind are the oracle's, every token and link."""
+    from oracle import Oracle
+    from paper_2311_04996_amd import Decoder, FLAG_DEAD, FLAG_LATTICE_OVERFLOW, WfstError
+    from test_gpu_lattice import gpu_rows, oracle_rows
+    g = _late_fan_graph(3000, 3000)
+    B, T, beam, ma = 5, 16, 5.0, 5000
+    over = (0, 2, 4)
+    ll = np.full((B, T, 3), -1000.0, np.float32)
+    rng = np.random.default_rng(17)
+    ll[:, :, 1:] = rng.choice([-0.25, -0.5, -1.0], (B, T, 2))     # labels 2 and 3
+    for b in over:
+        ll[b] = -1000.0
+        ll[b, :12, 1] = ll[b, 12:, 0] = 0.0
+    dec = Decoder(g, max_channels=B, max_frames=T, max_active_hint=1000, lattice_bytes_per_channel=8 * 4096, keep_token_records=True)
+    dev = torch_cuda.from_numpy(ll).cuda()
+    lengths = np.full(B, T, np.int32)
+    _, nwords, _, flags = (t.cpu().numpy() for t in dec.decode_batch(dev, lengths, beam, ma))
+    o = Oracle(g)
+    for b in range(B):
+        if b in over:
+            assert flags[b] & (FLAG_LATTICE_OVERFLOW | FLAG_DEAD) == FLAG_LATTICE_OVERFLOW | FLAG_DEAD and nwords[b] == 0
+            with pytest.raises(WfstError):
+                dec.get_lattice(b, dev[b], 4.0)
+            continue
+        L = o.lattice(ll[b], T, beam=beam, max_active=ma, lattice_beam=4.0)
+        lat = dec.get_lattice(b, dev[b], 4.0)
+        assert lat.frame_off.tolist() == L.set_off.tolist()
+        for t in range(T + 1):
+            a, e = int(L.set_off[t]), int(L.set_off[t + 1])
+            assert sorted(zip(lat.state[a:e].tolist(), lat.cost[a:e].tolist())) == sorted(zip(L.states[a:e].tolist(), L.costs[a:e].tolist()))
+        want, got = oracle_rows(o, g, L), gpu_rows(lat)
+        assert got.shape == want.shape and (got == want).all()
+    dec.close()
