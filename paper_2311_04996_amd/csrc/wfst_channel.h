@@ -113,7 +113,7 @@ struct alignas(16) Smem2 {
   unsigned ratio;
   int path_frames, trace_from, trace_words, sel_idx, job;
   unsigned long long red64, red64b;
-  long long ctr[8];
+  long long ctr[8], earc_before;               // (earc_before: ctr[kCtEarc] when the frame began)
   int bk[kBoostSlots]; float bv[kBoostSlots]; unsigned bft[kBoostSlots];
   long long prof[16];
   long long prof_t0;
@@ -144,7 +144,7 @@ struct Cx {                   // block-uniform view of one channel
 // instead of being kept (and spilled) through the frame loop.
 __device__ __forceinline__ int lane_id() { int t = threadIdx.x; asm volatile("" : "+v"(t)); return t; }
 // (one LDS instruction that nobody waits for)
-__device__ __forceinline__ void count2(Smem2 &sm, int which, int n) { atomicAdd((unsigned long long *)&sm.ctr[which], (unsigned long long)n); }
+__device__ __forceinline__ void count2(Smem2 &sm, int which, int n) { atomicAdd((unsigned long long *)&sm.ctr[which], (unsigned long long)(long long)n); }
 template <bool kProf> __device__ __forceinline__ void mark(Cx &x, int phase) {
   if (kProf && threadIdx.x == 0) {
     const long long now = (long long)wall_clock64();
@@ -1807,7 +1807,7 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
     for (int h = tid; h < kHubCap; h += kBlock) { sm.u.e.hub.ready[h] = 0; sm.u.e.hub.seg_next[h] = 0; }
     for (int h = tid; h <= (x.n >> 5); h += kBlock) sm.v.s.hasstay[h & (kQueueMax / 32 - 1)] = 0u;
     if (tid == 0) {
-      sm.next_run = kWaves; sm.done_waves = 0; sm.n_hub = 0; sm.status_before = sm.status;
+      sm.next_run = kWaves; sm.done_waves = 0; sm.n_hub = 0; sm.status_before = sm.status; sm.earc_before = sm.ctr[kCtEarc];
       sm.made[0] = 0; sm.made[1] = 0; sm.made[2] = 0; sm.made[3] = 0; sm.map_bad = 0; sm.n_win = 0; sm.overfull = 0;
       count2(sm, kCtTok, x.n);
       if (leader && t >= 0) count2(sm, kCtFrames, 1);
@@ -1836,7 +1836,13 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
         const int before = uni(sm.x_before);
         publish2<kCl, kOpt>(x, before != 0);
         open = false;
-        if (before) { __syncthreads(); if (tid == 0) sm.x_status = before; break; }
+        if (before) {                            // it has no digest, and what was expanded from it does not count
+          __syncthreads();
+          if (tid == 0) { sm.x_status = before; sm.ctr[kCtEarc] = sm.earc_before; count2(sm, kCtTok, -x.n); if (leader) count2(sm, kCtFrames, -1); }
+          if (kOpt && x.dig_sum && leader && tid == 0 && x.s.frame <= c.max_frames)
+            __hip_atomic_store(&x.dig_sum[x.s.frame], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          break;
+        }
       }
     } else {
       clear_table(sm);

@@ -468,7 +468,8 @@ def test_epsilon_arcs_around_the_sizes_of_a_waves_list(torch_cuda, cluster):
 @pytest.mark.parametrize("cluster", [1, 2, 4, 8], indirect=True)
 def test_an_overflow_in_a_frames_last_closure_round_stops_the_channel(torch_cuda, cluster):
     """10,002 tokens, 8,192 places, and no round and several frames after the one that finds no room: the channel is flagged
-    all the same, whether another workgroup learns of it in this frame or in the next."""
+    all the same, whether another workgroup learns of it in this frame or in the next, and for every number of workgroups
+    the frame has no digest and none of its tokens are expanded."""
     from paper_2311_04996_amd import Decoder, FLAG_CAPACITY, FLAG_DEAD
     from workloads.graphs import _csr
     n_dead, n_z = 6000, 4000
@@ -482,14 +483,19 @@ def test_an_overflow_in_a_frames_last_closure_round_stops_the_channel(torch_cuda
     ll = np.zeros((2, 4, 2), np.float32)
     ll[1, :, 0] = -1000.0                            # the second utterance keeps to the one state
     lengths = np.array([4, 4], np.int32)
-    dec = Decoder(g, max_channels=2, max_frames=4, max_active_hint=1000, lattice_bytes_per_channel=1 << 18, record_digests=True)
+    dec = Decoder(g, max_channels=2, max_frames=4, max_active_hint=1000, lattice_bytes_per_channel=1 << 18, record_digests=True,
+                  keep_token_records=True)
     _, nwords, cost, flags = dec.decode_batch(torch_cuda.from_numpy(ll).cuda(), lengths, 5.0, 5000)
     torch_cuda.cuda.synchronize()
     assert flags.tolist()[0] & (FLAG_CAPACITY | FLAG_DEAD) == FLAG_CAPACITY | FLAG_DEAD and int(nwords[0]) == 0
-    (ref,) = parity.oracle_batch(g, ll[1:], lengths[1:], 5.0, 5000)
+    first, ref = parity.oracle_batch(g, ll, [1, 4], 5.0, 5000)
     cnt, dig = dec.debug_frame_digests(1)
     assert int(flags[1]) == ref.flags and float(cost[1]) == ref.cost
     assert (cnt == ref.digest_count).all() and (dig == ref.digest_sum).all()
+    cnt, dig = dec.debug_frame_digests(0)
+    assert len(dig) == 2 and cnt[0] == first.digest_count[0] and dig[0] == first.digest_sum[0] and dig[1] == 0
+    # tokens expanded, arcs out of them, frames: of the stopped channel its one frame's
+    assert dec.get_counters()[[0, 1, 7]].tolist() == [int(first.counters[k] + ref.counters[k]) for k in (0, 1)] + [1 + 4]
     dec.close()
     parity.check_batch(torch_cuda, g, ll, lengths, 5.0, 5000, max_active_hint=10000)
 
