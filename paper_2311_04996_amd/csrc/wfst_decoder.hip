@@ -1685,6 +1685,7 @@ __device__ __forceinline__ bool finish_set(Ctx &x, int2 *NQ, unsigned lat_base) 
   if (x.dig_sum) {
     unsigned long long s = 0;
     for (int i = tid; i < n; i += kBlock) {
+      if (lat_base + (unsigned)i >= x.lat_cap) break;          // a token beyond the arena was never written
       const int2 sc = NQ[i];
       const int state = x.g.unit[2 * (size_t)((unsigned)sc.x & x.g.blk_mask)].x;     // the header names the state
       const unsigned b = ((unsigned)sc.x & kKeyMask) >> x.g.blk_bits;   // the token's state in the boosting acceptor

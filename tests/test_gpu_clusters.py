@@ -535,16 +535,17 @@ def _late_fan_graph(n_dead, n_z, n_few=20):
     return _csr(S, 0, 3, src, dst, il, np.where(il == 3, 7, 0), w)
 
 
-@pytest.mark.parametrize("cluster", [1, 2, 4, 8], indirect=True)
-def test_an_arena_that_ends_in_a_frames_only_closure_round_keeps_the_neighbours_records(torch_cuda, cluster):
+@pytest.mark.parametrize("cluster,ma", [(1, 5000), (1, 6000), (2, 5000), (4, 5000), (8, 5000)], indirect=["cluster"])
+def test_an_arena_that_ends_in_a_frames_only_closure_round_keeps_the_neighbours_records(torch_cuda, cluster, ma):
     """The 13th frame's 3,001 emitted tokens fit the arena of 4,096, the 3,000 its closure adds do not, and more frames
-    follow: the channel is flagged and its lattice refused, and the lattices of the channels whose arenas lie between
-    and behind are the oracle's, every token and link."""
+    follow: the channel is flagged and its lattice refused, and the digests and lattices of the channels whose arenas lie
+    between and behind are the oracle's, every token and link.  (One workgroup takes another kernel beyond a max-active of
+    5,000.)"""
     from oracle import Oracle
     from paper_2311_04996_amd import Decoder, FLAG_DEAD, FLAG_LATTICE_OVERFLOW, WfstError
     from test_gpu_lattice import gpu_rows, oracle_rows
     g = _late_fan_graph(3000, 3000)
-    B, T, beam, ma = 5, 16, 5.0, 5000
+    B, T, beam = 5, 16, 5.0
     over = (0, 2, 4)
     ll = np.full((B, T, 3), -1000.0, np.float32)
     rng = np.random.default_rng(17)
@@ -552,7 +553,8 @@ def test_an_arena_that_ends_in_a_frames_only_closure_round_keeps_the_neighbours_
     for b in over:
         ll[b] = -1000.0
         ll[b, :12, 1] = ll[b, 12:, 0] = 0.0
-    dec = Decoder(g, max_channels=B, max_frames=T, max_active_hint=1000, lattice_bytes_per_channel=8 * 4096, keep_token_records=True)
+    dec = Decoder(g, max_channels=B, max_frames=T, max_active_hint=1000, lattice_bytes_per_channel=8 * 4096, keep_token_records=True,
+                  record_digests=True)
     dev = torch_cuda.from_numpy(ll).cuda()
     lengths = np.full(B, T, np.int32)
     _, nwords, _, flags = (t.cpu().numpy() for t in dec.decode_batch(dev, lengths, beam, ma))
@@ -563,6 +565,8 @@ def test_an_arena_that_ends_in_a_frames_only_closure_round_keeps_the_neighbours_
             with pytest.raises(WfstError):
                 dec.get_lattice(b, dev[b], 4.0)
             continue
+        (ref,), (cnt, dig) = parity.oracle_batch(g, ll[b:b + 1], lengths[:1], beam, ma), dec.debug_frame_digests(b)
+        assert (cnt == ref.digest_count).all() and (dig == ref.digest_sum).all()
         L = o.lattice(ll[b], T, beam=beam, max_active=ma, lattice_beam=4.0)
         lat = dec.get_lattice(b, dev[b], 4.0)
         assert lat.frame_off.tolist() == L.set_off.tolist()
