@@ -52,6 +52,16 @@ def read_traffic(workload):
     return None
 
 
+def traffic_launches(rows, ctr, n):
+    """Values of counter `ctr` in the rows of the profiler's CSV: of the probe's copies, and of the channel kernel's last `n`
+    launches of the instance that the run began with.  (The launch with the phase clocks on comes last and is an instance
+    of its own, which spills registers that the timed one does not: up to an eighth more bytes.)"""
+    rows = sorted((r for r in rows if r.get("Counter_Name") == ctr), key=lambda r: int(r["Dispatch_Id"]))
+    kern = [r for r in rows if "wfst_channel_kernel" in r["Kernel_Name"]]
+    kern = [float(r["Counter_Value"]) for r in kern if r["Kernel_Name"] == kern[0]["Kernel_Name"]]
+    return kern[-n:], [float(r["Counter_Value"]) for r in rows if "probe_copy" in r["Kernel_Name"]]
+
+
 def measure_traffic(child_args, timeout_s=180):
     """HBM bytes per launch of the channel kernel, measured now: two child runs of this script (one
     batch in flight, 2 timed steps) under `rocprofv3 --pmc`, FETCH_SIZE then WRITE_SIZE (KiB per
@@ -82,18 +92,11 @@ def measure_traffic(child_args, timeout_s=180):
                 return None, f"the {ctr} run did not finish in {timeout_s} s"
             if r.returncode != 0:
                 return None, f"the {ctr} run ended with status {r.returncode}: {r.stderr[-300:]}"
-            kern, copy = [], []
-            for f in glob.glob(os.path.join(out, "**", "*counter_collection.csv"), recursive=True):
-                for row in csv.DictReader(open(f)):
-                    if row.get("Counter_Name") != ctr:
-                        continue
-                    if "wfst_channel_kernel" in row["Kernel_Name"]:
-                        kern.append(float(row["Counter_Value"]))
-                    elif "probe_copy" in row["Kernel_Name"]:
-                        copy.append(float(row["Counter_Value"]))
+            rows = [row for f in glob.glob(os.path.join(out, "**", "*counter_collection.csv"), recursive=True)
+                    for row in csv.DictReader(open(f))]
+            kern, copy = traffic_launches(rows, ctr, 2)         # the timed launches (the warm-up comes before them)
             if not kern or not copy or min(copy) <= 0:
                 return None, f"no {ctr} values for the kernel or the calibration copy in the profiler's output"
-            kern = kern[-2:]                                    # the timed launches (the first one is the warm-up)
             scale = (1 << 20) / (sum(copy) / len(copy))         # the copy moves 2^20 KiB each way
             detail[ctr] = {"kib_per_launch": sum(kern) / len(kern), "copy_kib": sum(copy) / len(copy), "scale": scale}
         total = sum(d["kib_per_launch"] * d["scale"] * 1024.0 for d in detail.values())
