@@ -192,19 +192,23 @@ template <bool kCl> __device__ __forceinline__ int2 get_lat(const int2 *p) {
   return make_int2((int)(unsigned)a, (int)(a >> 32));
 }
 
-// Wait until the word carries the tag (its bits from kShift on); returns the word.  The wait is bounded
-// (seconds): a partner that never posts ends the channel with an error instead of hanging the
-// launch.  The word is then 0 (no tag is) and sm.dead is set.
-template <int kShift>
+// Every wait is bounded (seconds): a partner that never posts ends the channel with an error instead of hanging the
+// launch.  Is it time to give up, after n looks in vain?  sm.dead is then set.
+__device__ __forceinline__ bool give_up_wait(Smem2 &sm, int n, int polls) {
+  const bool over = n >= polls || ((n & 1023) == 1023 && __hip_atomic_load(&sm.dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+  if (over) sm.dead = 1;
+  return over;
+}
+// Wait until the word carries the tag (its upper half); returns the word, or 0 (no tag is) for a wait that was given up.
 __device__ __forceinline__ unsigned long long poll_word(Smem2 &sm, const unsigned long long *p, unsigned tag, int polls) {
   for (int n = 0;; ++n) {
     const unsigned long long v = aload(p);
-    if ((unsigned)(v >> kShift) == tag) return v;
-    if (n >= polls || ((n & 1023) == 1023 && __hip_atomic_load(&sm.dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))) { sm.dead = 1; return 0; }
+    if ((unsigned)(v >> 32) == tag) return v;
+    if (give_up_wait(sm, n, polls)) return 0;
   }
 }
 __device__ __forceinline__ unsigned poll(Smem2 &sm, const unsigned long long *p, unsigned tag) {
-  return (unsigned)poll_word<32>(sm, p, tag, sm.polls);
+  return (unsigned)poll_word(sm, p, tag, sm.polls);
 }
 __device__ __forceinline__ unsigned long long *box_of(const Cx &x, int r) {
   return x.box0 + ((size_t)r * 2 + (x.xc & 1u)) * kBoxWords;
@@ -256,7 +260,7 @@ __device__ __forceinline__ void take_sizes(Cx &x) {
       const int r = lane >> lg, p = lane & (G - 1);
       bool lost = false;
       if (lane < G * G) {
-        const unsigned long long w = poll_word<32>(sm, box_of(x, r) + p, x.xc, sm.polls);
+        const unsigned long long w = poll_word(sm, box_of(x, r) + p, x.xc, sm.polls);
         v = (unsigned)w; lost = w == 0ull;
       }
       const unsigned long long any = __ballot(lost) ? 0ull : __ballot(v != 0);
@@ -282,7 +286,7 @@ __device__ __forceinline__ void take_sizes(Cx &x) {
     const bool second = tid >= 128;
     const int which = lane & 1;
     const bool mine = lane < kAux / 2 * x.G;
-    if (mine) w = poll_word<32>(sm, box_of(x, lane >> 1) + kBoxAux + which + (second ? 2 : 0), x.xc, sm.polls);
+    if (mine) w = poll_word(sm, box_of(x, lane >> 1) + kBoxAux + which + (second ? 2 : 0), x.xc, sm.polls);
     const unsigned v = (unsigned)w;
     if (second) {
       const unsigned made = wave_sum(mine && which == 0 ? v : 0u), ms = wave_min(mine && which == 1 ? v : kOrdNone);
@@ -421,7 +425,7 @@ __device__ __forceinline__ WaveItem item_of(const L &wl, int w, int &before) {
   before += __popc(lo) + __popc(hi);
   return wl.item[min(j, (int)(sizeof(wl.item) / sizeof(WaveItem)) - 1)];
 }
-// The tokens of a wave, one per lane (`valid`; gl: local number | number in the set << 16): a lane reads the
+// The tokens of a wave, one per lane (`valid`; id: local number | number in the set << 16): a lane reads the
 // 16 bytes at the end of its token's header (degrees and the first arc); the other arcs are flattened over the 64
 // lanes, and states with more than kHubDeg2 arcs are listed for all waves.  Returns the emitting arcs expanded
 // (wave-uniform).
@@ -471,30 +475,30 @@ __device__ __forceinline__ unsigned run2(Cx &x, WaveLds2 &wl, int2 tk, int id, b
   // two arcs per lane and step; the first step takes the batch's first arcs and 64 of the others.  (A state that found
   // the shared list full comes back with its next kHubDeg2 arcs: an item has no more.)
   for (int f0 = -64;; f0 = 0) {
-  const unsigned take = min(deg, (unsigned)kHubDeg2);
-  const unsigned M = (unsigned)list_items(wl, take, first, cost, srct);
-  n_arcs += M;
-  int w = 0, before = 0;
-  do {
-    int ok[2], src[2], arc[2]; int4 a[2]; float tc[2];
+    const unsigned take = min(deg, (unsigned)kHubDeg2);
+    const unsigned M = (unsigned)list_items(wl, take, first, cost, srct);
+    n_arcs += M;
+    int w = 0, before = 0;
+    do {
+      int ok[2], src[2], arc[2]; int4 a[2]; float tc[2];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int f = f0 + u * 64 + lane;
-      if (u == 0 && f0 < 0) { ok[0] = has; src[0] = srct; arc[0] = 2 * blk + 1; tc[0] = cost; a[0] = a0; continue; }
-      ok[u] = f < (int)M;
-      const WaveItem it = item_of(wl, w++, before);
-      src[u] = it.src; tc[u] = it.tcost;
-      arc[u] = it.abase + f;
-      a[u] = make_int4(0, 0, 1, 0);
-      if (ok[u]) a[u] = load_emitting_arc<false>(x.g, arc[u], boosted);
-    }
-    emit_arcs2<kCl, 2>(x, ok, a, tc, src, arc, beam, boosted);
-    f0 += 128;
-  } while (f0 < (int)M);
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  deg -= take; first += (int)take;
-  if (__ballot(deg != 0) == 0ull) break;
+      for (int u = 0; u < 2; ++u) {
+        const int f = f0 + u * 64 + lane;
+        if (u == 0 && f0 < 0) { ok[0] = has; src[0] = srct; arc[0] = 2 * blk + 1; tc[0] = cost; a[0] = a0; continue; }
+        ok[u] = f < (int)M;
+        const WaveItem it = item_of(wl, w++, before);
+        src[u] = it.src; tc[u] = it.tcost;
+        arc[u] = it.abase + f;
+        a[u] = make_int4(0, 0, 1, 0);
+        if (ok[u]) a[u] = load_emitting_arc<false>(x.g, arc[u], boosted);
+      }
+      emit_arcs2<kCl, 2>(x, ok, a, tc, src, arc, beam, boosted);
+      f0 += 128;
+    } while (f0 < (int)M);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    deg -= take; first += (int)take;
+    if (__ballot(deg != 0) == 0ull) break;
   }
   return n_arcs;
 }
@@ -951,7 +955,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
           bool there = (unsigned)(h >> 48) == (x.hc & 0xffffu);
           if (mine) { const unsigned long long w = aload(ps); v = (unsigned)w; there &= (unsigned)(w >> 32) == x.xc; }
           if (there) break;
-          if (n >= sm.polls || ((n & 1023) == 1023 && __hip_atomic_load(&sm.dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))) { sm.dead = 1; h = 0; v = 0; break; }
+          if (give_up_wait(sm, n, sm.polls)) { h = 0; v = 0; break; }
         }
         *reinterpret_cast<uint2 *>(&sm.v.s.gh[tid >> 7][2 * (tid & 127)]) = make_uint2((unsigned)h & 0xffffffu, (unsigned)(h >> 24) & 0xffffffu);
       }
@@ -1666,7 +1670,7 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
         astore(w.hello + 2 * (size_t)s0 + 1, u64_of(sm.job, (int)w.seq));
       } else {
         astore(w.hello + 2 * (size_t)slot, u64_of(1, (int)w.seq));
-        sm.job = (int)poll_word<32>(sm, w.hello + 2 * (size_t)s0 + 1, w.seq, kPolls);
+        sm.job = (int)poll_word(sm, w.hello + 2 * (size_t)s0 + 1, w.seq, kPolls);
       }
     }
     __syncthreads();
