@@ -1363,10 +1363,10 @@ __device__ __forceinline__ bool closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
 // The closed token set becomes A_f (f = x.s.frame): the workgroup's own part of that.  `bad`: some tokens found no room, and
 // were not written or have a number beyond the arena.
 template <bool kCl, bool kOpt>
-__device__ __forceinline__ void finish2(Cx &x, const int2 *NQ, const int *NGI, unsigned lat_base, bool bad) {
+__device__ __forceinline__ void finish2(Cx &x, const int2 *NQ, const int *NGI, int n_loc, unsigned lat_base, bool bad) {
   Smem2 &sm = x.sm;
   const int tid = lane_id();
-  const int n = uni(min(sm.n_loc, x.c.qcap));
+  const int n = min(n_loc, x.c.qcap);
   const int f = x.s.frame;
   if (kOpt && !bad) {
     if (x.dig_sum && f <= x.c.max_frames) {
@@ -1840,7 +1840,7 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
         const int before = uni(sm.x_before);
         publish2<kCl, kOpt>(x, before != 0);
         open = false;
-        if (before) {                            // it has no digest, and what was expanded from it does not count
+        if (__builtin_expect(before, 0)) {       // it has no digest, and what was expanded from it does not count
           __syncthreads();
           if (tid == 0) { sm.x_status = before; sm.ctr[kCtEarc] = sm.earc_before; count2(sm, kCtTok, -x.n); if (leader) count2(sm, kCtFrames, -1); }
           if (kOpt && x.dig_sum && leader && tid == 0 && x.s.frame <= c.max_frames)
@@ -1862,18 +1862,18 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
     open = closure2<kCl, kBoost, kProf>(x, NQ, NGI, lat_base, cut, last);
     x.s.frame++;
     cur ^= 1;
-    if (!kCl && tid == 0) sm.x_status = sm.status;
-    // (the workgroup's own status is final behind the closure's last barrier)
-    const bool bad = uni(sm.status) != 0;
-    stop = kCl ? !open && uni(sm.x_status) != 0 : bad;
-    stop |= kCl && uni(sm.dead) != 0;
-    finish2<kCl, kOpt>(x, NQ, NGI, lat_base, stop || bad);
+    // (one wait for all of these; the workgroup's own status is final behind the closure's last barrier)
+    const int n_loc = sm.n_loc, own = sm.status, of_cluster = sm.x_status, is_dead = sm.dead;
+    if (!kCl && tid == 0) sm.x_status = own;
+    const bool bad = uni(own) != 0, gone = kCl && uni(is_dead) != 0;
+    stop = gone || (kCl ? !open && uni(of_cluster) != 0 : bad);
+    finish2<kCl, kOpt>(x, NQ, NGI, uni(n_loc), lat_base, stop || bad);
     // If the set's size is still to come, the cluster learns of an overflow with it, behind ExpandArcs of the next
     // frame: until then the workgroup has the tokens of the emitting step, all of them written, and none to expand.
     if (kCl && bad) { x.n_front = 0; x.n = x.n_emit; }
     if (!open) publish2<kCl, kOpt>(x, stop);
     mark<kProf>(x, kPhFinish);
-    if (kCl && uni(sm.dead)) break;
+    if (gone) break;
   }
   __syncthreads();
   if (kCl && uni(sm.dead)) { if (tid == 0) sm.x_status |= kStCapacity; __syncthreads(); }
