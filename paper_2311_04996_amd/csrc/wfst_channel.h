@@ -27,6 +27,9 @@
 // XCD, so all of this stays in its L2.  Between compute units of different XCDs an exchange takes 1.1 us,
 // 0.75 us more with 2 KB of data; one made with device-scope fences takes 9 us on an idle chip and
 // over 100 us on a full one, since a fence writes back and invalidates whole L2 caches.
+//
+// The times in this file's comments are pairs, measured in turn on one card when the step was made, and later
+// steps have moved both; the same code differs by a few percent between cards.
 
 constexpr int kMaxG = 8;                      // workgroups of a cluster
 constexpr int kKR = 3;                        // candidate records a lane keeps in registers from fill to token
