@@ -216,6 +216,8 @@ __device__ __forceinline__ unsigned poll(Smem2 &sm, const unsigned long long *p,
 __device__ __forceinline__ unsigned long long *box_of(const Cx &x, int r) {
   return x.box0 + ((size_t)r * 2 + (x.xc & 1u)) * kBoxWords;
 }
+// The set of segments (of two) that the last exchange of sizes was about; candidates on their way go to the other one.
+__device__ __forceinline__ int seg_set(const Cx &x) { return (int)((x.xc - x.hc) & 1u); }
 __device__ __forceinline__ unsigned long long *hist_of(const Cx &x, int r) {
   return x.box0 + ((size_t)r * 2 + (x.hc & 1u)) * kBoxWords + kBoxHist;
 }
@@ -390,7 +392,7 @@ __device__ __forceinline__ void emit_arcs2(Cx &x, int (&ok)[N], const int4 (&a)[
     const unsigned m = wave_min(o);
     if ((threadIdx.x & 63) == 0) atomicMin(&sm.best_ord, m);
   }
-  push_cands2<kCl, N>(x, ok, next, nc, src, arc, 0);
+  push_cands2<kCl, N>(x, ok, next, nc, src, arc, kCl ? seg_set(x) ^ 1 : 0);
 }
 __device__ __forceinline__ int next_run2(Smem2 &sm) {
   int r = 0;
@@ -664,7 +666,7 @@ __device__ __forceinline__ unsigned long long stays2(Cx &x, const int2 *Q, int2 
   Smem2 &sm = x.sm;
   TableLds &t = sm.u.t;
   const int tid = lane_id(), n = x.n;
-  const int lg = kCl ? x.lg : 0;
+  const int lg = kCl ? x.lg : 0, buf = kCl ? seg_set(x) : 0;
   unsigned long long won = 0;
   for (int k = 0; k * kBlock < n; ++k) {
     const int i = k * kBlock + tid;
@@ -685,7 +687,7 @@ __device__ __forceinline__ unsigned long long stays2(Cx &x, const int2 *Q, int2 
         const unsigned long long v = t.vals[sl];
         const unsigned oc = f2ord(nc), cc = (unsigned)(v >> 32);
         win = (int)(oc < cc);
-        if (oc == cc) win = (int)(2u * ((unsigned)q.x & x.g.blk_mask) + 1u < (unsigned)get4<kCl>(cand_at<kCl>(x, (int)(unsigned)v, 0)).w);
+        if (oc == cc) win = (int)(2u * ((unsigned)q.x & x.g.blk_mask) + 1u < (unsigned)get4<kCl>(cand_at<kCl>(x, (int)(unsigned)v, buf)).w);
         if (win) t.vals[sl] = ((unsigned long long)oc << 32) | kRefStay;
       }
       if (win) atomicAdd(&sm.hist[b], 1u);
@@ -772,7 +774,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
   cut.best = init ? 0.0f : bo == kOrdNone ? INFINITY : ord2f(bo);
   cut.beam = x.s.beam; cut.scale = x.s.scale; cut.k_keep = 256;
   const unsigned ma = (unsigned)x.s.max_active;
-  const int S = kCl ? x.G : kRegions, lg = kCl ? x.lg : 0;
+  const int S = kCl ? x.G : kRegions, lg = kCl ? x.lg : 0, buf = kCl ? seg_set(x) : 0;
   // (the start token of an initialisation comes as its owner's only candidate and winner)
   const int start_mine = init && (!kCl || part_of(key_of((int)x.g.start), x.lg) == x.me);
   const int n_own = init ? start_mine : uni(sm.seg_pre[S]);
@@ -790,7 +792,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
     for (int i0 = 0; i0 < n_own; i0 += kBlock) {
       int r = -1;
       if (i0 + tid < n_own) {
-        const int4 cd = get4<kCl>(cand_at<kCl>(x, i0 + tid, 0));
+        const int4 cd = get4<kCl>(cand_at<kCl>(x, i0 + tid, buf));
         if (cut.in_beam(__int_as_float(cd.y))) r = part_of(key_of(cd.x), kRegionBits);
       }
 #pragma unroll
@@ -814,9 +816,9 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
     if (tid == 0) { sm.n_emit = start_mine; sm.gbase = 0; sm.n_emit_all = 1; sm.k_keep = 256; }
     __syncthreads();
   } else if (small) {
-    if (tid < n_own) rec0 = get4<kCl>(cand_at<kCl>(x, tid, 0));
-    if (kBlock + tid < n_own) rec1 = get4<kCl>(cand_at<kCl>(x, kBlock + tid, 0));
-    if (2 * kBlock + tid < n_own) rec2 = get4<kCl>(cand_at<kCl>(x, 2 * kBlock + tid, 0));
+    if (tid < n_own) rec0 = get4<kCl>(cand_at<kCl>(x, tid, buf));
+    if (kBlock + tid < n_own) rec1 = get4<kCl>(cand_at<kCl>(x, kBlock + tid, buf));
+    if (2 * kBlock + tid < n_own) rec2 = get4<kCl>(cand_at<kCl>(x, 2 * kBlock + tid, buf));
   } else if (n_own > kGroupTarget) {
     // ---- select: bins of the implied candidates, and of a sample of the others (one run of 64 in 2^sel_shift)
     if (tid < 256) { sm.hist2[tid] = 0; sm.hist3[tid] = 0; }
@@ -832,7 +834,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
     for (int i0 = (tid >> 6) << 6; (i0 << sh) < n_own; i0 += kBlock) {
       const int i = (i0 << sh) + lane;
       if (i < n_own) {
-        const float c = __int_as_float(get4<kCl>(cand_at<kCl>(x, i, 0)).y);
+        const float c = __int_as_float(get4<kCl>(cand_at<kCl>(x, i, buf)).y);
         if (cut.in_beam(c)) atomicAdd(&sm.hist2[cut.bin(c)], 1u);
       }
     }
@@ -887,19 +889,19 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
       const int r0 = !kCl && P > 1 ? uni(sm.seg_pre[g / (P / kRegions)]) : 0;
       const int r1 = !kCl && P > 1 ? uni(sm.seg_pre[g / (P / kRegions) + 1]) : n_own;
       int4 nxt = make_int4(0, 0, 0, 0);
-      if (!small && r0 + tid < r1) nxt = get4<kCl>(cand_at<kCl>(x, r0 + tid, 0));
+      if (!small && r0 + tid < r1) nxt = get4<kCl>(cand_at<kCl>(x, r0 + tid, buf));
       int2 tok0 = make_int2(0, 0);                 // (on its way while the table is filled)
       if (tid < n_tok) tok0 = Q[tid];
 #pragma unroll 1
       for (int k = 0, i0 = r0; i0 < r1; ++k, i0 += kBlock) {
         const int i = i0 + tid;
         const int4 cd = small ? rec_at(k) : nxt;
-        if (!small && i + kBlock < r1) nxt = get4<kCl>(cand_at<kCl>(x, i + kBlock, 0));
+        if (!small && i + kBlock < r1) nxt = get4<kCl>(cand_at<kCl>(x, i + kBlock, buf));
         const float c = __int_as_float(cd.y);
         const int key = key_of(cd.x);
         int take = (int)(i < r1) & (int)cut.in_beam(c) & (int)(cut.bin(c) < k_sel) & (int)((P == 1) | (group2(key, lg, P) == g));
         int sl = -1;
-        if (take) sl = insert2<kCl, false>(x, key, c, cd.w, cd.z, i, 0, nullptr, 0u);
+        if (take) sl = insert2<kCl, false>(x, key, c, cd.w, cd.z, i, buf, nullptr, 0u);
         if (small) set_slot(k, sl);
       }
       __syncthreads();
@@ -908,12 +910,12 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
       __syncthreads();
       mark<kProf>(x, kPhSelect);
       // every candidate that was inserted looks at its slot again: the one still there has won
-      if (!small && r0 + tid < r1) nxt = get4<kCl>(cand_at<kCl>(x, r0 + tid, 0));
+      if (!small && r0 + tid < r1) nxt = get4<kCl>(cand_at<kCl>(x, r0 + tid, buf));
 #pragma unroll 1
       for (int k = 0, i0 = r0; i0 < r1; ++k, i0 += kBlock) {
         const int i = i0 + tid;
         const int4 cd = small ? rec_at(k) : nxt;
-        if (!small && i + kBlock < r1) nxt = get4<kCl>(cand_at<kCl>(x, i + kBlock, 0));
+        if (!small && i + kBlock < r1) nxt = get4<kCl>(cand_at<kCl>(x, i + kBlock, buf));
         const float c = __int_as_float(cd.y);
         int sl = -1;
         if (small) sl = slot_at(k);
@@ -1190,8 +1192,10 @@ __device__ __forceinline__ void emit_eps2(Cx &x, int (&ok)[kU], const float (&tc
 // A round is bound by its chain (worklist, state, arcs, exchange, table, tokens), and every barrier adds to that the
 // wait for the slowest of 16 waves.  So each wave flattens the arcs of its own items (a flattening
 // over the block took three barriers more), and where no candidate's state has epsilon arcs the
-// round is the last, without one to find that out (if it is an odd one).  What only that exchange would tell, the size of the
+// round is the last, without one to find that out.  What only that exchange would tell, the size of the
 // set, comes with the next frame's first one: returns true if it is still to come (never with `last`, a launch's last frame).
+// The two sets of segments are used in turn, also from one frame to the next: what another workgroup may still be reading
+// when a frame ends is not what the next frame's arcs are written to.
 // (One utterance of 10.8 k tokens per frame 10.57 -> 9.93 ms, of 900 tokens 2.03 -> 1.90 ms, 64 on a graph that branches
 // everywhere 30.1 -> 28.4 ms.)
 template <bool kCl, bool kBoost, bool kProf>
@@ -1202,7 +1206,7 @@ __device__ __forceinline__ bool closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
   const bool boosted = kBoost && x.s.boost_n > 0;
   const int S = kCl ? x.G : kRegions, lg = kCl ? x.lg : 0;
   for (int round = 1;; ++round) {
-    const int sel = (round - 1) & 1, buf = kCl ? (round & 1) : 0;
+    const int sel = (round - 1) & 1, buf = kCl ? seg_set(x) ^ 1 : 0;
     const int4 *WL = x.wl0 + sel * x.c.qcap; int4 *WLN = x.wl0 + (sel ^ 1) * x.c.qcap;
     const int n_wl = uni(min(sm.made[2], x.c.qcap));
     if (!kCl && n_wl == 0) { __syncthreads(); break; }        // (the size of the set is known)
@@ -1355,9 +1359,7 @@ __device__ __forceinline__ bool closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
       }
       if (tid == 0 && map) sm.made[3] = n_map + uni(sm.n_loc) - n_loc0;
     }
-    // (the next frame's arcs go to the segments of even rounds at once, and another workgroup may still be reading those
-    // of this one: an even round needs the exchange behind it)
-    if (!more && !(kCl && (last || buf == 0))) { mark<kProf>(x, kPhEpsRecombine); return kCl; }
+    if (!more && !(kCl && last)) { mark<kProf>(x, kPhEpsRecombine); return kCl; }
   }
   mark<kProf>(x, kPhEpsRecombine);
   return false;

@@ -518,6 +518,28 @@ def test_survivors_around_the_number_a_wave_collects(torch_cuda, cluster):
         parity.check_batch(torch_cuda, g, ll, np.array([4, 2], np.int32), 20.0, 5000, max_active_hint=5000)
 
 
+@pytest.mark.parametrize("cluster", [1, 2, 4, 8], indirect=True)
+@pytest.mark.parametrize("n", [3, 700])
+def test_frames_whose_last_closure_round_is_any_of_the_first_five(torch_cuda, cluster, n):
+    """Label k leads to n chains of k - 1 epsilon arcs, and one label is ahead of the beam in every frame: the frame's number of
+    closure rounds is that label's, and whatever the round it ends with, the next frame's candidates do not meet the ones of
+    that round."""
+    from workloads.graphs import _csr
+    rng = np.random.default_rng(17)
+    arcs, first = [], 1
+    for k in range(1, 6):
+        at = first + np.arange(n * k).reshape(n, k)      # chain by chain
+        first += n * k
+        arcs += [(0, s, k, 0) for s in at[:, 0]] + [(s, d, 0, 0) for s, d in zip(at[:, :-1].ravel(), at[:, 1:].ravel())]
+        arcs += [(s, 0, 1 + (k + j) % 5, 3 + k) for s in at[:, -1] for j in (0, 2)] + [(s, s, k, 0) for s in at[:, -1]]
+    arcs += [(0, 0, k, 0) for k in range(1, 6)]
+    src, dst, il, ol = (np.array(v, np.int64) for v in zip(*arcs))
+    g = _csr(first, 0, 5, src, dst, il, ol, rng.choice([0.0, 0.25, 0.5], len(src)))
+    label = np.array([[0, 1, 2, 3, 4, 1, 1, 3, 3, 0, 2, 4], [4, 3, 2, 1, 0, 0, 2, 2, 4, 4, 1, 3]])
+    ll = np.where(np.arange(5) == label[..., None], -0.25, -100.0).astype(np.float32)
+    parity.check_batch(torch_cuda, g, ll, np.array([12, 11], np.int32), 20.0, 5000, max_active_hint=5000)
+
+
 def _late_fan_graph(n_dead, n_z, n_few=20):
     """Start -> a state with a loop over label 2, from where label 1 leads to `n_dead` dead ends and, over a hub's epsilon arcs,
     to `n_z` states with a self-loop, and label 3 to a few states and back over label 2."""
