@@ -90,12 +90,12 @@ struct alignas(16) Smem2 {
     struct { WaveEps w[kWaves]; WaveItem seg[kEpsSegs]; } ek;   // closure (of a segment `pad` is the number of arcs)
     struct {
       unsigned hasstay[kQueueMax / 32];       // bit i: local token i's first arc is the usual self-loop (other arcs follow)
-      unsigned gh[kMaxG][256];                // the cluster's histograms
+      unsigned all[256], before[256];         // sums of the cluster's histograms: of all workgroups, of those before this one
     } s;
     int4 mk[kWaves][64];                      // survivors on their way to become tokens
   } v;
   unsigned short tokof[kTabSlots];            // closure table: local token of a slot, 0xFFFF: none yet, or the last of a full set
-  unsigned hist[256], hist2[256], hist3[256];
+  alignas(16) unsigned hist[256]; unsigned hist2[256], hist3[256];
   unsigned wave_tot[kWaves];
   int n_seg[kMaxG];                           // candidates pushed per segment
   int seg_pre[kMaxG + 1];                     // own candidates: prefix sums over the segments
@@ -122,7 +122,7 @@ struct alignas(16) Smem2 {
   long long prof_t0;
 };
 static_assert(sizeof(Smem2) <= 160 * 1024, "LDS of a compute unit");
-static_assert(offsetof(Smem2, u) % 16 == 0 && sizeof(TableLds) % 16 == 0 && offsetof(Smem2, v.s.gh) % 16 == 0, "16 bytes at a time");
+static_assert(offsetof(Smem2, u) % 16 == 0 && sizeof(TableLds) % 16 == 0 && offsetof(Smem2, v.s.all) % 16 == 0 && offsetof(Smem2, hist) % 16 == 0, "16 bytes at a time");
 static_assert(kKR * kBlock <= kMapMax, "one register-held round fits the table");
 
 struct Cx {                   // block-uniform view of one channel
@@ -243,16 +243,25 @@ __device__ __forceinline__ void post_sizes(Cx &x) {
   const int tid = lane_id();
   if (!kCl) return;
   ++x.xc;
-  if (tid < x.G) { post(x, tid, (unsigned)sm.n_seg[tid]); sm.n_seg[tid] = 0; }
   static_assert(((kStLattice | kStCapacity) & ~0xff) == 0, "the word of the status has 8 bits for it");
-  if (tid >= 64 && tid < 64 + kAux)
-    post(x, kBoxAux + tid - 64, tid == 64 ? sm.best_ord : tid == 65 ? (unsigned)(sm.status | sm.status_before << 8 | sm.more << 16) : tid == 66 ? (unsigned)(x.sm.n_loc - x.n_emit) : sm.min_simple);
-  if (tid == 65) sm.more = 0;
+  static_assert(kBoxAux == kMaxG, "a lane per word");
+  if (tid < kBoxAux + kAux) {
+    const int q = tid - kBoxAux;
+    unsigned v = 0;
+    if (tid < x.G) { v = (unsigned)sm.n_seg[tid]; sm.n_seg[tid] = 0; }
+    const bool any = __ballot(v != 0) != 0ull;
+    if (q == 0) v = sm.best_ord;
+    if (q == 1) { v = (unsigned)(sm.status | sm.status_before << 8 | sm.more << 16 | (int)any << 17); sm.more = 0; }
+    if (q == 2) v = (unsigned)(sm.n_loc - x.n_emit);
+    if (q == 3) v = sm.min_simple;
+    if (tid < x.G || q >= 0) post(x, tid, v);
+  }
 }
 // Take the cluster's sizes: own candidates are [0, seg_pre[segments]) afterwards.  Ends with a barrier.  Three waves share the
 // work, and sums go by lane reads: the sizes through LDS, one wave for all of the rest and butterflies for minima made an exchange
 // 0.3 us longer (four or five exchanges a frame: one utterance of 10.8 k tokens 9.93 instead of 9.70 ms, with the other trips
-// through LDS that are now not waited for).
+// through LDS that are now not waited for).  A workgroup looks only at its own sizes and at those of the one it shares a
+// region with.
 template <bool kCl>
 __device__ __forceinline__ void take_sizes(Cx &x) {
   Smem2 &sm = x.sm;
@@ -260,25 +269,14 @@ __device__ __forceinline__ void take_sizes(Cx &x) {
   const int region_cap = x.c.region_cap;
   if (tid < 64) {
     if (kCl) {
-      const int G = x.G, lg = x.lg;
+      // lane r: writer r's segment for this workgroup; of a cluster of 8, lane 8 + r: for the one it shares a region with
       unsigned v = 0;
-      const int r = lane >> lg, p = lane & (G - 1);
-      bool lost = false;
-      if (lane < G * G) {
-        const unsigned long long w = poll_word(sm, box_of(x, r) + p, x.xc, sm.polls);
-        v = (unsigned)w; lost = w == 0ull;
-      }
-      const unsigned long long any = __ballot(lost) ? 0ull : __ballot(v != 0);
-      // lane r * G + p holds writer r's segment for owner p: the owner's, lane by lane, without a trip through LDS
-      v = min(v, (unsigned)x.seg_cap);
-      int run = 0, pre = 0, in = 0;
-      for (int q = 0; q < G; ++q) {
-        pre = lane == q ? run : pre;
-        run += __builtin_amdgcn_readlane((int)v, (q << lg) + x.me);
-        in += __builtin_amdgcn_readlane((int)v, (q << lg) + (x.me ^ 1));
-      }
-      if (lane <= G) sm.seg_pre[lane] = lane == G ? run : pre;
-      if (lane == 0) { sm.x_any = any != 0ull; sm.n_in = G == kMaxG ? in : 0; }
+      const int r = lane & (kMaxG - 1);
+      if (lane < (x.G == kMaxG ? 2 * kMaxG : x.G)) v = min((unsigned)poll_word(sm, box_of(x, r) + (x.me ^ (lane >> 3)), x.xc, sm.polls), (unsigned)x.seg_cap);
+      const unsigned inc = wave_scan_add(v);
+      const unsigned own = (unsigned)__builtin_amdgcn_readlane((int)inc, kMaxG - 1);
+      if (lane <= x.G) sm.seg_pre[lane] = (int)(inc - v);
+      if (lane == 2 * kMaxG - 1) sm.n_in = (int)(inc - own);         // (0 unless there are eight)
     } else {
       const int n = lane < kRegions ? min(sm.n_seg[lane], region_cap) : 0;
       const int inc = (int)wave_scan_add((unsigned)n);
@@ -301,8 +299,8 @@ __device__ __forceinline__ void take_sizes(Cx &x) {
       auto any = [&](unsigned bits) { return __ballot((st & bits) != 0) != 0ull; };
       const int now = (any(kStLattice) ? kStLattice : 0) | (any(kStCapacity) || __ballot(mine && w == 0ull) != 0ull ? kStCapacity : 0);
       const int before = (any(kStLattice << 8) ? kStLattice : 0) | (any(kStCapacity << 8) ? kStCapacity : 0);
-      const int more = any(1u << 16);
-      if (lane == 0) { sm.x_best = best; sm.x_status = now; sm.x_before = before; sm.x_more = more; }
+      const int more = any(1u << 16), some = any(1u << 17);
+      if (lane == 0) { sm.x_best = best; sm.x_status = now; sm.x_before = before; sm.x_more = more; sm.x_any = some; }
     }
   }
   __syncthreads();
@@ -962,7 +960,10 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
           if (there) break;
           if (give_up_wait(sm, n, sm.polls)) { h = 0; v = 0; break; }
         }
-        *reinterpret_cast<uint2 *>(&sm.v.s.gh[tid >> 7][2 * (tid & 127)]) = make_uint2((unsigned)h & 0xffffffu, (unsigned)(h >> 24) & 0xffffffu);
+        // (two bins with one add; the lanes of a wave have different ones)
+        const unsigned long long two = (h & 0xffffffull) | ((h >> 24) & 0xffffffull) << 32;
+        atomicAdd(reinterpret_cast<unsigned long long *>(&sm.v.s.all[2 * (tid & 127)]), two);
+        if ((tid >> 7) < x.me) atomicAdd(reinterpret_cast<unsigned long long *>(&sm.v.s.before[2 * (tid & 127)]), two);
       }
       if (tid < 64) {
         const unsigned ks = wave_min(mine && which == 0 ? v & 0xffffu : 256u);
@@ -976,18 +977,13 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
       __syncthreads();
     }
     if (tid < 64) {
-      const int S2 = kCl ? x.G : 1;
       const int ks = kCl ? sm.k_sel : k_sel, ns = kCl ? sm.n_sel : n_sel;
-      // (16 bytes at a time from the cluster's histograms; the workgroup's own is not aligned to that)
-      auto bins4 = [&](int r) {
-        if (kCl) return *reinterpret_cast<const uint4 *>(&sm.v.s.gh[r][4 * tid]);
-        return make_uint4(sm.hist[4 * tid], sm.hist[4 * tid + 1], sm.hist[4 * tid + 2], sm.hist[4 * tid + 3]);
-      };
-      unsigned h[4] = {0, 0, 0, 0};
-      for (int r = 0; r < S2; ++r) {
-        const uint4 q = bins4(r);
-        h[0] += q.x; h[1] += q.y; h[2] += q.z; h[3] += q.w;
-      }
+      // (sums that the lanes have made as the histograms came; read histogram by histogram, one wave took 1.5 us for this)
+      auto bins4 = [&](const unsigned (&b)[256]) { return *reinterpret_cast<const uint4 *>(&b[4 * tid]); };
+      const uint4 own4 = bins4(sm.hist);
+      uint4 all4 = own4, before4 = make_uint4(0, 0, 0, 0);
+      if (kCl) { all4 = bins4(sm.v.s.all); before4 = bins4(sm.v.s.before); }
+      unsigned h[4] = {all4.x, all4.y, all4.z, all4.w};
 #pragma unroll
       for (int j = 0; j < 4; ++j) if (4 * tid + j >= ks) h[j] = 0;
       const unsigned s = h[0] + h[1] + h[2] + h[3];
@@ -1005,17 +1001,10 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
         if (kk < 1) kk = 1;
       } else if (ks < 256) redo = 1;                 // too many duplicates among the selected
       // the survivors of every workgroup: where its tokens start in the set, and how many
-      unsigned before = 0, mine = 0, all = 0;
-      for (int r = 0; r < S2; ++r) {
-        const uint4 q = bins4(r);
-        const int lim = min(kk, ks) - 4 * tid;
-        const unsigned nb = (lim > 0 ? q.x : 0u) + (lim > 1 ? q.y : 0u) + (lim > 2 ? q.z : 0u) + (lim > 3 ? q.w : 0u);
-        if (kCl && r < x.me) before += nb;
-        if (!kCl || r == x.me) mine = nb;
-        all += nb;
-      }
-      mine = wave_sum(mine);
-      if (kCl) { before = wave_sum(before); all = wave_sum(all); } else all = mine;
+      const int lim = min(kk, ks) - 4 * tid;
+      auto kept = [&](const uint4 &q) { return wave_sum((lim > 0 ? q.x : 0u) + (lim > 1 ? q.y : 0u) + (lim > 2 ? q.z : 0u) + (lim > 3 ? q.w : 0u)); };
+      unsigned mine = kept(own4), before = 0, all = mine;
+      if (kCl) { before = kept(before4); all = kept(all4); }
       if (kCl && sm.dead) { kk = 0; redo = 0; mine = before = all = 0; }
       if (tid == 0) {
         sm.k_keep = kk; sm.redo = redo; sm.n_emit = (int)mine; sm.gbase = (int)before; sm.n_emit_all = (int)min(all, 0x7fffffffu);
@@ -1030,7 +1019,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
     if (!redo) break;
     if (attempt >= 12) { if (tid == 0) atomicOr(&sm.status, kStCapacity); break; }   // never expected: 2048 passes
     if (tid == 0 && (!kCl || x.me == 0)) sm.prof[15]++;   // counted, not timed: re-recombinations
-    if (tid < 256) sm.hist[tid] = 0;
+    if (tid < 256) { sm.hist[tid] = 0; if (kCl) { sm.v.s.all[tid] = 0; sm.v.s.before[tid] = 0; } }
     if (tid == 0) { sm.n_win = 0; sm.overfull = 0; }
     if (redo == 2) mult *= 2;
     else { k_sel = 256; n_sel = n_own + n_tok; n_sel_c = n_own; }
@@ -1277,7 +1266,7 @@ __device__ __forceinline__ bool closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
     // An overflow (or a cluster that has broken up) ends the closure, and with the frame the channel: a token that
     // found no room has left the number of its candidate in the table, which would now be looked for among this
     // round's candidates.
-    if (uni((int)(sm.x_any == 0) | sm.x_status)) break;
+    if (uni((int)(sm.x_any == 0) | sm.x_status | sm.dead)) break;
     const bool more = uni(sm.x_more) != 0;
     const int n_own = uni(sm.seg_pre[S]);
     mark<kProf>(x, kPhEpsRecombine);
@@ -1814,6 +1803,7 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
       }
     }
     for (int h = tid; h < kHubCap; h += kBlock) { sm.u.e.hub.ready[h] = 0; sm.u.e.hub.seg_next[h] = 0; }
+    if (kCl && tid < 256) { sm.v.s.all[tid] = 0; sm.v.s.before[tid] = 0; }
     for (int h = tid; h <= (x.n >> 5); h += kBlock) sm.v.s.hasstay[h & (kQueueMax / 32 - 1)] = 0u;
     if (tid == 0) {
       sm.next_run = kWaves; sm.done_waves = 0; sm.n_hub = 0; sm.status_before = sm.status; sm.earc_before = sm.ctr[kCtEarc];
