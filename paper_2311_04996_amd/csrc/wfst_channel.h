@@ -44,6 +44,7 @@ constexpr int kStartTicks = 5000;             // how long the first workgroup of
 constexpr int kXcds = 8;                      // XCDs of the chip
 constexpr int kHwXccId = 20 | (4 - 1) << 11;   // hardware register XCC_ID, bits 0-3: the XCD a wave runs on
 constexpr int kListInts = 2 + kXcds + 2;       // counters in a launch's lists (an even number: 64-bit entries before them)
+constexpr int kResetTid = 2 * 64, kStoredTid = 3 * 64, kPublishTid = 4 * 64;   // single threads' work between two frames, a wave each
 constexpr int kAux = 4;                       // best cost, status, tokens made by the closure, smallest cost in a simple state
 
 struct ClusterArgs {                          // device memory of the workgroups, by ticket of the cluster and number in it
@@ -514,11 +515,12 @@ __device__ __forceinline__ int run_size(const Cx &x) {
 template <bool kCl>
 __device__ __forceinline__ Run load_run(const Cx &x, const int2 *Q, const int *GI, int r, int size) {
   const int lane = lane_id() & 63, j = r * size + lane;
-  Run run{make_int2((int)kFlagSimple, 0), 0, 0, false};
-  if (lane < size && j < x.n_front + x.n - x.n_emit) {
-    const int i = j < x.n_front ? j : j - x.n_front + x.n_emit;
-    run.tk = Q[i]; run.i = i; if (kCl) run.gi = GI[i]; run.valid = true;
-  }
+  // (all lanes load, those without a token the first record: behind a branch the record would be copied, and so waited for)
+  Run run{};
+  run.valid = lane < size && j < x.n_front + x.n - x.n_emit;
+  run.i = !run.valid ? 0 : j < x.n_front ? j : j - x.n_front + x.n_emit;
+  run.tk = Q[run.i];
+  if (kCl) run.gi = GI[run.i];
   return run;
 }
 // On entry sm.next_run == kWaves, sm.done_waves == 0, sm.n_hub == 0 and the hub list's ready
@@ -535,12 +537,14 @@ __device__ __forceinline__ void expand2(Cx &x, const int2 *Q, const int *GI, Run
   // the simple tokens of the emitting step have one arc each
   unsigned long long n_arcs = tid < 64 ? (unsigned long long)(x.n_emit - x.n_front) : 0ull;
   for (int r = uni(wave); r * size < total;) {
-    const int rn = size * kWaves >= total ? kWaves : next_run2(sm);
-    const Run nxt = load_run<kCl>(x, Q, GI, rn, size);
-    const bool other = ((unsigned)run.tk.x & kFlagSimple) == 0;      // (valid)
+    r = size * kWaves >= total ? kWaves : next_run2(sm);
+    const bool more = r * size < total;
+    Run nxt{};
+    if (more) nxt = load_run<kCl>(x, Q, GI, r, size);
+    const bool other = run.valid && ((unsigned)run.tk.x & kFlagSimple) == 0;
     n_arcs += (unsigned)__popcll(__ballot(run.valid && !other));
     n_arcs += run2<kCl>(x, wl, run.tk, run.i | ((kCl ? run.gi : run.i) << 16), other, beam, boosted);
-    run = nxt; r = rn;
+    if (more) run = nxt;
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   if (lane == 0) atomicAdd(&sm.done_waves, 1);
@@ -1117,7 +1121,10 @@ __device__ __forceinline__ void apply2(Cx &x, int win, const int4 &rec, int slot
   if (kCl && lane == 2 && mn) at = (int)__hip_atomic_fetch_add(set_size_of(x), (unsigned)__popcll(mn), __ATOMIC_RELAXED, kStoreScope);
   const int rank = __popcll(mn & lt);
   if (fresh) { li = __builtin_amdgcn_readlane(at, 0) + rank; gx = kCl ? __builtin_amdgcn_readlane(at, 2) + rank : li; }
-  else if (win) gx = kCl ? NGI[li] : li;
+  else if (win) {
+    gx = kCl ? uni(sm.gbase) + li : li;
+    if (kCl && li >= x.n_emit) gx = NGI[li];     // (made by the closure)
+  }
   unsigned ms = kOrdNone;
   if (win) {
     bool room = gx < x.c.qcap && li < x.c.qcap;
@@ -1346,7 +1353,7 @@ __device__ __forceinline__ bool closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
         __syncthreads();
         mark<kProf>(x, kPhEpsTabScan);
       }
-      if (tid == 0 && map) sm.made[3] = n_map + uni(sm.n_loc) - n_loc0;
+      if (tid == kResetTid && map) sm.made[3] = n_map + uni(sm.n_loc) - n_loc0;
     }
     if (!more && !(kCl && last)) { mark<kProf>(x, kPhEpsRecombine); return kCl; }
   }
@@ -1381,7 +1388,7 @@ __device__ __forceinline__ void finish2(Cx &x, const int2 *NQ, const int *NGI, i
       }
     }
   }
-  if (tid == 0) count2(sm, kCtStored, n);
+  if (tid == kStoredTid) count2(sm, kCtStored, n);
   x.s.cur ^= 1;
   x.n = n;
 }
@@ -1392,7 +1399,7 @@ __device__ __forceinline__ void publish2(Cx &x, bool stop) {
   const unsigned lat_base = x.s.lat_used;
   const int total = uni(min(sm.n_emit_all + (kCl ? sm.x_made : sm.n_loc - x.n_emit), x.c.qcap));
   const int f = x.s.frame;
-  if (threadIdx.x == 0 && (!kCl || x.me == 0)) {
+  if (threadIdx.x == kPublishTid && (!kCl || x.me == 0)) {
     const int F = x.c.max_frames + 2;            // the per-frame tables are rings (a recycled channel outlives them)
     x.frame_off[ring_at(f, F)] = lat_base;
     x.frame_off[ring_at(f + 1, F)] = lat_base + (unsigned)total;
@@ -1805,7 +1812,7 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
     for (int h = tid; h < kHubCap; h += kBlock) { sm.u.e.hub.ready[h] = 0; sm.u.e.hub.seg_next[h] = 0; }
     if (kCl && tid < 256) { sm.v.s.all[tid] = 0; sm.v.s.before[tid] = 0; }
     for (int h = tid; h <= (x.n >> 5); h += kBlock) sm.v.s.hasstay[h & (kQueueMax / 32 - 1)] = 0u;
-    if (tid == 0) {
+    if (tid == kResetTid) {
       sm.next_run = kWaves; sm.done_waves = 0; sm.n_hub = 0; sm.status_before = sm.status; sm.earc_before = sm.ctr[kCtEarc];
       sm.made[0] = 0; sm.made[1] = 0; sm.made[2] = 0; sm.made[3] = 0; sm.map_bad = 0; sm.n_win = 0; sm.overfull = 0;
       count2(sm, kCtTok, x.n);
@@ -1830,6 +1837,7 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
         if (v + kBlock < a.V) load_row(t + 1, v + kBlock, row1);
       }
       take_sizes<kCl>(x);
+      asm volatile("" : "+v"(row0), "+v"(row1));   // (waited for here, where it has come: later it would be with the stores in between)
       mark<kProf>(x, kPhExpand);
       if (open) {                                // the last frame's set, and an overflow of its last round
         const int before = uni(sm.x_before);
