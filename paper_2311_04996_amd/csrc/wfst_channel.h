@@ -77,6 +77,7 @@ struct alignas(16) WaveLds2 {
 };
 // The closure does the same over epsilon arcs, with smaller lists (the table lies in the memory of the others).  A
 // state with more than kEpsDeg of them is listed in segments that all waves share.
+constexpr int kWlLds = 96;                     // first entries of a worklist, kept in LDS
 constexpr int kEpsTok = 32, kEpsDeg = 64, kEpsSeg = 64 * kU, kEpsSegs = 224;
 struct alignas(16) WaveEps {
   unsigned long long last[kEpsTok * kEpsDeg / 64];
@@ -95,6 +96,7 @@ struct alignas(16) Smem2 {
     } s;
     int4 mk[kWaves][64];                      // survivors on their way to become tokens
   } v;
+  int4 wl[2][kWlLds];                         // the closure's worklists, this round's and the next one's
   unsigned short tokof[kTabSlots];            // closure table: local token of a slot, 0xFFFF: none yet, or the last of a full set
   alignas(16) unsigned hist[256]; unsigned hist2[256], hist3[256];
   unsigned wave_tot[kWaves];
@@ -700,12 +702,17 @@ __device__ __forceinline__ unsigned long long stays2(Cx &x, const int2 *Q, int2 
 }
 
 // ------------------------------------------------------------------ token creation
+// An entry of a worklist of the closure {number in the set, key, cost, new}: a short list is read out of LDS.
+__device__ __forceinline__ void list_eps(Cx &x, int sel, int wi, int4 e) {
+  if (wi < kWlLds) x.sm.wl[sel][wi] = e;
+  else if (wi < x.c.qcap) (x.wl0 + sel * x.c.qcap)[wi] = e;
+}
 // New tokens of the emitting step (N per lane): own record, number in the set, backpointer, an entry in the
 // worklist if the state has epsilon arcs, and one in the closure's table if an epsilon arc enters it.
 // Tokens outside simple states are numbered from the front, the others from the back.
 template <bool kCl, bool kOpt>
 __device__ __forceinline__ void make2(Cx &x, int ok, int next, int costbits, int src, int arc, const Cutoff &cut,
-                                      int2 *NQ, int *NGI, unsigned lat_base, int4 *WL, int n_emit, int gbase) {
+                                      int2 *NQ, int *NGI, unsigned lat_base, int n_emit, int gbase) {
   Smem2 &sm = x.sm;
   TableLds &t = sm.u.t;
   const int lane = lane_id() & 63;
@@ -745,8 +752,7 @@ __device__ __forceinline__ void make2(Cx &x, int ok, int next, int costbits, int
       }
     }
     // (for a token without room the entry is one that comes to nothing: infinite cost)
-    if (((unsigned)next & kFlagHasEps) && wi < x.c.qcap)
-      WL[wi] = gidx < x.c.qcap ? make_int4(gidx, key_of(next), cb, 1) : make_int4(0, 0, __float_as_int(INFINITY), 0);
+    if ((unsigned)next & kFlagHasEps) list_eps(x, 0, wi, gidx < x.c.qcap ? make_int4(gidx, key_of(next), cb, 1) : make_int4(0, 0, __float_as_int(INFINITY), 0));
   }
   // smallest cost in a simple state: one lane's business, and only if it gets smaller
   const unsigned cur = __hip_atomic_load(&sm.min_simple, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1034,7 +1040,6 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
 
   // ---- survivors become tokens
   const int n_emit = uni(sm.n_emit), gbase = uni(sm.gbase);
-  int4 *WL = x.wl0;
   // First the candidates that won, then the tokens that stay where they are, made from the records of
   // the current set.  A third of the lanes have one at a time, and making a token is long (LDS counters, the closure's
   // table), so every wave collects 64 of them before it makes any: 32 utterances of 8.1 k tokens per frame 36.7 -> 36.0 ms,
@@ -1073,7 +1078,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     const int4 r = mk[lane];
-    make2<kCl, kOpt>(x, (int)(lane < n_mk), r.x, r.y, r.z, r.w, cut, NQ, NGI, lat_base, WL, n_emit, gbase);
+    make2<kCl, kOpt>(x, (int)(lane < n_mk), r.x, r.y, r.z, r.w, cut, NQ, NGI, lat_base, n_emit, gbase);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     if (ok && at >= 64) mk[at - 64] = cr;
@@ -1104,7 +1109,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
 // `full`: the workgroup had as many tokens as a set holds when the round began.
 // All lanes of the wave call it.
 template <bool kCl>
-__device__ __forceinline__ void apply2(Cx &x, int win, const int4 &rec, int slot, int2 *NQ, int *NGI, unsigned lat_base, int4 *WLN, bool full) {
+__device__ __forceinline__ void apply2(Cx &x, int win, const int4 &rec, int slot, int2 *NQ, int *NGI, unsigned lat_base, int sel, bool full) {
   Smem2 &sm = x.sm;
   TableLds &t = sm.u.t;
   const int lane = lane_id() & 63;
@@ -1145,7 +1150,7 @@ __device__ __forceinline__ void apply2(Cx &x, int win, const int4 &rec, int slot
     }
     if ((unsigned)rec.x & kFlagHasEps) {
       const int wi = __builtin_amdgcn_readlane(at, 1) + __popcll(mw & lt);
-      if (wi < x.c.qcap) WLN[wi] = room ? make_int4(gx, key_of(rec.x), rec.y, fresh) : make_int4(0, 0, __float_as_int(INFINITY), 0);
+      list_eps(x, sel, wi, room ? make_int4(gx, key_of(rec.x), rec.y, fresh) : make_int4(0, 0, __float_as_int(INFINITY), 0));
     }
   }
   const unsigned cur = __hip_atomic_load(&sm.min_simple, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1203,68 +1208,71 @@ __device__ __forceinline__ bool closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
   const int S = kCl ? x.G : kRegions, lg = kCl ? x.lg : 0;
   for (int round = 1;; ++round) {
     const int sel = (round - 1) & 1, buf = kCl ? seg_set(x) ^ 1 : 0;
-    const int4 *WL = x.wl0 + sel * x.c.qcap; int4 *WLN = x.wl0 + (sel ^ 1) * x.c.qcap;
     const int n_wl = uni(min(sm.made[2], x.c.qcap));
     if (!kCl && n_wl == 0) { __syncthreads(); break; }        // (the size of the set is known)
-    // ---- every wave expands items of its own; at least four, so that short lists don't keep all waves busy
-    const int size = min(kEpsTok, max(4, (n_wl + kWaves - 1) / kWaves));
-    WaveEps &we = sm.v.ek.w[wave];
-    unsigned xsum = 0;
-    for (int r = wave; r * size < n_wl; r += kWaves) {
-      const int i = r * size + lane;
-      int4 w = make_int4(0, 0, 0, 0);
-      unsigned deg = 0;
-      if (lane < size && i < n_wl) {
-        w = WL[i];                                            // w.y is the token's key: (state in B, block)
-        deg = (unsigned)x.g.unit[2 * (size_t)((unsigned)w.y & x.g.blk_mask)].w >> kPackXShift;   // the state's header
-      }
-      int first = 2 * (int)((unsigned)w.y & x.g.blk_mask) + 1;
-      const float cost = __int_as_float(w.z);                 // the token's cost when it was listed
-      const int src = w.x | (int)(((unsigned)w.y >> x.g.blk_bits) << 16);
-      xsum += w.w ? deg : 0u;
-      if (deg > (unsigned)kEpsDeg) {                          // to the shared list, as far as it has room
-        const int n = ((int)deg + kEpsSeg - 1) / kEpsSeg;
-        const int h = atomicAdd(&sm.n_eseg, n), fit = max(0, min(n, kEpsSegs - h));
-        for (int q = 0; q < fit; ++q, first += kEpsSeg) {
-          sm.v.ek.seg[h + q] = WaveItem{first, cost, src, min(kEpsSeg, (int)deg)};
-          deg -= min((unsigned)kEpsSeg, deg);
+    if (n_wl > 0) {                                           // (with nothing to do, what the others have is asked for at once)
+      // ---- every wave expands items of its own; at least four, so that short lists don't keep all waves busy
+      const int size = min(kEpsTok, max(4, (n_wl + kWaves - 1) / kWaves));
+      WaveEps &we = sm.v.ek.w[wave];
+      unsigned xsum = 0;
+      for (int r = wave; r * size < n_wl; r += kWaves) {
+        const int i = r * size + lane;
+        int4 w = make_int4(0, 0, 0, 0);
+        unsigned deg = 0;
+        if (lane < size && i < n_wl) {
+          w = sm.wl[sel][min(i, kWlLds - 1)];                   // w.y is the token's key: (state in B, block)
+          asm volatile("" : "+v"(w.x), "+v"(w.y), "+v"(w.z), "+v"(w.w));     // (or both would be one load of a generic address)
+          if (i >= kWlLds) w = (x.wl0 + sel * x.c.qcap)[i];
+          deg = (unsigned)x.g.unit[2 * (size_t)((unsigned)w.y & x.g.blk_mask)].w >> kPackXShift;   // the state's header
         }
-      }
-      do {
-        const unsigned take = min(deg, (unsigned)kEpsDeg);
-        const int M = list_items(we, take, first, cost, src);
-        for (int f0 = 0, q = 0, before = 0; f0 < M; f0 += 64 * kU) {
-          int ok[kU], isrc[kU], arc[kU]; float tc[kU];
-#pragma unroll
-          for (int u = 0; u < kU; ++u) {
-            const int f = f0 + u * 64 + lane;
-            const WaveItem it = item_of(we, q++, before);
-            ok[u] = f < M; isrc[u] = it.src; tc[u] = it.tcost; arc[u] = it.abase + f;
+        int first = 2 * (int)((unsigned)w.y & x.g.blk_mask) + 1;
+        const float cost = __int_as_float(w.z);                 // the token's cost when it was listed
+        const int src = w.x | (int)(((unsigned)w.y >> x.g.blk_bits) << 16);
+        xsum += w.w ? deg : 0u;
+        if (deg > (unsigned)kEpsDeg) {                          // to the shared list, as far as it has room
+          const int n = ((int)deg + kEpsSeg - 1) / kEpsSeg;
+          const int h = atomicAdd(&sm.n_eseg, n), fit = max(0, min(n, kEpsSegs - h));
+          for (int q = 0; q < fit; ++q, first += kEpsSeg) {
+            sm.v.ek.seg[h + q] = WaveItem{first, cost, src, min(kEpsSeg, (int)deg)};
+            deg -= min((unsigned)kEpsSeg, deg);
           }
-          emit_eps2<kCl>(x, ok, tc, isrc, arc, cut, boosted, buf);
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        deg -= take; first += (int)take;
-      } while (__ballot(deg != 0) != 0ull);
-    }
-    // epsilon arcs out of the set (a counter): every token is listed as new exactly once
-    xsum = wave_sum(xsum);
-    if (lane == 0 && xsum) atomicAdd((unsigned long long *)&sm.ctr[kCtXarc], (unsigned long long)xsum);
-    if (kCl) stores_done();
-    __syncthreads();
-    const int n_seg = uni(min(sm.n_eseg, kEpsSegs));
-    if (n_seg > 0) {                                          // ---- segments of states with many arcs
-      for (int q = wave; q < n_seg; q += kWaves) {
-        const WaveItem it = sm.v.ek.seg[q];
-        int ok[kU], isrc[kU], arc[kU]; float tc[kU];
+        do {
+          const unsigned take = min(deg, (unsigned)kEpsDeg);
+          const int M = list_items(we, take, first, cost, src);
+          for (int f0 = 0, q = 0, before = 0; f0 < M; f0 += 64 * kU) {
+            int ok[kU], isrc[kU], arc[kU]; float tc[kU];
 #pragma unroll
-        for (int u = 0; u < kU; ++u) { ok[u] = u * 64 + lane < it.pad; isrc[u] = it.src; tc[u] = it.tcost; arc[u] = it.abase + u * 64 + lane; }
-        emit_eps2<kCl>(x, ok, tc, isrc, arc, cut, boosted, buf);
+            for (int u = 0; u < kU; ++u) {
+              const int f = f0 + u * 64 + lane;
+              const WaveItem it = item_of(we, q++, before);
+              ok[u] = f < M; isrc[u] = it.src; tc[u] = it.tcost; arc[u] = it.abase + f;
+            }
+            emit_eps2<kCl>(x, ok, tc, isrc, arc, cut, boosted, buf);
+          }
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+          deg -= take; first += (int)take;
+        } while (__ballot(deg != 0) != 0ull);
       }
+      // epsilon arcs out of the set (a counter): every token is listed as new exactly once
+      xsum = wave_sum(xsum);
+      if (lane == 0 && xsum) atomicAdd((unsigned long long *)&sm.ctr[kCtXarc], (unsigned long long)xsum);
       if (kCl) stores_done();
       __syncthreads();
-      if (tid == 0) sm.n_eseg = 0;
+      const int n_seg = uni(min(sm.n_eseg, kEpsSegs));
+      if (n_seg > 0) {                                          // ---- segments of states with many arcs
+        for (int q = wave; q < n_seg; q += kWaves) {
+          const WaveItem it = sm.v.ek.seg[q];
+          int ok[kU], isrc[kU], arc[kU]; float tc[kU];
+#pragma unroll
+          for (int u = 0; u < kU; ++u) { ok[u] = u * 64 + lane < it.pad; isrc[u] = it.src; tc[u] = it.tcost; arc[u] = it.abase + u * 64 + lane; }
+          emit_eps2<kCl>(x, ok, tc, isrc, arc, cut, boosted, buf);
+        }
+        if (kCl) stores_done();
+        __syncthreads();
+        if (tid == 0) sm.n_eseg = 0;
+      }
     }
     if (tid == 0) sm.made[2] = 0;
     mark<kProf>(x, kPhEpsExpand);
@@ -1348,7 +1356,7 @@ __device__ __forceinline__ bool closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
             }
           }
           if (sl >= 0) win = (int)((unsigned)t.vals[sl] == (unsigned)i);
-          apply2<kCl>(x, win, cd, sl, NQ, NGI, lat_base, WLN, n_loc0 >= kQueueMax && x.c.qcap == kQueueMax);
+          apply2<kCl>(x, win, cd, sl, NQ, NGI, lat_base, sel ^ 1, n_loc0 >= kQueueMax && x.c.qcap == kQueueMax);
         }
         __syncthreads();
         mark<kProf>(x, kPhEpsTabScan);
