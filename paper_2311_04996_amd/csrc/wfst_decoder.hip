@@ -2307,7 +2307,8 @@ struct wfst_decoder {
   unsigned long long *d_set_links = nullptr; // [max_frames + 2] links per token set of the channel being read out
   std::vector<int> h_params[kRing];
   // device staging for host-side outputs
-  int *o_words = nullptr, *o_nwords = nullptr, *o_flags = nullptr; float *o_cost = nullptr;
+  int *h_out = nullptr;                // results on the host: pinned words, numbers of words, flags and costs, a row per channel
+  int *o_words = nullptr, *o_nwords = nullptr, *o_flags = nullptr; float *o_cost = nullptr;   // ... as the GPU addresses them
   // word-boost tables: pinned host staging per channel (keys, values, count) + what is on the device
   int *h_boost = nullptr;            // [channels][kBoostStage]: labels, scores, from | to << 16, {arcs, states}
   std::vector<int> boost_on_dev;     // entries of the table each channel currently has on the device
@@ -2600,10 +2601,15 @@ int alloc_channels(wfst_decoder *d) {
   if (o.keep_token_records)
     HIP_TRY(d, hipHostMalloc(reinterpret_cast<void **>(&d->h_pinned), (kHostHead + kScratchFrames + 2) * sizeof(unsigned)));
   if (o.outputs_on_host) {
-    if ((rc = dev_alloc(d, &d->o_words, N * (size_t)o.max_words))) return rc;
-    if ((rc = dev_alloc(d, &d->o_nwords, N))) return rc;
-    if ((rc = dev_alloc(d, &d->o_flags, N))) return rc;
-    if ((rc = dev_alloc(d, &d->o_cost, N))) return rc;
+    // the kernels write results straight into host memory: a row is written once, at a launch's end, and four copies
+    // behind it took 110 us of a call (one stream's chunk of 16 frames: 0.60 ms in the kernel)
+    const size_t cells = N * ((size_t)o.max_words + 3);
+    HIP_TRY(d, hipHostMalloc(reinterpret_cast<void **>(&d->h_out), cells * sizeof(int)));
+    std::memset(d->h_out, 0, cells * sizeof(int));
+    void *dev = nullptr;
+    HIP_TRY(d, hipHostGetDevicePointer(&dev, d->h_out, 0));
+    d->o_words = static_cast<int *>(dev); d->o_nwords = d->o_words + N * (size_t)o.max_words;
+    d->o_flags = d->o_nwords + N; d->o_cost = reinterpret_cast<float *>(d->o_flags + N);
   }
   HIP_TRY(d, hipDeviceSynchronize());
   return WFST_OK;
@@ -2845,6 +2851,18 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
   HIP_TRY(d, hipEventRecord(d->ev1[slot_id], st));
   d->timed[slot_id] = 1; d->running[slot_id] = !recorded;
   d->last_timed = slot_id;
+  return WFST_OK;
+}
+
+// The results of rows [row, row + n), `width` words each, once everything on the stream is done.
+int fetch_outputs(wfst_decoder *d, size_t row, size_t n, size_t width, int32_t *words, int32_t *nwords, float *cost, int32_t *flags, hipStream_t st) {
+  HIP_TRY(d, hipStreamSynchronize(st));
+  const size_t N = (size_t)d->opts.max_channels;
+  const int *w = d->h_out, *nw = w + N * (size_t)d->opts.max_words, *fl = nw + N, *co = fl + N;
+  std::memcpy(words, w + row * width, n * width * sizeof(int));
+  std::memcpy(nwords, nw + row, n * sizeof(int));
+  std::memcpy(flags, fl + row, n * sizeof(int));
+  std::memcpy(cost, co + row, n * sizeof(float));
   return WFST_OK;
 }
 
@@ -3207,6 +3225,7 @@ int32_t wfst_decoder_destroy(wfst_decoder *d) {
   for (void *p : d->allocs) (void)hipFree(p);
   if (d->h_boost) (void)hipHostFree(d->h_boost);
   if (d->h_pinned) (void)hipHostFree(d->h_pinned);
+  if (d->h_out) (void)hipHostFree(d->h_out);
   if (d->h_lat_batch) (void)hipHostFree(d->h_lat_batch);
   for (hipEvent_t e : d->ev0) if (e) (void)hipEventDestroy(e);
   for (hipEvent_t e : d->ev1) if (e) (void)hipEventDestroy(e);
@@ -3308,7 +3327,7 @@ int decode_batch_impl(wfst_decoder *d, int slot, const void *loglikes, const int
   a.ll = loglikes; a.ll_stride = (long long)T * V; a.V = V; a.ll_dtype = d->opts.loglike_dtype;
   a.mode = kModeInit | kModeFinal; a.finalize = 1;
   a.beam = beam; a.scale = 256.0f / beam; a.max_active = max_active;
-  // (host outputs are staged in device memory per channel, so the slots do not share any of it)
+  // (host outputs are staged per channel, so the slots do not share any of it)
   const size_t mw = (size_t)d->opts.max_words;
   a.words = host_out ? d->o_words + ch0 * mw : words; a.nwords = host_out ? d->o_nwords + ch0 : nwords;
   a.cost = host_out ? d->o_cost + ch0 : cost;         a.flags = host_out ? d->o_flags + ch0 : flags;
@@ -3316,11 +3335,7 @@ int decode_batch_impl(wfst_decoder *d, int slot, const void *loglikes, const int
   int rc = launch(d, chan, nfr, order, a, st, slot);
   if (rc) return rc;
   if (host_out) {
-    HIP_TRY(d, hipMemcpyAsync(words, d->o_words + ch0 * mw, B * mw * sizeof(int), hipMemcpyDeviceToHost, st));
-    HIP_TRY(d, hipMemcpyAsync(nwords, d->o_nwords + ch0, B * sizeof(int), hipMemcpyDeviceToHost, st));
-    HIP_TRY(d, hipMemcpyAsync(cost, d->o_cost + ch0, B * sizeof(float), hipMemcpyDeviceToHost, st));
-    HIP_TRY(d, hipMemcpyAsync(flags, d->o_flags + ch0, B * sizeof(int), hipMemcpyDeviceToHost, st));
-    HIP_TRY(d, hipStreamSynchronize(st));
+    if ((rc = fetch_outputs(d, (size_t)ch0, (size_t)B, mw, words, nwords, cost, flags, st))) return rc;
     for (int b = 0; b < B; ++b) {
       if (flags[b] & WFST_FLAG_LATTICE_OVERFLOW) return fail(d, WFST_ERR_LATTICE_OVERFLOW, "utterance " + std::to_string(b) + " ran out of lattice memory");
       if (flags[b] & WFST_FLAG_CAPACITY) return fail(d, WFST_ERR_CAPACITY, "utterance " + std::to_string(b) + " overflowed a work buffer");
@@ -3451,15 +3466,7 @@ int32_t wfst_advance_chunk_partial(wfst_decoder *d, const int32_t *channels, int
   a.max_words = d->opts.max_words;
   int rc = launch(d, chan, nfr, io, a, st);
   if (rc) return rc;
-  if (host_out) {
-    const size_t mw = (size_t)d->opts.max_words;
-    HIP_TRY(d, hipMemcpyAsync(words, d->o_words, n * mw * sizeof(int), hipMemcpyDeviceToHost, st));
-    HIP_TRY(d, hipMemcpyAsync(nwords, d->o_nwords, n * sizeof(int), hipMemcpyDeviceToHost, st));
-    HIP_TRY(d, hipMemcpyAsync(cost, d->o_cost, n * sizeof(float), hipMemcpyDeviceToHost, st));
-    HIP_TRY(d, hipMemcpyAsync(flags, d->o_flags, n * sizeof(int), hipMemcpyDeviceToHost, st));
-    HIP_TRY(d, hipStreamSynchronize(st));
-  }
-  return WFST_OK;
+  return host_out ? fetch_outputs(d, 0, (size_t)n, (size_t)d->opts.max_words, words, nwords, cost, flags, st) : WFST_OK;
 }
 
 int32_t wfst_get_partial(wfst_decoder *d, int32_t ch, int32_t finalize, int32_t *words, int32_t cap,
@@ -3477,14 +3484,7 @@ int32_t wfst_get_partial(wfst_decoder *d, int32_t ch, int32_t finalize, int32_t 
   a.max_words = cap;
   int rc = launch(d, {ch}, {0}, {0}, a, st);
   if (rc) return rc;
-  if (host_out) {
-    HIP_TRY(d, hipMemcpyAsync(nwords, d->o_nwords, sizeof(int), hipMemcpyDeviceToHost, st));
-    HIP_TRY(d, hipMemcpyAsync(cost, d->o_cost, sizeof(float), hipMemcpyDeviceToHost, st));
-    HIP_TRY(d, hipMemcpyAsync(flags, d->o_flags, sizeof(int), hipMemcpyDeviceToHost, st));
-    HIP_TRY(d, hipMemcpyAsync(words, d->o_words, (size_t)cap * sizeof(int), hipMemcpyDeviceToHost, st));
-    HIP_TRY(d, hipStreamSynchronize(st));
-  }
-  return WFST_OK;
+  return host_out ? fetch_outputs(d, 0, 1, (size_t)cap, words, nwords, cost, flags, st) : WFST_OK;
 }
 
 int32_t wfst_get_partial_batch(wfst_decoder *d, const int32_t *channels, int32_t n, int32_t finalize,
@@ -3512,15 +3512,7 @@ int32_t wfst_get_partial_batch(wfst_decoder *d, const int32_t *channels, int32_t
   a.max_words = d->opts.max_words;
   int rc = launch(d, chan, nfr, io, a, st);
   if (rc) return rc;
-  if (host_out) {
-    const size_t mw = (size_t)d->opts.max_words;
-    HIP_TRY(d, hipMemcpyAsync(words, d->o_words, n * mw * sizeof(int), hipMemcpyDeviceToHost, st));
-    HIP_TRY(d, hipMemcpyAsync(nwords, d->o_nwords, n * sizeof(int), hipMemcpyDeviceToHost, st));
-    HIP_TRY(d, hipMemcpyAsync(cost, d->o_cost, n * sizeof(float), hipMemcpyDeviceToHost, st));
-    HIP_TRY(d, hipMemcpyAsync(flags, d->o_flags, n * sizeof(int), hipMemcpyDeviceToHost, st));
-    HIP_TRY(d, hipStreamSynchronize(st));
-  }
-  return WFST_OK;
+  return host_out ? fetch_outputs(d, 0, (size_t)n, (size_t)d->opts.max_words, words, nwords, cost, flags, st) : WFST_OK;
 }
 
 int32_t wfst_debug_frame_digests(wfst_decoder *d, int32_t ch, uint64_t *digest, int32_t *count,
