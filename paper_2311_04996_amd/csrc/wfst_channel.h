@@ -813,12 +813,28 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
     if (tid == 0) sm.n_in = (int)max(max(n_reg[0], n_reg[1]), max(n_reg[2], n_reg[3]));
   }
   unsigned long long won = 0;
-  // With more candidates than registers hold, but no more than the table has slots, and one pass, a candidate's slot is noted
+  // With more candidates than registers hold, but no more in a pass than the table has slots, a candidate's slot is noted
   // in LDS (the closure's map is free), and a bit says which of a lane's candidates have won: the records are read only
   // where they go into the table and where they become tokens.
-  static_assert(kTabSlots <= 32 * kBlock, "a bit per candidate of a lane");
   bool noted = false;
-  unsigned won_c = 0;
+  unsigned long long won_c = 0;
+  // A pass reads the candidates of a part of the keys: one workgroup's four regions are parts of their own (or two and two),
+  // the segments of a cluster are one.
+  int parts = 1;
+  auto part_at = [&](int j) { return kCl ? (j ? n_own : 0) : uni(sm.seg_pre[j * (kRegions / parts)]); };
+  // Where the lane's candidate number k lies (a bit of won_c each, part by part).
+  auto place_of = [&](int k) {
+    if (kCl) return k * kBlock + tid;
+    int at = 0;
+    for (int j = 0; j < parts; ++j) {
+      const int r0 = part_at(j), n_it = (part_at(j + 1) - r0 + kBlock - 1) / kBlock;
+      at = r0 + k * kBlock + tid;
+      if (k < n_it) break;
+      k -= n_it;
+    }
+    return at;
+  };
+  int k_noted = 0;                                 // bits used
   // the lane's records, one per kBlock candidates: picked by a rolled loop (its body is large)
   static_assert(kKR == 3, "three named records");
   int4 rec0 = make_int4(0, 0, 0, 0), rec1 = rec0, rec2 = rec0; int slot0 = -1, slot1 = -1, slot2 = -1;
@@ -895,14 +911,22 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
   for (int attempt = 0; !init; ++attempt) {
     // ---- table passes over sub-groups of the keys; with the records in registers there is one, of everything in the beam
     int P = small || (n_sel_c <= kGroupTarget && mult == 1) ? 1 : min(2048, (int)((float)n_sel_c * 1.15f / (float)kGroupTarget + 1.0f) * mult);
-    if (!kCl && P > 1) P = (P + kRegions - 1) / kRegions * kRegions;        // whole regions: a pass reads only its own
-    won = 0; won_c = 0;
-    noted = !small && P == 1 && n_own <= kTabSlots;
+    // (one workgroup: whole regions, two at a time if two passes will do, so that a pass reads only its own; with four
+    // passes where two do, and the winners copied, six batches of 256 in flight took 309 instead of 302 ms)
+    if (!kCl && P > 2) P = (P + kRegions - 1) / kRegions * kRegions;
+    parts = kCl ? 1 : min(P, kRegions);
+    won = 0; won_c = 0; k_noted = 0;
+    noted = !small;
+    for (int j = 0; j < parts && noted; ++j) {
+      const int n_part = part_at(j + 1) - part_at(j);
+      noted = n_part <= kTabSlots;
+      k_noted += (n_part + kBlock - 1) / kBlock;
+    }
+    static_assert(kTabSlots * kRegions <= 64 * kBlock, "a bit per candidate of a lane");
     for (int g = 0; g < P; ++g) {
       if (g > 0) { clear_table(sm); __syncthreads(); }       // (before the first it is clear)
       mark<kProf>(x, kPhTabClear);
-      const int r0 = !kCl && P > 1 ? uni(sm.seg_pre[g / (P / kRegions)]) : 0;
-      const int r1 = !kCl && P > 1 ? uni(sm.seg_pre[g / (P / kRegions) + 1]) : n_own;
+      const int part = g / (P / parts), r0 = part_at(part), r1 = part_at(part + 1);
       int4 nxt = make_int4(0, 0, 0, 0);
       if (!small && r0 + tid < r1) nxt = get4<kCl>(cand_at<kCl>(x, r0 + tid, buf));
       int2 tok0 = make_int2(0, 0);                 // (on its way while the table is filled)
@@ -918,7 +942,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
         int sl = -1;
         if (take) sl = insert2<kCl, false>(x, key, c, cd.w, cd.z, i, buf, nullptr, 0u);
         if (small) set_slot(k, sl);
-        else if (noted && i < r1) sm.tokof[i] = (unsigned short)sl;
+        else if (noted && i < r1) sm.tokof[i - r0] = (unsigned short)sl;
       }
       __syncthreads();
       mark<kProf>(x, kPhTabFill);
@@ -927,17 +951,20 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
       mark<kProf>(x, kPhSelect);
       // every candidate that was inserted looks at its slot again: the one still there has won
       if (noted) {
+        int k = 0;
+        for (int q = 0; q < part; ++q) k += (part_at(q + 1) - part_at(q) + kBlock - 1) / kBlock;
 #pragma unroll 1
-        for (int k = 0; k * kBlock < n_own; ++k) {
-          const int i = k * kBlock + tid;
-          const unsigned sl = i < n_own ? sm.tokof[i] : 0xFFFFu;
+        for (int i0 = r0; i0 < r1; ++k, i0 += kBlock) {
+          const int i = i0 + tid;
+          const unsigned sl = i < r1 ? sm.tokof[i - r0] : 0xFFFFu;
           if (sl != 0xFFFFu) {
             const unsigned long long v = t.vals[sl];
-            if ((unsigned)v == (unsigned)i) { won_c |= 1u << k; atomicAdd(&sm.hist[cut.bin(ord2f((unsigned)(v >> 32)))], 1u); }
+            if ((unsigned)v == (unsigned)i) { won_c |= 1ull << k; atomicAdd(&sm.hist[cut.bin(ord2f((unsigned)(v >> 32)))], 1u); }
           }
         }
+        if (P > 1) __syncthreads();
         mark<kProf>(x, kPhTabScan);
-        break;
+        continue;
       }
       if (!small && r0 + tid < r1) nxt = get4<kCl>(cand_at<kCl>(x, r0 + tid, buf));
 #pragma unroll 1
@@ -1066,12 +1093,12 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
   // table), so every wave collects 64 of them before it makes any: 32 utterances of 8.1 k tokens per frame 36.7 -> 36.0 ms,
   // 64 of 11.7 k on a graph that branches everywhere 27.9 -> 27.2 ms; where a wave has fewer than 64 in all (900 tokens per
   // frame and workgroup) it makes no difference.
-  const int n_c = small || noted ? n_own : uni(min(sm.n_win, x.win_cap));
-  const int k_c = (n_c + kBlock - 1) / kBlock, k_all = k_c + (n_tok + kBlock - 1) / kBlock;
+  const int n_c = small ? n_own : uni(min(sm.n_win, x.win_cap));
+  const int k_c = noted ? k_noted : (n_c + kBlock - 1) / kBlock, k_all = k_c + (n_tok + kBlock - 1) / kBlock;
   int4 nxt = make_int4(0, 0, 0, 0);
-  auto is_winner = [&](int k) { return noted ? (int)((won_c >> (k & 31)) & 1u) : (int)(k * kBlock + tid < n_c); };
+  auto is_winner = [&](int k) { return noted ? (int)((won_c >> k) & 1ull) : (int)(k * kBlock + tid < n_c); };
   auto fetch = [&](int k) {
-    if (k < k_c) { if (!small && is_winner(k)) nxt = noted ? get4<kCl>(cand_at<kCl>(x, k * kBlock + tid, buf)) : x.win[k * kBlock + tid]; }
+    if (k < k_c) { if (!small && is_winner(k)) nxt = noted ? get4<kCl>(cand_at<kCl>(x, place_of(k), buf)) : x.win[k * kBlock + tid]; }
     else if ((k - k_c) * kBlock + tid < n_tok) { const int i = (k - k_c) * kBlock + tid; const int2 q = Q[i]; nxt.x = q.x; nxt.y = q.y; nxt.z = kCl ? GI[i] : i; }
   };
   fetch(0);
