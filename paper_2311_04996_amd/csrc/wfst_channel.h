@@ -101,7 +101,9 @@ struct alignas(16) Smem2 {
   alignas(16) unsigned hist[256]; unsigned hist2[256], hist3[256];
   unsigned wave_tot[kWaves];
   int n_seg[kMaxG];                           // candidates pushed per segment
-  int seg_pre[kMaxG + 1];                     // own candidates: prefix sums over the segments
+  alignas(16) int seg_lo[kMaxG]; unsigned seg_rel[kMaxG];   // own candidates, flattened: number of a segment's first one (none: INT_MAX),
+                                              // and what turns a candidate's number into its place in the work memory
+  int n_own;                                  // how many
   unsigned x_best, x_minsimple;
   int x_any, x_status, x_made;                // (the first two are read together)
   int x_more, x_before;                       // some candidate's state has epsilon arcs; overflows of the frame before
@@ -217,12 +219,12 @@ __device__ __forceinline__ unsigned poll(Smem2 &sm, const unsigned long long *p,
   return (unsigned)poll_word(sm, p, tag, sm.polls);
 }
 __device__ __forceinline__ unsigned long long *box_of(const Cx &x, int r) {
-  return x.box0 + ((size_t)r * 2 + (x.xc & 1u)) * kBoxWords;
+  return x.box0 + (unsigned)((r * 2 + (int)(x.xc & 1u)) * kBoxWords);
 }
 // The set of segments (of two) that the last exchange of sizes was about; candidates on their way go to the other one.
 __device__ __forceinline__ int seg_set(const Cx &x) { return (int)((x.xc - x.hc) & 1u); }
 __device__ __forceinline__ unsigned long long *hist_of(const Cx &x, int r) {
-  return x.box0 + ((size_t)r * 2 + (x.hc & 1u)) * kBoxWords + kBoxHist;
+  return x.box0 + (unsigned)((r * 2 + (int)(x.hc & 1u)) * kBoxWords + kBoxHist);
 }
 __device__ __forceinline__ void post(const Cx &x, int word, unsigned v) {
   astore(box_of(x, x.me) + word, ((unsigned long long)x.xc << 32) | v);
@@ -260,7 +262,7 @@ __device__ __forceinline__ void post_sizes(Cx &x) {
     if (tid < x.G || q >= 0) post(x, tid, v);
   }
 }
-// Take the cluster's sizes: own candidates are [0, seg_pre[segments]) afterwards.  Ends with a barrier.  Three waves share the
+// Take the cluster's sizes: own candidates are [0, n_own) afterwards.  Ends with a barrier.  Three waves share the
 // work, and sums go by lane reads: the sizes through LDS, one wave for all of the rest and butterflies for minima made an exchange
 // 0.3 us longer (four or five exchanges a frame: one utterance of 10.8 k tokens 9.93 instead of 9.70 ms, with the other trips
 // through LDS that are now not waited for).  A workgroup looks only at its own sizes and at those of the one it shares a
@@ -278,14 +280,19 @@ __device__ __forceinline__ void take_sizes(Cx &x) {
       if (lane < (x.G == kMaxG ? 2 * kMaxG : x.G)) v = min((unsigned)poll_word(sm, box_of(x, r) + (x.me ^ (lane >> 3)), x.xc, sm.polls), (unsigned)x.seg_cap);
       const unsigned inc = wave_scan_add(v);
       const unsigned own = (unsigned)__builtin_amdgcn_readlane((int)inc, kMaxG - 1);
-      if (lane <= x.G) sm.seg_pre[lane] = (int)(inc - v);
+      if (lane < kMaxG) {
+        const int lo = (int)(inc - v);
+        sm.seg_lo[lane] = lane < x.G ? lo : INT_MAX;
+        sm.seg_rel[lane] = (unsigned)(lane * 2 + seg_set(x)) * (unsigned)x.seg_stride + (unsigned)(x.me * x.seg_cap - lo);
+      }
+      if (lane == 0) sm.n_own = (int)own;
       if (lane == 2 * kMaxG - 1) sm.n_in = (int)(inc - own);         // (0 unless there are eight)
     } else {
       const int n = lane < kRegions ? min(sm.n_seg[lane], region_cap) : 0;
       const int inc = (int)wave_scan_add((unsigned)n);
-      if (lane < kRegions) { sm.seg_pre[lane + 1] = inc; sm.n_seg[lane] = 0; }
-      if (lane == 0) { sm.seg_pre[0] = 0; sm.x_best = sm.best_ord; sm.x_status = sm.status; sm.x_more = sm.more; sm.more = 0; }
-      if (lane == kRegions - 1) sm.x_any = inc > 0;
+      if (lane < kRegions) { sm.seg_lo[lane] = inc - n; sm.seg_rel[lane] = (unsigned)(lane * region_cap - (inc - n)); sm.n_seg[lane] = 0; }
+      if (lane == 0) { sm.x_best = sm.best_ord; sm.x_status = sm.status; sm.x_more = sm.more; sm.more = 0; }
+      if (lane == kRegions - 1) { sm.x_any = inc > 0; sm.n_own = inc; }
     }
   } else if (kCl && tid < 192) {                 // best costs and status, and (the next wave) tokens made and costs in simple states
     unsigned long long w = 0;
@@ -309,20 +316,21 @@ __device__ __forceinline__ void take_sizes(Cx &x) {
   __syncthreads();
 }
 
-// Address of own candidate i (flattened over the segments; `buf`: which of the two sets of segments).
+// Address of own candidate i (flattened over the segments of the last exchange): four LDS reads, a comparison and a
+// select per segment.  (With the segment's number, its first candidate and 64-bit products instead of one 32-bit offset it was
+// twice as many instructions: 256 utterances 62.0 instead of 61.5 ms, 32 32.35 instead of 32.13, one 8.86 instead of 8.80.)
 template <bool kCl>
-__device__ __forceinline__ const int4 *cand_at(const Cx &x, int i, int buf) {
+__device__ __forceinline__ const int4 *cand_at(const Cx &x, int i) {
   const Smem2 &sm = x.sm;
-  int r = 0, pre = 0;
-  const int S = kCl ? x.G : kRegions;
-#pragma unroll
-  for (int q = 1; q < kMaxG; ++q) {
-    if (!kCl && q >= kRegions) break;
-    const int p = sm.seg_pre[q];
-    if ((!kCl || q < S) && i >= p) { r = q; pre = p; }
-  }
-  if (kCl) return x.cand + (size_t)(r * 2 + buf) * x.seg_stride + (size_t)x.me * x.seg_cap + (i - pre);
-  return x.cand + (size_t)r * x.c.region_cap + (i - pre);
+  const int4 lo0 = *reinterpret_cast<const int4 *>(&sm.seg_lo[0]);
+  const uint4 re0 = *reinterpret_cast<const uint4 *>(&sm.seg_rel[0]);
+  unsigned rel = re0.x;
+  rel = i >= lo0.y ? re0.y : rel; rel = i >= lo0.z ? re0.z : rel; rel = i >= lo0.w ? re0.w : rel;
+  if (!kCl) return x.cand + (rel + (unsigned)i);
+  const int4 lo1 = *reinterpret_cast<const int4 *>(&sm.seg_lo[4]);
+  const uint4 re1 = *reinterpret_cast<const uint4 *>(&sm.seg_rel[4]);
+  rel = i >= lo1.x ? re1.x : rel; rel = i >= lo1.y ? re1.y : rel; rel = i >= lo1.z ? re1.z : rel; rel = i >= lo1.w ? re1.w : rel;
+  return x.cand + (rel + (unsigned)i);
 }
 
 // Append a batch of N candidates per lane to their owners' segments.  The lanes of a segment get
@@ -608,7 +616,7 @@ __device__ __forceinline__ int group2(int key, int lg, int P) {
 // entry may be a token of the set, and a claimed slot is marked as having none.  Returns the
 // slot, -1 if the table is overfull.
 template <bool kCl, bool kClosure>
-__device__ __forceinline__ int insert2(Cx &x, int dst, float cost, int arc, int src, int idx, int buf,
+__device__ __forceinline__ int insert2(Cx &x, int dst, float cost, int arc, int src, int idx,
                                        const int *NGI, unsigned lat_base) {
   TableLds &t = x.sm.u.t;
   unsigned s = probe_start(dst);
@@ -639,7 +647,7 @@ __device__ __forceinline__ int insert2(Cx &x, int dst, float cost, int arc, int 
         const int2 bp = at < (unsigned)x.c.qcap && lat_base + at < x.lat_cap ? get_lat<kCl>(x.lat + lat_base + at) : make_int2(0, 0);
         osrc = bp.x; oarc = bp.y;
       } else {
-        const int4 o = get4<kCl>(cand_at<kCl>(x, (int)low, buf));
+        const int4 o = get4<kCl>(cand_at<kCl>(x, (int)low));
         osrc = o.z; oarc = o.w;
       }
       better = (unsigned)arc < (unsigned)oarc;
@@ -670,7 +678,7 @@ __device__ __forceinline__ unsigned long long stays2(Cx &x, const int2 *Q, int2 
   Smem2 &sm = x.sm;
   TableLds &t = sm.u.t;
   const int tid = lane_id(), n = x.n;
-  const int lg = kCl ? x.lg : 0, buf = kCl ? seg_set(x) : 0;
+  const int lg = kCl ? x.lg : 0;
   unsigned long long won = 0;
   for (int k = 0; k * kBlock < n; ++k) {
     const int i = k * kBlock + tid;
@@ -691,7 +699,7 @@ __device__ __forceinline__ unsigned long long stays2(Cx &x, const int2 *Q, int2 
         const unsigned long long v = t.vals[sl];
         const unsigned oc = f2ord(nc), cc = (unsigned)(v >> 32);
         win = (int)(oc < cc);
-        if (oc == cc) win = (int)(2u * ((unsigned)q.x & x.g.blk_mask) + 1u < (unsigned)get4<kCl>(cand_at<kCl>(x, (int)(unsigned)v, buf)).w);
+        if (oc == cc) win = (int)(2u * ((unsigned)q.x & x.g.blk_mask) + 1u < (unsigned)get4<kCl>(cand_at<kCl>(x, (int)(unsigned)v)).w);
         if (win) t.vals[sl] = ((unsigned long long)oc << 32) | kRefStay;
       }
       if (win) atomicAdd(&sm.hist[b], 1u);
@@ -782,10 +790,10 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
   cut.best = init ? 0.0f : bo == kOrdNone ? INFINITY : ord2f(bo);
   cut.beam = x.s.beam; cut.scale = x.s.scale; cut.k_keep = 256;
   const unsigned ma = (unsigned)x.s.max_active;
-  const int S = kCl ? x.G : kRegions, lg = kCl ? x.lg : 0, buf = kCl ? seg_set(x) : 0;
+  const int lg = kCl ? x.lg : 0;
   // (the start token of an initialisation comes as its owner's only candidate and winner)
   const int start_mine = init && (!kCl || part_of(key_of((int)x.g.start), x.lg) == x.me);
-  const int n_own = init ? start_mine : uni(sm.seg_pre[S]);
+  const int n_own = init ? start_mine : uni(sm.n_own);
   const int n_tok = x.n;
   const bool small = n_own <= kKR * kBlock;
   int k_sel = 256, n_sel = n_own + n_tok, n_sel_c = n_own;
@@ -800,7 +808,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
     for (int i0 = 0; i0 < n_own; i0 += kBlock) {
       int r = -1;
       if (i0 + tid < n_own) {
-        const int4 cd = get4<kCl>(cand_at<kCl>(x, i0 + tid, buf));
+        const int4 cd = get4<kCl>(cand_at<kCl>(x, i0 + tid));
         if (cut.in_beam(__int_as_float(cd.y))) r = part_of(key_of(cd.x), kRegionBits);
       }
 #pragma unroll
@@ -821,7 +829,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
   // A pass reads the candidates of a part of the keys: one workgroup's four regions are parts of their own (or two and two),
   // the segments of a cluster are one.
   int parts = 1;
-  auto part_at = [&](int j) { return kCl ? (j ? n_own : 0) : uni(sm.seg_pre[j * (kRegions / parts)]); };
+  auto part_at = [&](int j) { return j == parts ? n_own : kCl ? 0 : uni(sm.seg_lo[j * (kRegions / parts)]); };
   // Where the lane's candidate number k lies (a bit of won_c each, part by part).
   auto place_of = [&](int k) {
     if (kCl) return k * kBlock + tid;
@@ -846,9 +854,9 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
     if (tid == 0) { sm.n_emit = start_mine; sm.gbase = 0; sm.n_emit_all = 1; sm.k_keep = 256; }
     __syncthreads();
   } else if (small) {
-    if (tid < n_own) rec0 = get4<kCl>(cand_at<kCl>(x, tid, buf));
-    if (kBlock + tid < n_own) rec1 = get4<kCl>(cand_at<kCl>(x, kBlock + tid, buf));
-    if (2 * kBlock + tid < n_own) rec2 = get4<kCl>(cand_at<kCl>(x, 2 * kBlock + tid, buf));
+    if (tid < n_own) rec0 = get4<kCl>(cand_at<kCl>(x, tid));
+    if (kBlock + tid < n_own) rec1 = get4<kCl>(cand_at<kCl>(x, kBlock + tid));
+    if (2 * kBlock + tid < n_own) rec2 = get4<kCl>(cand_at<kCl>(x, 2 * kBlock + tid));
   } else if (n_own > kGroupTarget) {
     // ---- select: bins of the implied candidates, and of a sample of the others (one run of 64 in 2^sel_shift)
     if (tid < 256) { sm.hist2[tid] = 0; sm.hist3[tid] = 0; }
@@ -864,7 +872,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
     for (int i0 = (tid >> 6) << 6; (i0 << sh) < n_own; i0 += kBlock) {
       const int i = (i0 << sh) + lane;
       if (i < n_own) {
-        const float c = __int_as_float(get4<kCl>(cand_at<kCl>(x, i, buf)).y);
+        const float c = __int_as_float(get4<kCl>(cand_at<kCl>(x, i)).y);
         if (cut.in_beam(c)) atomicAdd(&sm.hist2[cut.bin(c)], 1u);
       }
     }
@@ -928,19 +936,19 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
       mark<kProf>(x, kPhTabClear);
       const int part = g / (P / parts), r0 = part_at(part), r1 = part_at(part + 1);
       int4 nxt = make_int4(0, 0, 0, 0);
-      if (!small && r0 + tid < r1) nxt = get4<kCl>(cand_at<kCl>(x, r0 + tid, buf));
+      if (!small && r0 + tid < r1) nxt = get4<kCl>(cand_at<kCl>(x, r0 + tid));
       int2 tok0 = make_int2(0, 0);                 // (on its way while the table is filled)
       if (tid < n_tok) tok0 = Q[tid];
 #pragma unroll 1
       for (int k = 0, i0 = r0; i0 < r1; ++k, i0 += kBlock) {
         const int i = i0 + tid;
         const int4 cd = small ? rec_at(k) : nxt;
-        if (!small && i + kBlock < r1) nxt = get4<kCl>(cand_at<kCl>(x, i + kBlock, buf));
+        if (!small && i + kBlock < r1) nxt = get4<kCl>(cand_at<kCl>(x, i + kBlock));
         const float c = __int_as_float(cd.y);
         const int key = key_of(cd.x);
         int take = (int)(i < r1) & (int)cut.in_beam(c) & (int)(cut.bin(c) < k_sel) & (int)((P == 1) | (group2(key, lg, P) == g));
         int sl = -1;
-        if (take) sl = insert2<kCl, false>(x, key, c, cd.w, cd.z, i, buf, nullptr, 0u);
+        if (take) sl = insert2<kCl, false>(x, key, c, cd.w, cd.z, i, nullptr, 0u);
         if (small) set_slot(k, sl);
         else if (noted && i < r1) sm.tokof[i - r0] = (unsigned short)sl;
       }
@@ -966,12 +974,12 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
         mark<kProf>(x, kPhTabScan);
         continue;
       }
-      if (!small && r0 + tid < r1) nxt = get4<kCl>(cand_at<kCl>(x, r0 + tid, buf));
+      if (!small && r0 + tid < r1) nxt = get4<kCl>(cand_at<kCl>(x, r0 + tid));
 #pragma unroll 1
       for (int k = 0, i0 = r0; i0 < r1; ++k, i0 += kBlock) {
         const int i = i0 + tid;
         const int4 cd = small ? rec_at(k) : nxt;
-        if (!small && i + kBlock < r1) nxt = get4<kCl>(cand_at<kCl>(x, i + kBlock, buf));
+        if (!small && i + kBlock < r1) nxt = get4<kCl>(cand_at<kCl>(x, i + kBlock));
         const float c = __int_as_float(cd.y);
         int sl = -1;
         if (small) sl = slot_at(k);
@@ -1098,7 +1106,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
   int4 nxt = make_int4(0, 0, 0, 0);
   auto is_winner = [&](int k) { return noted ? (int)((won_c >> k) & 1ull) : (int)(k * kBlock + tid < n_c); };
   auto fetch = [&](int k) {
-    if (k < k_c) { if (!small && is_winner(k)) nxt = noted ? get4<kCl>(cand_at<kCl>(x, place_of(k), buf)) : x.win[k * kBlock + tid]; }
+    if (k < k_c) { if (!small && is_winner(k)) nxt = noted ? get4<kCl>(cand_at<kCl>(x, place_of(k))) : x.win[k * kBlock + tid]; }
     else if ((k - k_c) * kBlock + tid < n_tok) { const int i = (k - k_c) * kBlock + tid; const int2 q = Q[i]; nxt.x = q.x; nxt.y = q.y; nxt.z = kCl ? GI[i] : i; }
   };
   fetch(0);
@@ -1254,7 +1262,7 @@ __device__ __forceinline__ bool closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
   TableLds &t = sm.u.t;
   const int tid = lane_id(), lane = tid & 63, wave = uni(tid >> 6);
   const bool boosted = kBoost && x.s.boost_n > 0;
-  const int S = kCl ? x.G : kRegions, lg = kCl ? x.lg : 0;
+  const int lg = kCl ? x.lg : 0;
   for (int round = 1;; ++round) {
     const int sel = (round - 1) & 1, buf = kCl ? seg_set(x) ^ 1 : 0;
     const int n_wl = uni(min(sm.made[2], x.c.qcap));
@@ -1332,7 +1340,7 @@ __device__ __forceinline__ bool closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
     // round's candidates.
     if (uni((int)(sm.x_any == 0) | sm.x_status | sm.dead)) break;
     const bool more = uni(sm.x_more) != 0;
-    const int n_own = uni(sm.seg_pre[S]);
+    const int n_own = uni(sm.n_own);
     mark<kProf>(x, kPhEpsRecombine);
     if (n_own > 0) {
       const int n_map = uni(sm.made[3]), n_loc0 = uni(sm.n_loc);
@@ -1352,9 +1360,9 @@ __device__ __forceinline__ bool closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
           const int i = i0 + tid;
           int4 cd = make_int4(0, 0, 0, 0); int sl = -1;
           if (i < n_own) {
-            cd = get4<kCl>(cand_at<kCl>(x, i, buf));
+            cd = get4<kCl>(cand_at<kCl>(x, i));
             const int key = key_of(cd.x);
-            if (P == 1 || group2(key, lg, P) == g) sl = insert2<kCl, true>(x, key, __int_as_float(cd.y), cd.w, cd.z, i, buf, NGI, lat_base);
+            if (P == 1 || group2(key, lg, P) == g) sl = insert2<kCl, true>(x, key, __int_as_float(cd.y), cd.w, cd.z, i, NGI, lat_base);
           }
           if (i0 == 0) { rec0 = cd; slot0 = sl; }
         }
@@ -1381,7 +1389,7 @@ __device__ __forceinline__ bool closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
             const unsigned oc = f2ord(__int_as_float(q.y)), cc = (unsigned)(v >> 32);
             bool stays = oc < cc;
             if (oc == cc) {
-              const int4 cd = get4<kCl>(cand_at<kCl>(x, (int)(unsigned)v, buf));
+              const int4 cd = get4<kCl>(cand_at<kCl>(x, (int)(unsigned)v));
               const unsigned at = (unsigned)(kCl ? NGI[i] : i);
               const int2 bp = at < (unsigned)x.c.qcap && lat_base + at < x.lat_cap ? get_lat<kCl>(x.lat + lat_base + at) : make_int2(0, 0);
               stays = !((unsigned)cd.w < (unsigned)bp.y || (cd.w == bp.y && ((unsigned)cd.z >> 16) < ((unsigned)bp.x >> 16)));
@@ -1399,7 +1407,7 @@ __device__ __forceinline__ bool closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
           if (i0 > 0) {
             sl = -1;
             if (i < n_own) {
-              cd = get4<kCl>(cand_at<kCl>(x, i, buf));
+              cd = get4<kCl>(cand_at<kCl>(x, i));
               const int key = key_of(cd.x);
               if (P == 1 || group2(key, lg, P) == g) sl = find2(sm, key);
             }
@@ -1910,7 +1918,7 @@ __global__ __launch_bounds__(kBlock, WFST_MIN_WAVES) void wfst_channel_kernel2(D
       }
     } else {
       clear_table(sm);
-      if (tid == 0) { sm.x_best = kOrdNone; for (int r = 0; r <= kMaxG; ++r) sm.seg_pre[r] = 0; }
+      if (tid == 0) { sm.x_best = kOrdNone; sm.n_own = 0; }
       __syncthreads();
     }
     // a recycled arena is a ring over whole frames: a frame's tokens (at most qcap) never straddle
