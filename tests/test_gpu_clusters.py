@@ -465,6 +465,26 @@ def test_epsilon_arcs_around_the_sizes_of_a_waves_list(torch_cuda, cluster):
                            max_active_hint=8000)
 
 
+@pytest.mark.parametrize("cluster", [1, 2], indirect=True)
+@pytest.mark.parametrize("times,n", [(1, 8100), (1, 9000), (1, 10100), (1, 11200), (1, 12600), (1, 21000), (3, 8000)])
+def test_candidates_around_what_a_table_and_the_notes_hold(torch_cuda, cluster, times, n):
+    """As many candidates for one destination (the start, from every leaf) as slots are noted in LDS and in each of the
+    registers behind, and more; closure rounds (hubs that lead to `n` leaves, each leaf `times` over) with fewer and
+    more new destinations than the closure's table holds."""
+    from workloads.graphs import _csr
+    rng = np.random.default_rng([23, n])
+    per_hub = 3500
+    hubs = np.arange(1, 1 + -(-n * times // per_hub))
+    leaves = 1 + len(hubs) + np.arange(n)
+    S = 1 + len(hubs) + n
+    src = np.concatenate([np.zeros(len(hubs), np.int64), 1 + np.arange(n * times) // per_hub, leaves, leaves])
+    dst = np.concatenate([hubs, np.concatenate([rng.permutation(leaves) for _ in range(times)]), leaves, np.zeros(n, np.int64)])
+    il = np.concatenate([1 + hubs % 2, np.zeros(n * times, np.int64), np.ones(n, np.int64), 1 + leaves % 2])
+    g = _csr(S, 0, 2, src, dst, il, np.where(rng.random(len(src)) < 0.2, 7, 0), rng.choice([0.0, 0.25, 0.5, 1.0], len(src)))
+    ll = rng.choice([-0.5, -1.0, -1.5], (2, 5, 2)).astype(np.float32)
+    parity.check_batch(torch_cuda, g, ll, np.array([5, 3], np.int32), 20.0, 30000, max_active_hint=60000)
+
+
 @pytest.mark.parametrize("cluster", [1, 2, 4, 8], indirect=True)
 def test_an_overflow_in_a_frames_last_closure_round_stops_the_channel(torch_cuda, cluster):
     """10,002 tokens, 8,192 places, and no round and several frames after the one that finds no room: the channel is flagged
