@@ -26,8 +26,10 @@ def kernel_of(dec, w, narrow_arcs=False):
     per_utt = dec.debug_last_launch()[1]
     if per_utt > 1:
         return f"wfst_channel_kernel2 ({per_utt} workgroups per utterance)"
-    few = min(w.max_active, w.graph.num_states) <= 5000 and not narrow_arcs
-    return "wfst_channel_kernel2" if few else "wfst_channel_kernel"
+    k = min(w.max_active, w.graph.num_states)
+    plain = w.boosts is None and w.boost_fsts is None and np.mean(np.diff(w.graph.row_offsets) == 1) >= 0.5
+    solo2 = (k <= 5000 or (k <= 12000 and plain)) and not narrow_arcs
+    return "wfst_channel_kernel2" if solo2 else "wfst_channel_kernel"
 
 
 def algorithmic_bytes(counters, V):

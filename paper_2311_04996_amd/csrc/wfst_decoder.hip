@@ -2348,6 +2348,7 @@ struct wfst_decoder {
   int last_wgs = 0, last_per_utt = 0;  // of the last launch (wfst_debug_last_launch)
   unsigned launch_seq = 0;
   int n_cu = 0;
+  bool mostly_simple = false;          // half of the graph's states or more are simple ones
   std::string err;
 };
 
@@ -2463,6 +2464,7 @@ int upload_graph(wfst_decoder *d, const wfst_graph_csr *g) {
           loop_first[s] = 1;
           simple[s] = g->row_offsets[s + 1] - g->row_offsets[s] == 1;
         }
+      d->mostly_simple = std::count(simple.begin(), simple.end(), 1) >= (S + 1) / 2;
     }
   }
   auto named = [&](int32_t s) {
@@ -2647,14 +2649,12 @@ int launches_in_flight(wfst_decoder *d, int slot_id) {
 // runs, but what counts is then the time per batch: a part of the launch's, and no less than its
 // compute-unit time over the chip's.  Large graph, 128 workgroups per launch, three slots, ms per batch by the launch's own
 // time and by this: batches of 128 38.4 and 33.7, of 64 28.9 and 23.8, of 32 (medium graph) 21.6 to 26.5 and 19.0.
-int plan_clusters(wfst_decoder *d, const std::vector<int> &frames, int max_active, int in_flight, bool solo, int &n_clusters, bool &lean) {
+int plan_clusters(wfst_decoder *d, const std::vector<int> &frames, int max_active, int in_flight, bool solo, int &n_clusters) {
   const int n = (int)frames.size();
   const int n_launches = 1 + std::min(in_flight, kHwQueues - 1);
   const int budget = d->launch_workgroups > 0 ? std::min(d->launch_workgroups, d->n_cu) : d->n_cu / n_launches;
   const float k_tok = (float)std::min(max_active, d->g.S) * 1e-3f;
-  // solo: the kernel that keeps records in registers up to about 5,000 tokens, the older one beyond
-  lean = k_tok <= 5.0f;
-  const float t_us[4] = {lean ? 13.0f + 7.5f * k_tok : 20.0f + 6.8f * k_tok, 19.0f + 4.6f * k_tok, 19.0f + 2.8f * k_tok, 21.0f + 1.9f * k_tok};
+  const float t_us[4] = {k_tok <= 5.0f ? 13.0f + 7.5f * k_tok : 20.0f + 6.8f * k_tok, 19.0f + 4.6f * k_tok, 19.0f + 2.8f * k_tok, 21.0f + 1.9f * k_tok};
   long long total = 0;
   for (int f : frames) total += f;
   // clusters start on all XCDs alike (a launch has G workgroups on each for every eight of them)
@@ -2675,6 +2675,18 @@ int plan_clusters(wfst_decoder *d, const std::vector<int> &frames, int max_activ
     for (best = 0; (2 << best) <= d->cluster_size && room(best + 1) > 0;) ++best;
   n_clusters = std::min(n, room(best));
   return 1 << best;
+}
+
+// Which kernel decodes an utterance (`whole`, or a chunk of it) with one workgroup: the cluster kernel, with a cluster of one, or the first one.  The former
+// keeps a set's records in registers, or notes their table slots in LDS, where the latter reads them again and copies the
+// winners; but it has no filter of destinations for the tokens that stay.  First and cluster kernel, ms, 256 utterances of up
+// to 60 frames on a workgroup each: with 7,664 tokens per frame 5.97 and 5.96; six batches of 256 with 10,990, 304.3 and 297.7;
+// with 21,589 (its notes do not hold a frame's candidates) 11.98 and 12.96.  With word lists 12.08 and 12.35, with
+// token records 7.54 and 7.67 (instances that hold more in registers); with 11,810 on a graph without simple states 14.60 and
+// 14.89.  A chunk finds its set in no particular order, as the cluster kernel wants it: 512 streams 28.4 and 28.5.
+bool cluster_kernel_solo(const wfst_decoder *d, int max_active, bool whole, bool boost, bool opt) {
+  const int k = std::min(max_active, d->g.S);
+  return k <= 5000 || (k <= 12000 && whole && !boost && !opt && d->mostly_simple);
 }
 
 void dev_free(wfst_decoder *d, void *p, size_t bytes) {
@@ -2773,8 +2785,12 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
   // workgroups of the launch: one per entry, or at most launch_workgroups, which then take the
   // entries in list order from a counter that travels with the lists
   int n_clusters = 0;
-  bool lean = false;
   int G = 1;
+  bool boost = false;                          // does any channel of the launch have a boosting table or acceptor?
+  for (int ch : chan) boost = boost || d->boost_on_dev[ch] > 0;
+  const bool opt = d->c.cost_offset || d->c.recycle || d->c.tokrec || d->c.frame_best || d->c.dig_sum;
+  const int max_active = a.mode & kModeInit ? a.max_active : d->stream_max_active;
+  const bool solo2 = cluster_kernel_solo(d, max_active, (a.mode & kModeInit) && (a.mode & kModeFinal), boost, opt);
   // A launch that is recorded into a graph runs with the same arguments at every replay, and the number of the launch,
   // by which the workgroups of a cluster know each other, is one of them; nor can it allocate.
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
@@ -2783,8 +2799,7 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
   {
     std::vector<int> by_length(nfr);
     std::sort(by_length.begin(), by_length.end(), std::greater<int>());
-    G = plan_clusters(d, by_length, a.mode & kModeInit ? a.max_active : d->stream_max_active,
-                      recorded ? 0 : launches_in_flight(d, slot_id), recorded, n_clusters, lean);
+    G = plan_clusters(d, by_length, max_active, recorded ? 0 : launches_in_flight(d, slot_id), recorded, n_clusters);
     if (a.mode & kModeInit && !(a.mode & kModeFinal)) d->stream_max_active = a.max_active;
   }
   int n_wg = d->launch_workgroups > 0 ? std::min(n, d->launch_workgroups) : n;
@@ -2815,9 +2830,6 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
   HIP_TRY(d, hipMemcpyAsync(slot, pack.data(), pack.size() * sizeof(int), hipMemcpyHostToDevice, st));
   a.lists = slot; a.n_jobs = n;
   HIP_TRY(d, hipEventRecord(d->ev0[slot_id], st));
-  bool boost = false;                          // does any channel of the launch have a boosting table or acceptor?
-  for (int ch : chan) boost = boost || d->boost_on_dev[ch] > 0;
-  const bool opt = d->c.cost_offset || d->c.recycle || d->c.tokrec || d->c.frame_best || d->c.dig_sum;
 #define WFST_LAUNCH(NARROW, BOOST, PROF, OPT) \
   do { \
     if (n_wg < n) hipLaunchKernelGGL((wfst_channel_kernel<NARROW, BOOST, PROF, OPT, true>), dim3(n_wg), dim3(kBlock), 0, st, d->g, d->c, a); \
@@ -2825,7 +2837,7 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
   } while (0)
 #define WFST_LAUNCH2(CL, BOOST, PROF, OPT, QUEUE) \
   hipLaunchKernelGGL((wfst_channel_kernel2<CL, BOOST, PROF, OPT, QUEUE>), dim3(n_wg), dim3(kBlock), 0, st, d->g, d->c, a, cl)
-  if ((G > 1 || lean) && !d->g.earc8) {
+  if ((G > 1 || solo2) && !d->g.earc8) {
     const bool q = n_wg < n;
     if (G > 1) {
       if (d->phase_timing) { if (boost) WFST_LAUNCH2(true, true, true, true, true); else if (opt) WFST_LAUNCH2(true, false, true, true, true); else WFST_LAUNCH2(true, false, true, false, true); }
@@ -2836,7 +2848,7 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
     else if (opt) WFST_LAUNCH2(false, false, false, true, true);
     else if (q) WFST_LAUNCH2(false, false, false, false, true); else WFST_LAUNCH2(false, false, false, false, false);
   } else
-  if (d->g.earc8) {                            // (no lean instances and no phase timing with narrow arc records)
+  if (d->g.earc8) {                            // (no instances without options and no phase timing with narrow arc records)
     if (boost) WFST_LAUNCH(true, true, false, true); else WFST_LAUNCH(true, false, false, true);
   } else if (d->phase_timing) {
     if (boost) { if (opt) WFST_LAUNCH(false, true, true, true); else WFST_LAUNCH(false, true, true, false); }

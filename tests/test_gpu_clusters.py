@@ -48,6 +48,28 @@ def test_options_and_streams(torch_cuda, c1, c2, c2_refs, cluster):
     parity.test_recycled_lattice_stream_ten_times_the_window(torch_cuda, c2)
 
 
+@pytest.mark.parametrize("cluster", [1], indirect=True)
+@pytest.mark.parametrize("ma", [5000, 5001, 12000, 12001])
+def test_either_side_of_the_sizes_one_workgroup_of_the_cluster_kernel_takes(torch_cuda, c2, cluster, ma):
+    """No option on and no boosting, as the rule asks: results and counters on both sides of its ends, with a workgroup per
+    utterance and with fewer, twice on one decoder."""
+    from paper_2311_04996_amd import Decoder
+    ll, lengths = np.ascontiguousarray(c2.loglikes[:4, :40]), np.array([40, 33, 40, 1], np.int32)
+    refs = parity.oracle_batch(c2.graph, ll, lengths, 20.0, ma)
+    want = np.sum([r.counters for r in refs], axis=0)
+    dec = Decoder(c2.graph, max_channels=4, max_frames=40, max_active_hint=ma)
+    dev = torch_cuda.from_numpy(ll).cuda()
+    for n_wg in (0, 2):
+        dec.set_launch_workgroups(n_wg)
+        dec.get_counters(reset=True)
+        words, nwords, cost, flags = (t.cpu().numpy() for t in dec.decode_batch(dev, lengths, 20.0, ma))
+        assert dec.debug_last_launch()[1] == 1
+        for b, r in enumerate(refs):
+            assert words[b, :nwords[b]].tolist() == r.words.tolist() and int(flags[b]) == r.flags and cost[b] == np.float32(r.cost), b
+        assert dec.get_counters()[:7].tolist() == want[:7].tolist()
+    dec.close()
+
+
 def test_a_stream_whose_chunks_are_decoded_by_different_numbers_of_workgroups(torch_cuda, c2, c2_refs):
     from paper_2311_04996_amd import Decoder
     b = int(np.argmax(c2.lengths))
@@ -581,8 +603,8 @@ def _late_fan_graph(n_dead, n_z, n_few=20):
 def test_an_arena_that_ends_in_a_frames_only_closure_round_keeps_the_neighbours_records(torch_cuda, cluster, ma):
     """The 13th frame's 3,001 emitted tokens fit the arena of 4,096, the 3,000 its closure adds do not, and more frames
     follow: the channel is flagged and its lattice refused, and the digests and lattices of the channels whose arenas lie
-    between and behind are the oracle's, every token and link.  (One workgroup takes another kernel beyond a max-active of
-    5,000.)"""
+    between and behind are the oracle's, every token and link.  (With digests one workgroup takes another kernel beyond a
+    max-active of 5,000.)"""
     from oracle import Oracle
     from paper_2311_04996_amd import Decoder, FLAG_DEAD, FLAG_LATTICE_OVERFLOW, WfstError
     from test_gpu_lattice import gpu_rows, oracle_rows
