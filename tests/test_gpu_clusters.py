@@ -582,6 +582,30 @@ def test_frames_whose_last_closure_round_is_any_of_the_first_five(torch_cuda, cl
     parity.check_batch(torch_cuda, g, ll, np.array([12, 11], np.int32), 20.0, 5000, max_active_hint=5000)
 
 
+@pytest.mark.parametrize("cluster", [2, 4, 8], indirect=True)
+def test_closure_rounds_in_which_most_workgroups_get_nothing(torch_cuda, cluster):
+    """Chains of 40 and 23 epsilon arcs, so a round has one or two candidates and most workgroups of a cluster go from one
+    exchange to the next with nothing to expand and nothing to recombine, some forty times a frame: all waves of all of them
+    leave the closure in the same round, with the oracle's sets, links and words (one per arc of the chains)."""
+    import test_gpu_lattice as lattice
+    from workloads.graphs import _csr
+    rng = np.random.default_rng(29)
+    arcs = [(0, 0, 2, 0)]
+    for first, n, label in ((1, 40, 1), (42, 23, 2)):
+        chain = first + np.arange(n + 1)
+        arcs += [(0, first, label, 0)] + [(int(s), int(s) + 1, 0, int(s)) for s in chain[:-1]]
+        arcs += [(int(chain[-1]), 0, 1, 70 + label), (int(chain[-1]), int(chain[-1]), 2, 0), (int(chain[n // 2]), 0, 2, 0)]
+    src, dst, il, ol = (np.array(v, np.int64) for v in zip(*arcs))
+    final = np.full(66, np.inf)
+    final[41] = 0.0                                    # the longer chain's end
+    g = _csr(66, 0, 2, src, dst, il, ol, rng.choice([0.0, 0.25, 0.5], len(src)), final)
+    B, T = 40, 6                                       # more than the 32 clusters there are of 8
+    ll = rng.choice([-0.25, -0.5, -1.0], (B, T, 2)).astype(np.float32)
+    refs = parity.check_batch(torch_cuda, g, ll, (T - np.arange(B) % 5).astype(np.int32), 40.0, 5000, max_active_hint=5000)
+    assert min(len(r.words) for r in refs) >= 40
+    lattice.check_lattice(torch_cuda, g, ll[0], T, 40.0, 5000, 20.0)
+
+
 def _late_fan_graph(n_dead, n_z, n_few=20):
     """Start -> a state with a loop over label 2, from where label 1 leads to `n_dead` dead ends and, over a hub's epsilon arcs,
     to `n_z` states with a self-loop, and label 3 to a few states and back over label 2."""
