@@ -243,8 +243,10 @@ __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)
 // Owner of a key among 2^lg parts: the top bits of its hash.
 __device__ __forceinline__ int part_of(int key, int lg) { return (int)((hash_state(key) >> 1) >> (31 - lg)); }
 
-// Post the sizes of the segments this workgroup has filled, its best cost and its status.  All
-// threads call it, right behind a barrier that followed stores_done().
+// Post the sizes of the segments this workgroup has filled, its best cost and its status.  All threads call it, when
+// what the others go on to read or add to is in the L2: the candidates of all waves, by stores_done() and then a barrier, and the
+// set's counter, which thread 0 of the first workgroup stores before a frame's first closure round, by stores_done() of
+// its wave, which posts.
 template <bool kCl>
 __device__ __forceinline__ void post_sizes(Cx &x) {
   Smem2 &sm = x.sm;
@@ -1349,7 +1351,7 @@ __device__ __forceinline__ bool closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
         __syncthreads();
         if (tid == 0) sm.n_eseg = 0;
       }
-    }
+    } else if (kCl && round == 1) stores_done();              // (nothing to expand: the set's counter alone)
     if (tid == 0) sm.made[2] = 0;
     mark<kProf>(x, kPhEpsExpand);
     post_sizes<kCl>(x);

@@ -606,6 +606,31 @@ def test_closure_rounds_in_which_most_workgroups_get_nothing(torch_cuda, cluster
     lattice.check_lattice(torch_cuda, g, ll[0], T, 40.0, 5000, 20.0)
 
 
+@pytest.mark.parametrize("cluster", [2, 4, 8], indirect=True)
+def test_token_numbers_where_the_first_workgroup_has_no_epsilon_arcs_to_expand(torch_cuda, cluster):
+    """Label k leads to 200 dead ends and one hub, of 24 states between the workgroups, whose 300 epsilon arcs make the frame's other
+    tokens: in many frames the first workgroup, which stores the number of tokens the closure starts from, has nothing to
+    expand, and the others' tokens still get numbers, places in the lattice and backpointers of their own."""
+    import test_gpu_lattice as lattice
+    from workloads.graphs import _csr
+    rng = np.random.default_rng(31)
+    n_hub, n_dead, n_leaf = 24, 200, 300
+    hubs, dead = np.arange(1, 1 + n_hub), 1 + n_hub + np.arange(n_dead)
+    leaves = 1 + n_hub + n_dead + np.arange(n_leaf)
+    src = np.concatenate([np.zeros(n_hub * (1 + n_dead), np.int64), np.repeat(hubs, n_leaf), np.repeat(leaves, n_hub)])
+    dst = np.concatenate([hubs, np.tile(dead, n_hub), np.tile(leaves, n_hub), np.zeros(n_leaf * n_hub, np.int64)])
+    il = np.concatenate([hubs, np.repeat(hubs, n_dead), np.zeros(n_hub * n_leaf, np.int64), np.tile(hubs, n_leaf)])
+    ol = np.concatenate([hubs, np.zeros(n_dead * n_hub, np.int64), np.tile(100 + leaves, n_hub), np.zeros(n_leaf * n_hub, np.int64)])
+    g = _csr(1 + n_hub + n_dead + n_leaf, 0, n_hub, src, dst, il, ol, rng.choice([0.0, 0.25, 0.5, 1.0], len(src)),
+             np.where(np.arange(1 + n_hub + n_dead + n_leaf) < 1 + n_hub + n_dead, np.inf, 0.0))
+    B, T = 12, 24
+    label = rng.integers(0, n_hub, (B, T))
+    ll = np.where(np.arange(n_hub) == label[..., None], -0.25, -100.0).astype(np.float32)
+    refs = parity.check_batch(torch_cuda, g, ll, np.full(B, T - 1, np.int32), 20.0, 5000, max_active_hint=5000)
+    assert min(len(r.words) for r in refs) == T and refs[0].digest_count[1] == 1 + n_dead + n_leaf
+    lattice.check_lattice(torch_cuda, g, ll[0], T - 1, 20.0, 5000, 10.0)
+
+
 def _late_fan_graph(n_dead, n_z, n_few=20):
     """Start -> a state with a loop over label 2, from where label 1 leads to `n_dead` dead ends and, over a hub's epsilon arcs,
     to `n_z` states with a self-loop, and label 3 to a few states and back over label 2."""
