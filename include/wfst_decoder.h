@@ -256,7 +256,8 @@ int32_t wfst_decode_batch_slot(wfst_decoder *dec, int32_t slot, const void *logl
  * 3.1 GB with 2 or 4 workgroups and 5.2 GB with 8, for each batch slot whose calls use all compute units.  A call
  * that needs more of it than those before allocates it, at least twice as much as there was; a call
  * that replaces smaller memory first waits for the launch that used it, and giving that back can wait
- * for other work on the GPU.  If there is none left, the call decodes with one workgroup per utterance.
+ * for other work on the GPU.  If there is none left, the call decodes with one workgroup per utterance.  (A
+ * candidate_capacity beyond 2^27 has at most four of them, beyond 2^29 two, beyond 2^30 one.)
  * wfst_device_bytes includes it. */
 int32_t wfst_set_launch_workgroups(wfst_decoder *dec, int32_t n);
 

@@ -2632,6 +2632,12 @@ int launches_in_flight(wfst_decoder *d, int slot_id) {
   return d->in_flight;
 }
 
+// Records per segment of a cluster of G.  A workgroup addresses the cluster's candidates by 32-bit numbers (cand_at), so a decoder
+// whose candidate_capacity gives larger clusters more than 2^32 of them (beyond 2^27 for eight workgroups, 2^29 for four,
+// 2^30 for two) has smaller ones.
+int segment_capacity(const wfst_decoder *d, int G) { return d->c.region_cap * std::max(1, kRegions / G); }
+bool candidates_have_numbers(const wfst_decoder *d, int G) { return 2ull * G * G * (unsigned long long)segment_capacity(d, G) <= 1ull << 32; }
+
 // How many workgroups decode each utterance of a launch (1, 2, 4 or 8), and how many such clusters
 // the launch gets.  `frames`: what every utterance consumes, longest first.
 //
@@ -2658,7 +2664,7 @@ int plan_clusters(wfst_decoder *d, const std::vector<int> &frames, int max_activ
   long long total = 0;
   for (int f : frames) total += f;
   // clusters start on all XCDs alike (a launch has G workgroups on each for every eight of them)
-  auto room = [&](int lg) { return lg == 0 ? budget : (budget >> lg) / kXcds * kXcds; };
+  auto room = [&](int lg) { return lg == 0 ? budget : candidates_have_numbers(d, 1 << lg) ? (budget >> lg) / kXcds * kXcds : 0; };
   int best = 0; float best_t = 0.0f;
   for (int lg = 0; (1 << lg) <= kMaxG && room(lg) > 0; ++lg) {
     const int C = std::min(n, room(lg));
@@ -2734,7 +2740,7 @@ int cluster_area(wfst_decoder *d, int slot_id, int n_clusters, int n_wg, int G, 
   if (d->areas.empty()) d->areas.resize((size_t)d->n_slots + 1);
   auto &ar = d->areas[slot_id];
   const size_t region = (size_t)d->c.region_cap;
-  const int seg_cap = (int)(region * (size_t)std::max(1, 4 / G));
+  const int seg_cap = segment_capacity(d, G);
   const size_t w = (size_t)n_clusters * G, cand = w * 2 * G * (size_t)seg_cap, boxes = (size_t)n_wg;
   const Sizes old = ar.n;
   if (old.wgs < w || old.boxes < boxes || old.cand < cand) {

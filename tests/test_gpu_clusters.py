@@ -284,6 +284,25 @@ def test_the_candidate_capacity_is_the_same_for_every_number_of_workgroups(torch
         dec.close()
 
 
+@pytest.mark.parametrize("capacity,size", [(1 << 27, 8), ((1 << 27) + 4, 4)])
+def test_clusters_have_as_many_workgroups_as_32_bits_number_candidates_of(torch_cuda, c2, capacity, size):
+    """2 * 8 * 8 segments of a quarter of the capacity each are 2^32 records at 2^27, the last of them in the last segment; with
+    more, eight workgroups become four."""
+    from paper_2311_04996_amd import Decoder
+    n = 24
+    b = int(np.argmax(c2.lengths))
+    rows = np.ascontiguousarray(c2.loglikes[b:b + 1, :n])
+    (ref,) = parity.oracle_batch(c2.graph, rows, [n], c2.beam, c2.max_active)
+    dec = Decoder(c2.graph, max_channels=1, max_frames=n, max_active_hint=c2.max_active, candidate_capacity=capacity, record_digests=True)
+    dec.debug_set_cluster_size(8)
+    words, nwords, cost, flags = (t.cpu().numpy() for t in dec.decode_batch(torch_cuda.from_numpy(rows).cuda(), [n], c2.beam, c2.max_active))
+    assert dec.debug_last_launch()[1] == size
+    cnt, dig = dec.debug_frame_digests(0)
+    assert (cnt == ref.digest_count).all() and (dig == ref.digest_sum).all()
+    assert words[0, :nwords[0]].tolist() == ref.words.tolist() and cost[0] == np.float32(ref.cost) and flags[0] == ref.flags
+    dec.close()
+
+
 @pytest.mark.parametrize("cluster", [1, 2], indirect=True)
 @pytest.mark.parametrize("n_z", [2000, 4000])          # the closure's rounds meet in the kept table, or in one of their own
 def test_the_last_token_of_a_full_set_can_still_improve(torch_cuda, cluster, n_z):
