@@ -1367,8 +1367,9 @@ __device__ __forceinline__ bool closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
     if (n_own > 0) {
       const int n_map = uni(sm.made[3]), n_loc0 = uni(sm.n_loc);
       // (in the map as long as it may do: half of the candidates new ones; if they are more than it holds, the round begins again.
-      // One workgroup takes it only when it is sure to do; with that rule in clusters one utterance took 8.83 instead of 8.74 ms
-      // and a stream 4.79 instead of 4.74.)
+      // One workgroup takes it only for as many as it has room for; with that rule in clusters one utterance took 8.83 instead of 8.74
+      // ms and a stream 4.79 instead of 4.74.  Room is not enough: of 6,144 keys at regular distances, as the states of a
+      // list have them, some find no free slot within kProbeLimit probes in up to 97 of 100 orders.)
       bool map = !uni(sm.map_bad) && (kCl ? n_map + n_own / 2 <= kTabSlots * 7 / 8 : n_map + n_own <= kMapMax);
       int P = map ? 1 : max(1, (n_own + kGroupTarget - 1) / kGroupTarget);
       for (int g = 0; g < P; ++g) {
@@ -1382,7 +1383,7 @@ __device__ __forceinline__ bool closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
         int4 rec0 = make_int4(0, 0, 0, 0); int slot0 = -1;
 #pragma unroll 1
         for (int i0 = 0; i0 < n_own; i0 += kBlock) {
-          if (kCl && map && i0 > 0 && uni(sm.overfull)) break;
+          if (map && i0 > 0 && uni(sm.overfull)) break;
           const int i = i0 + tid;
           int4 cd = make_int4(0, 0, 0, 0); int sl = -1;
           if (i < n_own) {
@@ -1393,7 +1394,7 @@ __device__ __forceinline__ bool closure2(Cx &x, int2 *NQ, int *NGI, unsigned lat
           if (i0 == 0) { rec0 = cd; slot0 = sl; }
         }
         __syncthreads();
-        if (kCl && map && __builtin_expect(uni(sm.overfull), 0)) {     // too many new destinations: without the map, from the start
+        if (map && __builtin_expect(uni(sm.overfull), 0)) {     // some destination found no slot: without the map, from the start
           map = false; P = max(1, (n_own + kGroupTarget - 1) / kGroupTarget); g = -1;
           continue;
         }

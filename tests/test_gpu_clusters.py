@@ -526,6 +526,25 @@ def test_candidates_around_what_a_table_and_the_notes_hold(torch_cuda, cluster, 
     parity.check_batch(torch_cuda, g, ll, np.array([5, 3], np.int32), 20.0, 30000, max_active_hint=60000)
 
 
+@pytest.mark.parametrize("cluster,n", [(1, 6144), (2, 11000), (2, 12288)], indirect=["cluster"])
+def test_a_closure_whose_destinations_lie_at_regular_distances(torch_cuda, cluster, n):
+    """`n` states of three blocks each one behind the other, all reached over epsilon arcs in one round: as many as a closure's
+    table (8,192 slots) takes, or nearly, but with probe sequences so alike that in four of five orders one of 6,144 finds no
+    slot in the number of probes there are.  It is not lost: sets, words, counters of the oracle."""
+    from workloads.graphs import _csr
+    rng = np.random.default_rng([41, n])
+    per_hub = 3500
+    hubs = 1 + np.arange(-(-n // per_hub))
+    leaves = 1 + len(hubs) + np.arange(n)
+    src = np.concatenate([np.zeros(len(hubs), np.int64), 1 + np.arange(n) // per_hub, np.repeat(leaves, 5)])
+    dst = np.concatenate([hubs, rng.permutation(leaves), np.zeros(5 * n, np.int64)])
+    il = np.concatenate([1 + hubs % 2, np.zeros(n, np.int64), np.tile([1, 2, 1, 2, 1], n)])
+    g = _csr(1 + len(hubs) + n, 0, 2, src, dst, il, rng.integers(1, 1000, len(src)), rng.choice([0.0, 0.25, 0.5, 1.0], len(src)))
+    ll = rng.choice([-0.5, -1.0, -1.5], (8, 5, 2)).astype(np.float32)
+    refs = parity.check_batch(torch_cuda, g, ll, np.full(8, 5, np.int32), 20.0, 5000, max_active_hint=20000)
+    assert all(r.digest_count.tolist() == [1, len(hubs) + n] * 3 for r in refs)
+
+
 @pytest.mark.parametrize("cluster", [1, 2, 4, 8], indirect=True)
 def test_an_overflow_in_a_frames_last_closure_round_stops_the_channel(torch_cuda, cluster):
     """10,002 tokens, 8,192 places, and no round and several frames after the one that finds no room: the channel is flagged
