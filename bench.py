@@ -21,15 +21,11 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 
 
-def kernel_of(dec, w, narrow_arcs=False):
+def kernel_of(dec):
     """The kernel of the decoder's last launch, and how many of its workgroups decode an utterance together."""
     per_utt = dec.debug_last_launch()[1]
-    if per_utt > 1:
-        return f"wfst_channel_kernel2 ({per_utt} workgroups per utterance)"
-    k = min(w.max_active, w.graph.num_states)
-    plain = w.boosts is None and w.boost_fsts is None and np.mean(np.diff(w.graph.row_offsets) == 1) >= 0.5
-    solo2 = (k <= 5000 or (k <= 12000 and plain)) and not narrow_arcs
-    return "wfst_channel_kernel2" if solo2 else "wfst_channel_kernel"
+    name = ("no launch", "wfst_channel_kernel", "wfst_channel_kernel2")[dec.debug_last_kernel()]
+    return f"{name} ({per_utt} workgroups per utterance)" if per_utt > 1 else name
 
 
 def algorithmic_bytes(counters, V):
@@ -465,7 +461,7 @@ def main():
     dec.get_counters(reset=True)
     # one batch in flight: the kernel's own duration (for the roofline) and the unpipelined rate
     wall_one, kernel_ms = run_steps(1, args.steps, True)
-    kernel_one, wgs_one = kernel_of(dec, w, args.narrow_arcs), dec.debug_last_launch()[0]
+    kernel_one, wgs_one = kernel_of(dec), dec.debug_last_launch()[0]
     counters = dec.get_counters() // max(1, args.steps)
     # the timed region proper: `pipeline` batches in flight
     wall = run_steps(n_slots, args.steps, False)[0] if n_slots > 1 else wall_one

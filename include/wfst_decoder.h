@@ -437,6 +437,8 @@ int32_t wfst_debug_set_cluster_waits(wfst_decoder *dec, int32_t start_ticks, int
 int32_t wfst_debug_set_cluster_memory(wfst_decoder *dec, int64_t bytes);
 /* Of the decoder's last launch: how many workgroups, and how many of them decode an utterance together. */
 int32_t wfst_debug_last_launch(wfst_decoder *dec, int32_t *workgroups, int32_t *per_utterance);
+/* The kernel of that launch: 1 wfst_channel_kernel, 2 wfst_channel_kernel2, 0 if there has been none. */
+int32_t wfst_debug_last_kernel(wfst_decoder *dec, int32_t *kernel);
 int32_t wfst_debug_phase_ticks(wfst_decoder *dec, int64_t ticks[16], int32_t reset);
 
 /* Device memory the decoder holds, in bytes (graph + channel state). */

@@ -25,7 +25,7 @@ EXPORTS = ["wfst_decoder_create", "wfst_decoder_destroy", "wfst_decode_batch", "
            "wfst_get_lattice_noalloc", "wfst_get_lattice_batch",
            "wfst_debug_frame_digests",
            "wfst_debug_get_tokens", "wfst_debug_get_token_pairs", "wfst_get_counters", "wfst_debug_phase_ticks", "wfst_debug_set_phase_timing", "wfst_debug_set_cluster_size", "wfst_debug_set_cluster_waits", "wfst_debug_set_cluster_memory",
-           "wfst_debug_last_launch", "wfst_set_launch_workgroups", "wfst_device_bytes",
+           "wfst_debug_last_launch", "wfst_debug_last_kernel", "wfst_set_launch_workgroups", "wfst_device_bytes",
            "wfst_last_kernel_ms", "wfst_last_error"]
 
 
@@ -127,6 +127,7 @@ def load_library():
     lib.wfst_debug_set_cluster_waits.argtypes = [p, i32, i32]
     lib.wfst_debug_set_cluster_memory.argtypes = [p, i64]
     lib.wfst_debug_last_launch.argtypes = [p, C.POINTER(i32), C.POINTER(i32)]
+    lib.wfst_debug_last_kernel.argtypes = [p, C.POINTER(i32)]
     lib.wfst_set_launch_workgroups.argtypes = [p, i32]
     lib.wfst_device_bytes.argtypes = [p]
     lib.wfst_device_bytes.restype = i64
@@ -523,6 +524,12 @@ class Decoder:
         n, g = C.c_int32(), C.c_int32()
         self._check(self.lib.wfst_debug_last_launch(self.h, C.byref(n), C.byref(g)))
         return n.value, g.value
+
+    def debug_last_kernel(self):
+        """Which kernel the last launch ran: 1 wfst_channel_kernel, 2 wfst_channel_kernel2 (0: no launch yet)."""
+        k = C.c_int32()
+        self._check(self.lib.wfst_debug_last_kernel(self.h, C.byref(k)))
+        return k.value
 
     def debug_set_phase_timing(self, on=True):
         self._check(self.lib.wfst_debug_set_phase_timing(self.h, int(bool(on))))

@@ -2345,7 +2345,7 @@ struct wfst_decoder {
   struct ClusterArea { ClusterSizes n; size_t bytes = 0, refused = 0; std::vector<std::pair<void *, size_t>> mem; ClusterArgs a{}; };
   std::vector<ClusterArea> areas;
   int64_t cluster_bytes_max = -1;      // most memory all areas together may take (wfst_debug_set_cluster_memory); -1: no limit
-  int last_wgs = 0, last_per_utt = 0;  // of the last launch (wfst_debug_last_launch)
+  int last_wgs = 0, last_per_utt = 0, last_kernel = 0;   // of the last launch (wfst_debug_last_launch, wfst_debug_last_kernel)
   unsigned launch_seq = 0;
   int n_cu = 0;
   bool mostly_simple = false;          // half of the graph's states or more are simple ones
@@ -2817,7 +2817,8 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
     else if (rca) return rca;
     else n_wg = n_all;
   }
-  d->last_wgs = n_wg; d->last_per_utt = G;
+  const bool second = (G > 1 || solo2) && !d->g.earc8;
+  d->last_wgs = n_wg; d->last_per_utt = G; d->last_kernel = second ? 2 : 1;
   // (the lists live on the device until the kernel ends, since its workgroups read them as they go:
   // one area per batch slot, and one for the calls that name channels; calls that share an area do
   // not overlap in time, so the stream orders this copy after the last kernel that read the area)
@@ -2843,7 +2844,7 @@ int launch(wfst_decoder *d, const std::vector<int> &chan, const std::vector<int>
   } while (0)
 #define WFST_LAUNCH2(CL, BOOST, PROF, OPT, QUEUE) \
   hipLaunchKernelGGL((wfst_channel_kernel2<CL, BOOST, PROF, OPT, QUEUE>), dim3(n_wg), dim3(kBlock), 0, st, d->g, d->c, a, cl)
-  if ((G > 1 || solo2) && !d->g.earc8) {
+  if (second) {
     const bool q = n_wg < n;
     if (G > 1) {
       if (d->phase_timing) { if (boost) WFST_LAUNCH2(true, true, true, true, true); else if (opt) WFST_LAUNCH2(true, false, true, true, true); else WFST_LAUNCH2(true, false, true, false, true); }
@@ -3658,6 +3659,12 @@ int32_t wfst_debug_set_cluster_memory(wfst_decoder *d, int64_t bytes) {
 int32_t wfst_debug_last_launch(wfst_decoder *d, int32_t *workgroups, int32_t *per_utterance) {
   if (!d || !workgroups || !per_utterance) return WFST_ERR_INVALID_ARG;
   *workgroups = d->last_wgs; *per_utterance = d->last_per_utt;
+  return WFST_OK;
+}
+
+int32_t wfst_debug_last_kernel(wfst_decoder *d, int32_t *kernel) {
+  if (!d || !kernel) return WFST_ERR_INVALID_ARG;
+  *kernel = d->last_kernel;
   return WFST_OK;
 }
 

@@ -48,26 +48,99 @@ def test_options_and_streams(torch_cuda, c1, c2, c2_refs, cluster):
     parity.test_recycled_lattice_stream_ten_times_the_window(torch_cuda, c2)
 
 
+def _same_results(dec, out, refs):
+    words, nwords, cost, flags = (t.cpu().numpy() for t in out)
+    for b, r in enumerate(refs):
+        assert words[b, :nwords[b]].tolist() == r.words.tolist() and int(flags[b]) == r.flags and cost[b] == np.float32(r.cost), b
+    assert dec.get_counters()[:7].tolist() == np.sum([r.counters for r in refs], axis=0)[:7].tolist()
+
+
+def _candidates(g, ll, length, beam, max_active):
+    """Per frame, the arcs out of the oracle's token set that end inside the beam, without the usual self-loops: at least
+    as many are a workgroup's candidates (while the frame's best cost is not known yet, it lets more in)."""
+    from oracle import Oracle
+    deg, row = np.diff(g.row_offsets), g.row_offsets
+    src = np.repeat(np.arange(g.num_states), deg)
+    has_eps = np.zeros(g.num_states, bool)
+    has_eps[src[g.ilabel == 0]] = True
+    first = np.zeros(len(src), bool)
+    first[row[:-1][deg > 0]] = True
+    loop = first & (g.next_state == src) & (g.olabel == 0) & ~has_eps[src]
+    kinds, which = np.unique(np.stack([g.ilabel[loop], g.weight[loop].view(np.int32)]), axis=1, return_inverse=True)
+    usual = np.zeros(len(src), bool)
+    usual[np.nonzero(loop)[0]] = which.ravel() == np.argmax(np.bincount(which.ravel()))
+    n = []
+    frames = Oracle(g).decode(ll, length=length, beam=beam, max_active=max_active, want_frames=True).frames
+    for t, (states, costs) in enumerate(frames[:length]):
+        d = deg[states]
+        arcs = np.repeat(row[states] - np.cumsum(d) + d, d) + np.arange(d.sum())
+        emit = g.ilabel[arcs] > 0
+        arcs, cost = arcs[emit], np.repeat(costs, d)[emit]
+        cost = cost + g.weight[arcs] - ll[t, g.ilabel[arcs] - 1]
+        n.append(int(((cost - cost.min() <= beam) & ~usual[arcs]).sum()))
+    return n
+
+
 @pytest.mark.parametrize("cluster", [1], indirect=True)
 @pytest.mark.parametrize("ma", [5000, 5001, 12000, 12001])
 def test_either_side_of_the_sizes_one_workgroup_of_the_cluster_kernel_takes(torch_cuda, c2, cluster, ma):
     """No option on and no boosting, as the rule asks: results and counters on both sides of its ends, with a workgroup per
-    utterance and with fewer, twice on one decoder."""
+    utterance and with fewer, twice on one decoder.  The frames have more candidates than registers hold (3,072) and than
+    one pass takes (6,144), and with the larger sets more than four regions' notes hold (11,264 each)."""
     from paper_2311_04996_amd import Decoder
     ll, lengths = np.ascontiguousarray(c2.loglikes[:4, :40]), np.array([40, 33, 40, 1], np.int32)
     refs = parity.oracle_batch(c2.graph, ll, lengths, 20.0, ma)
-    want = np.sum([r.counters for r in refs], axis=0)
+    n = _candidates(c2.graph, ll[0], 40, 20.0, ma)
+    assert min(n) > 6144 and max(n) > (4 * 11264 if ma > 5001 else 2 * 11264)
     dec = Decoder(c2.graph, max_channels=4, max_frames=40, max_active_hint=ma)
     dev = torch_cuda.from_numpy(ll).cuda()
     for n_wg in (0, 2):
         dec.set_launch_workgroups(n_wg)
         dec.get_counters(reset=True)
-        words, nwords, cost, flags = (t.cpu().numpy() for t in dec.decode_batch(dev, lengths, 20.0, ma))
-        assert dec.debug_last_launch()[1] == 1
-        for b, r in enumerate(refs):
-            assert words[b, :nwords[b]].tolist() == r.words.tolist() and int(flags[b]) == r.flags and cost[b] == np.float32(r.cost), b
-        assert dec.get_counters()[:7].tolist() == want[:7].tolist()
+        out = dec.decode_batch(dev, lengths, 20.0, ma)
+        assert dec.debug_last_launch()[1] == 1 and dec.debug_last_kernel() == (2 if ma <= 12000 else 1)
+        _same_results(dec, out, refs)
     dec.close()
+
+
+@pytest.mark.parametrize("cluster", [1], indirect=True)
+def test_the_kernel_of_a_launch_with_one_workgroup_per_utterance(torch_cuda, c2, cluster):
+    """Up to a max-active of 5,000 the cluster kernel; up to 12,000 whole utterances without boosting and options on graphs
+    of which half the states or more have the usual self-loop alone; the first kernel for the rest and for narrow records."""
+    from paper_2311_04996_amd import Decoder
+    from workloads.boost import boost_fsts
+    from workloads.configs import boost_tables
+    from workloads.graphs import _csr
+    T = 3
+    dev = torch_cuda.from_numpy(np.ascontiguousarray(c2.loglikes[:2, :T])).cuda()
+    words, fsts = boost_tables(3, 2, 20_000), boost_fsts(3, 2, 20_000, per_utt=20)
+
+    def kernels(g, dev, max_actives, options=None, boost=None, stream=False):
+        got = []
+        dec = Decoder(g, max_channels=2, max_frames=T, max_active_hint=4000, **(options or {}))
+        for ma in max_actives:
+            if stream:
+                dec.init_channels([0, 1], 17.0, ma)
+                dec.advance_chunk_partial([0, 1], dev, [T, T], finalize=True)
+            else:
+                dec.decode_batch(dev, [T, T], 17.0, ma, **(boost or {}))
+            assert dec.debug_last_launch()[1] == 1
+            got.append(dec.debug_last_kernel())
+        dec.close()
+        return got
+    assert kernels(c2.graph, dev, (1000, 5000, 5001, 12000, 12001)) == [2, 2, 2, 2, 1]
+    for kw in (dict(boost=dict(boosts=words)), dict(boost=dict(boost_fsts=fsts)), dict(stream=True),
+               dict(options=dict(record_digests=True)), dict(options=dict(cost_offset=True)),
+               dict(options=dict(keep_token_records=True)), dict(options=dict(recycle_lattice=True, lattice_bytes_per_channel=1 << 20))):
+        assert kernels(c2.graph, dev, (5000, 5001), **kw) == [2, 1], kw
+    assert kernels(c2.graph, dev, (1000, 5001), options=dict(narrow_arcs=True)) == [1, 1]
+    for n_simple, want in ((4000, 2), (3999, 1)):          # of 8,000 states
+        s = np.arange(8000)
+        more = s[n_simple:]
+        g = _csr(8000, n_simple, 129, np.concatenate([s, more]), np.concatenate([s, (more + 1) % 8000]),
+                 np.concatenate([np.ones(8000, np.int64), 2 + more % 100]), np.zeros(8000 + len(more), np.int64), np.zeros(8000 + len(more)))
+        assert kernels(g, dev, (5001,)) == [want]
+        assert kernels(g, dev, (5000,)) == [2]
 
 
 def test_a_stream_whose_chunks_are_decoded_by_different_numbers_of_workgroups(torch_cuda, c2, c2_refs):
@@ -506,7 +579,7 @@ def test_epsilon_arcs_around_the_sizes_of_a_waves_list(torch_cuda, cluster):
                            max_active_hint=8000)
 
 
-@pytest.mark.parametrize("cluster", [1, 2], indirect=True)
+@pytest.mark.parametrize("cluster", [2], indirect=True)
 @pytest.mark.parametrize("times,n", [(1, 8100), (1, 9000), (1, 10100), (1, 11200), (1, 12600), (1, 21000), (3, 8000)])
 def test_candidates_around_what_a_table_and_the_notes_hold(torch_cuda, cluster, times, n):
     """As many candidates for one destination (the start, from every leaf) as slots are noted in LDS and in each of the
@@ -524,6 +597,37 @@ def test_candidates_around_what_a_table_and_the_notes_hold(torch_cuda, cluster, 
     g = _csr(S, 0, 2, src, dst, il, np.where(rng.random(len(src)) < 0.2, 7, 0), rng.choice([0.0, 0.25, 0.5, 1.0], len(src)))
     ll = rng.choice([-0.5, -1.0, -1.5], (2, 5, 2)).astype(np.float32)
     parity.check_batch(torch_cuda, g, ll, np.array([5, 3], np.int32), 20.0, 30000, max_active_hint=60000)
+
+
+@pytest.mark.parametrize("cluster", [1], indirect=True)
+@pytest.mark.parametrize("n", [3072, 3073, 6144, 6145, 8192, 8193, 9216, 9217, 10240, 10241, 11264, 11265, 15000, 21000])
+def test_candidates_around_what_one_workgroup_notes(torch_cuda, cluster, n):
+    """One workgroup of the cluster kernel: `n` tokens have an arc each, all to one state, or each to a state of its own.  Sizes
+    around what the registers, one pass, the notes in LDS and each of the registers behind them hold, for the fullest
+    of its regions; twice as many candidates from tokens with two arcs."""
+    from paper_2311_04996_amd import Decoder
+    from workloads.graphs import _csr
+    rng = np.random.default_rng([37, n])
+    hubs = 1 + np.arange(-(-n // 3500))
+    leaves = 1 + len(hubs) + np.arange(n)
+    ends = 1 + len(hubs) + n + np.arange(n + len(hubs) + 1)        # with the usual self-loop alone: half of the states
+    S = int(ends[-1]) + 1
+    ll = rng.choice([-0.5, -1.0, -1.5], (2, 4, 2)).astype(np.float32)
+    lengths = np.array([4, 2], np.int32)
+    for dst in (np.zeros(n, np.int64), ends[:n], np.concatenate([np.zeros(n, np.int64), rng.permutation(ends[:n])])):
+        src = np.resize(leaves, len(dst))
+        a_src = np.concatenate([np.zeros(len(hubs), np.int64), 1 + np.arange(n) // 3500, src, ends])
+        a_dst = np.concatenate([hubs, rng.permutation(leaves), dst, ends])
+        il = np.concatenate([1 + hubs % 2, np.zeros(n, np.int64), 1 + src % 2, np.ones(len(ends), np.int64)])
+        g = _csr(S, 0, 2, a_src, a_dst, il, np.where(a_src == a_dst, 0, rng.integers(1, 1000, len(a_src))),
+                 np.where(a_src == a_dst, 0.0, rng.choice([0.0, 0.25, 0.5, 1.0], len(a_src))))
+        refs = parity.oracle_batch(g, ll, lengths, 20.0, 12000)
+        assert _candidates(g, ll[0], 2, 20.0, 12000)[1] == len(dst)
+        dec = Decoder(g, max_channels=2, max_frames=4, max_active_hint=60000)
+        out = dec.decode_batch(torch_cuda.from_numpy(ll).cuda(), lengths, 20.0, 12000)
+        assert dec.debug_last_launch()[1] == 1 and dec.debug_last_kernel() == 2
+        _same_results(dec, out, refs)
+        dec.close()
 
 
 @pytest.mark.parametrize("cluster,n", [(1, 6144), (2, 11000), (2, 12288)], indirect=["cluster"])
