@@ -865,6 +865,9 @@ __device__ __forceinline__ unsigned probe_step(int key) {
 // afterwards; exact cost ties are decided by the arc ids of the two records.
 // With a boosting acceptor two tokens of one graph state can take the same arc into the same
 // (graph state, B state) pair; then the lower B state of the source token wins (src = its index).
+// kExact: a pass of the closure, planned from exact counts: there is a free slot for every candidate, and the odd step comes to
+// all slots.  (States one behind the other have probe sequences so alike that of 6,144 some go beyond kProbeLimit.)
+template <bool kExact>
 __device__ __forceinline__ int table_insert(Ctx &x, int dst, float cost, int arc, int src, int idx) {
   TableLds &t = x.sm.u.t;
   unsigned s = probe_start(dst);
@@ -875,10 +878,10 @@ __device__ __forceinline__ int table_insert(Ctx &x, int dst, float cost, int arc
     old = atomicCAS(&t.keys[s], kKeyEmpty, dst);
     if (old == kKeyEmpty || old == dst) break;
     s = (s + step) & kTabMask;
-    if (probes >= kProbeLimit) { old = kKeyNone; break; }
+    if (probes >= (kExact ? kTabSlots : kProbeLimit)) { old = kKeyNone; break; }
   }
-  // a probe sequence this long means that the pass has far more destinations than it was planned
-  // for (at the loads passes are planned for, 0.75, one in 10^30 gets here): the caller plans again.
+  // a probe sequence this long means (but for keys at regular distances) that the pass has far more destinations than it was
+  // planned for: the caller plans again.
   // (Leaving the loop first and returning here compiles to a faster loop than returning inside it.)
   if (old == kKeyNone) { atomicOr(&x.sm.overfull, 1); return -1; }
   const unsigned oc = f2ord(cost);
@@ -939,7 +942,7 @@ __device__ __forceinline__ void table_fill(Ctx &x, int r0, int r1, int g, int G,
       int take = (int)(G == 1) | (int)(group_of(key, G) == g);
       if (kSelect) take &= (int)cut.in_beam(c) & (int)(cut.bin(c) < k_sel);
       int slot = -1;
-      if (take) slot = table_insert(x, key, c, cd.w, cd.z, base + i);
+      if (take) slot = table_insert<!kSelect>(x, key, c, cd.w, cd.z, base + i);
       if (pos0 + i < kTabSlots) x.sm.occ[pos0 + i] = (unsigned short)slot;
     }
     pos0 += (n + kBlock - 1) / kBlock * kBlock;
@@ -1511,7 +1514,7 @@ __device__ __forceinline__ void eps_closure(Ctx &x, int2 *NQ, unsigned lat_base,
           __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
 #pragma unroll
           for (int u = 0; u < kU; ++u)
-            if (ok[u]) sm.occ[ci[u]] = (unsigned short)table_insert(x, key_of(next[u]), nc[u], arc[u], src[u], ci[u]);
+            if (ok[u]) sm.occ[ci[u]] = (unsigned short)table_insert<true>(x, key_of(next[u]), nc[u], arc[u], src[u], ci[u]);
         } else {
           push_cands<kU>(x, ok, next, nc, src, arc);
         }
@@ -1662,7 +1665,7 @@ __device__ __forceinline__ void eps_closure(Ctx &x, int2 *NQ, unsigned lat_base,
     }
     __syncthreads();
     n_wl = uni(min(sm.n_wl_next, x.c.qcap));
-    // (the closure's passes are planned from exact counts: a table that overfills is not expected)
+    // (the closure's passes are planned from exact counts, 6,144 candidates each on average: a table that fills up is not expected)
     const bool stop = (uni(sm.status) | uni(sm.overfull)) != 0;
     __syncthreads();
     if (tid == 0 && sm.overfull) { atomicOr(&sm.status, kStCapacity); sm.overfull = 0; }

@@ -630,11 +630,12 @@ def test_candidates_around_what_one_workgroup_notes(torch_cuda, cluster, n):
         dec.close()
 
 
-@pytest.mark.parametrize("cluster,n", [(1, 6144), (2, 11000), (2, 12288)], indirect=["cluster"])
-def test_a_closure_whose_destinations_lie_at_regular_distances(torch_cuda, cluster, n):
+@pytest.mark.parametrize("cluster,n,ma", [(1, 6144, 5000), (2, 11000, 5000), (2, 12288, 5000), (1, 6144, 6000), (1, 12000, 6000)], indirect=["cluster"])
+def test_a_closure_whose_destinations_lie_at_regular_distances(torch_cuda, cluster, n, ma):
     """`n` states of three blocks each one behind the other, all reached over epsilon arcs in one round: as many as a closure's
     table (8,192 slots) takes, or nearly, but with probe sequences so alike that in four of five orders one of 6,144 finds no
-    slot in the number of probes there are.  It is not lost: sets, words, counters of the oracle."""
+    slot in the number of probes there are.  It is not lost, nor the channel stopped: sets, words, counters of the oracle.
+    (With digests one workgroup takes another kernel beyond a max-active of 5,000.)"""
     from workloads.graphs import _csr
     rng = np.random.default_rng([41, n])
     per_hub = 3500
@@ -645,7 +646,7 @@ def test_a_closure_whose_destinations_lie_at_regular_distances(torch_cuda, clust
     il = np.concatenate([1 + hubs % 2, np.zeros(n, np.int64), np.tile([1, 2, 1, 2, 1], n)])
     g = _csr(1 + len(hubs) + n, 0, 2, src, dst, il, rng.integers(1, 1000, len(src)), rng.choice([0.0, 0.25, 0.5, 1.0], len(src)))
     ll = rng.choice([-0.5, -1.0, -1.5], (8, 5, 2)).astype(np.float32)
-    refs = parity.check_batch(torch_cuda, g, ll, np.full(8, 5, np.int32), 20.0, 5000, max_active_hint=20000)
+    refs = parity.check_batch(torch_cuda, g, ll, np.full(8, 5, np.int32), 20.0, ma, max_active_hint=20000)
     assert all(r.digest_count.tolist() == [1, len(hubs) + n] * 3 for r in refs)
 
 
