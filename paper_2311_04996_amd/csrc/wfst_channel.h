@@ -806,7 +806,7 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
   const int start_mine = init && (!kCl || part_of(key_of((int)x.g.start), x.lg) == x.me);
   const int n_own = init ? start_mine : uni(sm.told[kCl ? x.xc & 1u : 0].x);
   const int n_tok = x.n;
-  const bool small = n_own <= kKR * kBlock;
+  bool small = n_own <= kKR * kBlock;
   int k_sel = 256, n_sel = n_own + n_tok, n_sel_c = n_own;
   if (kCl && !init && n_own + uni(sm.n_in) > x.c.region_cap) {
     // One workgroup's buffer has four regions, by the top bits of the key's hash, and a channel whose
@@ -1108,7 +1108,9 @@ __device__ __forceinline__ void prune2(Cx &x, const int2 *Q, const int *GI, int2
     if (tid == 0 && (!kCl || x.me == 0)) sm.prof[15]++;   // counted, not timed: re-recombinations
     if (tid < 256) { sm.hist[tid] = 0; if (kCl) { sm.v.s.all[tid] = 0; sm.v.s.before[tid] = 0; } }
     if (tid == 0) { sm.n_win = 0; sm.overfull = 0; }
-    if (redo == 2) mult *= 2;
+    // (a table has room for what registers hold, but room is not enough: of 3,000 keys at regular distances one can have 1,000 others
+    // ahead of it.  The records are then read again, and the passes are more.)
+    if (redo == 2) { mult *= 2; small = false; }
     else { k_sel = 256; n_sel = n_own + n_tok; n_sel_c = n_own; }
     __syncthreads();
   }

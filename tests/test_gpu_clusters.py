@@ -650,6 +650,42 @@ def test_a_closure_whose_destinations_lie_at_regular_distances(torch_cuda, clust
     assert all(r.digest_count.tolist() == [1, len(hubs) + n] * 3 for r in refs)
 
 
+def _probe(taken, key):
+    """Probes of a key in a table of 8,192 slots until it comes to a free one, and that slot."""
+    h, n = int(key) * 0x9E3779B1 & 0xFFFFFFFF, 0
+    at, step = h >> 6 & 8191, (h >> 19 | 1) & 8191
+    while taken[at]:
+        at, n = (at + step) & 8191, n + 1
+    return n, at
+
+
+@pytest.mark.parametrize("cluster", [1], indirect=True)
+@pytest.mark.parametrize("ma,narrow", [(5000, False), (500, False), (5000, True)])
+def test_few_candidates_whose_destinations_lie_at_regular_distances(torch_cuda, cluster, ma, narrow):
+    """3,000 states of three blocks each, a third of a table, but the probe sequence of the one that comes last runs through more
+    than 257 others: with one that finds no slot the candidates, as many as registers hold, are recombined in more passes, and
+    no channel stops.  (Narrow records: the other kernel.)"""
+    from workloads.graphs import _csr
+    n, rng = 3000, np.random.default_rng(43)
+    leaves = 1 + np.arange(n)
+    key = (n + 2) // 2 + 3 * np.arange(n)              # behind the start: a header and n arcs, two to a block
+    taken = np.zeros(8192, bool)
+    for k in key:
+        taken[_probe(taken, k)[1]] = True
+    last = int(np.argmax([_probe(taken, k)[0] for k in key]))
+    order = np.concatenate([np.delete(leaves, last), [leaves[last]]])
+    taken[:] = False
+    for k in key[order[:-1] - 1]:
+        taken[_probe(taken, k)[1]] = True
+    assert _probe(taken, key[last])[0] > 300
+    src = np.concatenate([np.zeros(n, np.int64), np.repeat(leaves, 5)])
+    dst = np.concatenate([order, np.zeros(5 * n, np.int64)])
+    il = np.concatenate([np.ones(n, np.int64), np.tile([1, 2, 1, 2, 1], n)])
+    g = _csr(1 + n, 0, 2, src, dst, il, rng.integers(1, 1000, len(src)), np.concatenate([rng.choice([0.0, 0.015625], n), rng.choice([0.0, 0.25], 5 * n)]))
+    ll = rng.choice([-0.5, -1.0, -1.5], (4, 5, 2)).astype(np.float32)
+    parity.check_batch(torch_cuda, g, ll, np.full(4, 5, np.int32), 20.0, ma, max_active_hint=20000, narrow_arcs=narrow)
+
+
 @pytest.mark.parametrize("cluster", [1, 2, 4, 8], indirect=True)
 def test_an_overflow_in_a_frames_last_closure_round_stops_the_channel(torch_cuda, cluster):
     """10,002 tokens, 8,192 places, and no round and several frames after the one that finds no room: the channel is flagged
