@@ -623,9 +623,10 @@ __device__ __forceinline__ int group2(int key, int lg, int P) {
 }
 
 // Lower the destination's table entry to this candidate if (cost, arc id, source's B state) is
-// smaller.  `list`: candidates are records of a list instead of segments.  In the closure (kClosure) the
-// entry may be a token of the set, and a claimed slot is marked as having none.  Returns the
-// slot, -1 if the table is overfull.
+// smaller.  In the closure (kClosure) the entry may be a token of the set, and a claimed slot is marked as
+// having none.  Returns the slot, or -1 and sm.overfull if kProbeLimit probes have found none: the table is (nearly) full, or
+// the keys lie at regular distances, as those of states one behind the other do, and their probe sequences are alike.  Every
+// caller goes on from there with more passes.
 template <bool kCl, bool kClosure>
 __device__ __forceinline__ int insert2(Cx &x, int dst, float cost, int arc, int src, int idx,
                                        const int *NGI, unsigned lat_base) {
@@ -726,7 +727,7 @@ __device__ __forceinline__ void list_eps(Cx &x, int sel, int wi, int4 e) {
   if (wi < kWlLds) x.sm.wl[sel][wi] = e;
   else if (wi < x.c.qcap) (x.wl0 + sel * x.c.qcap)[wi] = e;
 }
-// New tokens of the emitting step (N per lane): own record, number in the set, backpointer, an entry in the
+// New tokens of the emitting step, one per lane: own record, number in the set, backpointer, an entry in the
 // worklist if the state has epsilon arcs, and one in the closure's table if an epsilon arc enters it.
 // Tokens outside simple states are numbered from the front, the others from the back.
 template <bool kCl, bool kOpt>
@@ -1268,7 +1269,7 @@ __device__ __forceinline__ void emit_eps2(Cx &x, int (&ok)[kU], const float (&tc
 // improved in the previous round that have epsilon arcs.  The set's tokens that an epsilon arc can
 // enter sit in the LDS table (put there when they were made), so a round's candidates meet them
 // directly.  If they do not fit, every round's candidates go into an empty table and all tokens look
-// themselves up.  On entry wl0 holds sm.made[2] entries.
+// themselves up.  On entry the first worklist holds sm.made[2] entries: kWlLds in sm.wl[0], the others in wl0.
 //
 // A round is bound by its chain (worklist, state, arcs, exchange, table, tokens), and every barrier adds to that the
 // wait for the slowest of 16 waves.  So each wave flattens the arcs of its own items (a flattening

@@ -2646,7 +2646,9 @@ bool candidates_have_numbers(const wfst_decoder *d, int G) { return 2ull * G * G
 //
 // The estimate: a frame takes a cluster a fixed time (barriers, exchanges, chains of dependent loads) plus its
 // share of the work, which goes with the tokens, at most about max_active of them; measured at 1,000 and
-// 11,000 tokens per frame.  The launch ends with its busiest cluster: no earlier than the longest
+// 11,000 tokens per frame with the first version of the cluster kernel (and, beyond 5,000 with one workgroup, with the first
+// kernel).  Frames have since become shorter, with eight workgroups 29 instead of 40 us at 10,000 tokens: what the rule
+// would choose by new figures has not been measured.  The launch ends with its busiest cluster: no earlier than the longest
 // utterance, than an equal share of all frames, and than the k + 1 shortest of the k * clusters + 1 longest.
 //
 // Several workgroups take more of the chip's time per frame than one (at 7,000 tokens 2, 4 and 8 of them
